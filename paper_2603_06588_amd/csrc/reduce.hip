@@ -1,5 +1,5 @@
-// Score reductions over the mass tensor: one wave per sequence, lanes over (probed head, row)
-// pairs, fp32 sums in a fixed order (lane-strided partial sums, then a butterfly), so the
+// Score reductions over the mass tensor: one workgroup per sequence (and per 64 spans), fp32 sums in a
+// fixed order (strided partial sums per thread, a butterfly inside the wave, the waves in turn), so the
 // result does not depend on anything but the inputs.
 #include "../../include/hook_api.h"
 #include "hook_device.h"
@@ -9,6 +9,7 @@ namespace {
 
 struct ReduceParams {
   int num_seqs, P, NQ, S, mode, span_a, span_b, accumulate;
+  int lanes_log2;   // SPAN_MEAN: 2^lanes_log2 neighbouring threads take neighbouring spans of one row
   const float* mass;
   const int* query_sel;
   const int* cu_q_lens;
@@ -16,57 +17,87 @@ struct ReduceParams {
   float* scores;
 };
 
+// What is read is a few KB to a few MB and every pair of (head, row) is independent, so the kernel is
+// bound by how many loads are in flight: kInFlight rows per thread, and as many threads as the pairs need
+// (256, or 1024 from kManyPairs pairs on, where 256 threads would take several trips to memory in turn).
+constexpr int kInFlight = 8;
+constexpr int kManyPairs = 128;
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
   return v;
 }
 
-__global__ __launch_bounds__(256) void k_reduce_mass(const ReduceParams p) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= p.num_seqs) return;
-  int nv = p.NQ;
+struct SeqRows { int skip, nv; };   // slots skip .. skip + nv - 1 hold selected rows
+
+__device__ __forceinline__ SeqRows selected_slots(const ReduceParams& p, int i) {
+  SeqRows s = {0, p.NQ};
   if (p.query_sel) {
     const int qb = p.query_sel[2 * i];
     int qe = min(p.query_sel[2 * i + 1], qb + p.NQ);
     if (p.cu_q_lens) qe = min(qe, p.cu_q_lens[i + 1] - p.cu_q_lens[i]);
-    nv = max(qe - max(qb, 0), 0);
+    s.nv = max(qe - max(qb, 0), 0);
     // slots of rows before the chunk (negative t) come first and hold zeros; they do not count
+    s.skip = qb < 0 ? min(-qb, p.NQ) : 0;
   }
-  const float* m = p.mass + (size_t)i * p.P * p.NQ * p.S;
-  const float inv_nv = nv > 0 ? 1.0f / (float)nv : 0.0f;
-  const int skip = (p.query_sel && p.query_sel[2 * i] < 0) ? min(-p.query_sel[2 * i], p.NQ) : 0;
-  const int npairs = p.P * nv;
-  if (p.mode == HOOK_REDUCE_SPAN_MEAN) {
-    for (int r0 = 0; r0 < p.S; r0 += kMaxSpans) {   // kMaxSpans spans at a time in registers
-      float acc[kMaxSpans];
+  return s;
+}
+
+// Scores per span.  A row's spans are neighbours in memory, so neighbouring threads take neighbouring
+// spans of one row and the groups of threads share the (head, row) pairs: every load is coalesced.
+// (One wave per sequence, eight spans per pass over the pairs, read 4 x 8 heads x 32 rows x 88 spans in
+// 96 us; this form takes 4.)
+template <int NT>
+__global__ __launch_bounds__(NT) void k_reduce_spans(const ReduceParams p) {
+  __shared__ float red[NT / 64][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i = blockIdx.x;
+  const int lanes = 1 << p.lanes_log2;
+  const int r = blockIdx.y * 64 + (tid & (lanes - 1));
+  const int sub = tid >> p.lanes_log2, nsub = NT >> p.lanes_log2;
+  const SeqRows rows = selected_slots(p, i);
+  const float* m = p.mass + (size_t)i * p.P * p.NQ * p.S + r;
+  const int npairs = p.P * rows.nv;
+  float acc = 0.0f;
+  if (r < p.S) {
+    for (int e0 = sub; e0 < npairs; e0 += kInFlight * nsub) {
+      float v[kInFlight], wp[kInFlight];
 #pragma unroll
-      for (int r = 0; r < kMaxSpans; ++r) acc[r] = 0.0f;
-      for (int e = lane; e < npairs; e += 64) {
-        const int ph = e / nv, t = skip + e - ph * nv;
-        const float wp = p.w ? p.w[ph] : 1.0f / (float)p.P;
-        const float* row = m + ((size_t)ph * p.NQ + t) * p.S + r0;
-#pragma unroll
-        for (int r = 0; r < kMaxSpans; ++r)
-          if (r0 + r < p.S) acc[r] += wp * row[r];
+      for (int u = 0; u < kInFlight; ++u) {
+        const int e = min(e0 + u * nsub, npairs - 1);   // past the end: a repeated load with weight 0
+        const int ph = e / rows.nv, t = rows.skip + e - ph * rows.nv;
+        v[u] = m[((size_t)ph * p.NQ + t) * p.S];
+        wp[u] = p.w ? p.w[ph] : 1.0f / (float)p.P;
       }
 #pragma unroll
-      for (int r = 0; r < kMaxSpans; ++r) {
-        if (r0 + r < p.S) {
-          const float v = wave_sum(acc[r]) * inv_nv;
-          if (lane == 0) {
-            float* dst = p.scores + (size_t)i * p.S + r0 + r;
-            *dst = p.accumulate ? *dst + v : v;
-          }
-        }
-      }
+      for (int u = 0; u < kInFlight; ++u) acc += (e0 + u * nsub < npairs) ? wp[u] * v[u] : 0.0f;
     }
-    return;
   }
+  for (int off = lanes; off < 64; off <<= 1) acc += __shfl_xor(acc, off);
+  if (lane < lanes) red[wave][lane] = acc;
+  __syncthreads();
+  if (tid < lanes && r < p.S) {
+    float sum = 0.0f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) sum += red[w][tid];
+    const float v = sum * (rows.nv > 0 ? 1.0f / (float)rows.nv : 0.0f);
+    float* dst = p.scores + (size_t)i * p.S + r;
+    *dst = p.accumulate ? *dst + v : v;
+  }
+}
+
+// One ratio per sequence: threads over the (head, row) pairs.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_reduce_ratio(const ReduceParams p) {
+  __shared__ float red[2][NT / 64];
+  const int tid = threadIdx.x, i = blockIdx.x;
+  const SeqRows rows = selected_slots(p, i);
+  const float* m = p.mass + (size_t)i * p.P * p.NQ * p.S;
+  const int npairs = p.P * rows.nv;
   float sa = 0.0f, sb = 0.0f;   // RATIO_MEAN uses sa only
-  for (int e = lane; e < npairs; e += 64) {
-    const int ph = e / nv, t = skip + e - ph * nv;
+  for (int e = tid; e < npairs; e += NT) {
+    const int ph = e / rows.nv, t = rows.skip + e - ph * rows.nv;
     const float wp = p.w ? p.w[ph] : 1.0f / (float)p.P;
     const float* row = m + ((size_t)ph * p.NQ + t) * p.S;
     const float a = row[p.span_a], b = row[p.span_b];
@@ -80,14 +111,17 @@ __global__ __launch_bounds__(256) void k_reduce_mass(const ReduceParams p) {
   }
   sa = wave_sum(sa);
   sb = wave_sum(sb);
-  float v;
-  if (p.mode == HOOK_REDUCE_RATIO_MEAN) {
-    v = sa * inv_nv;
-  } else {
-    const float A = sa * inv_nv, B = sb * inv_nv;
-    v = (A + B) != 0.0f ? A / (A + B) : 0.0f;
-  }
-  if (lane == 0) p.scores[i] = p.accumulate ? p.scores[i] + v : v;
+  if ((tid & 63) == 0) { red[0][tid >> 6] = sa; red[1][tid >> 6] = sb; }
+  __syncthreads();
+  if (tid != 0) return;
+  float A = 0.0f, B = 0.0f;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) { A += red[0][w]; B += red[1][w]; }
+  const float inv_nv = rows.nv > 0 ? 1.0f / (float)rows.nv : 0.0f;
+  A *= inv_nv;
+  B *= inv_nv;
+  const float v = p.mode == HOOK_REDUCE_RATIO_MEAN ? A : ((A + B) != 0.0f ? A / (A + B) : 0.0f);
+  p.scores[i] = p.accumulate ? p.scores[i] + v : v;
 }
 
 }  // namespace
@@ -111,7 +145,17 @@ extern "C" hook_status hook_reduce_mass(const hook_reduce_args* a) {
   p.mode = a->mode; p.span_a = a->span_a; p.span_b = a->span_b; p.accumulate = a->accumulate;
   p.mass = a->mass; p.query_sel = a->query_sel; p.cu_q_lens = a->cu_q_lens; p.w = a->head_weights;
   p.scores = a->scores;
-  hipLaunchKernelGGL(k_reduce_mass, dim3((unsigned)((p.num_seqs + 3) / 4)), dim3(256), 0,
-                     static_cast<hipStream_t>(a->stream), p);
+  hipStream_t st = static_cast<hipStream_t>(a->stream);
+  const bool many = (long long)p.P * p.NQ >= kManyPairs;
+  if (p.mode == HOOK_REDUCE_SPAN_MEAN) {
+    while ((1 << p.lanes_log2) < p.S && p.lanes_log2 < 6) ++p.lanes_log2;
+    const dim3 grid((unsigned)p.num_seqs, (unsigned)((p.S + 63) / 64));
+    if (many) hipLaunchKernelGGL(k_reduce_spans<1024>, grid, dim3(1024), 0, st, p);
+    else hipLaunchKernelGGL(k_reduce_spans<256>, grid, dim3(256), 0, st, p);
+  } else if (many) {
+    hipLaunchKernelGGL(k_reduce_ratio<1024>, dim3((unsigned)p.num_seqs), dim3(1024), 0, st, p);
+  } else {
+    hipLaunchKernelGGL(k_reduce_ratio<256>, dim3((unsigned)p.num_seqs), dim3(256), 0, st, p);
+  }
   return hipGetLastError() == hipSuccess ? HOOK_OK : HOOK_ERR_LAUNCH;
 }
