@@ -282,37 +282,42 @@ __device__ __forceinline__ void load_q(const SpanParams& p, const RowBlock& r, i
   for (int s = 0; s < D / 32; ++s) qf[s] = qp[4 * s + quarter];
 }
 
-constexpr int kSplitWaves = 4;
+// Both kernels are bound by latency, not by the bytes (4 prompts of 6-14 k tokens, 8 heads: 84 MB of keys
+// per pass): a wave spends most of its time in the chain lengths -> rows -> block ids -> keys.  So the work
+// is cut fine and the workgroups are small, which lets the chip start them all at once and even out
+// sequences of unequal length: pass 1 takes 1024 keys with 4 waves (2048 keys: 4 waves 38 us, 16 waves 40;
+// 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27), pass 2 gives every span a wave of its own, two to a
+// workgroup (two spans per wave in turn, four waves: 45 us; one span: 8 waves 38 us, 4 waves 32, 2 waves 30).
+constexpr int kStatWaves = 4;     // waves per workgroup of pass 1
+constexpr int kSumWaves = 2;      // waves (spans at a time) per workgroup of pass 2
 constexpr int kSplitBlocks = 2;   // blocks of 16 rows per workgroup: they share every K fetch
+constexpr int kSplitKeys = 1024;  // keys of one workgroup of pass 1 (until kMaxSplits is reached)
+constexpr int kMaxSplits = 16;    // key splits of pass 1
 
-// The kSplitBlocks row blocks of workgroup column `bx`.  A block without rows shadows a block that
-// has some (same loads and arithmetic, nothing written); false if no block has rows.
+// The kSplitBlocks row blocks of workgroup column `bx`.  A block without rows shadows the other one
+// (same loads and arithmetic, nothing written); false if no block has rows.
 __device__ __forceinline__ bool row_blocks(const SpanParams& p, int i, int ps, int bx, int j,
                                            RowBlock (&r)[kSplitBlocks], bool (&has)[kSplitBlocks], int& pos_max) {
-  int good = -1;
+  static_assert(kSplitBlocks == 2, "each block has one other block to shadow");
+#pragma unroll
+  for (int nb = 0; nb < kSplitBlocks; ++nb) has[nb] = row_block(p, i, ps, kSplitBlocks * bx + nb, j, r[nb]);
+  if (!has[0] && !has[1]) return false;
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) {
-    has[nb] = row_block(p, i, ps, kSplitBlocks * bx + nb, j, r[nb]);
-    if (has[nb] && good < 0) good = nb;
-  }
-  if (good < 0) return false;
-  pos_max = 0;
-#pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) {
-    if (!has[nb]) {
-      r[nb] = r[good];
+    if (!has[nb]) {   // (a computed index here would move the whole array into LDS)
+      r[nb] = r[1 - nb];
       r[nb].slot0 = kSmRows * (kSplitBlocks * bx + nb);
       r[nb].row_ok = false;
     }
-    pos_max = max(pos_max, r[nb].pos_max);
   }
+  pos_max = max(r[0].pos_max, r[1].pos_max);
   return true;
 }
 
 template <int D, bool KV8>
-__global__ __launch_bounds__(kSplitWaves * 64) void k_span_stats(const SpanParams p) {
-  __shared__ float sh_m[kSplitWaves][kSplitBlocks][kSmRows];
-  __shared__ float sh_l[kSplitWaves][kSplitBlocks][kSmRows];
+__global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams p) {
+  __shared__ float sh_m[kStatWaves][kSplitBlocks][kSmRows];
+  __shared__ float sh_l[kStatWaves][kSplitBlocks][kSmRows];
   // every workgroup helps zero-filling mass (the second kernel writes only entries with a row and a span)
   {
     const size_t nmass = (size_t)p.num_seqs * p.P * p.NQ * p.S;
@@ -339,7 +344,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_span_stats(const SpanParam
   float m[kSplitBlocks], l[kSplitBlocks];
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) { m[nb] = -INFINITY; l[nb] = 0.0f; }
-  stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, lo + 16 * kSmGroup * wave, 16 * kSmGroup * kSplitWaves,
+  stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, lo + 16 * kSmGroup * wave, 16 * kSmGroup * kStatWaves,
                                hi, pos_max, [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
 #pragma unroll
     for (int nb = 0; nb < kSplitBlocks; ++nb) {
@@ -375,10 +380,10 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_span_stats(const SpanParam
     const int nb = threadIdx.x / kSmRows, jj = threadIdx.x % kSmRows;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) M = fmaxf(M, sh_m[w][nb][jj]);
+    for (int w = 0; w < kStatWaves; ++w) M = fmaxf(M, sh_m[w][nb][jj]);
     float Ls = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) {
+    for (int w = 0; w < kStatWaves; ++w) {
       const float mw = sh_m[w][nb][jj];
       if (mw != -INFINITY) Ls += sh_l[w][nb][jj] * fast_exp2(mw - M);
     }
@@ -388,7 +393,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_span_stats(const SpanParam
 }
 
 template <int D, bool KV8>
-__global__ __launch_bounds__(kSplitWaves * 64) void k_span_sums(const SpanParams p) {
+__global__ __launch_bounds__(kSumWaves * 64) void k_span_sums(const SpanParams p) {
   const int i = blockIdx.z / p.sgroups, sg = blockIdx.z % p.sgroups, ps = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -409,19 +414,28 @@ __global__ __launch_bounds__(kSplitWaves * 64) void k_span_sums(const SpanParams
     M[nb] = 0.0f;
     inv[nb] = 0.0f;
     if (has[nb]) {   // uniform; a shadow block has no statistics of its own and writes nothing
+      // the four lanes of a row take a quarter of the splits each
       const float2* st = p.stats + (((size_t)i * p.P + ps) * p.nq_pad + r[nb].slot0 + j) * p.nsplit;
-      float mx = -INFINITY;
-      for (int sp = 0; sp < p.nsplit; ++sp) mx = fmaxf(mx, st[sp].x);
-      float Lsum = 0.0f;
-      for (int sp = 0; sp < p.nsplit; ++sp) {
-        const float2 v = st[sp];
-        if (v.x != -INFINITY) Lsum += v.y * fast_exp2(v.x - mx);
+      float2 v[kMaxSplits / 4];
+#pragma unroll
+      for (int u = 0; u < kMaxSplits / 4; ++u) {
+        const int sp = kMaxSplits / 4 * quarter + u;
+        v[u] = sp < p.nsplit ? st[sp] : make_float2(-INFINITY, 0.0f);
       }
+      float mx = -INFINITY, Lsum = 0.0f;
+#pragma unroll
+      for (int u = 0; u < kMaxSplits / 4; ++u) mx = fmaxf(mx, v[u].x);
+      mx = fmaxf(mx, __shfl_xor(mx, 16));
+      mx = fmaxf(mx, __shfl_xor(mx, 32));
+#pragma unroll
+      for (int u = 0; u < kMaxSplits / 4; ++u) Lsum += v[u].y * fast_exp2(v[u].x - mx);   // an empty split adds 0
+      Lsum += __shfl_xor(Lsum, 16);
+      Lsum += __shfl_xor(Lsum, 32);
       M[nb] = mx;
       inv[nb] = 1.0f / Lsum;
     }
   }
-  for (int s = sg * kSplitWaves + wave; s < p.S; s += p.sgroups * kSplitWaves) {
+  for (int s = sg * kSumWaves + wave; s < p.S; s += p.sgroups * kSumWaves) {
     const int a = max(p.key_spans[((size_t)i * p.S + s) * 2], 0);
     const int e = min(p.key_spans[((size_t)i * p.S + s) * 2 + 1], pos_max + 1);
     if (e <= a) continue;                          // uniform; mass was zero-filled
@@ -455,15 +469,17 @@ struct SplitGeom { int nsplit, sgroups, nq_pad; size_t bytes; bool usable; };
 inline SplitGeom split_geometry(const hook_attn_probe_args* a) {
   SplitGeom g{};
   const long long max_ctx = (long long)a->max_blocks_per_seq * kBlock;
-  g.nsplit = (int)((max_ctx + 2047) / 2048);
+  g.nsplit = (int)((max_ctx + kSplitKeys - 1) / kSplitKeys);
   if (g.nsplit < 1) g.nsplit = 1;
-  if (g.nsplit > 16) g.nsplit = 16;
-  g.sgroups = (a->max_spans + 2 * kSplitWaves - 1) / (2 * kSplitWaves);
+  if (g.nsplit > kMaxSplits) g.nsplit = kMaxSplits;
+  if ((long long)a->num_seqs * g.nsplit > 65535) g.nsplit = 65535 / a->num_seqs;   // likewise
+  // one span per wave, as long as the launch grid's third dimension (65535) holds the groups
+  g.sgroups = (a->max_spans + kSumWaves - 1) / kSumWaves;
   if (g.sgroups < 1) g.sgroups = 1;
-  if (g.sgroups > 32) g.sgroups = 32;
+  if (a->num_seqs > 0 && g.sgroups > 65535 / a->num_seqs) g.sgroups = 65535 / a->num_seqs;
   g.nq_pad = (a->max_sel_q + kSmRows - 1) / kSmRows * kSmRows;
   g.bytes = (size_t)a->num_seqs * a->num_probe_heads * g.nq_pad * g.nsplit * sizeof(float2);
-  g.usable = (long long)a->num_seqs * g.nsplit <= 65535 && (long long)a->num_seqs * g.sgroups <= 65535;
+  g.usable = g.nsplit >= 1 && g.sgroups >= 1;
   return g;
 }
 
@@ -507,25 +523,27 @@ extern "C" hook_status hook_span_mass(const hook_attn_probe_args* a) {
   hipStream_t st = static_cast<hipStream_t>(a->stream);
 
   // with enough scratch memory: pass 1 split over the keys, pass 2 over the spans
-  const SplitGeom geo = split_geometry(a);
-  if (geo.usable && a->workspace && a->workspace_bytes >= geo.bytes &&
-      (reinterpret_cast<uintptr_t>(a->workspace) % 8) == 0) {
+  // (as many key splits as the scratch memory holds, at least one)
+  SplitGeom geo = split_geometry(a);
+  const size_t per_split = geo.bytes / (size_t)geo.nsplit;
+  if (a->workspace_bytes < geo.bytes) geo.nsplit = (int)(a->workspace_bytes / per_split);
+  if (geo.usable && a->workspace && geo.nsplit >= 1 && (reinterpret_cast<uintptr_t>(a->workspace) % 8) == 0) {
     p.stats = static_cast<float2*>(a->workspace);
     p.nsplit = geo.nsplit; p.sgroups = geo.sgroups; p.nq_pad = geo.nq_pad;
     const unsigned gx = (unsigned)((geo.nq_pad / kSmRows + kSplitBlocks - 1) / kSplitBlocks);
     const dim3 ga(gx, (unsigned)P, (unsigned)(p.num_seqs * geo.nsplit)), gb(gx, (unsigned)P, (unsigned)(p.num_seqs * geo.sgroups));
-    const dim3 tb(kSplitWaves * 64);
+    const dim3 ta(kStatWaves * 64), tb(kSumWaves * 64);
     if (a->head_dim == 128 && !kv8) {
-      hipLaunchKernelGGL((k_span_stats<128, false>), ga, tb, 0, st, p);
+      hipLaunchKernelGGL((k_span_stats<128, false>), ga, ta, 0, st, p);
       hipLaunchKernelGGL((k_span_sums<128, false>), gb, tb, 0, st, p);
     } else if (a->head_dim == 128) {
-      hipLaunchKernelGGL((k_span_stats<128, true>), ga, tb, 0, st, p);
+      hipLaunchKernelGGL((k_span_stats<128, true>), ga, ta, 0, st, p);
       hipLaunchKernelGGL((k_span_sums<128, true>), gb, tb, 0, st, p);
     } else if (!kv8) {
-      hipLaunchKernelGGL((k_span_stats<64, false>), ga, tb, 0, st, p);
+      hipLaunchKernelGGL((k_span_stats<64, false>), ga, ta, 0, st, p);
       hipLaunchKernelGGL((k_span_sums<64, false>), gb, tb, 0, st, p);
     } else {
-      hipLaunchKernelGGL((k_span_stats<64, true>), ga, tb, 0, st, p);
+      hipLaunchKernelGGL((k_span_stats<64, true>), ga, ta, 0, st, p);
       hipLaunchKernelGGL((k_span_sums<64, true>), gb, tb, 0, st, p);
     }
     return hipGetLastError() == hipSuccess ? HOOK_OK : HOOK_ERR_LAUNCH;
