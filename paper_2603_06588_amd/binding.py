@@ -166,8 +166,8 @@ def _p(t: Optional[torch.Tensor]) -> int:
 
 
 def _stream_handle(stream) -> int:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:      # the current stream's handle itself: building a Stream object takes ten times as long
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream)
 
 
