@@ -81,10 +81,9 @@ typedef enum { HOOK_KV_SAME = 0, HOOK_KV_FP8_E4M3 = 1 } hook_kv_dtype;
  * With a hint the launches that cannot have work are left out (two of four for a prefill-only
  * batch).  A sequence that contradicts the hint is NOT computed: its rows of `out` stay untouched,
  * its `mass` entries are zero and bit 3 of the device status word is set.
- * A small HOOK_BATCH_DECODE_ONLY batch (HOOK_BF16, at most 512 (sequence, kv head, head group)
- * triples, i.e. up to 64 sequences at 8 kv heads) plans itself: every sequence is cut into the same
- * number of parts, the workgroups read the lengths themselves and the planning launch is left out
- * (two launches instead of three).  Results are the same to rounding order; the status word is
+ * A HOOK_BATCH_DECODE_ONLY batch of at most 512 sequences (HOOK_BF16) plans itself: the contexts are
+ * cut into equal ranges, the workgroups find theirs from the lengths and the planning launch is left
+ * out (two launches instead of three).  Results are the same to rounding order; the status word is
  * written as always.  A HOOK_BATCH_PREFILL_ONLY call that holds ONE sequence (a single prompt;
  * HOOK_BF16, head_dim 128) needs no planning launch either: the chunk kernel works out its row
  * blocks itself, with results bit for bit those of the planned call.
@@ -199,7 +198,8 @@ typedef struct hook_attn_probe_args {
   /* optional: the new tokens' keys and values, [total_q, Hkv, d] of `dtype`, device.  When both are
      given the call first writes them into k_cache / v_cache at positions L_i - n_i + t (exactly what
      hook_kv_write does, quantising for an 8-bit cache) and only then reads the caches - inside the
-     planning launch where the call has one, else in a launch of its own ahead of the attention
+     planning launch where the call has one, in the streaming kernel of a decode-only batch that plans
+     itself (each new row by the workgroup that reads its position), else in a launch ahead of the attention
      kernels: the one place where the call writes through k_cache / v_cache. */
   const void*  k_new;
   const void*  v_new;

@@ -11,15 +11,11 @@ namespace {
 using namespace hook;
 
 constexpr size_t kAlign = 256;
-// A batch of single rows with at most this many (sequence, kv head, head group) triples plans
-// itself: every sequence is cut into the same number of parts and the planning launch, a quarter
-// of such a call, is left out.  Larger batches keep the planner, which balances ragged lengths.
-constexpr long long kSelfPlanMaxTriples = 512;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
   size_t off_hdr, off_pf, off_dec, off_seq, off_part, total;
-  int pf_cap, dec_cap, hpw, rows_per_wg, hgroups, dec_hp, dec_hgroups;
+  int pf_cap, dec_cap, ranges, hpw, rows_per_wg, hgroups, dec_hp, dec_hgroups;
 };
 
 bool shapes_supported(const hook_attn_probe_args* a) {
@@ -50,6 +46,18 @@ int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_p
   return (int)cap;
 }
 
+// Ranges of a self-planned batch of single rows (decode.hip), 0 where the planner is kept: one resident
+// round of workgroups (256 compute units times the 3 workgroups each holds, 2 for groups of 8 heads) - a
+// second, partial round costs more than its finer balance gains - but no range shorter than
+// kStreamMinBlocks.  Up to kStreamMaxSeqs sequences, whose lengths every workgroup can afford to scan.
+int stream_ranges(const hook_attn_probe_args* a, const Layout& l) {
+  if (a->dtype != HOOK_BF16 || a->num_seqs <= 0 || a->num_seqs > kStreamMaxSeqs) return 0;
+  const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3), wgs = (long long)a->num_kv_heads * l.dec_hgroups;
+  const long long finest = ((long long)a->num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks;
+  const long long ranges = (one_round + wgs - 1) / wgs;
+  return (int)(ranges < finest ? ranges : finest);
+}
+
 Layout make_layout(const hook_attn_probe_args* a) {
   Layout l{};
   const int G = a->num_q_heads / a->num_kv_heads;
@@ -62,6 +70,9 @@ Layout make_layout(const hook_attn_probe_args* a) {
     l.pf_cap = a->total_q / l.rows_per_wg + a->num_seqs;
     l.dec_cap = decode_item_bound(a->num_seqs < a->total_q ? a->num_seqs : a->total_q,
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
+    // a self-planned batch numbers its records by range + sequence
+    l.ranges = stream_ranges(a, l);
+    if (l.ranges > 0 && l.dec_cap < l.ranges + a->num_seqs) l.dec_cap = l.ranges + a->num_seqs;
   }
   size_t off = 0;
   l.off_hdr = off;  off = align_up(off + sizeof(PlanHeader));
@@ -72,22 +83,6 @@ Layout make_layout(const hook_attn_probe_args* a) {
   off = align_up(off + sizeof(float) * (size_t)l.dec_cap * a->num_q_heads * (a->head_dim + kPartialPad));
   l.total = off;
   return l;
-}
-
-// Parts per sequence of a self-planned batch of single rows, 0 where the planner is kept.  As many
-// parts as give one resident round of workgroups (256 compute units times the 3 workgroups each
-// holds, 2 for groups of 8 heads): measured on 4-32 sequences of 1-64 k tokens this beats both
-// fewer and more (a second, partial round costs more than its finer balance gains).  The records
-// of part j of sequence i sit in slot i * parts + j, so the slot capacity of the workspace bounds
-// the count as well.
-int self_plan_parts(const hook_attn_probe_args* a, const Layout& l) {
-  if (a->dtype != HOOK_BF16 || a->batch_kind != HOOK_BATCH_DECODE_ONLY || a->num_seqs <= 0) return 0;
-  const long long triples = (long long)a->num_seqs * a->num_kv_heads * l.dec_hgroups;
-  if (triples > kSelfPlanMaxTriples) return 0;
-  const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3);
-  long long parts = (one_round + triples - 1) / triples;
-  if (parts > l.dec_cap / a->num_seqs) parts = l.dec_cap / a->num_seqs;
-  return (int)parts;
 }
 
 }  // namespace
@@ -197,7 +192,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.hpw = l.hpw; p.rows_per_wg = l.rows_per_wg; p.hgroups = l.hgroups;
   p.dec_hp = l.dec_hp; p.dec_hgroups = l.dec_hgroups;
   p.batch_kind = a->batch_kind;
-  p.dec_parts = self_plan_parts(a, l);
+  p.dec_ranges = a->batch_kind == HOOK_BATCH_DECODE_ONLY ? l.ranges : 0;
   // a single prompt on its own needs no planner either (head_dim 128: the kernel that can plan for itself)
   p.pf_self = a->dtype == HOOK_BF16 && a->head_dim == 128 && !kv8 && a->batch_kind == HOOK_BATCH_PREFILL_ONLY &&
               a->num_seqs == 1;
@@ -206,8 +201,9 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   hipStream_t st = static_cast<hipStream_t>(a->stream);
   auto mark = [&](int i) { return !ev || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return HOOK_ERR_LAUNCH;
-  // the planning launch carries the cache write; where there is no such launch it gets its own
-  if (writes_kv && (a->dtype == HOOK_F32 || a->plan_mode == HOOK_PLAN_REUSE || p.dec_parts > 0 || p.pf_self) &&
+  // a self-planned batch of single rows writes its rows while streaming, else the planning launch carries the
+  // cache write; where there is no such launch it gets its own
+  if (writes_kv && p.dec_ranges == 0 && (a->dtype == HOOK_F32 || a->plan_mode == HOOK_PLAN_REUSE || p.pf_self) &&
       launch_kv_write(p.kvw, st) != hipSuccess)
     return HOOK_ERR_LAUNCH;
   if (a->dtype == HOOK_F32) {
@@ -218,7 +214,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   }
   // a reusing call finds the work lists of the same batch in the workspace; a self-planned batch
   // of single rows needs none
-  if ((a->plan_mode == HOOK_PLAN_FRESH && p.dec_parts == 0 && !p.pf_self && launch_plan(p, st) != hipSuccess) || !mark(1))
+  if ((a->plan_mode == HOOK_PLAN_FRESH && p.dec_ranges == 0 && !p.pf_self && launch_plan(p, st) != hipSuccess) || !mark(1))
     return HOOK_ERR_LAUNCH;
   const bool chunks = a->batch_kind != HOOK_BATCH_DECODE_ONLY, singles = a->batch_kind != HOOK_BATCH_PREFILL_ONLY;
   if ((chunks && launch_prefill(p, a->head_dim, st) != hipSuccess) || !mark(2)) return HOOK_ERR_LAUNCH;

@@ -9,12 +9,14 @@
 //     whose accumulator gives lane (head j, key group kq) the scores of 4 keys;
 //   - every (head, key group) lane runs its own online softmax over the keys it sees, so
 //     the loop has no cross-lane reduction; exponentials are handed to the lanes that hold
-//     the matching V rows with a lane shuffle, and P V is plain fp32 FMAs on V in its
+//     the matching V rows with a DPP broadcast, and P V is plain fp32 FMAs on V in its
 //     natural layout;
 //   - the key-group streams of a wave, the waves of a workgroup and finally the chunks of a
 //     sequence are merged with the usual (max, sum) weights; probe span sums ride along with
 //     the normaliser in every merge.
-#include "hook_device.h"
+#include "kv_write_device.h"
+
+#include <type_traits>
 
 namespace hook {
 
@@ -39,38 +41,77 @@ __device__ __forceinline__ uint32_t fp8x2_to_bf16x2(uint32_t w, bool upper_half)
   return u;
 }
 
+// The kernel's argument block, through a pointer whose origin the compiler cannot see.
+__device__ __forceinline__ const AttnParams& reread_arguments() {
+  auto a = (const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return *(const AttnParams*)(const __attribute__((address_space(4))) AttnParams*)a;
+}
+
+// A pointer read through it is not known to point to global memory unless this says so.
+template <typename T>
+__device__ __forceinline__ T* in_global(T* ptr) {
+  return (T*)(__attribute__((address_space(1))) T*)ptr;
+}
+
+// Value of `x` in lane H of this lane's group of 16 (a DPP move: no trip through LDS)
+template <int H>
+__device__ __forceinline__ float row_bcast(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(x), 0x150 + H, 0xf, 0xf, false));
+}
+template <int N, typename F, int H = 0>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (H < N) {
+    f(std::integral_constant<int, H>{});
+    static_for<N, F, H + 1>(static_cast<F&&>(f));
+  }
+}
+
 // KV8: the caches hold 8-bit E4M3 bytes ([num_blocks, Hkv, 16, D] bytes), one fp32 scale per kv head.
 // The key scale is folded into the softmax scale and the value scale into the partial output, so
-// the loop differs from the 16-bit one only in its loads and conversions: a block is half as many
-// bytes, so loads run two blocks ahead instead of one to keep as many bytes in flight.
+// the loop differs from the 16-bit one only in its loads and conversions.
 // The keys [kstart, kend) of one sequence for one (kv head, head group): four waves split the cache
 // blocks, merge in LDS and leave one partial record per head in slot `item`.
+// new_pos >= 0: the call brings the sequence's new key/value row (that position, row `qrow` of k_new / v_new);
+// the wave that meets the position takes the row from there instead of the cache and, if `store_new`,
+// writes it into the cache on the way, so no launch of its own has to do that first.
 template <int D, int HP, bool KV8>
 __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4][HP][DecodeCfg<D>::PSTR], int tid, int lane,
                                              int w, int kvh, int head0, int seq, int qrow, int kstart, int kend,
-                                             int item) {
+                                             int item, int new_pos, bool store_new) {
   using C = DecodeCfg<D>;
   constexpr int NW = 4;
+  const int blk0 = kstart >> 4;                         // first block of the range inside the sequence
   const int nblk = (kend - kstart + kBlock - 1) / kBlock;
   const int bpw = (nblk + NW - 1) / NW;
   const int b0 = min(w * bpw, nblk), b1 = min(b0 + bpw, nblk);
 
-  const __bf16* const qg = static_cast<const __bf16*>(p.q);
-  const __bf16* const kg_ = static_cast<const __bf16*>(p.k_cache);
-  const __bf16* const vg_ = static_cast<const __bf16*>(p.v_cache);
-  const unsigned char* const kg8 = static_cast<const unsigned char*>(p.k_cache);
-  const unsigned char* const vg8 = static_cast<const unsigned char*>(p.v_cache);
-  const int* const bt = p.block_table + (size_t)seq * p.max_blocks;
-  const size_t blk_stride = (size_t)p.Hkv * kBlock * D;   // in elements (bytes for the 8-bit cache)
-  const size_t head_off = (size_t)kvh * kBlock * D;
+  const int* const bt = in_global(p.block_table) + (size_t)seq * p.max_blocks + blk0;
+  constexpr int ESZ = KV8 ? 1 : 2;                      // bytes per cache element
+  const char* const kbase = static_cast<const char*>(in_global(p.k_cache)) + (size_t)kvh * kBlock * D * ESZ;
+  const char* const vbase = static_cast<const char*>(in_global(p.v_cache)) + (size_t)kvh * kBlock * D * ESZ;
+  const unsigned blk_bytes = (unsigned)p.Hkv * kBlock * D * ESZ;
 
   // score-lane role: head j = lane % 16 (real if j < HP), key group kq = lane / 16
   const int j = lane & 15, kq = lane >> 4;
   // value-lane role: key group vk, 16-byte chunk ch; its keys KPL*vk .. KPL*vk+KPL-1 all
-  // belong to score key group (KPL*vk)/4
+  // belong to score key group (KPL*vk)/4 = lane / 16, so exponentials only move inside a group of 16 lanes
   const int vk = lane / C::CHV, ch = lane % C::CHV;
-  const int src_base = 16 * ((C::KPL * vk) >> 2);     // lane of head 0 in the matching score group
 
+  // everything that does not depend on block ids is requested together with the first of them: block
+  // ids (64 to a register, one per lane), query rows, probed heads
+  auto load_ids = [&](int first) {
+    const int blk = bt[min(first + lane, nblk - 1)];
+    return ((unsigned)blk < (unsigned)p.num_blocks) ? blk : 0;
+  };
+  int ids = load_ids(b0), ids_next = 0;
+  if (bpw > 64) ids_next = load_ids(b0 + 64);
+  int qb = 0, qe = 0, ph0 = -1;
+  if (p.P > 0) {
+    qb = cload(p.query_sel, 2 * seq);
+    qe = min(cload(p.query_sel, 2 * seq + 1), qb + p.NQ);
+    if (lane < p.P) ph0 = in_global(p.probe_heads)[lane];
+  }
   bf16x8 qf[C::KSTEPS];
 #pragma unroll
   for (int s = 0; s < C::KSTEPS; ++s) {
@@ -80,32 +121,56 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     // dimensions 64 (s / 2) + 16 kq + 8 (s % 2) + 0..7 instead of 32 s + 8 kq + 0..7
     const int dim0 = KV8 ? 64 * (s >> 1) + 16 * kq + 8 * (s & 1) : 32 * s + 8 * kq;
     if (j < HP)
-      v = *reinterpret_cast<const uint4*>(qg + ((size_t)qrow * p.Hq + head0 + j) * D + dim0);
+      v = *reinterpret_cast<const uint4*>(static_cast<const __bf16*>(in_global(p.q)) + ((size_t)qrow * p.Hq + head0 + j) * D + dim0);
     __builtin_memcpy(&qf[s], &v, 16);
   }
 
-  // probe set-up: per score lane (its head), spans uniform
+  // 16-byte pieces per lane and block: K rows for the score MFMA, V rows for P V (8-bit V: 8 bytes)
+  constexpr int kKr = KV8 ? C::KSTEPS / 2 : C::KSTEPS;
+  struct Block { uint4 k[kKr]; uint4 v[C::KPL]; };
+  const unsigned koff = (unsigned)j * D * ESZ + 16 * kq;
+  const unsigned voff = (unsigned)(C::KPL * vk) * D * ESZ + 8 * ESZ * ch;
+  // Rows past the last token lie in a block the sequence owns, and what they hold (anything, NaN included) is
+  // replaced before use in the range's last block.  Loads are always issued, so that the compiler knows how
+  // many are outstanding at a wait; past the wave's last block all lanes fetch the same 16 bytes.
+  auto load_block = [&](int b, Block& d) {
+    const unsigned long long off = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(ids, (b - b0) & 63) * blk_bytes;
+    global_bytes kb = (global_bytes)(kbase + off), vb = (global_bytes)(vbase + off);
+    unsigned ko = b < b1 ? koff : 0, vo = b < b1 ? voff : 0;     // (opaque, so that the loads take a scalar base and a 32-bit lane offset)
+    asm("" : "+v"(ko), "+v"(vo));
+#pragma unroll
+    for (int s = 0; s < kKr; ++s) d.k[s] = load_stream16(kb + ko + 64 * s);
+#pragma unroll
+    for (int i = 0; i < C::KPL; ++i) {
+      if constexpr (KV8) {
+        const uint2 v = load_stream8(vb + vo + i * D);
+        d.v[i] = make_uint4(v.x, v.y, 0, 0);
+      } else {
+        d.v[i] = load_stream16(vb + vo + i * D * 2);
+      }
+    }
+  };
+  Block ring[2];
+  if (b0 < b1) load_block(b0, ring[0]);
+
+  // probe set-up: per score lane (its head), spans uniform.  The single row t = 0 is selected when
+  // begin <= 0 < min(end, begin + NQ); its slot is -begin
   int sp_a[kMaxSpans], sp_b[kMaxSpans];
 #pragma unroll
   for (int s = 0; s < kMaxSpans; ++s) { sp_a[s] = 0; sp_b[s] = 0; }
-  bool any_probe = false;
   bool lane_probe = false;
-  if (p.P > 0) {
-    // the single row t = 0 is selected when begin <= 0 < min(end, begin + NQ); its slot is -begin
-    const int qb = p.query_sel[2 * seq], qe = min(p.query_sel[2 * seq + 1], qb + p.NQ);
-    any_probe = (qb <= 0 && qe > 0);
-    if (any_probe) {
-      // is head0 + h probed?  The list is read 64 entries at a time, one per lane, and matched
-      // with a ballot, so the answer costs one load instead of a search per head
-      for (int i0 = 0; i0 < p.P; i0 += 64) {
-        const int ph = (i0 + lane < p.P) ? p.probe_heads[i0 + lane] : -1;
+  const bool any_probe = p.P > 0 && qb <= 0 && qe > 0;
+  if (any_probe) {
+    load_spans_uniform(p.key_spans, seq, p.S, sp_a, sp_b);
+    // is head0 + h probed?  The list is read 64 entries at a time, one per lane, and matched
+    // with a ballot, so the answer costs one load instead of a search per head
+    for (int i0 = 0; i0 < p.P; i0 += 64) {
+      const int ph = i0 == 0 ? ph0 : (i0 + lane < p.P) ? in_global(p.probe_heads)[i0 + lane] : -1;
 #pragma unroll
-        for (int h = 0; h < HP; ++h) {
-          const bool hit = __builtin_amdgcn_ballot_w64(ph == head0 + h) != 0;
-          if (j == h) lane_probe = lane_probe || hit;
-        }
+      for (int h = 0; h < HP; ++h) {
+        const bool hit = __builtin_amdgcn_ballot_w64(ph == head0 + h) != 0;
+        if (j == h) lane_probe = lane_probe || hit;
       }
-      load_spans(p.key_spans, seq, p.S, sp_a, sp_b);
     }
   }
 
@@ -118,69 +183,68 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
   for (int h = 0; h < HP; ++h)
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[h][e] = 0.0f;
-  const float c = KV8 ? p.scale_log2 * p.k_scale[kvh] : p.scale_log2;
+  const float c = KV8 ? p.scale_log2 * cloadf(p.k_scale, kvh) : p.scale_log2;
 
-  constexpr int kRing = KV8 ? 3 : 2;                       // blocks in registers
-  constexpr int kKr = KV8 ? C::KSTEPS / 2 : C::KSTEPS;     // 16-byte K pieces per lane and block
-  uint4 kr[kRing][kKr];
-  uint4 vr[kRing][C::KPL];                                 // 8-bit cache: only .x, .y are used
-
-  auto load_block = [&](int b, uint4 (&kd)[kKr], uint4 (&vd)[C::KPL]) {
-    const int jb = (kstart >> 4) + b;                   // block index inside the sequence
-    int blk = bt[jb];
-    blk = ((unsigned)blk < (unsigned)p.num_blocks) ? blk : 0;
-    const int key_k = jb * kBlock + j;                  // this lane's key as a score-lane
-    const bool ok_k = key_k < kend;
-    if constexpr (KV8) {
-      const unsigned char* kb = kg8 + (size_t)blk * blk_stride + head_off;
-      const unsigned char* vb = vg8 + (size_t)blk * blk_stride + head_off;
-#pragma unroll
-      for (int h = 0; h < kKr; ++h) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (ok_k) v = load_stream16(kb + (size_t)j * D + 64 * h + 16 * kq);
-        kd[h] = v;
-      }
-#pragma unroll
-      for (int i = 0; i < C::KPL; ++i) {
-        const int kl = C::KPL * vk + i;
-        uint2 v = make_uint2(0, 0);
-        if (jb * kBlock + kl < kend) v = *reinterpret_cast<const uint2*>(vb + (size_t)kl * D + 8 * ch);
-        vd[i] = make_uint4(v.x, v.y, 0, 0);
-      }
-    } else {
-      const __bf16* kb = kg_ + (size_t)blk * blk_stride + head_off;
-      const __bf16* vb = vg_ + (size_t)blk * blk_stride + head_off;
-#pragma unroll
-      for (int s = 0; s < C::KSTEPS; ++s) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (ok_k) v = load_stream16(kb + (size_t)j * D + 32 * s + 8 * kq);
-        kd[s] = v;
-      }
-#pragma unroll
-      for (int i = 0; i < C::KPL; ++i) {
-        const int kl = C::KPL * vk + i;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (jb * kBlock + kl < kend) v = load_stream16(vb + (size_t)kl * D + 8 * ch);
-        vd[i] = v;
-      }
-    }
-  };
-
-  auto compute_block = [&](int b, const uint4 (&kd)[kKr], const uint4 (&vd)[C::KPL]) {
+  auto compute_block = [&](int b, Block& d) {
     const int key0 = kstart + b * kBlock;
+    const bool last = key0 + kBlock >= kend;     // uniform
+    if (last) {
+      const int r = new_pos - key0;        // the new row's place in this block
+      if (new_pos >= 0 && r < kBlock) {    // uniform
+        store_new = store_new && (unsigned)cload(bt, b) < (unsigned)p.num_blocks;   // a clamped id is not written to
+        const char* kn = reinterpret_cast<const char*>(in_global(p.kvw.k_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
+        const char* vn = reinterpret_cast<const char*>(in_global(p.kvw.v_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
+        const size_t off = (size_t)(unsigned)__builtin_amdgcn_readlane(ids, (b - b0) & 63) * blk_bytes;
+        char* kdst = const_cast<char*>(kbase) + off;
+        char* vdst = const_cast<char*>(vbase) + off;
+        if (j == r) {
+#pragma unroll
+          for (int s = 0; s < kKr; ++s) {
+            uint4 v;
+            if constexpr (KV8) {
+              const uint4* src = reinterpret_cast<const uint4*>(kn + 2 * (64 * s + 16 * kq));
+              const float sc = cloadf(p.k_scale, kvh);
+              const uint2 lo = quantize_chunk_e4m3(src[0], sc), hi = quantize_chunk_e4m3(src[1], sc);
+              v = make_uint4(lo.x, lo.y, hi.x, hi.y);
+            } else {
+              v = *reinterpret_cast<const uint4*>(kn + 64 * s + 16 * kq);
+            }
+            d.k[s] = v;
+            if (store_new) *reinterpret_cast<uint4*>(kdst + koff + 64 * s) = v;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < C::KPL; ++i) {
+          if (C::KPL * vk + i == r) {
+            const uint4 raw = *reinterpret_cast<const uint4*>(vn + 16 * ch);
+            if constexpr (KV8) {
+              const uint2 v = quantize_chunk_e4m3(raw, cloadf(p.v_scale, kvh));
+              d.v[i] = make_uint4(v.x, v.y, 0, 0);
+              if (store_new) *reinterpret_cast<uint2*>(vdst + voff + i * D) = v;
+            } else {
+              d.v[i] = raw;
+              if (store_new) *reinterpret_cast<uint4*>(vdst + voff + i * D * 2) = raw;
+            }
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < C::KPL; ++i)           // 0 * NaN would poison the output
+        if (key0 + C::KPL * vk + i >= kend) d.v[i] = make_uint4(0, 0, 0, 0);
+    }
     f32x4 sacc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int s = 0; s < C::KSTEPS; ++s) {
       bf16x8 a;
       if constexpr (KV8) {
         // bytes 8 (s % 2) .. 8 (s % 2) + 7 of piece s / 2
-        const uint32_t w0 = (s & 1) ? kd[s >> 1].z : kd[s >> 1].x;
-        const uint32_t w1 = (s & 1) ? kd[s >> 1].w : kd[s >> 1].y;
+        const uint32_t w0 = (s & 1) ? d.k[s >> 1].z : d.k[s >> 1].x;
+        const uint32_t w1 = (s & 1) ? d.k[s >> 1].w : d.k[s >> 1].y;
         const uint4 cv = make_uint4(fp8x2_to_bf16x2(w0, false), fp8x2_to_bf16x2(w0, true),
                                     fp8x2_to_bf16x2(w1, false), fp8x2_to_bf16x2(w1, true));
         __builtin_memcpy(&a, &cv, 16);
       } else {
-        __builtin_memcpy(&a, &kd[s], 16);
+        __builtin_memcpy(&a, &d.k[s], 16);
       }
       sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[s], sacc, 0, 0, 0);
     }
@@ -189,7 +253,11 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       tt[r] = sacc[r] * c;
-      if (key0 + 4 * kq + r >= kend) tt[r] = -INFINITY;
+    }
+    if (last) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (key0 + 4 * kq + r >= kend) tt[r] = -INFINITY;
     }
     const float bm = fmaxf(fmaxf(tt[0], tt[1]), fmaxf(tt[2], tt[3]));
     const bool upd = bm > m_run + kLazyTau;
@@ -199,12 +267,11 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
       l_run *= alpha;
 #pragma unroll
       for (int s = 0; s < kMaxSpans; ++s) am[s] *= alpha;
+      static_for<HP>([&](auto h) {
+        const float ah = row_bcast<decltype(h)::value>(alpha);
 #pragma unroll
-      for (int h = 0; h < HP; ++h) {
-        const float ah = __shfl(alpha, src_base + h);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[h][e] *= ah;
-      }
+        for (int e = 0; e < 8; ++e) acc[decltype(h)::value][e] *= ah;
+      });
     }
     const float m_safe = (m_run == -INFINITY) ? 0.0f : m_run;
     float pr[4];
@@ -235,61 +302,51 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     // P V on the value lanes
 #pragma unroll
     for (int i = 0; i < C::KPL; ++i) {
+      const uint4 v = d.v[i];
       float vf[8];
       if constexpr (KV8) {
-        const f32x2 a0 = __builtin_amdgcn_cvt_pk_f32_fp8(vd[i].x, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8(vd[i].x, true);
-        const f32x2 a2 = __builtin_amdgcn_cvt_pk_f32_fp8(vd[i].y, false), a3 = __builtin_amdgcn_cvt_pk_f32_fp8(vd[i].y, true);
+        const f32x2 a0 = __builtin_amdgcn_cvt_pk_f32_fp8(v.x, false), a1 = __builtin_amdgcn_cvt_pk_f32_fp8(v.x, true);
+        const f32x2 a2 = __builtin_amdgcn_cvt_pk_f32_fp8(v.y, false), a3 = __builtin_amdgcn_cvt_pk_f32_fp8(v.y, true);
         vf[0] = a0[0]; vf[1] = a0[1]; vf[2] = a1[0]; vf[3] = a1[1];
         vf[4] = a2[0]; vf[5] = a2[1]; vf[6] = a3[0]; vf[7] = a3[1];
       } else {
-        vf[0] = bf16_lo(vd[i].x); vf[1] = bf16_hi(vd[i].x);
-        vf[2] = bf16_lo(vd[i].y); vf[3] = bf16_hi(vd[i].y);
-        vf[4] = bf16_lo(vd[i].z); vf[5] = bf16_hi(vd[i].z);
-        vf[6] = bf16_lo(vd[i].w); vf[7] = bf16_hi(vd[i].w);
+        vf[0] = bf16_lo(v.x); vf[1] = bf16_hi(v.x);
+        vf[2] = bf16_lo(v.y); vf[3] = bf16_hi(v.y);
+        vf[4] = bf16_lo(v.z); vf[5] = bf16_hi(v.z);
+        vf[6] = bf16_lo(v.w); vf[7] = bf16_hi(v.w);
       }
-#pragma unroll
-      for (int h = 0; h < HP; ++h) {
-        float ph;
+      // the exponential of this lane's key i sits in register i (four keys per lane), or in register
+      // 2 (vk % 2) + i (two keys per lane)
+      static_for<HP>([&](auto h) {
+        float phv;
         if constexpr (C::KPL == 4) {
-          ph = __shfl(pr[i], src_base + h);
+          phv = row_bcast<decltype(h)::value>(pr[i]);
         } else {
-          const float lo = __shfl(pr[i], src_base + h);
-          const float hi = __shfl(pr[2 + i], src_base + h);
-          ph = (vk & 1) ? hi : lo;
+          const float lo = row_bcast<decltype(h)::value>(pr[i]);
+          const float hi = row_bcast<decltype(h)::value>(pr[(2 + i) & 3]);
+          phv = (vk & 1) ? hi : lo;
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[h][e] = __builtin_fmaf(ph, vf[e], acc[h][e]);
-      }
+        for (int e = 0; e < 8; ++e) acc[decltype(h)::value][e] = __builtin_fmaf(phv, vf[e], acc[decltype(h)::value][e]);
+      });
+      __builtin_amdgcn_sched_barrier(0);   // one key's widened values at a time
     }
   };
 
-  if constexpr (KV8) {
-    // stream this wave's blocks, two blocks of loads in flight ahead of the arithmetic
-    if (b0 < b1) load_block(b0, kr[0], vr[0]);
-    if (b0 + 1 < b1) load_block(b0 + 1, kr[1], vr[1]);
-    for (int b = b0; b < b1; b += 3) {
-      if (b + 2 < b1) load_block(b + 2, kr[2], vr[2]);
-      compute_block(b, kr[0], vr[0]);
-      if (b + 1 < b1) {
-        if (b + 3 < b1) load_block(b + 3, kr[0], vr[0]);
-        compute_block(b + 1, kr[1], vr[1]);
-      }
-      if (b + 2 < b1) {
-        if (b + 4 < b1) load_block(b + 4, kr[1], vr[1]);
-        compute_block(b + 2, kr[2], vr[2]);
-      }
+  // stream this wave's blocks with the next block's loads in flight during the arithmetic on this one
+  for (int b = b0; b < b1; b += 2) {
+    load_block(b + 1, ring[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    compute_block(b, ring[0]);
+    if (((b + 2 - b0) & 63) == 0) {      // the next 64 block ids
+      ids = ids_next;
+      ids_next = load_ids(b + 2 + 64);
     }
-  } else {
-    // stream this wave's blocks, one block of loads in flight ahead of the arithmetic
-    if (b0 < b1) load_block(b0, kr[0], vr[0]);
-    for (int b = b0; b < b1; b += 2) {
-      if (b + 1 < b1) load_block(b + 1, kr[1], vr[1]);
-      compute_block(b, kr[0], vr[0]);
-      if (b + 1 < b1) {
-        if (b + 2 < b1) load_block(b + 2, kr[0], vr[0]);
-        compute_block(b + 1, kr[1], vr[1]);
-      }
-    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_block(b + 2, ring[0]);
+    __builtin_amdgcn_sched_barrier(0);
+    if (b + 1 < b1) compute_block(b + 1, ring[1]);
+    __builtin_amdgcn_sched_barrier(0);
   }
 
   // merge the key-group streams of this wave
@@ -307,18 +364,17 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     v += __shfl_xor(v, 32);
     am_w[s] = v;
   }
-#pragma unroll
-  for (int h = 0; h < HP; ++h) {
-    const float wh = __shfl(wgt, src_base + h);
+  static_for<HP>([&](auto h) {
+    const float wh = row_bcast<decltype(h)::value>(wgt);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      float v = acc[h][e] * wh;
+      float v = acc[decltype(h)::value][e] * wh;
       if constexpr (C::VK == 8) v += __shfl_xor(v, 8);
       v += __shfl_xor(v, 16);
       v += __shfl_xor(v, 32);
-      acc[h][e] = v;
+      acc[decltype(h)::value][e] = v;
     }
-  }
+  });
   // lanes with vk == 0 hold o[h][8 ch + e]; score lanes with kq == 0 hold (m, l, a) of head j
   if (vk == 0) {
 #pragma unroll
@@ -335,7 +391,7 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
   __syncthreads();
 
   // merge the 4 waves and write one partial record per head
-  const float vscale = KV8 ? p.v_scale[kvh] : 1.0f;
+  const float vscale = KV8 ? cloadf(p.v_scale, kvh) : 1.0f;
   for (int idx = tid; idx < HP * C::PSTR; idx += 256) {
     const int h = idx / C::PSTR, col = idx % C::PSTR;
     float mm = red[0][h][D];
@@ -353,210 +409,329 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
       }
       if (KV8 && col < D) out *= vscale;
     }
-    p.partials[((size_t)item * p.Hq + head0 + h) * C::PSTR + col] = out;
+    in_global(p.partials)[((size_t)item * p.Hq + head0 + h) * C::PSTR + col] = out;
   }
 }
 
-// SELF: the variant for batches of few single rows, where the planning launch is a large part of
-// the call.  Every sequence is cut into the same number of parts (p.dec_parts, chosen on the host so
-// that the grid fills the chip and the records fit the workspace) and a workgroup works out its own
-// part from the sequence length, so no planner runs: part 0 of a sequence also zero-fills the
-// sequence's `mass` entries and tells the merge kernel how many records to expect, and workgroup 0
-// writes the status word.
-template <int D, int HP, bool KV8, bool SELF>
-__global__ __launch_bounds__(256) void k_decode(const AttnParams p) {
-  using C = DecodeCfg<D>;
-  constexpr int NW = 4;
-  __shared__ float red[NW][HP][C::PSTR];
+// What a batch of single rows looks like to the kernel that plans itself: cache blocks of sequence i to
+// stream, 0 where there is nothing to compute.
+struct DecodeSeq { int L, qrow, nblk, bits; };
 
+__device__ __forceinline__ DecodeSeq decode_seq(const AttnParams& p, int Lraw, int r0, int r1) {
+  const int max_ctx = p.max_blocks * kBlock, n = r1 - r0;
+  DecodeSeq s = {min(Lraw, max_ctx), r0, 0, 0};
+  if (Lraw < 0 || n < 0) { s.bits = kStatNegative; return s; }
+  if (Lraw > max_ctx) s.bits |= kStatLenClamped;
+  if (n > s.L) s.bits |= kStatQGtL;
+  else if (r0 < 0 || r0 + n > p.total_q) s.bits |= kStatNegative;
+  else if (n > 1) s.bits |= kStatHint;          // a row block in a batch promised to hold single rows
+  else if (n == 1) s.nblk = (s.L + kBlock - 1) / kBlock;
+  return s;
+}
+
+// The planner's items: one (sequence, chunk) per workgroup, longest first.
+template <int D, int HP, bool KV8>
+__global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParams p) {
+  __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bid = blockIdx.x;
   const int kvh = bid % p.Hkv;
   const int rest = bid / p.Hkv;
   const int hg = rest % p.dec_hgroups;
   const int turn = rest / p.dec_hgroups;
-  const int head0 = kvh * p.G + hg * HP;
-  int seq, L, qrow, kstart, kend, item;
-  bool active = true;
-  // what this workgroup owes besides its part (SELF only; stores, so kept behind every load of the
-  // batch description: a store ahead of them would turn those scalar loads into vector loads)
-  bool owes_seq = false;      // zero-fill the sequence's `mass` entries of its heads, announce the record count
-  int n_records = 0;
-  auto settle = [&]() {
-    if constexpr (SELF) {
-      if (owes_seq) {
-        // (a reusing call keeps its promise of writing selected rows only; the merge kernel fills
-        // the selected entries in afterwards)
-        if (p.P > 0 && p.plan_fresh) {
-          const int per = p.NQ * p.S;
-          for (int ps = 0; ps < p.P; ++ps) {
-            const int ph = p.probe_heads[ps];
-            if (ph >= head0 && ph < head0 + HP)
-              for (int e = tid; e < per; e += 256) p.mass[((size_t)seq * p.P + ps) * per + e] = 0.0f;
-          }
-        }
-        if (kvh == 0 && hg == 0 && tid == 0) p.seq_dec[seq] = make_int2(seq * p.dec_parts, n_records);
-      }
-      if (bid == 0) {   // the status word a planner would have written: one pass over the batch
-        __shared__ int sh_status;
-        if (tid == 0) sh_status = 0;
-        __syncthreads();
-        const int max_ctx = p.max_blocks * kBlock;
-        int bits = 0;
-        for (int i = tid; i < p.num_seqs; i += 256) {
-          const int Li = p.seq_lens[i], r0 = p.cu_q_lens[i], ni = p.cu_q_lens[i + 1] - r0;
-          if (Li < 0 || ni < 0) { bits |= kStatNegative; continue; }
-          if (Li > max_ctx) bits |= kStatLenClamped;
-          if (ni > min(Li, max_ctx)) bits |= kStatQGtL;
-          else if (r0 < 0 || r0 + ni > p.total_q) bits |= kStatNegative;
-          else if (ni > 1) bits |= kStatHint;   // a row block in a batch promised to hold single rows
-        }
-        if (bits) atomicOr(&sh_status, bits);
-        __syncthreads();
-        if (tid == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = sh_status; }
-      }
-    }
-  };
-  if constexpr (SELF) {
-    const int P = p.dec_parts;
-    seq = turn / P;
-    const int part = turn - seq * P;
-    const int Lraw = p.seq_lens[seq];
-    qrow = p.cu_q_lens[seq];
-    const int n = p.cu_q_lens[seq + 1] - qrow;
-    L = min(Lraw, p.max_blocks * kBlock);
-    const bool valid = Lraw >= 0 && n == 1 && L >= 1 && qrow >= 0 && qrow < p.total_q;
-    const int nblk_seq = valid ? (L + kBlock - 1) / kBlock : 0;
-    const int bpp = (nblk_seq + P - 1) / P;          // cache blocks per part
-    owes_seq = part == 0;
-    n_records = valid ? (nblk_seq + bpp - 1) / bpp : 0;
-    active = valid && part * bpp < nblk_seq;   // uniform over the workgroup
-    // (all of this is uniform over the workgroup; saying so keeps it out of the vector registers)
-    kstart = __builtin_amdgcn_readfirstlane(part * bpp * kBlock);
-    kend = __builtin_amdgcn_readfirstlane(min(L, kstart + bpp * kBlock));
-    qrow = __builtin_amdgcn_readfirstlane(qrow);
-    seq = __builtin_amdgcn_readfirstlane(seq);
-    item = turn;
-  } else {
-    // the grid covers the whole item capacity, so the turn's records (longest chunks first) can be
-    // fetched together with the item count instead of after it
-    const WorkItem it = p.dec_items[2 * turn];
-    const int slot = p.dec_items[2 * turn + 1].x;
-    if (turn >= p.hdr->n_decode) return;
-    // the clamp only matters if the planner's capacity bound were ever violated
-    item = min(max(slot, 0), p.dec_cap - 1);
-    seq = it.x; L = it.z; qrow = it.w;
-    const int CH = p.hdr->chunk_keys;
-    kstart = it.y * CH;
-    kend = min(L, kstart + CH);
-  }
-
-  if (active) decode_range<D, HP, KV8>(p, red, tid, lane, w, kvh, head0, seq, qrow, kstart, kend, item);
-  settle();
+  // the grid covers the whole item capacity, so the turn's records can be fetched together with the
+  // item count instead of after it
+  const WorkItem it = p.dec_items[2 * turn];
+  const int slot = p.dec_items[2 * turn + 1].x;
+  if (turn >= p.hdr->n_decode) return;
+  // the clamp only matters if the planner's capacity bound were ever violated
+  const int item = min(max(slot, 0), p.dec_cap - 1);
+  const int CH = p.hdr->chunk_keys;
+  const int kstart = it.y * CH;
+  decode_range<D, HP, KV8>(p, red, tid, tid & 63, w, kvh, kvh * p.G + hg * HP, it.x, it.w, kstart, min(it.z, kstart + CH),
+                           item, -1, false);
 }
 
-// One workgroup per (sequence, 4 q heads): wave = head, lane = output columns.
-template <int D>
-__global__ __launch_bounds__(256) void k_combine(const AttnParams p) {
-  using C = DecodeCfg<D>;
-  const int seq = blockIdx.x;
-  const int2 sd = p.seq_dec[seq];
-  if (sd.y <= 0) return;
-  const int lane = threadIdx.x & 63;
-  const int head = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (head >= p.Hq) return;
-  const float* rec0 = p.partials + ((size_t)sd.x * p.Hq + head) * C::PSTR;
-  const size_t rstride = (size_t)p.Hq * C::PSTR;
+// A batch of single rows that plans itself.  The cache blocks of all its sequences, laid end to end, are cut
+// into p.dec_ranges equal ranges (one resident round of workgroups per kv head and head group), so every
+// workgroup streams the same number of blocks however ragged the contexts are; a range may cover the end of
+// one sequence and the beginning of the next.  A workgroup finds its range by a scan over the lengths (each
+// wave on its own, lane l takes sequences l K .. l K + K - 1), which costs about a microsecond instead of a
+// planning launch (8 us).  Range g and sequence i share at most one piece and the path through the pairs is a
+// staircase, so g + i numbers the partial records without gaps between the records of one sequence.
+constexpr int kScanPerLane = kStreamMaxSeqs / 64;
 
-  // The records were written by other workgroups, possibly under another L2, so every first touch
-  // pays a trip to memory: the chunks' (max, sum) pairs are fetched one per lane in one go, and the
-  // accumulation below keeps four records in flight instead of walking them one by one.
-  float mstar = -INFINITY;
-  for (int c0 = 0; c0 < sd.y && sd.y > 1; c0 += 64) {
-    const float mc = (c0 + lane < sd.y) ? rec0[(size_t)(c0 + lane) * rstride + D] : -INFINITY;
-    mstar = fmaxf(mstar, mc);
-  }
+// Inclusive prefix sum over the wave with DPP moves: inside the rows of 16 lanes, then across them.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+struct BlockScan {
+  int K;                        // sequences per lane
+  int nblk[kScanPerLane];       // blocks of this lane's sequences
+  int L[kScanPerLane], qrow[kScanPerLane];
+  int excl;                     // blocks in front of this lane's first sequence
+  int total;                    // blocks of the batch
+  int bpr;                      // blocks per range
+  int bits;                     // status bits of this lane's sequences
+};
+
+__device__ __forceinline__ BlockScan scan_blocks(const AttnParams& p, int lane) {
+  BlockScan sc;
+  sc.K = (p.num_seqs + 63) >> 6;
+  sc.bits = 0;
+  int sum = 0;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mstar = fmaxf(mstar, __shfl_xor(mstar, off));
-  float l = 0.0f;
-  float o[D / 64];
-#pragma unroll
-  for (int e = 0; e < D / 64; ++e) o[e] = 0.0f;
-  float a = 0.0f;  // lane s < S merges span s
-  if (sd.y == 1) {   // a single chunk needs no weights: its record is the result up to the division
-    l = rec0[D + 1];
-#pragma unroll
-    for (int e = 0; e < D / 64; ++e) o[e] = rec0[lane + 64 * e];
-    if (lane < kMaxSpans) a = rec0[D + 2 + lane];
-  }
-  for (int c0 = 0; c0 < sd.y && sd.y > 1; c0 += 64) {
-    // lane c holds the weight of chunk c0 + c
-    float wl = 0.0f, wgt_mine = 0.0f;
-    if (c0 + lane < sd.y) {
-      const float* rec = rec0 + (size_t)(c0 + lane) * rstride;
-      const float mc = rec[D];
-      wgt_mine = (mc == -INFINITY) ? 0.0f : fast_exp2(mc - mstar);
-      wl = wgt_mine * rec[D + 1];
+  for (int u = 0; u < kScanPerLane; ++u) {
+    sc.nblk[u] = sc.L[u] = sc.qrow[u] = 0;
+    const int i = lane * sc.K + u;
+    if (u < sc.K && i < p.num_seqs) {
+      const DecodeSeq s = decode_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
+      sc.nblk[u] = s.nblk;
+      sc.L[u] = s.L;
+      sc.qrow[u] = s.qrow;
+      sc.bits |= s.bits;
     }
+    sum += sc.nblk[u];
+  }
+  const int incl = wave_scan(sum);
+  sc.excl = incl - sum;
+  sc.total = __builtin_amdgcn_readlane(incl, 63);
+  sc.bpr = max((sc.total + p.dec_ranges - 1) / p.dec_ranges, kStreamMinBlocks);
+  return sc;
+}
+
+template <int D, int HP, bool KV8>
+__global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const AttnParams p) {
+  __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int bid = blockIdx.x;
+  const int kvh = bid % p.Hkv;
+  const int rest = bid / p.Hkv;
+  const int hg = rest % p.dec_hgroups;
+  const int g = rest / p.dec_hgroups;
+
+  const BlockScan sc = scan_blocks(p, lane);
+
+  int x = g * sc.bpr;
+  const int x1 = min(sc.total, x + sc.bpr);
+  if (x >= x1) return;
+  // the sequence that block x belongs to, and x's place in it
+  int seq, o, L, qrow;
+  {
+    int my_seq = 0, my_o = 0, my_L = 0, my_row = 0, start = sc.excl;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) wl += __shfl_xor(wl, off);
-    l += wl;
-    const int nc = min(64, sd.y - c0);
-    int c = 0;
-    for (; c + 4 <= nc; c += 4) {
-      float v[4][D / 64], sp[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float* rec = rec0 + (size_t)(c0 + c + u) * rstride;
-#pragma unroll
-        for (int e = 0; e < D / 64; ++e) v[u][e] = rec[lane + 64 * e];
-        sp[u] = (lane < kMaxSpans) ? rec[D + 2 + lane] : 0.0f;
+    for (int u = 0; u < kScanPerLane; ++u) {
+      if (x >= start && x < start + sc.nblk[u]) {
+        my_seq = lane * sc.K + u;
+        my_o = x - start;
+        my_L = sc.L[u];
+        my_row = sc.qrow[u];
       }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const float wg = __shfl(wgt_mine, c + u);
-#pragma unroll
-        for (int e = 0; e < D / 64; ++e) o[e] += wg * v[u][e];
-        a += wg * sp[u];
-      }
+      start += sc.nblk[u];
     }
-    for (; c < nc; ++c) {
-      const float* rec = rec0 + (size_t)(c0 + c) * rstride;
-      const float wg = __shfl(wgt_mine, c);
-#pragma unroll
-      for (int e = 0; e < D / 64; ++e) o[e] += wg * rec[lane + 64 * e];
-      if (lane < kMaxSpans) a += wg * rec[D + 2 + lane];
-    }
+    const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(x >= sc.excl && x < start));
+    seq = __builtin_amdgcn_readlane(my_seq, from);
+    o = __builtin_amdgcn_readlane(my_o, from);
+    L = __builtin_amdgcn_readlane(my_L, from);
+    qrow = __builtin_amdgcn_readlane(my_row, from);
   }
-  const float inv = 1.0f / l;
+  const int head0 = kvh * p.G + hg * HP;
+  for (;;) {
+    const int take = min((L + kBlock - 1) / kBlock - o, x1 - x);
+    const int kend = min(L, (o + take) * kBlock);
+    // (a length beyond the block table is clamped: its new row has no place in the cache)
+    const bool has_new = p.kvw.k_new != nullptr && kend == L && cload(p.seq_lens, seq) == L;
+    // Arguments and lane number are made opaque per piece: otherwise everything derived from them is kept in
+    // registers across the loop (60 vector registers spilled instead of a few instructions repeated).
+    const AttnParams& pp = reread_arguments();
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    decode_range<D, HP, KV8>(pp, red, w * 64 + ln, ln, w, kvh, head0, seq, qrow, o * kBlock, kend, g + seq, has_new ? L - 1 : -1,
+                             hg == 0);
+    // where the merge kernel finds the sequence's records
+    if (o == 0 && kvh == 0 && hg == 0 && tid == 0)
+      p.seq_dec[seq] = make_int2(g + seq, (x + (L + kBlock - 1) / kBlock - 1) / sc.bpr - g + 1);
+    x += take;
+    if (x >= x1) break;
+    __syncthreads();      // `red` is written again
+    DecodeSeq s;
+    do {
+      ++seq;
+      s = decode_seq(p, cload(p.seq_lens, seq), cload(p.cu_q_lens, seq), cload(p.cu_q_lens, seq + 1));
+    } while (s.nblk == 0 && seq + 1 < p.num_seqs);
+    if (s.nblk == 0) break;     // (never: x < total says that there is one)
+    o = 0;
+    L = s.L;
+    qrow = s.qrow;
+  }
+}
+
+// What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word, and
+// the cache write of rows that contradict the hint (they are not computed, so no workgroup meets them while streaming).
+template <int NT>
+__device__ __forceinline__ void settle_batch(const AttnParams& p) {
+  __shared__ long long dst_row[kKvRowTile];
+  __shared__ int sh_bits;
+  if (threadIdx.x == 0) sh_bits = 0;
+  __syncthreads();
+  int bits = 0;
+  for (int i = threadIdx.x; i < p.num_seqs; i += NT)
+    bits |= decode_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]).bits;
+  if (bits) atomicOr(&sh_bits, bits);
+  __syncthreads();
+  bits = sh_bits;
+  if (threadIdx.x == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = bits; }
+  if ((bits & kStatHint) && p.kvw.k_new != nullptr) {
+    const int ntiles = (p.total_q + kKvRowTile - 1) / kKvRowTile;
+    for (int t = 0; t < ntiles; ++t) kv_write_tile<NT>(p.kvw, t, threadIdx.x, dst_row);
+  }
+}
+
+// Merges the partial records of a sequence: WPH waves per q head take its records in turn (a workgroup is
+// max(4, WPH) waves), lane = output columns.  In a self-planned batch the wave that owns a probed head also
+// zero-fills the `mass` slots without a row.  Every first touch of a record is a trip to memory (other
+// workgroups wrote them under other L2s), and trips are all this kernel's time, so a wave requests
+// kInFlight whole records before it waits for any: as long as a sequence has at most WPH * kInFlight records
+// there are two trips, the record count and the records.
+template <int D, int WPH>
+__global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const AttnParams p) {
+  using C = DecodeCfg<D>;
+  constexpr int kInFlight = WPH == 1 ? 4 : 8, E = D / 64, NWV = WPH > 4 ? WPH : 4;
+  __shared__ float sh_o[WPH > 1 ? NWV : 1][D + kMaxSpans];
+  __shared__ float sh_m[NWV], sh_l[NWV];
+  const int seq = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % WPH;
+  const int head = blockIdx.y * (NWV / WPH) + wave / WPH;
+  const bool stream = p.dec_ranges > 0;
+  int2 sd = p.seq_dec[seq];
   const int qrow = p.cu_q_lens[seq];
-  __bf16* og = static_cast<__bf16*>(p.out) + ((size_t)qrow * p.Hq + head) * D;
-#pragma unroll
-  for (int e = 0; e < D / 64; ++e) og[lane + 64 * e] = (__bf16)(o[e] * inv);
-  if (p.P > 0 && lane < p.S) {
+  // (the clamps only matter if the work lists were not this batch's: no record outside the workspace is read)
+  sd.x = min(max(sd.x, 0), p.dec_cap - 1);
+  int count = min(sd.y, p.dec_cap - sd.x);
+  // (a self-planned batch announces records only for sequences that have some)
+  if (stream && decode_seq(p, p.seq_lens[seq], qrow, p.cu_q_lens[seq + 1]).nblk == 0) count = 0;
+  if (count <= 0 && !stream) return;
+  const bool live = head < p.Hq && count > 0;
+
+  int pslot = -1, slot_row = -1;       // this head's place in the probe list; the selected row's slot, -1: none
+  if (p.P > 0 && head < p.Hq) {
+    for (int i0 = 0; i0 < p.P; i0 += 64) {
+      const int ph = i0 + lane < p.P ? p.probe_heads[i0 + lane] : -1;
+      const unsigned long long hit = __builtin_amdgcn_ballot_w64(ph == head);
+      if (hit) { pslot = i0 + __builtin_ctzll(hit); break; }
+    }
+    // row t = 0 sits in slot t - begin, as on every other path
     const int qb = p.query_sel[2 * seq], qe = min(p.query_sel[2 * seq + 1], qb + p.NQ);
-    if (qb <= 0 && qe > 0) {   // row t = 0 sits in slot t - begin, as on every other path
-      const int pslot = find_probe_slot(p.probe_heads, p.P, head);
-      if (pslot >= 0) p.mass[(((size_t)seq * p.P + pslot) * p.NQ + (-qb)) * p.S + lane] = a * inv;
+    if (qb <= 0 && qe > 0) slot_row = -qb;
+  }
+
+  float m = -INFINITY, l = 0.0f, a = 0.0f;   // a: lane s < S merges span s
+  float o[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) o[e] = 0.0f;
+  if (live) {
+    const size_t rstride = (size_t)p.Hq * C::PSTR;
+    const float* rec0 = p.partials + ((size_t)sd.x * p.Hq + head) * C::PSTR;
+    for (int c = part; c < count; c += kInFlight * WPH) {
+      float v[kInFlight][E], sp[kInFlight], rm[kInFlight], rl[kInFlight];
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const float* r = rec0 + (size_t)min(c + u * WPH, count - 1) * rstride;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[u][e] = r[E * lane + e];
+        sp[u] = (lane < kMaxSpans) ? r[D + 2 + lane] : 0.0f;
+        rm[u] = c + u * WPH < count ? r[D] : -INFINITY;
+        rl[u] = r[D + 1];
+      }
+      float mn = m;
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) mn = fmaxf(mn, rm[u]);
+      const float keep = fast_exp2(m - mn);        // mn is finite: record c exists
+      m = mn;
+      l *= keep;
+      a *= keep;
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] *= keep;
+#pragma unroll
+      for (int u = 0; u < kInFlight; ++u) {
+        const float wg = fast_exp2(rm[u] - mn);
+        l = __builtin_fmaf(wg, rl[u], l);
+        a = __builtin_fmaf(wg, sp[u], a);
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(wg, v[u][e], o[e]);
+      }
     }
   }
+  if constexpr (WPH > 1) {
+    if (lane == 0) { sh_m[wave] = m; sh_l[wave] = l; }
+#pragma unroll
+    for (int e = 0; e < E; ++e) sh_o[wave][E * lane + e] = o[e];
+    if (lane < kMaxSpans) sh_o[wave][D + lane] = a;
+    __syncthreads();
+    if (part == 0 && live) {
+      float mn = m;
+#pragma unroll
+      for (int k = 1; k < WPH; ++k) mn = fmaxf(mn, sh_m[wave + k]);
+      const float keep = fast_exp2(m - mn);
+      l *= keep;
+      a *= keep;
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] *= keep;
+#pragma unroll
+      for (int k = 1; k < WPH; ++k) {
+        const float wg = fast_exp2(sh_m[wave + k] - mn);
+        l = __builtin_fmaf(wg, sh_l[wave + k], l);
+        if (lane < kMaxSpans) a = __builtin_fmaf(wg, sh_o[wave + k][D + lane], a);
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(wg, sh_o[wave + k][E * lane + e], o[e]);
+      }
+    }
+  }
+  if (part == 0) {
+    const float inv = 1.0f / l;
+    if (live) {
+      __bf16* og = static_cast<__bf16*>(p.out) + ((size_t)qrow * p.Hq + head) * D;
+      if constexpr (E == 2) reinterpret_cast<uint32_t*>(og)[lane] = pack_bf16(o[0] * inv, o[1] * inv);
+      else og[lane] = (__bf16)(o[0] * inv);
+    }
+    if (pslot >= 0) {
+      float* const mass = p.mass + ((size_t)seq * p.P + pslot) * p.NQ * p.S;
+      const bool has = live && slot_row >= 0;
+      if (has && lane < p.S) mass[slot_row * p.S + lane] = a * inv;
+      if (stream && p.plan_fresh) {
+        const int lo = has ? slot_row * p.S : 0, hi = has ? lo + p.S : 0;
+        for (int e = lane; e < p.NQ * p.S; e += 64)
+          if (e < lo || e >= hi) mass[e] = 0.0f;
+      }
+    }
+  }
+  if (stream && seq == 0 && blockIdx.y == 0) settle_batch<64 * NWV>(p);
 }
 
 template <int D, int HP>
 hipError_t launch_decode_dh(const AttnParams& p, hipStream_t st) {
+  if (p.dec_ranges > 0) {
+    const long long grid = (long long)p.dec_ranges * p.Hkv * p.dec_hgroups;
+    if (!grid_fits(grid)) return hipErrorInvalidValue;
+    if (p.kv8) hipLaunchKernelGGL((k_decode_stream<D, HP, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((k_decode_stream<D, HP, false>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    return hipGetLastError();
+  }
   const long long grid = (long long)p.dec_cap * p.Hkv * p.dec_hgroups;
   if (grid <= 0) return hipSuccess;
   if (!grid_fits(grid)) return hipErrorInvalidValue;
-  if (p.dec_parts > 0) {   // self-planned: the grid is exact
-    const long long sgrid = (long long)p.num_seqs * p.dec_parts * p.Hkv * p.dec_hgroups;
-    if (p.kv8) hipLaunchKernelGGL((k_decode<D, HP, true, true>), dim3((unsigned)sgrid), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((k_decode<D, HP, false, true>), dim3((unsigned)sgrid), dim3(256), 0, st, p);
-    return hipGetLastError();
-  }
-  if (p.kv8) hipLaunchKernelGGL((k_decode<D, HP, true, false>), dim3((unsigned)grid), dim3(256), 0, st, p);
-  else hipLaunchKernelGGL((k_decode<D, HP, false, false>), dim3((unsigned)grid), dim3(256), 0, st, p);
+  if (p.kv8) hipLaunchKernelGGL((k_decode<D, HP, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
+  else hipLaunchKernelGGL((k_decode<D, HP, false>), dim3((unsigned)grid), dim3(256), 0, st, p);
   return hipGetLastError();
 }
 
@@ -581,9 +756,17 @@ hipError_t launch_decode(const AttnParams& p, int D, hipStream_t st) {
 
 hipError_t launch_combine(const AttnParams& p, int D, hipStream_t st) {
   if (p.dec_cap <= 0 || p.num_seqs <= 0) return hipSuccess;
-  const dim3 grid((unsigned)p.num_seqs, (unsigned)((p.Hq + 3) / 4));
-  if (D == 128) hipLaunchKernelGGL(k_combine<128>, grid, dim3(256), 0, st, p);
-  else if (D == 64) hipLaunchKernelGGL(k_combine<64>, grid, dim3(256), 0, st, p);
+  // as many waves per head as let a sequence's records be fetched in one go: the planner's chunks are long, so
+  // its sequences have few records; a self-planned sequence has about ranges / num_seqs + 2
+  const int per_seq = p.dec_ranges > 0 ? p.dec_ranges / p.num_seqs + 2 : 1;
+  const int wph = per_seq > 32 ? 16 : per_seq > 4 ? 4 : 1;
+  const dim3 grid((unsigned)p.num_seqs, (unsigned)(wph == 1 ? (p.Hq + 3) / 4 : p.Hq));
+  if (D == 128 && wph == 16) hipLaunchKernelGGL((k_combine<128, 16>), grid, dim3(1024), 0, st, p);
+  else if (D == 128 && wph == 4) hipLaunchKernelGGL((k_combine<128, 4>), grid, dim3(256), 0, st, p);
+  else if (D == 128) hipLaunchKernelGGL((k_combine<128, 1>), grid, dim3(256), 0, st, p);
+  else if (D == 64 && wph == 16) hipLaunchKernelGGL((k_combine<64, 16>), grid, dim3(1024), 0, st, p);
+  else if (D == 64 && wph == 4) hipLaunchKernelGGL((k_combine<64, 4>), grid, dim3(256), 0, st, p);
+  else if (D == 64) hipLaunchKernelGGL((k_combine<64, 1>), grid, dim3(256), 0, st, p);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }

@@ -27,6 +27,10 @@ constexpr int kPlanBuckets = 2048;  // counting-sort buckets (tile counts) of th
 constexpr int kChunkSizes = 5;
 constexpr int kMaxChunkKeys = 512 << (kChunkSizes - 1);
 constexpr int kDecodeFillWgs = 2048;
+// Batches of single rows with at most this many sequences plan themselves (decode.hip); a range of
+// blocks is never shorter than one block per wave of a workgroup.
+constexpr int kStreamMaxSeqs = 512;
+constexpr int kStreamMinBlocks = 4;
 // A running maximum is only raised when a tile's maximum exceeds it by more than this many
 // powers of two; exponentials then stay below 2^kLazyTau, far inside fp32 range, and the
 // normaliser carries the same reference, so the result is the exact softmax.
@@ -94,9 +98,9 @@ struct AttnParams {
   int pf_cap;
   WorkItem* dec_items;              // two records per turn, longest chunks first: {seq, chunk, L, q row}, {partial slot, -, -, -}
   int dec_cap;
-  int2* seq_dec;                    // per sequence {first decode item, number of chunks}
+  int2* seq_dec;                    // per sequence {first partial record, number of records}
   float* partials;                  // [dec_cap, Hq, D + kPartialPad]
-  int dec_parts;                    // > 0: no planner; every single-row sequence is cut into this many parts
+  int dec_ranges;                   // > 0: no planner; the blocks of all single rows are cut into this many ranges
   int plan_fresh;                   // the call promises a fully written `mass` (not a reused plan)
   int pf_self;                      // one sequence of query rows, head_dim 128: the chunk kernel plans itself
   // geometry chosen on the host from G
@@ -130,6 +134,27 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+typedef const __attribute__((address_space(1))) char* global_bytes;   // a pointer that is known to be global memory
+__device__ __forceinline__ uint4 load_stream16(global_bytes p) {
+  const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4*)p);
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint2 load_stream8(global_bytes p) {
+  const u32x2 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x2*)p);
+  return make_uint2(v.x, v.y);
+}
+
+// Element of an array that no kernel of the launch writes, at a uniform index: always a scalar load.  (Through
+// an ordinary pointer the compiler may only use one while no store can have come before it.)
+__device__ __forceinline__ int cload(const int* p, int i) {
+  return ((const __attribute__((address_space(4))) int*)p)[i];
+}
+
+__device__ __forceinline__ float cloadf(const float* p, int i) {
+  return ((const __attribute__((address_space(4))) float*)p)[i];
+}
+
 // 16-byte store of data that this kernel does not read again.
 __device__ __forceinline__ void store_stream16(void* p, const uint4 v) {
   u32x4 x;
@@ -161,6 +186,20 @@ __device__ __forceinline__ void load_spans(const int* key_spans, int seq, int S,
   for (int s = 0; s < kMaxSpans; ++s) {
     sp_a[s] = s < S ? max(v[s].x, 0) : 0;
     sp_b[s] = s < S ? v[s].y : 0;
+  }
+}
+
+// The same for a uniform `seq` on a path that has stored something before.
+__device__ __forceinline__ void load_spans_uniform(const int* key_spans, int seq, int S, int (&sp_a)[kMaxSpans],
+                                                   int (&sp_b)[kMaxSpans]) {
+  const int* sp = key_spans + (size_t)seq * S * 2;
+  int a[kMaxSpans], b[kMaxSpans];
+#pragma unroll
+  for (int s = 0; s < kMaxSpans; ++s) { a[s] = cload(sp, 2 * min(s, S - 1)); b[s] = cload(sp, 2 * min(s, S - 1) + 1); }
+#pragma unroll
+  for (int s = 0; s < kMaxSpans; ++s) {
+    sp_a[s] = s < S ? max(a[s], 0) : 0;
+    sp_b[s] = s < S ? b[s] : 0;
   }
 }
 
