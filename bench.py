@@ -27,8 +27,8 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 # until the counters are taken again.
 TRAFFIC = {
     # key: (bytes per launch, source files, hash of those files when the counters were taken)
-    "k_prefill128/c2": (797424994, ("prefill128.hip", "hook_device.h"), "2a8a49143a6fb91c"),
-    "k_prefill128/c4": (5191965184, ("prefill128.hip", "hook_device.h"), "2a8a49143a6fb91c"),
+    "k_prefill128/c2": (797424994, ("prefill.hip", "hook_device.h"), "2a8a49143a6fb91c"),
+    "k_prefill128/c4": (5191965184, ("prefill.hip", "hook_device.h"), "2a8a49143a6fb91c"),
     "k_decode/c3": (4910675161, ("decode.hip", "hook_device.h"), "6a4b00fc927a5ed1"),
     "k_decode/c3_fp8": (2440025513, ("decode.hip", "hook_device.h"), "6a4b00fc927a5ed1"),
 }
@@ -260,7 +260,7 @@ def main() -> int:
     flops2 = attn_flops(b2)
     ov2 = interleaved_overhead(call2, call2_off, max(10, K // 2), 3)
     value = flops2 / (t2["mean_ms"] * 1e-3) / 1e12
-    roofline = roofline_obj("mfma", "k_prefill128", flops2, k2["prefill_ms"], "k_prefill128/c2")
+    roofline = roofline_obj("mfma", "k_prefill<128>", flops2, k2["prefill_ms"], "k_prefill128/c2")
     pre_tflops = roofline["achieved"]
     cpu_baseline = None
     if not args.no_cpu_baseline:
@@ -349,7 +349,7 @@ def main() -> int:
         extra["single_prompt_2048"] = {
             "workload": "one prefill of 2048 tokens, 32 q / 8 kv heads, d 128, 8 probed heads, last row",
             "us_per_call_back_to_back": t1p * 1e3, "kernels_ms": k1p,
-            "roofline": roofline_obj("mfma", "k_prefill128", attn_flops(b1p), k1p["prefill_ms"])}
+            "roofline": roofline_obj("mfma", "k_prefill<128>", attn_flops(b1p), k1p["prefill_ms"])}
         del b1p, call1p
         torch.cuda.empty_cache()
 
@@ -363,7 +363,7 @@ def main() -> int:
         extra["prefill_c2_fp8_cache"] = {
             "workload": "c2_prefill_8b with 8-bit E4M3 key/value caches", "ms_per_step": t2q["mean_ms"],
             "kernels_ms": k2q,
-            "roofline": roofline_obj("mfma", "k_prefill<128,fp8>", attn_flops(b2q), k2q["prefill_ms"])}
+            "roofline": roofline_obj("mfma", "k_prefill<128,kv8>", attn_flops(b2q), k2q["prefill_ms"])}
         del b2q, call2q
         torch.cuda.empty_cache()
 
@@ -379,7 +379,7 @@ def main() -> int:
         extra["long_prefill_c4"] = {
             "workload": "c4_long_prefill_70b", "value": fl4 / (t4["mean_ms"] * 1e-3) / 1e12, "unit": "TFLOP/s",
             "ms_per_step": t4["mean_ms"], "kernels_ms": k4,
-            "roofline": roofline_obj("mfma", "k_prefill128", fl4, k4["prefill_ms"], "k_prefill128/c4"),
+            "roofline": roofline_obj("mfma", "k_prefill<128>", fl4, k4["prefill_ms"], "k_prefill128/c4"),
             "probe_overhead_pct": ov4["overhead_pct"],
         }
         if not args.no_cpu_baseline:
@@ -431,7 +431,7 @@ def main() -> int:
         extra["mixed_c5"] = {
             "workload": "c5_mixed", "attn_plus_steer_ms": t5["mean_ms"], "attn_ms": t5a["mean_ms"],
             "kernels_ms": k5,
-            "roofline_prefill": roofline_obj("mfma", "k_prefill128", fl5, k5["prefill_ms"]) if k5["prefill_ms"] > 0 else None,
+            "roofline_prefill": roofline_obj("mfma", "k_prefill<128>", fl5, k5["prefill_ms"]) if k5["prefill_ms"] > 0 else None,
             "roofline_decode": roofline_obj("hbm", "k_decode<128,4>", by5, k5["decode_ms"]) if k5["decode_ms"] > 0 else None,
             "roofline_max_ms": t_roof_ms, "roofline_sum_ms": t_sum_ms,
             "probe_overhead_pct": ov5["overhead_pct"],

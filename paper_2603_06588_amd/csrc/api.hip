@@ -193,9 +193,8 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.dec_hp = l.dec_hp; p.dec_hgroups = l.dec_hgroups;
   p.batch_kind = a->batch_kind;
   p.dec_ranges = a->batch_kind == HOOK_BATCH_DECODE_ONLY ? l.ranges : 0;
-  // a single prompt on its own needs no planner either (head_dim 128: the kernel that can plan for itself)
-  p.pf_self = a->dtype == HOOK_BF16 && a->head_dim == 128 && !kv8 && a->batch_kind == HOOK_BATCH_PREFILL_ONLY &&
-              a->num_seqs == 1;
+  // a single prompt on its own needs no planner either
+  p.pf_self = a->dtype == HOOK_BF16 && a->batch_kind == HOOK_BATCH_PREFILL_ONLY && a->num_seqs == 1;
   p.plan_fresh = a->plan_mode == HOOK_PLAN_FRESH;
 
   hipStream_t st = static_cast<hipStream_t>(a->stream);

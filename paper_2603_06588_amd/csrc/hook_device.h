@@ -139,6 +139,10 @@ __device__ __forceinline__ uint4 load_stream16(global_bytes p) {
   const u32x4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4*)p);
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+__device__ __forceinline__ uint4 load_global16(global_bytes p) {
+  const u32x4 v = *(const __attribute__((address_space(1))) u32x4*)p;
+  return make_uint4(v.x, v.y, v.z, v.w);
+}
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint2 load_stream8(global_bytes p) {
   const u32x2 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x2*)p);
@@ -172,6 +176,16 @@ __device__ __forceinline__ int find_probe_slot(const int* probe_heads, int P, in
     if (probe_heads[mid] < head) lo = mid + 1; else hi = mid;
   }
   return (lo < P && probe_heads[lo] == head) ? lo : -1;
+}
+
+// The same for a uniform `head` on a path that has stored something before.
+__device__ __forceinline__ int find_probe_slot_uniform(const int* probe_heads, int P, int head) {
+  int lo = 0, hi = P;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (cload(probe_heads, mid) < head) lo = mid + 1; else hi = mid;
+  }
+  return (lo < P && cload(probe_heads, lo) == head) ? lo : -1;
 }
 
 // Spans of one sequence, all fetched before any is waited for (entries past S repeat the last
@@ -224,7 +238,6 @@ inline bool grid_fits(long long workgroups) { return workgroups >= 0 && workgrou
 hipError_t launch_plan(const AttnParams& p, hipStream_t st);
 hipError_t launch_kv_write(const KvWriteParams& p, hipStream_t st);
 hipError_t launch_prefill(const AttnParams& p, int D, hipStream_t st);
-hipError_t launch_prefill128(const AttnParams& p, hipStream_t st);
 hipError_t launch_decode(const AttnParams& p, int D, hipStream_t st);
 hipError_t launch_combine(const AttnParams& p, int D, hipStream_t st);
 hipError_t launch_attn_f32(const AttnParams& p, int D, hipStream_t st);
