@@ -81,12 +81,10 @@ typedef enum { HOOK_KV_SAME = 0, HOOK_KV_FP8_E4M3 = 1 } hook_kv_dtype;
  * With a hint the launches that cannot have work are left out (two of four for a prefill-only
  * batch).  A sequence that contradicts the hint is NOT computed: its rows of `out` stay untouched,
  * its `mass` entries are zero and bit 3 of the device status word is set.
- * A HOOK_BATCH_DECODE_ONLY batch of at most 512 sequences (HOOK_BF16) plans itself: the contexts are
- * cut into equal ranges, the workgroups find theirs from the lengths and the planning launch is left
- * out (two launches instead of three).  Results are the same to rounding order; the status word is
- * written as always.  A HOOK_BATCH_PREFILL_ONLY call that holds ONE sequence (a single prompt;
- * HOOK_BF16, head_dim 128) needs no planning launch either: the chunk kernel works out its row
- * blocks itself, with results bit for bit those of the planned call.
+ * In a batch of at most 512 sequences (HOOK_BF16) single rows need no planning launch: the contexts
+ * are cut into equal ranges and the workgroups find theirs from the lengths.  Query chunks need none
+ * either when there is one sequence or when they are few; results are bit for bit those of the planned
+ * call.  The status word is written as always.
  */
 typedef enum hook_batch_kind {
   HOOK_BATCH_MIXED = 0,         /* anything (default) */

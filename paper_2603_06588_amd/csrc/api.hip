@@ -11,6 +11,11 @@ namespace {
 using namespace hook;
 
 constexpr size_t kAlign = 256;
+// Row blocks find their work themselves up to this many workgroups (two resident rounds).  Finding it costs every
+// workgroup about a thousand cycles, the planning launch costs the call 4-5 us and sorts better: 2 prompts of 200
+// tokens 16.2 us planned, 11.6 by themselves; 8 of 200-600 (800 workgroups) 31.6 and 29.3; 3 of 1500-2048 (1350
+// workgroups) 81.1 and 82.7.
+constexpr long long kSelfPlanMaxWgs = 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
@@ -192,18 +197,23 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.hpw = l.hpw; p.rows_per_wg = l.rows_per_wg; p.hgroups = l.hgroups;
   p.dec_hp = l.dec_hp; p.dec_hgroups = l.dec_hgroups;
   p.batch_kind = a->batch_kind;
-  p.dec_ranges = a->batch_kind == HOOK_BATCH_DECODE_ONLY ? l.ranges : 0;
-  // a single prompt on its own needs no planner either
-  p.pf_self = a->dtype == HOOK_BF16 && a->batch_kind == HOOK_BATCH_PREFILL_ONLY && a->num_seqs == 1;
+  // up to kStreamMaxSeqs sequences single rows find their work themselves, and so do row blocks while there are
+  // few of them (or the planner would have nothing to sort)
+  const bool self = a->dtype == HOOK_BF16 && l.ranges > 0;
+  p.dec_ranges = self && a->batch_kind != HOOK_BATCH_PREFILL_ONLY ? l.ranges : 0;
+  p.pf_self = self && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
+              (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups <= kSelfPlanMaxWgs);
+  p.dec_write = writes_kv && self && a->batch_kind == HOOK_BATCH_DECODE_ONLY;
   p.plan_fresh = a->plan_mode == HOOK_PLAN_FRESH;
 
   hipStream_t st = static_cast<hipStream_t>(a->stream);
   auto mark = [&](int i) { return !ev || hipEventRecord(ev[i], st) == hipSuccess; };
   if (!mark(0)) return HOOK_ERR_LAUNCH;
-  // a self-planned batch of single rows writes its rows while streaming, else the planning launch carries the
-  // cache write; where there is no such launch it gets its own
-  if (writes_kv && p.dec_ranges == 0 && (a->dtype == HOOK_F32 || a->plan_mode == HOOK_PLAN_REUSE || p.pf_self) &&
-      launch_kv_write(p.kvw, st) != hipSuccess)
+  // a self-planned batch of single rows writes its rows while streaming, the planning launch carries the
+  // cache write where there is one, else it gets a launch of its own
+  const bool plans = a->dtype == HOOK_BF16 && a->plan_mode == HOOK_PLAN_FRESH &&
+                     !(a->batch_kind == HOOK_BATCH_DECODE_ONLY ? self : p.pf_self != 0);
+  if (writes_kv && !p.dec_write && !plans && launch_kv_write(p.kvw, st) != hipSuccess)
     return HOOK_ERR_LAUNCH;
   if (a->dtype == HOOK_F32) {
     if (launch_attn_f32(p, a->head_dim, st) != hipSuccess) return HOOK_ERR_LAUNCH;
@@ -211,10 +221,8 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
       if (!mark(i)) return HOOK_ERR_LAUNCH;
     return HOOK_OK;
   }
-  // a reusing call finds the work lists of the same batch in the workspace; a self-planned batch
-  // of single rows needs none
-  if ((a->plan_mode == HOOK_PLAN_FRESH && p.dec_ranges == 0 && !p.pf_self && launch_plan(p, st) != hipSuccess) || !mark(1))
-    return HOOK_ERR_LAUNCH;
+  // (a reusing call finds the work lists of the same batch in the workspace)
+  if ((plans && launch_plan(p, st) != hipSuccess) || !mark(1)) return HOOK_ERR_LAUNCH;
   const bool chunks = a->batch_kind != HOOK_BATCH_DECODE_ONLY, singles = a->batch_kind != HOOK_BATCH_PREFILL_ONLY;
   if ((chunks && launch_prefill(p, a->head_dim, st) != hipSuccess) || !mark(2)) return HOOK_ERR_LAUNCH;
   if ((singles && launch_decode(p, a->head_dim, st) != hipSuccess) || !mark(3)) return HOOK_ERR_LAUNCH;

@@ -424,7 +424,7 @@ __device__ __forceinline__ DecodeSeq decode_seq(const AttnParams& p, int Lraw, i
   if (Lraw > max_ctx) s.bits |= kStatLenClamped;
   if (n > s.L) s.bits |= kStatQGtL;
   else if (r0 < 0 || r0 + n > p.total_q) s.bits |= kStatNegative;
-  else if (n > 1) s.bits |= kStatHint;          // a row block in a batch promised to hold single rows
+  else if (n > 1) s.bits |= p.batch_kind == 2 ? kStatHint : 0;   // a row block (in a batch promised to hold single rows)
   else if (n == 1) s.nblk = (s.L + kBlock - 1) / kBlock;
   return s;
 }
@@ -461,17 +461,6 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
 // planning launch (8 us).  Range g and sequence i share at most one piece and the path through the pairs is a
 // staircase, so g + i numbers the partial records without gaps between the records of one sequence.
 constexpr int kScanPerLane = kStreamMaxSeqs / 64;
-
-// Inclusive prefix sum over the wave with DPP moves: inside the rows of 16 lanes, then across them.
-__device__ __forceinline__ int wave_scan(int x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
-  return x;
-}
 
 struct BlockScan {
   int K;                        // sequences per lane
@@ -549,7 +538,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
     const int take = min((L + kBlock - 1) / kBlock - o, x1 - x);
     const int kend = min(L, (o + take) * kBlock);
     // (a length beyond the block table is clamped: its new row has no place in the cache)
-    const bool has_new = p.kvw.k_new != nullptr && kend == L && cload(p.seq_lens, seq) == L;
+    const bool has_new = p.dec_write && kend == L && cload(p.seq_lens, seq) == L;
     // Arguments and lane number are made opaque per piece: otherwise everything derived from them is kept in
     // registers across the loop (60 vector registers spilled instead of a few instructions repeated).
     const AttnParams& pp = reread_arguments();
@@ -590,7 +579,7 @@ __device__ __forceinline__ void settle_batch(const AttnParams& p) {
   __syncthreads();
   bits = sh_bits;
   if (threadIdx.x == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = bits; }
-  if ((bits & kStatHint) && p.kvw.k_new != nullptr) {
+  if ((bits & kStatHint) && p.dec_write) {
     const int ntiles = (p.total_q + kKvRowTile - 1) / kKvRowTile;
     for (int t = 0; t < ntiles; ++t) kv_write_tile<NT>(p.kvw, t, threadIdx.x, dst_row);
   }
@@ -618,8 +607,13 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
   // (the clamps only matter if the work lists were not this batch's: no record outside the workspace is read)
   sd.x = min(max(sd.x, 0), p.dec_cap - 1);
   int count = min(sd.y, p.dec_cap - sd.x);
-  // (a self-planned batch announces records only for sequences that have some)
-  if (stream && decode_seq(p, p.seq_lens[seq], qrow, p.cu_q_lens[seq + 1]).nblk == 0) count = 0;
+  if (stream) {     // (a self-planned batch announces records only for sequences that have some)
+    const int Lraw = p.seq_lens[seq], n = p.cu_q_lens[seq + 1] - qrow;
+    const DecodeSeq ds = decode_seq(p, Lraw, qrow, qrow + n);
+    if (ds.nblk == 0) count = 0;
+    // a row block's `mass` belongs to the kernel that computes it
+    if (p.batch_kind == 0 && n >= 2 && ds.bits != kStatNegative && !(ds.bits & (kStatQGtL | kStatNegative))) return;
+  }
   if (count <= 0 && !stream) return;
   const bool live = head < p.Hq && count > 0;
 
@@ -715,7 +709,7 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
       }
     }
   }
-  if (stream && seq == 0 && blockIdx.y == 0) settle_batch<64 * NWV>(p);
+  if (stream && p.batch_kind == 2 && seq == 0 && blockIdx.y == 0) settle_batch<64 * NWV>(p);
 }
 
 template <int D, int HP>

@@ -101,8 +101,9 @@ struct AttnParams {
   int2* seq_dec;                    // per sequence {first partial record, number of records}
   float* partials;                  // [dec_cap, Hq, D + kPartialPad]
   int dec_ranges;                   // > 0: no planner; the blocks of all single rows are cut into this many ranges
+  int dec_write;                    // the streaming kernel stores the new rows (k_new / v_new) itself
   int plan_fresh;                   // the call promises a fully written `mass` (not a reused plan)
-  int pf_self;                      // one sequence of query rows, head_dim 128: the chunk kernel plans itself
+  int pf_self;                      // the chunk kernel finds its row blocks itself, no planner
   // geometry chosen on the host from G
   int batch_kind;                   // 0 mixed, 1 no single-row sequences, 2 only single-row sequences
   int hpw;                          // q heads per prefill workgroup (4, 2 or 1)
@@ -164,6 +165,28 @@ __device__ __forceinline__ void store_stream16(void* p, const uint4 v) {
   u32x4 x;
   x.x = v.x; x.y = v.y; x.z = v.z; x.w = v.w;
   __builtin_nontemporal_store(x, static_cast<u32x4*>(p));
+}
+
+// Inclusive prefix sum over the wave with DPP moves: inside the rows of 16 lanes, then across them.
+__device__ __forceinline__ int wave_scan(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Maximum over the wave of a value that is not negative, in every lane.
+__device__ __forceinline__ int wave_max(int x) {
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));   // the moves of wave_scan
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));
+  x = max(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));
+  return __builtin_amdgcn_readlane(x, 63);
 }
 
 // Index of `head` in the strictly increasing list probe_heads[0..P), or -1: a binary search, so

@@ -38,6 +38,7 @@ __device__ __forceinline__ SeqInfo read_seq(const AttnParams& p, int i, int* sta
     *status |= kStatHint;
     s.kind = 0;
   }
+  if (s.kind == 2 && p.dec_ranges > 0) s.kind = 0;   // the single rows of this batch find their work themselves
   return s;
 }
 

@@ -542,7 +542,7 @@ __device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned char* sm
 }
 
 // One work item: rows [row0, row0 + rows_per_wg) of sequence `seq` (context L, n rows, first q row
-// qbase) for the heads of (kvh, hg).  ZERO_REST (self-planned call only): the wave that owns a probed
+// qbase) for the heads of (kvh, hg).  ZERO_REST (self-planned calls): the wave that owns a probed
 // head in the item of row 0 also writes zeros to that head's `mass` slots that hold no row, so that
 // every entry of `mass` is written exactly once without a planner's zero-fill.
 template <int D, bool KV8, bool ZERO_REST>
@@ -710,11 +710,137 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   }
 }
 
-// PLANNED: the work item comes from the planner's list.  Otherwise the call holds ONE sequence and
-// plans itself (no planning launch, which is a sixth of a 2048-token prompt's call): the row blocks are
-// taken last block first (longest first), workgroup 0 writes the status word, and `mass` is written
-// entry by entry by the waves that own the entries.  All stores sit behind the body, so that the loads
-// of the batch description stay scalar loads.
+// ---- batches that plan themselves ----------------------------------------------------------
+// Row blocks in processing order without a planner.  The deep row blocks (many key tiles) should start first, or
+// the launch ends with a few of them alone; a full sort is not needed for that.  The range of depths is cut
+// into kDepthParts equal parts and the order is: the deepest part of every sequence, the next part of every sequence, ...
+// with descending blocks inside.  An item's block then follows from sums over the sequences, which every wave forms
+// for itself (lane l takes sequences l K .. l K + K - 1): one trip to memory for the lengths instead of a planning
+// launch (7-9 us) and two trips for its record.  It costs a workgroup about a thousand cycles, so launches of many
+// rounds keep the planner (kSelfPlanMaxWgs).  (2 or 8 parts: 1-3 % slower on 16 ragged prompts; 16: 7 %, as
+// neighbouring workgroups then share fewer tiles in L2.)
+constexpr int kSeqsPerLane = kStreamMaxSeqs / 64;
+
+struct ChunkSeq { int L, n, qbase, bits; bool valid; };
+
+// one sequence as the planner sees it; valid: it has row blocks to compute
+__device__ __forceinline__ ChunkSeq chunk_seq(const AttnParams& p, int Lraw, int r0, int r1) {
+  const int max_ctx = p.max_blocks * kBlock;
+  ChunkSeq s = {min(Lraw, max_ctx), r1 - r0, r0, 0, false};
+  if (Lraw < 0 || s.n < 0) { s.bits = kStatNegative; return s; }
+  if (Lraw > max_ctx) s.bits |= kStatLenClamped;
+  if (s.n > s.L) s.bits |= kStatQGtL;
+  else if (r0 < 0 || r1 > p.total_q) s.bits |= kStatNegative;
+  else if (s.n == 1 && p.batch_kind == 1) s.bits |= kStatHint;   // a single row in a call promised to hold chunks: dropped
+  else s.valid = s.n >= 2;
+  return s;
+}
+
+constexpr int kDepthParts = 4;
+
+// row blocks of a sequence with at most `tiles` key tiles (they are its first ones)
+__device__ __forceinline__ int blocks_up_to(int L, int n, int nblk, int tiles, int rows_log2) {
+  if (L <= kTileKeys * tiles) return nblk;
+  return min(max((kTileKeys * tiles - (L - n)) >> rows_log2, 0), nblk);
+}
+
+struct ChunkItem { int seq, block, L, n, qbase; };
+
+// the item-th row block in processing order; false: there are not that many
+__device__ __forceinline__ bool find_item(const AttnParams& p, int item, int lane, ChunkItem& it) {
+  if (p.num_seqs == 1) {
+    const ChunkSeq s = chunk_seq(p, cload(p.seq_lens, 0), cload(p.cu_q_lens, 0), cload(p.cu_q_lens, 1));
+    const int nblk = s.valid ? (s.n + p.rows_per_wg - 1) / p.rows_per_wg : 0;
+    it = {0, nblk - 1 - item, s.L, s.n, s.qbase};
+    return item < nblk;
+  }
+  const int K = (p.num_seqs + 63) >> 6;
+  const int rows_log2 = p.rows_per_wg == 32 ? 5 : p.rows_per_wg == 64 ? 6 : 7;
+  int nblk[kSeqsPerLane], L[kSeqsPerLane], n[kSeqsPerLane], qbase[kSeqsPerLane];
+  int deepest = 0;
+#pragma unroll
+  for (int u = 0; u < kSeqsPerLane; ++u) {
+    nblk[u] = L[u] = n[u] = qbase[u] = 0;
+    const int i = lane * K + u;
+    if (u < K && i < p.num_seqs) {
+      const ChunkSeq s = chunk_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
+      if (s.valid) {
+        L[u] = s.L; n[u] = s.n; qbase[u] = s.qbase;
+        nblk[u] = (s.n + p.rows_per_wg - 1) >> rows_log2;
+        deepest = max(deepest, s.L);
+      }
+    }
+  }
+  constexpr int N = kDepthParts;
+  // part q (0: deepest) holds the blocks of more than bound[N - 1 - q] and at most bound[N - q] tiles
+  const int max_tiles = (wave_max(deepest) + kTileKeys - 1) / kTileKeys;
+  int bound[N + 1], total[N + 1];
+  bound[0] = total[0] = 0;
+#pragma unroll
+  for (int k = 1; k <= N; ++k) {
+    bound[k] = max_tiles * k / N;
+    int sum = 0;
+#pragma unroll
+    for (int u = 0; u < kSeqsPerLane; ++u)
+      if (u < K) sum += blocks_up_to(L[u], n[u], nblk[u], bound[k], rows_log2);
+    total[k] = __builtin_amdgcn_readlane(wave_scan(sum), 63);
+  }
+  if (item >= total[N]) return false;
+  int first = 0, lo = bound[N - 1], hi = bound[N];
+#pragma unroll
+  for (int k = 1; k < N; ++k)
+    if (item >= total[N] - total[N - k]) { first = total[N] - total[N - k]; lo = bound[N - k - 1]; hi = bound[N - k]; }
+  const int rel = item - first;
+  int mine = 0;
+#pragma unroll
+  for (int u = 0; u < kSeqsPerLane; ++u)
+    if (u < K) mine += blocks_up_to(L[u], n[u], nblk[u], hi, rows_log2) - (lo ? blocks_up_to(L[u], n[u], nblk[u], lo, rows_log2) : 0);
+  const int incl = wave_scan(mine);
+  int start = incl - mine;
+  const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(rel >= start && rel < incl));
+  ChunkItem f = {0, 0, 0, 0, 0};
+#pragma unroll
+  for (int u = 0; u < kSeqsPerLane; ++u)
+    if (u < K) {
+      const int end = blocks_up_to(L[u], n[u], nblk[u], hi, rows_log2);
+      const int size = end - (lo ? blocks_up_to(L[u], n[u], nblk[u], lo, rows_log2) : 0);
+      if (rel >= start && rel < start + size) f = {lane * K + u, end - 1 - (rel - start), L[u], n[u], qbase[u]};
+      start += size;
+    }
+  it.seq = __builtin_amdgcn_readlane(f.seq, from);
+  it.block = __builtin_amdgcn_readlane(f.block, from);
+  it.L = __builtin_amdgcn_readlane(f.L, from);
+  it.n = __builtin_amdgcn_readlane(f.n, from);
+  it.qbase = __builtin_amdgcn_readlane(f.qbase, from);
+  return true;
+}
+
+// What the planner does besides, by a workgroup of its own: the header with the status word, and zeros in the `mass`
+// entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those).
+__device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
+  int* const skip = sh + 2;     // [kStreamMaxSeqs]
+  const int tid = threadIdx.x;
+  if (tid < 2) sh[tid] = 0;
+  __syncthreads();
+  int bits = 0, blocks = 0;
+  for (int i = tid; i < p.num_seqs; i += 256) {
+    const ChunkSeq s = chunk_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
+    bits |= s.bits;
+    if (s.valid) blocks += (s.n + p.rows_per_wg - 1) / p.rows_per_wg;
+    skip[i] = s.valid ? 0 : 1;
+  }
+  if (bits) atomicOr(&sh[0], bits);
+  if (blocks) atomicAdd(&sh[1], blocks);
+  __syncthreads();
+  if (tid == 0) { p.hdr->n_prefill = sh[1]; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = sh[0]; }
+  if (p.batch_kind == 1 && p.plan_fresh && p.P > 0)
+    for (int i = 0; i < p.num_seqs; ++i)
+      if (skip[i])
+        for (int e = tid; e < p.P * p.NQ * p.S; e += 256) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
+}
+
+// PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
+// of the grid settles the rest, and `mass` is written entry by entry by the waves that own the entries.
 template <int D, bool KV8, bool PLANNED>
 __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -735,27 +861,15 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     if (item >= nitems) return;
     prefill_item<D, KV8, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
   } else {
-    const int max_ctx = p.max_blocks * kBlock;
-    const int Lraw = p.seq_lens[0], qbase = p.cu_q_lens[0], n = p.cu_q_lens[1] - qbase;
-    const int L = min(Lraw, max_ctx);
-    int status = 0;
-    bool valid = false;
-    if (Lraw < 0 || n < 0) status = kStatNegative;
-    else {
-      if (Lraw > max_ctx) status |= kStatLenClamped;
-      if (n > L) status |= kStatQGtL;
-      else if (qbase < 0 || qbase + n > p.total_q) status |= kStatNegative;
-      else if (n == 1) status |= kStatHint;      // a single row in a call promised to hold chunks: dropped
-      else valid = n >= 2;
+    if (bid == (int)gridDim.x - 1) {
+      settle_chunks(p, reinterpret_cast<int*>(smem));
+      return;
     }
-    const int nitems = valid ? (n + p.rows_per_wg - 1) / p.rows_per_wg : 0;
-    if (item < nitems)
-      prefill_item<D, KV8, true>(p, smem, kvh, hg, 0, (nitems - 1 - item) * p.rows_per_wg, L, n, qbase);
-    if (bid == 0) {
-      if (threadIdx.x == 0) { p.hdr->n_prefill = nitems; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = status; }
-      if (!valid && p.plan_fresh)     // nothing ran: every entry of `mass` is zero
-        for (int e = threadIdx.x; e < p.P * p.NQ * p.S; e += 256) p.mass[e] = 0.0f;
-    }
+    ChunkItem it;
+    const bool some = find_item(p, item, threadIdx.x & 63, it);
+    asm volatile("" :: "s"(p.block_table), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache));
+    if (!some) return;
+    prefill_item<D, KV8, true>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
   }
 }
 
@@ -772,7 +886,7 @@ hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_prefill(const AttnParams& p, int D, hipStream_t st) {
-  const long long grid = (long long)p.pf_cap * p.Hkv * p.hgroups;
+  const long long grid = (long long)p.pf_cap * p.Hkv * p.hgroups + (p.pf_self ? 1 : 0);
   if (grid <= 0) return hipSuccess;
   if (!grid_fits(grid)) return hipErrorInvalidValue;
   if (D == 128 && !p.kv8) return p.pf_self ? launch<128, false, false>(p, grid, st) : launch<128, false, true>(p, grid, st);

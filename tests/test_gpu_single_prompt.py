@@ -115,3 +115,38 @@ def test_single_prompt_with_new_rows_written_in_the_call():
     call.launch()
     torch.cuda.synchronize()
     assert torch.equal(bits(call.out), bits(ref.out)) and torch.equal(bits(call.mass), bits(ref.mass))
+
+
+@pytest.mark.parametrize("d,kv8", [(64, False), (64, True), (128, True)])
+def test_single_prompt_other_head_size_and_cache_type(d, kv8):
+    b = W.random_batch(1440 + d, [777], [300], 8, 2, d, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=3)
+    if kv8:
+        b = W.fp8_cache_variant(b, 1441)
+    own, planned = _run(b, binding.BATCH_PREFILL_ONLY), _run(b, binding.BATCH_MIXED)
+    assert torch.equal(bits(own.out), bits(planned.out)) and torch.equal(bits(own.mass), bits(planned.mass))
+    print("      ", compare_with_oracle(b, own.out, own.mass, label="single"), flush=True)
+
+
+@pytest.mark.parametrize("nseq,lo,hi,rows,kind", [(2, 2, 70, None, 1), (63, 2, 60, None, 1), (66, 2, 40, None, 0), (130, 2, 20, None, 0),
+                                                  (5, 300, 900, 40, 1), (7, 30, 500, 200, 0)])
+def test_several_prompts_find_their_row_blocks(nseq, lo, hi, rows, kind):
+    """Batches small enough to plan themselves: every row block is found exactly once, with single rows, empty and
+    invalid sequences between the chunks (their rows stay untouched, their `mass` is zero)."""
+    lens = [lo + (i * 7919) % (hi - lo + 1) for i in range(nseq)]
+    qlens = [min(L, rows) if rows else L for L in lens]
+    if kind == 0:
+        qlens = [1 if i % 3 == 1 else 0 if i % 7 == 4 else n for i, n in enumerate(qlens)]
+    b = W.random_batch(1450 + nseq, lens, qlens, 8, 2, 128, torch.bfloat16, num_probe_heads=3, max_sel_q=3, max_spans=2)
+    call = _run(b, kind)
+    assert call.device_status() == 0
+    from helpers import valid_rows
+    written = torch.isfinite(call.out.float()).all(dim=2).all(dim=1).cpu()
+    assert bool((written == valid_rows(b)).all())
+    print("      ", compare_with_oracle(b, call.out, call.mass, label="several"), flush=True)
+    bad = b.to("cpu")
+    bad.seq_lens = bad.seq_lens.clone()
+    bad.seq_lens[1] = -3
+    hit = _run(bad, kind, sentinel=7.0)
+    cu = b.cu_q_lens.tolist()
+    assert hit.device_status() == 4 and (hit.mass[1] == 0).all() and (hit.out[cu[1]:cu[2]] == 7.0).all()
+    assert torch.equal(bits(hit.out[:cu[1]]), bits(call.out[:cu[1]])) and torch.equal(bits(hit.mass[0]), bits(call.mass[0]))
