@@ -191,10 +191,11 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     if (last) {
       const int r = new_pos - key0;        // the new row's place in this block
       if (new_pos >= 0 && r < kBlock) {    // uniform
-        store_new = store_new && (unsigned)cload(bt, b) < (unsigned)p.num_blocks;   // a clamped id is not written to
+        const int id = cload(bt, b);       // (`ids` may hold the next 64 ids already)
+        store_new = store_new && (unsigned)id < (unsigned)p.num_blocks;   // a clamped id is not written to
         const char* kn = reinterpret_cast<const char*>(in_global(p.kvw.k_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
         const char* vn = reinterpret_cast<const char*>(in_global(p.kvw.v_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
-        const size_t off = (size_t)(unsigned)__builtin_amdgcn_readlane(ids, (b - b0) & 63) * blk_bytes;
+        const size_t off = (size_t)(unsigned)id * blk_bytes;
         char* kdst = const_cast<char*>(kbase) + off;
         char* vdst = const_cast<char*>(vbase) + off;
         if (j == r) {

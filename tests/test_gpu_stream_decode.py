@@ -65,3 +65,26 @@ def test_new_rows_are_stored_by_the_streaming_kernel(kv8, d, Hq, Hkv):
         assert torch.equal(bits(call.out[cu[i]]), bits(ref.out[cu[i]])), i
         assert torch.equal(bits(call.mass[i]), bits(ref.mass[i])), i
     assert call.device_status() == ref.device_status() == 2
+
+
+def test_new_row_in_a_range_of_256_blocks():
+    """Each range is one whole context and each wave streams exactly the 64 blocks whose ids fill its register."""
+    n, heads, d = 6, 128, 64                 # 128 workgroups per range: six ranges
+    b = W.random_batch(2300, [4096] + [16] * (n - 1), [1] * n, heads, heads, d, torch.bfloat16, num_probe_heads=1, max_sel_q=1,
+                       max_spans=1, poison=False)
+    for i in range(1, n):                    # the other contexts: the first one's blocks and a last block of their own
+        b.block_table[i, 255] = b.block_table[i, 0]
+        b.block_table[i, :255] = b.block_table[0, :255]
+    b.seq_lens[:] = 4096
+    gen = torch.Generator().manual_seed(6)
+    k_new, v_new = (torch.randn((n, heads, d), generator=gen).to(torch.bfloat16).to(DEV) for _ in range(2))
+    first, second = b.to(DEV), b.to(DEV)
+    second.k_cache, second.v_cache = first.k_cache.clone(), first.v_cache.clone()
+    binding.hook_kv_write(k_new, v_new, first.block_table, first.seq_lens, first.cu_q_lens, first.k_cache, first.v_cache)
+    ref = binding.call_from_batch(first, batch_kind=binding.BATCH_DECODE_ONLY)
+    ref.launch()
+    call = binding.call_from_batch(second, batch_kind=binding.BATCH_DECODE_ONLY, k_new=k_new, v_new=v_new)
+    call.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(bits(first.k_cache), bits(second.k_cache)) and torch.equal(bits(first.v_cache), bits(second.v_cache))
+    assert torch.equal(bits(call.out), bits(ref.out)) and torch.equal(bits(call.mass), bits(ref.mass))
