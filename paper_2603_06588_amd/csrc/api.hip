@@ -63,6 +63,19 @@ int stream_ranges(const hook_attn_probe_args* a, const Layout& l) {
   return (int)(ranges < finest ? ranges : finest);
 }
 
+// Carves the workspace up for the layout's capacities; returns its size.
+size_t place(const hook_attn_probe_args* a, Layout& l) {
+  size_t off = 0;
+  l.off_hdr = off;  off = align_up(off + sizeof(PlanHeader));
+  l.off_pf = off;   off = align_up(off + 2 * sizeof(WorkItem) * (size_t)l.pf_cap);
+  l.off_dec = off;  off = align_up(off + 2 * sizeof(WorkItem) * (size_t)l.dec_cap);
+  l.off_seq = off;  off = align_up(off + sizeof(int2) * (size_t)(a->num_seqs > 0 ? a->num_seqs : 1));
+  l.off_part = off;
+  off = align_up(off + sizeof(float) * (size_t)l.dec_cap * a->num_q_heads * (a->head_dim + kPartialPad));
+  l.total = off;
+  return l.total;
+}
+
 Layout make_layout(const hook_attn_probe_args* a) {
   Layout l{};
   const int G = a->num_q_heads / a->num_kv_heads;
@@ -75,18 +88,17 @@ Layout make_layout(const hook_attn_probe_args* a) {
     l.pf_cap = a->total_q / l.rows_per_wg + a->num_seqs;
     l.dec_cap = decode_item_bound(a->num_seqs < a->total_q ? a->num_seqs : a->total_q,
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
-    // a self-planned batch numbers its records by range + sequence
+    // A self-planned batch numbers its records by range + sequence, which can take more slots than the planner's
+    // items.  Where the extra slots would push a batch out of the static scratch it keeps the planner.
     l.ranges = stream_ranges(a, l);
-    if (l.ranges > 0 && l.dec_cap < l.ranges + a->num_seqs) l.dec_cap = l.ranges + a->num_seqs;
+    if (l.ranges > 0 && l.dec_cap < l.ranges + a->num_seqs) {
+      const int planned_cap = l.dec_cap;
+      const bool fitted = place(a, l) <= (size_t)HOOK_STATIC_SCRATCH_BYTES;
+      l.dec_cap = l.ranges + a->num_seqs;
+      if (fitted && place(a, l) > (size_t)HOOK_STATIC_SCRATCH_BYTES) { l.dec_cap = planned_cap; l.ranges = 0; }
+    }
   }
-  size_t off = 0;
-  l.off_hdr = off;  off = align_up(off + sizeof(PlanHeader));
-  l.off_pf = off;   off = align_up(off + 2 * sizeof(WorkItem) * (size_t)l.pf_cap);
-  l.off_dec = off;  off = align_up(off + 2 * sizeof(WorkItem) * (size_t)l.dec_cap);
-  l.off_seq = off;  off = align_up(off + sizeof(int2) * (size_t)(a->num_seqs > 0 ? a->num_seqs : 1));
-  l.off_part = off;
-  off = align_up(off + sizeof(float) * (size_t)l.dec_cap * a->num_q_heads * (a->head_dim + kPartialPad));
-  l.total = off;
+  place(a, l);
   return l;
 }
 

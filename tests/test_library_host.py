@@ -146,6 +146,15 @@ def _args(binding, **kw):
     return a
 
 
+def test_short_contexts_of_many_sequences_fit_the_static_scratch(binding):
+    # 420 single rows x 64 heads: 15.1 MB of records with one per sequence, 17.3 MB with the extra slots that
+    # self-planned batches number by
+    lib = binding.load_library()
+    need = lib.hook_attn_probe_workspace_bytes(ctypes.byref(_args(binding, num_seqs=420, total_q=420, num_q_heads=64, num_kv_heads=8,
+                                                                  max_blocks_per_seq=16, num_blocks=420 * 16)))
+    assert 14 << 20 < need <= lib.hook_attn_probe_static_capacity()
+
+
 def test_rejects_bad_arguments_before_launch(binding):
     lib = binding.load_library()
     call = lambda a: lib.hook_attn_probe(ctypes.byref(a))
