@@ -488,26 +488,19 @@ __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem
                                               l_run, am, sp_a, sp_b);
 }
 
-// The first tiles of an item: K(0), V(0) and K(1) into the LDS buffers, for 8-bit caches also the bytes of K(2) and
-// V(1) into the staging area.  On return K(0) has landed for every wave.  16-bit: the loads are in flight
-// behind whatever the caller has requested before, and complete in issue order.
+// The first tiles of an item into the LDS buffers.  16-bit: K(0) is requested here, V(0) and K(1) by the second
+// function once the query rows have arrived.  8-bit caches: K(0), V(0) and K(1) here, and the bytes of V(1)
+// and K(2) into the staging area.
 template <int D, bool KV8>
 __device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, unsigned long long boff0,
                                             unsigned long long boff1, unsigned long long boff2) {
   using C = Cfg<D, KV8>;
   constexpr int NI = C::NI;
   const unsigned lds_k = cx.lds_base + cx.w * kBlock * C::RB;                    // this wave's rows of K buffer 0
-  const unsigned lds_v = lds_k + 2 * C::TILE;
   if constexpr (!KV8) {
     fetch_k<D, false, 0>(cx, boff0, lds_k);
     if constexpr (NI > 1) fetch_k<D, false, 1>(cx, boff0, lds_k);
     if constexpr (NI > 2) { fetch_k<D, false, 2>(cx, boff0, lds_k); fetch_k<D, false, 3>(cx, boff0, lds_k); }
-    fetch_v<D, false, 0, true>(cx, boff0, 0, lds_v);
-    if constexpr (NI > 1) fetch_v<D, false, 1, true>(cx, boff0, 0, lds_v);
-    if constexpr (NI > 2) { fetch_v<D, false, 2, true>(cx, boff0, 0, lds_v); fetch_v<D, false, 3, true>(cx, boff0, 0, lds_v); }
-    fetch_k<D, false, 0>(cx, boff1, lds_k + C::TILE);
-    if constexpr (NI > 1) fetch_k<D, false, 1>(cx, boff1, lds_k + C::TILE);
-    if constexpr (NI > 2) { fetch_k<D, false, 2>(cx, boff1, lds_k + C::TILE); fetch_k<D, false, 3>(cx, boff1, lds_k + C::TILE); }
   } else {
     // through registers: nothing to overlap with yet
     const int t1 = min(1, ntiles - 1);
@@ -538,6 +531,22 @@ __device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned char* sm
       widen_to<D>(kd + C::TILE, r, ch, k_swizzle<D>(r), k1[jj].x, k1[jj].y);
       widen_to<D>(kd + C::TILE, r, ch + 1, k_swizzle<D>(r), k1[jj].z, k1[jj].w);
     }
+  }
+}
+
+template <int D, bool KV8>
+__device__ __forceinline__ void rest_of_first_tiles(const WaveCtx& cx, unsigned long long boff0, unsigned long long boff1) {
+  using C = Cfg<D, KV8>;
+  if constexpr (!KV8) {
+    constexpr int NI = C::NI;
+    const unsigned lds_k = cx.lds_base + cx.w * kBlock * C::RB;
+    const unsigned lds_v = lds_k + 2 * C::TILE;
+    fetch_v<D, false, 0, true>(cx, boff0, 0, lds_v);
+    if constexpr (NI > 1) fetch_v<D, false, 1, true>(cx, boff0, 0, lds_v);
+    if constexpr (NI > 2) { fetch_v<D, false, 2, true>(cx, boff0, 0, lds_v); fetch_v<D, false, 3, true>(cx, boff0, 0, lds_v); }
+    fetch_k<D, false, 0>(cx, boff1, lds_k + C::TILE);
+    if constexpr (NI > 1) fetch_k<D, false, 1>(cx, boff1, lds_k + C::TILE);
+    if constexpr (NI > 2) { fetch_k<D, false, 2>(cx, boff1, lds_k + C::TILE); fetch_k<D, false, 3>(cx, boff1, lds_k + C::TILE); }
   }
 }
 
@@ -575,16 +584,13 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   auto first_id = [&](int tile) { return cload(bt, min(4 * min(tile, ntiles - 1) + w, cx.last_blk)); };
   const int id0 = first_id(0), id1 = first_id(1), id2 = KV8 ? first_id(2) : 0;
 
-  // Query rows, in assembly like the tile fetches behind them, so that the one wait below can leave the
-  // younger of those in flight (a wait of the compiler's own would be for everything)
-  u32x4 qraw[C::KSTEPS];
+  // Query rows.  The compiler does not count the tile fetches (assembly), so its wait for these rows is a wait for
+  // the fetches issued before it as well: only K(0) is (first_tiles / rest_of_first_tiles).
+  uint4 qraw[C::KSTEPS];
   {
-    const __bf16* const qg = static_cast<const __bf16*>(p.q);
-    const unsigned long long base = (unsigned long long)(size_t)(qg + (size_t)qbase * p.Hq * D + (size_t)head * D);
-    const unsigned long long a = base + ((size_t)t * p.Hq * D + 8 * hf) * 2;
+    const __bf16* const qg = static_cast<const __bf16*>(p.q) + ((size_t)(qbase + t) * p.Hq + head) * D + 8 * hf;
 #pragma unroll
-    for (int s = 0; s < C::KSTEPS; ++s)
-      asm volatile("global_load_dwordx4 %0, %1, off offset:%2" : "=v"(qraw[s]) : "v"(a), "n"(32 * s) : "memory");
+    for (int s = 0; s < C::KSTEPS; ++s) qraw[s] = load_global16((global_bytes)(unsigned long long)(size_t)(qg + 16 * s));
   }
 
   cx.hf = hf;
@@ -644,10 +650,11 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   // until the top of the first iteration
   bf16x8 qf[C::KSTEPS];
 #pragma unroll
-  for (int s = 0; s < C::KSTEPS; ++s)
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(qraw[s]) : "n"(2 * C::NI) : "memory");
-#pragma unroll
   for (int s = 0; s < C::KSTEPS; ++s) __builtin_memcpy(&qf[s], &qraw[s], 16);
+#pragma unroll
+  for (int s = 0; s < C::KSTEPS; ++s) asm volatile("" : "+v"(qf[s]) :: "memory");     // Q has arrived here
+  rest_of_first_tiles<D, KV8>(cx, boff0, boff1);
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NI) : "memory");
   __syncthreads();
 
   if (wave_probe)
