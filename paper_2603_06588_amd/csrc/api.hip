@@ -58,7 +58,8 @@ int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_p
 int stream_ranges(const hook_attn_probe_args* a, const Layout& l) {
   if (a->dtype != HOOK_BF16 || a->num_seqs <= 0 || a->num_seqs > kStreamMaxSeqs) return 0;
   const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3), wgs = (long long)a->num_kv_heads * l.dec_hgroups;
-  const long long finest = ((long long)a->num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks;
+  // (and one range per sequence more, for ranges that end with their sequence)
+  const long long finest = ((long long)a->num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks + a->num_seqs;
   const long long ranges = (one_round + wgs - 1) / wgs;
   return (int)(ranges < finest ? ranges : finest);
 }

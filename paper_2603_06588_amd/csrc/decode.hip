@@ -461,7 +461,12 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
 // wave on its own, lane l takes sequences l K .. l K + K - 1), which costs about a microsecond instead of a
 // planning launch (8 us).  Range g and sequence i share at most one piece and the path through the pairs is a
 // staircase, so g + i numbers the partial records without gaps between the records of one sequence.
+// A piece costs a workgroup its start-up (ids, query, first keys, merge), so where whole sequences can be dealt
+// out to the ranges with hardly more blocks each, no range covers two: a sequence then takes its blocks divided by
+// `bpr` ranges, rounded up, which fits while bpr is at least total / (ranges - sequences).  kPieceBlocks is about
+// what a second piece costs in blocks.
 constexpr int kScanPerLane = kStreamMaxSeqs / 64;
+constexpr int kPieceBlocks = 4;
 
 struct BlockScan {
   int K;                        // sequences per lane
@@ -470,6 +475,7 @@ struct BlockScan {
   int excl;                     // blocks in front of this lane's first sequence
   int total;                    // blocks of the batch
   int bpr;                      // blocks per range
+  bool whole;                   // ranges end with their sequence
   int bits;                     // status bits of this lane's sequences
 };
 
@@ -495,6 +501,10 @@ __device__ __forceinline__ BlockScan scan_blocks(const AttnParams& p, int lane) 
   sc.excl = incl - sum;
   sc.total = __builtin_amdgcn_readlane(incl, 63);
   sc.bpr = max((sc.total + p.dec_ranges - 1) / p.dec_ranges, kStreamMinBlocks);
+  const int spare = p.dec_ranges - p.num_seqs;
+  const int bpr_whole = spare > 0 ? max((sc.total + spare - 1) / spare, kStreamMinBlocks) : 0;
+  sc.whole = spare > 0 && bpr_whole <= sc.bpr + kPieceBlocks;
+  if (sc.whole) sc.bpr = bpr_whole;
   return sc;
 }
 
@@ -511,29 +521,42 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
 
   const BlockScan sc = scan_blocks(p, lane);
 
-  int x = g * sc.bpr;
-  const int x1 = min(sc.total, x + sc.bpr);
-  if (x >= x1) return;
-  // the sequence that block x belongs to, and x's place in it
+  // the sequence that the range begins in, and its place there: by blocks, or by ranges where those end with
+  // their sequence
+  int at = g * sc.bpr, excl = sc.excl, total = sc.total;
+  if (sc.whole) {
+    int sum = 0;
+#pragma unroll
+    for (int u = 0; u < kScanPerLane; ++u) sum += (sc.nblk[u] + sc.bpr - 1) / sc.bpr;
+    const int incl = wave_scan(sum);
+    at = g;
+    excl = incl - sum;
+    total = __builtin_amdgcn_readlane(incl, 63);
+  }
+  if (at >= total) return;
   int seq, o, L, qrow;
   {
-    int my_seq = 0, my_o = 0, my_L = 0, my_row = 0, start = sc.excl;
+    int my_seq = 0, my_o = 0, my_L = 0, my_row = 0, start = excl;
 #pragma unroll
     for (int u = 0; u < kScanPerLane; ++u) {
-      if (x >= start && x < start + sc.nblk[u]) {
+      const int size = sc.whole ? (sc.nblk[u] + sc.bpr - 1) / sc.bpr : sc.nblk[u];
+      if (at >= start && at < start + size) {
         my_seq = lane * sc.K + u;
-        my_o = x - start;
+        my_o = (at - start) * (sc.whole ? sc.bpr : 1);
         my_L = sc.L[u];
         my_row = sc.qrow[u];
       }
-      start += sc.nblk[u];
+      start += size;
     }
-    const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(x >= sc.excl && x < start));
+    const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(at >= excl && at < start));
     seq = __builtin_amdgcn_readlane(my_seq, from);
     o = __builtin_amdgcn_readlane(my_o, from);
     L = __builtin_amdgcn_readlane(my_L, from);
     qrow = __builtin_amdgcn_readlane(my_row, from);
   }
+  // [x, x1): the range's blocks, counted from any origin
+  int x = sc.whole ? o : at;
+  const int x1 = sc.whole ? min((L + kBlock - 1) / kBlock, o + sc.bpr) : min(total, at + sc.bpr);
   const int head0 = kvh * p.G + hg * HP;
   for (;;) {
     const int take = min((L + kBlock - 1) / kBlock - o, x1 - x);
@@ -549,7 +572,8 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
                              hg == 0);
     // where the merge kernel finds the sequence's records
     if (o == 0 && kvh == 0 && hg == 0 && tid == 0)
-      p.seq_dec[seq] = make_int2(g + seq, (x + (L + kBlock - 1) / kBlock - 1) / sc.bpr - g + 1);
+      p.seq_dec[seq] = make_int2(g + seq, sc.whole ? ((L + kBlock - 1) / kBlock + sc.bpr - 1) / sc.bpr
+                                                   : (x + (L + kBlock - 1) / kBlock - 1) / sc.bpr - g + 1);
     x += take;
     if (x >= x1) break;
     __syncthreads();      // `red` is written again

@@ -13,7 +13,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("nseq,hi,Hq,Hkv,d", [(64, 300, 8, 2, 128), (65, 300, 8, 2, 128), (512, 90, 8, 2, 64), (513, 90, 8, 2, 64),
-                                              (200, 40, 32, 8, 128), (3, 5000, 16, 2, 128)])
+                                              (200, 40, 32, 8, 128), (3, 5000, 16, 2, 128),
+                                              (14, 500, 32, 8, 128), (4, 131, 64, 8, 128), (95, 200, 32, 8, 128)])
 def test_ranges_over_many_sequences(nseq, hi, Hq, Hkv, d):
     lens = [1 + (i * 7919) % hi for i in range(nseq)]
     qlens = [0 if i % 11 == 5 else 1 for i in range(nseq)]
