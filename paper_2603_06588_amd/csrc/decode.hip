@@ -524,10 +524,16 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   // the sequence that the range begins in, and its place there: by blocks, or by ranges where those end with
   // their sequence
   int at = g * sc.bpr, excl = sc.excl, total = sc.total;
+  int size[kScanPerLane];
+#pragma unroll
+  for (int u = 0; u < kScanPerLane; ++u) size[u] = sc.nblk[u];
   if (sc.whole) {
     int sum = 0;
 #pragma unroll
-    for (int u = 0; u < kScanPerLane; ++u) sum += (sc.nblk[u] + sc.bpr - 1) / sc.bpr;
+    for (int u = 0; u < kScanPerLane; ++u) {
+      if (u < sc.K) size[u] = (sc.nblk[u] + sc.bpr - 1) / sc.bpr;      // (uniform: few sequences, few divisions)
+      sum += size[u];
+    }
     const int incl = wave_scan(sum);
     at = g;
     excl = incl - sum;
@@ -539,14 +545,13 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
     int my_seq = 0, my_o = 0, my_L = 0, my_row = 0, start = excl;
 #pragma unroll
     for (int u = 0; u < kScanPerLane; ++u) {
-      const int size = sc.whole ? (sc.nblk[u] + sc.bpr - 1) / sc.bpr : sc.nblk[u];
-      if (at >= start && at < start + size) {
+      if (at >= start && at < start + size[u]) {
         my_seq = lane * sc.K + u;
         my_o = (at - start) * (sc.whole ? sc.bpr : 1);
         my_L = sc.L[u];
         my_row = sc.qrow[u];
       }
-      start += size;
+      start += size[u];
     }
     const int from = __builtin_ctzll(__builtin_amdgcn_ballot_w64(at >= excl && at < start));
     seq = __builtin_amdgcn_readlane(my_seq, from);
