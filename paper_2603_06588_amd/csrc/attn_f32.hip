@@ -47,7 +47,7 @@ __device__ __forceinline__ void f32_block(const AttnParams& p, int seq, int firs
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, quarter = lane >> 4;
   const int t = min(r0 + j, rows - 1);          // lanes without a row repeat the last one
-  const int pos = L - n + t;
+  const int pos = L - n + t, pos_min = L - n + r0;
   const int ntile = (L - n + min(r0 + kF32Rows, rows) - 1) / kBlock + 1;
   const int kvh = head / p.G;
 
@@ -140,13 +140,52 @@ __device__ __forceinline__ void f32_block(const AttnParams& p, int seq, int firs
       for (int cc = 0; cc < 4; ++cc)
 #pragma unroll
         for (int r = 0; r < 4; ++r) o[i][cc][r] *= alpha;
+    // A key that only some of the rows see meets the others with a probability of 0, and 0 * Inf is not 0: where such a
+    // tile holds a value that is not finite, the product takes 0 in its place and the rows that see it add it afterwards.
+    float poison = 0.0f;
+    if (kBlock * kt + kBlock - 1 > pos_min) {      // uniform
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
-      for (int i = 0; i < VI; ++i)
+        for (int i = 0; i < VI; ++i)
 #pragma unroll
-        for (int cc = 0; cc < 4; ++cc)
-          o[i][cc] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(v[e][i], cc), pr[e], o[i][cc], 0, 0, 0);
+          for (int cc = 0; cc < 4; ++cc) poison = __builtin_fmaf(comp(v[e][i], cc), 0.0f, poison);
+    }
+    if (__builtin_amdgcn_ballot_w64(poison != poison) == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < VI; ++i)
+#pragma unroll
+          for (int cc = 0; cc < 4; ++cc)
+            o[i][cc] = __builtin_amdgcn_mfma_f32_16x16x4f32(comp(v[e][i], cc), pr[e], o[i][cc], 0, 0, 0);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < VI; ++i)
+#pragma unroll
+          for (int cc = 0; cc < 4; ++cc) {
+            const float x = comp(v[e][i], cc);
+            o[i][cc] = __builtin_amdgcn_mfma_f32_16x16x4f32(__builtin_isfinite(x) ? x : 0.0f, pr[e], o[i][cc], 0, 0, 0);
+          }
+#pragma unroll 1
+      for (int kq = 0; kq < 4; ++kq)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float pk = __shfl(pr[e], 16 * kq + j);
+          const bool sees = kBlock * kt + 4 * kq + e <= pos;
+#pragma unroll
+          for (int i = 0; i < VI; ++i)
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) {
+                const float x = __shfl(comp(v[e][i], cc), 16 * kq + 4 * quarter + r);
+                if (sees && !__builtin_isfinite(x)) o[i][cc][r] = __builtin_fmaf(pk, x, o[i][cc][r]);
+              }
+        }
+    }
     if (pslot >= 0) {
 #pragma unroll
       for (int sp = 0; sp < kMaxSpans; ++sp)
