@@ -438,8 +438,54 @@ __device__ __forceinline__ float tile_iter(const WaveCtx& cx, unsigned char* sme
   return mx_next;
 }
 
-template <int D, bool KV8, bool PROBE>
-__device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, int n_nomask, BlockIds& ids,
+// The same iteration for a wave that has no key left: the tiles behind its rows' positions are for the other row blocks
+// of the workgroup (groups of fewer than four heads), and it only fetches its cache blocks of them.  (Going through
+// them with every score masked would let 0 * Inf from their values into its rows.)
+template <int D, bool KV8>
+__device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, BlockIds& ids,
+                                           const int* bt, unsigned long long& boff) {
+  using C = Cfg<D, KV8>;
+  constexpr int NI = C::NI;
+  wait_vmem();
+  __syncthreads();
+  if (kt == ntiles - 1) return;
+  const int tv = min(kt + (KV8 ? 2 : 1), ntiles - 1), tk = min(kt + (KV8 ? 3 : 2), ntiles - 1);
+  if ((tk >> 4) > ids.grp + 1) {
+    ids.grp += 1;
+    ids.cur = ids.nxt;
+    ids.nxt = load_ids(bt, 64 * (ids.grp + 1), cx.lane, cx.last_blk);
+  }
+  const int sel = ((tk >> 4) == ids.grp) ? ids.cur : ids.nxt;
+  const unsigned rows = cx.w * kBlock * C::RB, vb = (2 + ((kt + 1) & 1)) * C::TILE + rows, kb = (kt & 1) * C::TILE + rows;
+  unsigned lds_v = cx.lds_base + vb, lds_k = cx.lds_base + kb;
+  if constexpr (KV8) {
+    const unsigned staged = 4 * C::TILE + cx.w * C::STAGE;
+#pragma unroll
+    for (int q = 0; q < 2 * NI; ++q) {
+      const uint4 st = *reinterpret_cast<const uint4*>(smem + staged + (q / NI) * C::BLK + (q % NI) * 1024 + 16 * cx.lane);
+      const int r = C::RPI * (q % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR);
+      unsigned char* const dst = smem + (q < NI ? kb : vb);
+      const int swz = q < NI ? k_swizzle<D>(r) : v_swizzle<D>(r);
+      widen_to<D>(dst, r, ch, swz, st.x, st.y);
+      widen_to<D>(dst, r, ch + 1, swz, st.z, st.w);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the staging area is free
+    lds_k = cx.lds_base + staged;
+    lds_v = lds_k + C::BLK;
+  }
+  fetch_v<D, KV8, 0, true>(cx, boff, tv, lds_v);
+  if constexpr (NI > 1) fetch_v<D, KV8, 1, true>(cx, boff, tv, lds_v);
+  if constexpr (NI > 2) { fetch_v<D, KV8, 2, true>(cx, boff, tv, lds_v); fetch_v<D, KV8, 3, true>(cx, boff, tv, lds_v); }
+  boff = block_offset(cx, sel, tk);
+  fetch_k<D, KV8, 0>(cx, boff, lds_k);
+  if constexpr (NI > 1) fetch_k<D, KV8, 1>(cx, boff, lds_k);
+  if constexpr (NI > 2) { fetch_k<D, KV8, 2>(cx, boff, lds_k); fetch_k<D, KV8, 3>(cx, boff, lds_k); }
+}
+
+// mine: tiles up to the position of the wave's last row.  SHARED: that can be fewer than the workgroup's.
+template <int D, bool KV8, bool SHARED, bool PROBE>
+__device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, int mine, int n_nomask, BlockIds& ids,
                                           unsigned long long& boff, const bf16x8 (&qf)[D / 16], f32x16 (&O)[D / 32],
                                           float& m_run, float& l_run, float (&am)[kMaxSpans],
                                           const int (&sp_a)[kMaxSpans], const int (&sp_b)[kMaxSpans], const int* bt) {
@@ -477,11 +523,16 @@ __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem
     kt += 1;
   }
   // tiles whose successor needs the causal mask
-  while (kt < ntiles - 1) {
+  const int fetching = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
+  while (kt < fetching) {
     mx = tile_iter<D, KV8, true, true, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
                                               l_run, am, sp_a, sp_b);
     S0[0] = S1[0]; S0[1] = S1[1];
     kt += 1;
+  }
+  if (SHARED && mine < ntiles) {
+    for (; kt < ntiles; ++kt) fetch_iter<D, KV8>(cy, smem, kt, ntiles, ids, bt, boff);
+    return;
   }
   // last tile
   (void)tile_iter<D, KV8, true, false, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
@@ -554,7 +605,7 @@ __device__ __forceinline__ void rest_of_first_tiles(const WaveCtx& cx, unsigned 
 // qbase) for the heads of (kvh, hg).  ZERO_REST (self-planned calls): the wave that owns a probed
 // head in the item of row 0 also writes zeros to that head's `mass` slots that hold no row, so that
 // every entry of `mass` is written exactly once without a planner's zero-fill.
-template <int D, bool KV8, bool ZERO_REST>
+template <int D, bool KV8, bool SHARED, bool ZERO_REST>
 __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem, int kvh, int hg, int seq,
                                              int row0, int L, int n, int qbase) {
   using C = Cfg<D, KV8>;
@@ -571,6 +622,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   const int wg_pos_max = L - n + min(row0 + p.rows_per_wg, n) - 1;
   const int ntiles = wg_pos_max / kTileKeys + 1;
   const int n_nomask = (wave_pos_min + 1) / kTileKeys;   // tiles whose last key is within every row's horizon
+  const int mine = (L - n + min(wrow0 + kWaveRows, n) - 1) / kTileKeys + 1;     // tiles with a key within some row's
 
   const int* const bt = p.block_table + (size_t)seq * p.max_blocks;
   WaveCtx cx;
@@ -658,9 +710,9 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   __syncthreads();
 
   if (wave_probe)
-    run_tiles<D, KV8, true>(cx, smem, ntiles, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
+    run_tiles<D, KV8, SHARED, true>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
   else
-    run_tiles<D, KV8, false>(cx, smem, ntiles, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
+    run_tiles<D, KV8, SHARED, false>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
 
   // epilogue: normalise, transpose through LDS (16-byte chunks swizzled by row), coalesced stores
   const float l_tot = l_run + __shfl_xor(l_run, 32);
@@ -848,7 +900,9 @@ __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
 
 // PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
 // of the grid settles the rest, and `mass` is written entry by entry by the waves that own the entries.
-template <int D, bool KV8, bool PLANNED>
+// SHARED: several row blocks to a workgroup (groups of fewer than four heads).  An instantiation of its own, because the
+// spills that the fetch-only iterations bring cost a prompt of 2048 tokens at 32 / 8 heads 1.5 of its 49.5 us.
+template <int D, bool KV8, bool SHARED, bool PLANNED>
 __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
@@ -866,7 +920,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     asm volatile("" :: "s"(it.x), "s"(it.y), "s"(it.z), "s"(it.w), "s"(qbase), "s"(nitems), "s"(p.block_table), "s"(p.q),
                  "s"(p.k_cache), "s"(p.v_cache));
     if (item >= nitems) return;
-    prefill_item<D, KV8, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
+    prefill_item<D, KV8, SHARED, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
   } else {
     if (bid == (int)gridDim.x - 1) {
       settle_chunks(p, reinterpret_cast<int*>(smem));
@@ -876,18 +930,25 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     const bool some = find_item(p, item, threadIdx.x & 63, it);
     asm volatile("" :: "s"(p.block_table), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache));
     if (!some) return;
-    prefill_item<D, KV8, true>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
+    prefill_item<D, KV8, SHARED, true>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
   }
 }
 
-template <int D, bool KV8, bool PLANNED>
-hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
+template <int D, bool KV8, bool SHARED, bool PLANNED>
+hipError_t launch_kernel(const AttnParams& p, long long grid, hipStream_t st) {
   static std::atomic<unsigned long long> configured{0};
   constexpr int lds = Cfg<D, KV8>::LDS;
-  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, PLANNED>), lds, configured);
+  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, SHARED, PLANNED>), lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_prefill<D, KV8, PLANNED>), dim3((unsigned)grid), dim3(256), lds, st, p);
+  hipLaunchKernelGGL((k_prefill<D, KV8, SHARED, PLANNED>), dim3((unsigned)grid), dim3(256), lds, st, p);
   return hipGetLastError();
+}
+
+template <int D, bool KV8>
+hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
+  if (p.rows_per_wg == kWaveRows)
+    return p.pf_self ? launch_kernel<D, KV8, false, false>(p, grid, st) : launch_kernel<D, KV8, false, true>(p, grid, st);
+  return p.pf_self ? launch_kernel<D, KV8, true, false>(p, grid, st) : launch_kernel<D, KV8, true, true>(p, grid, st);
 }
 
 }  // namespace
@@ -896,10 +957,8 @@ hipError_t launch_prefill(const AttnParams& p, int D, hipStream_t st) {
   const long long grid = (long long)p.pf_cap * p.Hkv * p.hgroups + (p.pf_self ? 1 : 0);
   if (grid <= 0) return hipSuccess;
   if (!grid_fits(grid)) return hipErrorInvalidValue;
-  if (D == 128 && !p.kv8) return p.pf_self ? launch<128, false, false>(p, grid, st) : launch<128, false, true>(p, grid, st);
-  if (D == 128) return p.pf_self ? launch<128, true, false>(p, grid, st) : launch<128, true, true>(p, grid, st);
-  if (D == 64 && !p.kv8) return p.pf_self ? launch<64, false, false>(p, grid, st) : launch<64, false, true>(p, grid, st);
-  if (D == 64) return p.pf_self ? launch<64, true, false>(p, grid, st) : launch<64, true, true>(p, grid, st);
+  if (D == 128) return !p.kv8 ? launch<128, false>(p, grid, st) : launch<128, true>(p, grid, st);
+  if (D == 64) return !p.kv8 ? launch<64, false>(p, grid, st) : launch<64, true>(p, grid, st);
   return hipErrorInvalidValue;
 }
 

@@ -49,3 +49,25 @@ def test_fp32_rows_before_a_value_that_is_not_finite(d, at, what):
     bad.v_cache = b.v_cache
     bad.k_cache[blk, 1, r, 3] = float("nan")
     assert torch.equal(bits(_run(bad).out[:at]), bits(clean.out[:at]))
+
+
+@pytest.mark.parametrize("G,d,kv8", [(1, 64, False), (2, 64, False), (3, 64, True), (1, 128, False), (2, 128, True), (1, 128, True), (4, 128, False)])
+@pytest.mark.parametrize("at", [70, 200])
+def test_row_blocks_before_a_tile_whose_value_is_not_finite(G, d, kv8, at):
+    """Row blocks that share a workgroup (groups of fewer than four heads) walk its tiles together, but a block of 32
+    rows never multiplies a tile of 64 keys behind its last row."""
+    b = W.random_batch(3200 + d, [300, 140], [300, 140], 2 * G, 2, d, torch.bfloat16, num_probe_heads=2, max_sel_q=300, max_spans=2)
+    b.query_sel[:, 0], b.query_sel[:, 1] = 0, 300
+    if kv8:
+        b = W.fp8_cache_variant(b, 3201)
+    clean = _run(b, batch_kind=binding.BATCH_PREFILL_ONLY)
+    bad = b.to("cpu")
+    bad.v_cache = b.v_cache.clone()
+    blk, r = _row(b, 0, at)
+    bad.v_cache[blk, 1, r, 5] = 0x7F if kv8 else float("inf")
+    got = _run(bad, batch_kind=binding.BATCH_PREFILL_ONLY)
+    first = at // 64 * 64
+    assert torch.equal(bits(got.out[:first]), bits(clean.out[:first])) and torch.equal(bits(got.out[300:]), bits(clean.out[300:]))
+    assert torch.equal(bits(got.out[:, :G]), bits(clean.out[:, :G])) and torch.equal(bits(got.mass), bits(clean.mass))
+    hit = ~torch.isfinite(got.out[at:300, G:, 5].float())
+    assert bool(hit.all()) and torch.isfinite(got.out[:300, :, :5].float()).all()
