@@ -196,9 +196,10 @@ typedef struct hook_attn_probe_args {
   /* optional: the new tokens' keys and values, [total_q, Hkv, d] of `dtype`, device.  When both are
      given the call first writes them into k_cache / v_cache at positions L_i - n_i + t (exactly what
      hook_kv_write does, quantising for an 8-bit cache) and only then reads the caches - inside the
-     planning launch where the call has one, in the streaming kernel of a decode-only batch that plans
-     itself (each new row by the workgroup that reads its position), else in a launch ahead of the attention
-     kernels: the one place where the call writes through k_cache / v_cache. */
+     planning launch where the call has one, else in a launch ahead of the attention kernels: the one
+     place where the call writes through k_cache / v_cache.  (In a decode-only batch of at most 64
+     sequences the streaming kernel stores the rows and takes every new row it reads from k_new / v_new,
+     whichever sequence it belongs to, with the same results.) */
   const void*  k_new;
   const void*  v_new;
 } hook_attn_probe_args;

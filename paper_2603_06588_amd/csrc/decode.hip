@@ -72,13 +72,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 // the loop differs from the 16-bit one only in its loads and conversions.
 // The keys [kstart, kend) of one sequence for one (kv head, head group): four waves split the cache
 // blocks, merge in LDS and leave one partial record per head in slot `item`.
-// new_pos >= 0: the call brings the sequence's new key/value row (that position, row `qrow` of k_new / v_new);
-// the wave that meets the position takes the row from there instead of the cache and, if `store_new`,
-// writes it into the cache on the way, so no launch of its own has to do that first.
+// NewRows: the call brings the new key/value rows of its sequences, and nothing has written them into the cache
+// before.  Lane i holds where the row of sequence i goes, so a wave knows of every block it streams which rows
+// of it are new - its own sequence's or another's that shares the block - and takes those from k_new / v_new.
+// The workgroup of `store` writes its own sequence's row into the cache on the way.
+struct NewRows {
+  int blk;      // cache block, -1: none
+  int at;       // 16 * row of k_new / v_new + place in the block
+  bool store;
+};
 template <int D, int HP, bool KV8>
 __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4][HP][DecodeCfg<D>::PSTR], int tid, int lane,
                                              int w, int kvh, int head0, int seq, int qrow, int kstart, int kend,
-                                             int item, int new_pos, bool store_new) {
+                                             int item, const NewRows& fresh) {
   using C = DecodeCfg<D>;
   constexpr int NW = 4;
   const int blk0 = kstart >> 4;                         // first block of the range inside the sequence
@@ -127,14 +133,15 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
 
   // 16-byte pieces per lane and block: K rows for the score MFMA, V rows for P V (8-bit V: 8 bytes)
   constexpr int kKr = KV8 ? C::KSTEPS / 2 : C::KSTEPS;
-  struct Block { uint4 k[kKr]; uint4 v[C::KPL]; };
+  struct Block { uint4 k[kKr]; uint4 v[C::KPL]; int id; };
   const unsigned koff = (unsigned)j * D * ESZ + 16 * kq;
   const unsigned voff = (unsigned)(C::KPL * vk) * D * ESZ + 8 * ESZ * ch;
   // Rows past the last token lie in a block the sequence owns, and what they hold (anything, NaN included) is
   // replaced before use in the range's last block.  Loads are always issued, so that the compiler knows how
   // many are outstanding at a wait; past the wave's last block all lanes fetch the same 16 bytes.
   auto load_block = [&](int b, Block& d) {
-    const unsigned long long off = (unsigned long long)(unsigned)__builtin_amdgcn_readlane(ids, (b - b0) & 63) * blk_bytes;
+    d.id = __builtin_amdgcn_readlane(ids, (b - b0) & 63);
+    const unsigned long long off = (unsigned long long)(unsigned)d.id * blk_bytes;
     global_bytes kb = (global_bytes)(kbase + off), vb = (global_bytes)(vbase + off);
     unsigned ko = b < b1 ? koff : 0, vo = b < b1 ? voff : 0;     // (opaque, so that the loads take a scalar base and a 32-bit lane offset)
     asm("" : "+v"(ko), "+v"(vo));
@@ -188,47 +195,57 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
   auto compute_block = [&](int b, Block& d) {
     const int key0 = kstart + b * kBlock;
     const bool last = key0 + kBlock >= kend;     // uniform
-    if (last) {
-      const int r = new_pos - key0;        // the new row's place in this block
-      if (new_pos >= 0 && r < kBlock) {    // uniform
-        const int id = cload(bt, b);       // (`ids` may hold the next 64 ids already)
-        store_new = store_new && (unsigned)id < (unsigned)p.num_blocks;   // a clamped id is not written to
-        const char* kn = reinterpret_cast<const char*>(in_global(p.kvw.k_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
-        const char* vn = reinterpret_cast<const char*>(in_global(p.kvw.v_new)) + ((size_t)qrow * p.Hkv + kvh) * D * 2;
-        const size_t off = (size_t)(unsigned)id * blk_bytes;
-        char* kdst = const_cast<char*>(kbase) + off;
-        char* vdst = const_cast<char*>(vbase) + off;
+    for (unsigned long long hit = __builtin_amdgcn_ballot_w64(fresh.blk == d.id); hit != 0; hit &= hit - 1) {
+      const int owner = __builtin_ctzll(hit), at = __builtin_amdgcn_readlane(fresh.at, owner), r = at & 15;
+      const bool store = fresh.store && owner == seq;
+      const size_t row = ((size_t)(at >> 4) * p.Hkv + kvh) * D * 2, off = (size_t)(unsigned)d.id * blk_bytes;
+      global_bytes kn = (global_bytes)(unsigned long long)(size_t)p.kvw.k_new + row;
+      global_bytes vn = (global_bytes)(unsigned long long)(size_t)p.kvw.v_new + row;
+      char* kdst = const_cast<char*>(kbase) + off;
+      char* vdst = const_cast<char*>(vbase) + off;
+      // 16-bit rows are requested straight into the block's registers and stored once all of them are there
+      if (j == r) {
+#pragma unroll
+        for (int s = 0; s < kKr; ++s) {
+          if constexpr (KV8) {
+            const uint4 a = load_global16(kn + 128 * s + 32 * kq), b = load_global16(kn + 128 * s + 32 * kq + 16);
+            const float sc = cloadf(p.k_scale, kvh);
+            const uint2 lo = quantize_chunk_e4m3(a, sc), hi = quantize_chunk_e4m3(b, sc);
+            d.k[s] = make_uint4(lo.x, lo.y, hi.x, hi.y);
+          } else {
+            d.k[s] = load_global16(kn + 64 * s + 16 * kq);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < C::KPL; ++i) {
+        if (C::KPL * vk + i == r) {
+          d.v[i] = load_global16(vn + 16 * ch);
+          if constexpr (KV8) {
+            const uint2 v = quantize_chunk_e4m3(d.v[i], cloadf(p.v_scale, kvh));
+            d.v[i] = make_uint4(v.x, v.y, 0, 0);
+          }
+        }
+      }
+      // (and the blocks without a new row wait for their own loads only)
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+      __builtin_amdgcn_sched_barrier(0);
+      if (store) {
         if (j == r) {
 #pragma unroll
-          for (int s = 0; s < kKr; ++s) {
-            uint4 v;
-            if constexpr (KV8) {
-              const uint4* src = reinterpret_cast<const uint4*>(kn + 2 * (64 * s + 16 * kq));
-              const float sc = cloadf(p.k_scale, kvh);
-              const uint2 lo = quantize_chunk_e4m3(src[0], sc), hi = quantize_chunk_e4m3(src[1], sc);
-              v = make_uint4(lo.x, lo.y, hi.x, hi.y);
-            } else {
-              v = *reinterpret_cast<const uint4*>(kn + 64 * s + 16 * kq);
-            }
-            d.k[s] = v;
-            if (store_new) *reinterpret_cast<uint4*>(kdst + koff + 64 * s) = v;
-          }
+          for (int s = 0; s < kKr; ++s) *reinterpret_cast<uint4*>(kdst + koff + 64 * s) = d.k[s];
         }
 #pragma unroll
         for (int i = 0; i < C::KPL; ++i) {
           if (C::KPL * vk + i == r) {
-            const uint4 raw = *reinterpret_cast<const uint4*>(vn + 16 * ch);
-            if constexpr (KV8) {
-              const uint2 v = quantize_chunk_e4m3(raw, cloadf(p.v_scale, kvh));
-              d.v[i] = make_uint4(v.x, v.y, 0, 0);
-              if (store_new) *reinterpret_cast<uint2*>(vdst + voff + i * D) = v;
-            } else {
-              d.v[i] = raw;
-              if (store_new) *reinterpret_cast<uint4*>(vdst + voff + i * D * 2) = raw;
-            }
+            if constexpr (KV8) *reinterpret_cast<uint2*>(vdst + voff + i * D) = make_uint2(d.v[i].x, d.v[i].y);
+            else *reinterpret_cast<uint4*>(vdst + voff + i * D * 2) = d.v[i];
           }
         }
       }
+    }
+    if (last) {
 #pragma unroll
       for (int i = 0; i < C::KPL; ++i)           // 0 * NaN would poison the output
         if (key0 + C::KPL * vk + i >= kend) d.v[i] = make_uint4(0, 0, 0, 0);
@@ -451,7 +468,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
   const int CH = p.hdr->chunk_keys;
   const int kstart = it.y * CH;
   decode_range<D, HP, KV8>(p, red, tid, tid & 63, w, kvh, kvh * p.G + hg * HP, it.x, it.w, kstart, min(it.z, kstart + CH),
-                           item, -1, false);
+                           item, NewRows{-1, 0, false});
 }
 
 // A batch of single rows that plans itself.  The cache blocks of all its sequences, laid end to end, are cut
@@ -521,6 +538,25 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
 
   const BlockScan sc = scan_blocks(p, lane);
 
+  // where the new rows go (at most one sequence per lane: dec_write).  A length beyond the block table is clamped, so
+  // its new row has no place in the cache.
+  NewRows fresh = {-1, 0, hg == 0};
+  if (p.dec_write) {
+    if (sc.nblk[0] > 0 && !(sc.bits & kStatLenClamped)) {
+      const int blk = p.block_table[(size_t)lane * p.max_blocks + ((sc.L[0] - 1) >> 4)];
+      fresh.blk = (unsigned)blk < (unsigned)p.num_blocks ? blk : -1;
+      fresh.at = 16 * sc.qrow[0] + ((sc.L[0] - 1) & 15);
+    }
+    // Rows of a sequence that contradicts the hint are nobody's to store on the way: every workgroup writes all rows
+    // (the same bytes) before it reads.
+    if (__builtin_amdgcn_ballot_w64((sc.bits & kStatHint) != 0) != 0) {
+      for (int t = 0; t * kKvRowTile < p.total_q; ++t)
+        kv_write_tile<256, 1>(p.kvw, t, tid, reinterpret_cast<long long*>(&red[0][0][0]));
+      __threadfence();
+      __syncthreads();
+    }
+  }
+
   // the sequence that the range begins in, and its place there: by blocks, or by ranges where those end with
   // their sequence
   int at = g * sc.bpr, excl = sc.excl, total = sc.total;
@@ -566,15 +602,12 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   for (;;) {
     const int take = min((L + kBlock - 1) / kBlock - o, x1 - x);
     const int kend = min(L, (o + take) * kBlock);
-    // (a length beyond the block table is clamped: its new row has no place in the cache)
-    const bool has_new = p.dec_write && kend == L && cload(p.seq_lens, seq) == L;
     // Arguments and lane number are made opaque per piece: otherwise everything derived from them is kept in
     // registers across the loop (60 vector registers spilled instead of a few instructions repeated).
     const AttnParams& pp = reread_arguments();
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    decode_range<D, HP, KV8>(pp, red, w * 64 + ln, ln, w, kvh, head0, seq, qrow, o * kBlock, kend, g + seq, has_new ? L - 1 : -1,
-                             hg == 0);
+    decode_range<D, HP, KV8>(pp, red, w * 64 + ln, ln, w, kvh, head0, seq, qrow, o * kBlock, kend, g + seq, fresh);
     // where the merge kernel finds the sequence's records
     if (o == 0 && kvh == 0 && hg == 0 && tid == 0)
       p.seq_dec[seq] = make_int2(g + seq, sc.whole ? ((L + kBlock - 1) / kBlock + sc.bpr - 1) / sc.bpr
@@ -594,11 +627,9 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   }
 }
 
-// What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word, and
-// the cache write of rows that contradict the hint (they are not computed, so no workgroup meets them while streaming).
+// What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word.
 template <int NT>
 __device__ __forceinline__ void settle_batch(const AttnParams& p) {
-  __shared__ long long dst_row[kKvRowTile];
   __shared__ int sh_bits;
   if (threadIdx.x == 0) sh_bits = 0;
   __syncthreads();
@@ -609,10 +640,6 @@ __device__ __forceinline__ void settle_batch(const AttnParams& p) {
   __syncthreads();
   bits = sh_bits;
   if (threadIdx.x == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = bits; }
-  if ((bits & kStatHint) && p.dec_write) {
-    const int ntiles = (p.total_q + kKvRowTile - 1) / kKvRowTile;
-    for (int t = 0; t < ntiles; ++t) kv_write_tile<NT>(p.kvw, t, threadIdx.x, dst_row);
-  }
 }
 
 // Merges the partial records of a sequence: WPH waves per q head take its records in turn (a workgroup is

@@ -30,7 +30,7 @@ __device__ __forceinline__ uint2 quantize_chunk_e4m3(const uint4 v, float scale)
 // (binary search in cu_q_lens) and its cache slot; then every thread moves 16-byte chunks.
 // Rows of invalid sequences, positions beyond the block table and block ids outside the cache are
 // dropped: nothing outside the cache is ever written.
-template <int NT>
+template <int NT, int kInFlight = 4>
 __device__ __forceinline__ void kv_write_tile(const KvWriteParams& p, int tile, int tid, long long* dst_row) {
   const int rc = p.row_chunks;
   const int row0 = tile * kKvRowTile;
@@ -63,7 +63,6 @@ __device__ __forceinline__ void kv_write_tile(const KvWriteParams& p, int tile, 
   const int nchunks = nrow * row_stride;
   const uint4* ksrc = p.k_new + (size_t)row0 * row_stride;
   const uint4* vsrc = p.v_new + (size_t)row0 * row_stride;
-  constexpr int kInFlight = 4;
   for (int base = tid; base < nchunks; base += NT * kInFlight) {
     uint4 kv[kInFlight], vv[kInFlight];
 #pragma unroll

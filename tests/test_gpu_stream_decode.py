@@ -89,3 +89,40 @@ def test_new_row_in_a_range_of_256_blocks():
     torch.cuda.synchronize()
     assert torch.equal(bits(first.k_cache), bits(second.k_cache)) and torch.equal(bits(first.v_cache), bits(second.v_cache))
     assert torch.equal(bits(call.out), bits(ref.out)) and torch.equal(bits(call.mass), bits(ref.mass))
+
+
+@pytest.mark.parametrize("nseq,kv8,d,Hq,Hkv", [(3, False, 128, 32, 8), (40, False, 128, 32, 2), (64, True, 128, 32, 8), (17, False, 64, 8, 2),
+                                               (20, True, 64, 16, 4), (65, False, 128, 32, 8)])
+@pytest.mark.parametrize("chunk", [False, True])
+def test_new_rows_are_read_by_the_other_sequences_of_the_call(nseq, kv8, d, Hq, Hkv, chunk):
+    """Rows of one context at consecutive positions: each reads the rows that those in front of it bring, as if all had
+    been written before the call.  (One context also meets the block again further in front; with `chunk` one sequence
+    contradicts the hint, whose rows are written and read all the same.)"""
+    print(f"[case] shared context nseq={nseq} kv8={kv8} d={d} Hq={Hq} Hkv={Hkv} chunk={chunk}", flush=True)
+    lens, qlens = [300 + i for i in range(nseq)], [1] * nseq
+    if chunk:
+        lens[1], qlens[1], qlens[2] = 302, 2, 0              # brings the rows at positions 300 and 301
+    b = W.random_batch(2400 + nseq, lens, qlens, Hq, Hkv, d, torch.bfloat16, num_probe_heads=4, max_sel_q=1, max_spans=2, poison=False)
+    if kv8:
+        b = W.fp8_cache_variant(b, 2401)
+    last = nseq - 1
+    b.block_table[:] = b.block_table[last]
+    b.block_table[0, 2] = b.block_table[last, (300 - 1) // 16]
+    b.query_sel[:, 0], b.query_sel[:, 1] = 0, 1
+    gen = torch.Generator().manual_seed(7)
+    k_new, v_new = (3 * torch.randn((b.total_q, Hkv, d), generator=gen).to(torch.bfloat16).to(DEV) for _ in range(2))
+    first, second = b.to(DEV), b.to(DEV)
+    first.k_cache, first.v_cache = b.k_cache.clone().to(DEV), b.v_cache.clone().to(DEV)
+    second.k_cache, second.v_cache = b.k_cache.clone().to(DEV), b.v_cache.clone().to(DEV)
+    binding.hook_kv_write(k_new, v_new, first.block_table, first.seq_lens, first.cu_q_lens, first.k_cache, first.v_cache,
+                          k_scale=first.k_scale, v_scale=first.v_scale)
+    ref = binding.call_from_batch(first, batch_kind=binding.BATCH_DECODE_ONLY)
+    call = binding.call_from_batch(second, batch_kind=binding.BATCH_DECODE_ONLY, k_new=k_new, v_new=v_new)
+    for c in (ref, call):
+        c.out.fill_(7.0)                                      # (rows that are not computed stay untouched)
+        c.launch()
+    torch.cuda.synchronize()
+    view = (lambda t: t) if kv8 else bits
+    assert torch.equal(view(first.k_cache), view(second.k_cache)) and torch.equal(view(first.v_cache), view(second.v_cache))
+    assert torch.equal(bits(call.out), bits(ref.out)) and torch.equal(bits(call.mass), bits(ref.mass))
+    assert call.device_status() == ref.device_status() == (8 if chunk else 0)
