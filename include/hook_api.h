@@ -96,7 +96,8 @@ typedef enum hook_batch_kind {
  * The work lists in the workspace depend only on the batch description (seq_lens, cu_q_lens, the
  * shape fields and batch_kind), not on q, the caches or the probe arguments, and every layer of a
  * model step sees the same batch.  HOOK_PLAN_REUSE tells a call that the workspace still holds the
- * lists a HOOK_PLAN_FRESH call wrote for exactly this batch: the planning kernel is left out.
+ * lists a HOOK_PLAN_FRESH call wrote for exactly this batch (and was given as `workspace_bytes` what
+ * this call is given): the planning kernel is left out.
  * Because that kernel is also what zero-fills `mass`, a reusing call writes only the entries of
  * valid selected rows and leaves every other entry of `mass` as it is (give it a zeroed buffer
  * once; those entries are never written afterwards).  Reusing lists of a different batch is a
@@ -181,7 +182,7 @@ typedef struct hook_attn_probe_args {
 
   /* scratch (device, caller-allocated, 256-byte aligned) and stream */
   void*  workspace;
-  size_t workspace_bytes;      /* >= hook_attn_probe_workspace_bytes(args) */
+  size_t workspace_bytes;      /* hook_attn_probe_workspace_bytes(args) or more */
   void*  stream;               /* hipStream_t; null = the default stream */
 
   /* what the caller knows about the batch (it built cu_q_lens on the host); 0 is always valid */
@@ -208,6 +209,10 @@ typedef struct hook_attn_probe_args {
  * Bytes of workspace hook_attn_probe needs for these shapes.  Reads only the
  * scalar shape fields (num_seqs, total_q, head counts, head_dim,
  * max_blocks_per_seq, max_spans, dtype); returns 0 if they are unsupported.
+ * The size never falls as num_seqs, total_q or max_blocks_per_seq grow, so a workspace asked for once for
+ * the largest batch serves the smaller ones.  (A workspace that holds the work lists and records of a
+ * planned call, but not those that single rows need to plan themselves, is accepted too, at the
+ * cost of the planning launch; HOOK_ERR_WORKSPACE is returned below that.)
  */
 size_t hook_attn_probe_workspace_bytes(const hook_attn_probe_args* args);
 
@@ -216,8 +221,8 @@ size_t hook_attn_probe_workspace_bytes(const hook_attn_probe_args* args);
  * waiting.  Sequences with one query row take a split-key decode path whose
  * partial results are merged by a combine kernel; longer chunks take the tiled
  * prefill path; both may be mixed in one call.  Results are deterministic: the
- * same inputs (batch_kind included: a hint may change how single rows are split,
- * which changes the order of the sums) give bit-identical `out` and `mass` on
+ * same inputs (batch_kind and workspace_bytes included: they may change how single rows are
+ * split, which changes the order of the sums) give bit-identical `out` and `mass` on
  * every call, for any physical block permutation, and `out` does not depend on
  * the probe arguments.
  * HOOK_F32 inputs take one full-precision kernel that needs no work lists: batch_kind and plan_mode
@@ -229,7 +234,7 @@ hook_status hook_attn_probe(const hook_attn_probe_args* args);
 /*
  * hook_attn_probe for callers that cannot allocate device memory and have no workspace to pass:
  * code under HIP graph capture, tight serving loops, harnesses that forbid allocation.  The same
- * launches with the same results bit for bit, but the work lists and decode partial results live
+ * launches with the same results bit for bit as with a workspace of the reported size, but the work lists and decode partial results live
  * in a fixed array of HOOK_STATIC_SCRATCH_BYTES that is part of the library's device image (every
  * GPU the library runs on holds its own copy until the process ends).  args->workspace and
  * args->workspace_bytes are ignored; inputs and outputs are still the caller's.  The call makes no

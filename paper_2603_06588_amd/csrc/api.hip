@@ -19,7 +19,8 @@ constexpr long long kSelfPlanMaxWgs = 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-  size_t off_hdr, off_pf, off_dec, off_seq, off_part, total;
+  size_t off_hdr, off_pf, off_dec, off_seq, off_part;
+  size_t needed, reported;      // smallest workspace that is accepted; size to ask for
   int pf_cap, dec_cap, ranges, hpw, rows_per_wg, hgroups, dec_hp, dec_hgroups;
 };
 
@@ -51,15 +52,14 @@ int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_p
   return (int)cap;
 }
 
-// Ranges of a self-planned batch of single rows (decode.hip), 0 where the planner is kept: one resident
+// Ranges of a self-planned batch of single rows (decode.hip): one resident
 // round of workgroups (256 compute units times the 3 workgroups each holds, 2 for groups of 8 heads) - a
 // second, partial round costs more than its finer balance gains - but no range shorter than
-// kStreamMinBlocks.  Up to kStreamMaxSeqs sequences, whose lengths every workgroup can afford to scan.
-int stream_ranges(const hook_attn_probe_args* a, const Layout& l) {
-  if (a->dtype != HOOK_BF16 || a->num_seqs <= 0 || a->num_seqs > kStreamMaxSeqs) return 0;
+// kStreamMinBlocks.
+int stream_ranges(const hook_attn_probe_args* a, const Layout& l, int num_seqs) {
   const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3), wgs = (long long)a->num_kv_heads * l.dec_hgroups;
   // (and one range per sequence more, for ranges that end with their sequence)
-  const long long finest = ((long long)a->num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks + a->num_seqs;
+  const long long finest = ((long long)num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks + num_seqs;
   const long long ranges = (one_round + wgs - 1) / wgs;
   return (int)(ranges < finest ? ranges : finest);
 }
@@ -73,11 +73,17 @@ size_t place(const hook_attn_probe_args* a, Layout& l) {
   l.off_seq = off;  off = align_up(off + sizeof(int2) * (size_t)(a->num_seqs > 0 ? a->num_seqs : 1));
   l.off_part = off;
   off = align_up(off + sizeof(float) * (size_t)l.dec_cap * a->num_q_heads * (a->head_dim + kPartialPad));
-  l.total = off;
-  return l.total;
+  return off;
 }
 
-Layout make_layout(const hook_attn_probe_args* a) {
+// The layout for a workspace of `bytes`.  Single rows of up to kStreamMaxSeqs sequences, whose lengths every
+// workgroup can afford to scan, plan themselves where their records fit; those are numbered by range + sequence, which
+// can take more slots than the planner's items.  A smaller workspace keeps the planner, so every size that holds the
+// planner's items is accepted.
+// The size reported is no smaller for a larger batch (one buffer, asked for once, serves every batch up to that one with
+// the kernels that its own size would have got it): beyond kStreamMaxSeqs it still holds the records of that many, and
+// up to the static scratch's size it asks for no more than that.
+Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
   Layout l{};
   const int G = a->num_q_heads / a->num_kv_heads;
   l.hpw = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
@@ -89,17 +95,19 @@ Layout make_layout(const hook_attn_probe_args* a) {
     l.pf_cap = a->total_q / l.rows_per_wg + a->num_seqs;
     l.dec_cap = decode_item_bound(a->num_seqs < a->total_q ? a->num_seqs : a->total_q,
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
-    // A self-planned batch numbers its records by range + sequence, which can take more slots than the planner's
-    // items.  Where the extra slots would push a batch out of the static scratch it keeps the planner.
-    l.ranges = stream_ranges(a, l);
-    if (l.ranges > 0 && l.dec_cap < l.ranges + a->num_seqs) {
-      const int planned_cap = l.dec_cap;
-      const bool fitted = place(a, l) <= (size_t)HOOK_STATIC_SCRATCH_BYTES;
-      l.dec_cap = l.ranges + a->num_seqs;
-      if (fitted && place(a, l) > (size_t)HOOK_STATIC_SCRATCH_BYTES) { l.dec_cap = planned_cap; l.ranges = 0; }
+    l.needed = l.reported = place(a, l);
+    if (a->num_seqs > 0) {
+      const int planned_cap = l.dec_cap, n = a->num_seqs < kStreamMaxSeqs ? a->num_seqs : kStreamMaxSeqs;
+      const int ranges = stream_ranges(a, l, n);
+      if (l.dec_cap < ranges + n) l.dec_cap = ranges + n;
+      const size_t streaming = place(a, l), fixed = (size_t)HOOK_STATIC_SCRATCH_BYTES;
+      l.reported = l.needed > fixed || streaming < fixed ? streaming : fixed;
+      if (n == a->num_seqs && bytes >= streaming) { l.ranges = ranges; return l; }
+      l.dec_cap = planned_cap;
     }
   }
-  place(a, l);
+  const size_t total = place(a, l);
+  if (a->dtype != HOOK_BF16) l.needed = l.reported = total;
   return l;
 }
 
@@ -109,7 +117,7 @@ extern "C" {
 
 size_t hook_attn_probe_workspace_bytes(const hook_attn_probe_args* a) {
   if (!a || !shapes_supported(a)) return 0;
-  return make_layout(a).total;
+  return make_layout(a, 0).reported;
 }
 
 }  // extern "C"
@@ -156,13 +164,13 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   if (checked != HOOK_OK || nothing_to_do) return checked;
   const int P = a->num_probe_heads;
   const bool kv8 = a->kv_dtype == HOOK_KV_FP8_E4M3;
-  const Layout l = make_layout(a);
+  const Layout l = make_layout(a, workspace_bytes);
   // one-dimensional launch grids over the item capacities
   if (a->dtype == HOOK_BF16 &&
       (!grid_fits((long long)l.pf_cap * a->num_kv_heads * l.hgroups) ||
        !grid_fits((long long)l.dec_cap * a->num_kv_heads * l.dec_hgroups)))
     return HOOK_ERR_UNSUPPORTED;
-  if (!workspace || workspace_bytes < l.total || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
+  if (!workspace || workspace_bytes < l.needed || (reinterpret_cast<uintptr_t>(workspace) % kAlign) != 0)
     return HOOK_ERR_WORKSPACE;
 
   AttnParams p{};
@@ -212,7 +220,8 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.batch_kind = a->batch_kind;
   // up to kStreamMaxSeqs sequences single rows find their work themselves, and so do row blocks while there are
   // few of them (or the planner would have nothing to sort)
-  const bool self = a->dtype == HOOK_BF16 && l.ranges > 0;
+  const bool self = a->dtype == HOOK_BF16 && a->num_seqs <= kStreamMaxSeqs &&
+                    (l.ranges > 0 || a->batch_kind == HOOK_BATCH_PREFILL_ONLY);
   p.dec_ranges = self && a->batch_kind != HOOK_BATCH_PREFILL_ONLY ? l.ranges : 0;
   p.pf_self = self && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
               (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups <= kSelfPlanMaxWgs);
@@ -285,7 +294,7 @@ hook_status hook_attn_probe_static(const hook_attn_probe_args* a) {
   bool nothing_to_do = false;
   const hook_status checked = hook::check_attn_probe_args(a, &nothing_to_do);
   if (checked != HOOK_OK || nothing_to_do) return checked;
-  if (make_layout(a).total > (size_t)HOOK_STATIC_SCRATCH_BYTES) return HOOK_ERR_WORKSPACE;
+  if (make_layout(a, 0).needed > (size_t)HOOK_STATIC_SCRATCH_BYTES) return HOOK_ERR_WORKSPACE;
   void* ws = scratch_on_current_device();
   if (!ws) return HOOK_ERR_LAUNCH;
   return run_attn_probe(a, nullptr, ws, (size_t)HOOK_STATIC_SCRATCH_BYTES);
