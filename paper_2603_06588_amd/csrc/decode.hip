@@ -41,13 +41,6 @@ __device__ __forceinline__ uint32_t fp8x2_to_bf16x2(uint32_t w, bool upper_half)
   return u;
 }
 
-// The kernel's argument block, through a pointer whose origin the compiler cannot see.
-__device__ __forceinline__ const AttnParams& reread_arguments() {
-  auto a = (const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(a));
-  return *(const AttnParams*)(const __attribute__((address_space(4))) AttnParams*)a;
-}
-
 // A pointer read through it is not known to point to global memory unless this says so.
 template <typename T>
 __device__ __forceinline__ T* in_global(T* ptr) {
@@ -627,19 +620,21 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   }
 }
 
-// What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word.
+// What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word, zeros
+// for elements of the head list that no head owns.
 template <int NT>
 __device__ __forceinline__ void settle_batch(const AttnParams& p) {
   __shared__ int sh_bits;
   if (threadIdx.x == 0) sh_bits = 0;
   __syncthreads();
-  int bits = 0;
+  int bits = p.plan_fresh && bad_head_list<NT>(p) ? kBadHeadList : 0;
   for (int i = threadIdx.x; i < p.num_seqs; i += NT)
     bits |= decode_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]).bits;
   if (bits) atomicOr(&sh_bits, bits);
   __syncthreads();
   bits = sh_bits;
-  if (threadIdx.x == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = bits; }
+  if (threadIdx.x == 0) { p.hdr->n_prefill = 0; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = bits & ~kBadHeadList; }
+  if (bits & kBadHeadList) zero_unowned_mass<NT>(p);
 }
 
 // Merges the partial records of a sequence: WPH waves per q head take its records in turn (a workgroup is
@@ -659,6 +654,10 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), part = wave % WPH;
   const int head = blockIdx.y * (NWV / WPH) + wave / WPH;
   const bool stream = p.dec_ranges > 0;
+  if (seq == p.num_seqs) {      // the column behind the sequences': nothing to wait for but its own trip
+    if (blockIdx.y == 0) settle_batch<64 * NWV>(p);
+    return;
+  }
   int2 sd = p.seq_dec[seq];
   const int qrow = p.cu_q_lens[seq];
   // (the clamps only matter if the work lists were not this batch's: no record outside the workspace is read)
@@ -676,11 +675,16 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
 
   int pslot = -1, slot_row = -1;       // this head's place in the probe list; the selected row's slot, -1: none
   if (p.P > 0 && head < p.Hq) {
+    // (find_probe_slot's answer without its chain of loads, as long as the list is in order)
+    bool ordered = true;
     for (int i0 = 0; i0 < p.P; i0 += 64) {
-      const int ph = i0 + lane < p.P ? p.probe_heads[i0 + lane] : -1;
+      const int i = i0 + lane;
+      const int ph = i < p.P ? p.probe_heads[i] : -1, before = i < p.P && i > 0 ? p.probe_heads[i - 1] : -2;
       const unsigned long long hit = __builtin_amdgcn_ballot_w64(ph == head);
-      if (hit) { pslot = i0 + __builtin_ctzll(hit); break; }
+      if (hit && pslot < 0) pslot = i0 + __builtin_ctzll(hit);
+      ordered = ordered && __builtin_amdgcn_ballot_w64(i < p.P && i > 0 && ph <= before) == 0;
     }
+    if (!ordered) pslot = find_probe_slot(p.probe_heads, p.P, head);
     // row t = 0 sits in slot t - begin, as on every other path
     const int qb = p.query_sel[2 * seq], qe = min(p.query_sel[2 * seq + 1], qb + p.NQ);
     if (qb <= 0 && qe > 0) slot_row = -qb;
@@ -766,7 +770,6 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
       }
     }
   }
-  if (stream && p.batch_kind == 2 && seq == 0 && blockIdx.y == 0) settle_batch<64 * NWV>(p);
 }
 
 template <int D, int HP>
@@ -811,7 +814,8 @@ hipError_t launch_combine(const AttnParams& p, int D, hipStream_t st) {
   // its sequences have few records; a self-planned sequence has about ranges / num_seqs + 2
   const int per_seq = p.dec_ranges > 0 ? p.dec_ranges / p.num_seqs + 2 : 1;
   const int wph = per_seq > 32 ? 16 : per_seq > 4 ? 4 : 1;
-  const dim3 grid((unsigned)p.num_seqs, (unsigned)(wph == 1 ? (p.Hq + 3) / 4 : p.Hq));
+  const int settles = p.dec_ranges > 0 && p.batch_kind == 2 ? 1 : 0;
+  const dim3 grid((unsigned)(p.num_seqs + settles), (unsigned)(wph == 1 ? (p.Hq + 3) / 4 : p.Hq));
   if (D == 128 && wph == 16) hipLaunchKernelGGL((k_combine<128, 16>), grid, dim3(1024), 0, st, p);
   else if (D == 128 && wph == 4) hipLaunchKernelGGL((k_combine<128, 4>), grid, dim3(256), 0, st, p);
   else if (D == 128) hipLaunchKernelGGL((k_combine<128, 1>), grid, dim3(256), 0, st, p);

@@ -38,6 +38,7 @@ constexpr float kLazyTau = 8.0f;
 
 // Device-side status bits written by the plan kernel.
 enum : int { kStatQGtL = 1, kStatLenClamped = 2, kStatNegative = 4, kStatHint = 8 };
+constexpr int kBadHeadList = 1 << 16;   // beside them inside a kernel, never reported
 
 struct PlanHeader {
   int n_prefill;   // prefill work items (row blocks)
@@ -112,6 +113,13 @@ struct AttnParams {
   int dec_hp;                       // q heads per decode workgroup (8, 4, 2 or 1)
   int dec_hgroups;                  // G / dec_hp
 };
+
+// The kernel's argument block, through a pointer whose origin the compiler cannot see.
+__device__ __forceinline__ const AttnParams& reread_arguments() {
+  auto a = (const __attribute__((address_space(4))) void*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return *(const AttnParams*)(const __attribute__((address_space(4))) AttnParams*)a;
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -209,6 +217,31 @@ __device__ __forceinline__ int find_probe_slot_uniform(const int* probe_heads, i
     if (cload(probe_heads, mid) < head) lo = mid + 1; else hi = mid;
   }
   return (lo < P && cload(probe_heads, lo) == head) ? lo : -1;
+}
+
+// Calls without a planner: every entry of `mass` is written by the wave that owns its head, so elements of the head list
+// that no head owns (find_probe_slot does not lead to them: repeated, out of range, out of order) are cleared by one
+// workgroup of NT threads.  Whether there can be any: this thread's share of the list, to be fetched with whatever else
+// that workgroup waits for.
+template <int NT>
+__device__ __forceinline__ bool bad_head_list(const AttnParams& p) {
+  bool bad = false;
+  for (int i = threadIdx.x; i < p.P; i += NT) {
+    const int h = p.probe_heads[i];
+    if ((unsigned)h >= (unsigned)p.Hq || (i > 0 && h <= p.probe_heads[i - 1])) bad = true;
+  }
+  return bad;
+}
+
+template <int NT>
+__device__ __forceinline__ void zero_unowned_mass(const AttnParams& p) {
+  const int per = p.NQ * p.S;
+  for (int ps = 0; ps < p.P; ++ps) {
+    const int h = p.probe_heads[ps];
+    if ((unsigned)h < (unsigned)p.Hq && find_probe_slot(p.probe_heads, p.P, h) == ps) continue;
+    for (int i = 0; i < p.num_seqs; ++i)
+      for (int e = threadIdx.x; e < per; e += NT) p.mass[((size_t)i * p.P + ps) * per + e] = 0.0f;
+  }
 }
 
 // Spans of one sequence, all fetched before any is waited for (entries past S repeat the last

@@ -875,13 +875,14 @@ __device__ __forceinline__ bool find_item(const AttnParams& p, int item, int lan
 }
 
 // What the planner does besides, by a workgroup of its own: the header with the status word, and zeros in the `mass`
-// entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those).
+// entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those) and of elements
+// of the head list that no head owns.
 __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   int* const skip = sh + 2;     // [kStreamMaxSeqs]
   const int tid = threadIdx.x;
   if (tid < 2) sh[tid] = 0;
   __syncthreads();
-  int bits = 0, blocks = 0;
+  int bits = p.plan_fresh && bad_head_list<256>(p) ? kBadHeadList : 0, blocks = 0;
   for (int i = tid; i < p.num_seqs; i += 256) {
     const ChunkSeq s = chunk_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
     bits |= s.bits;
@@ -891,11 +892,12 @@ __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   if (bits) atomicOr(&sh[0], bits);
   if (blocks) atomicAdd(&sh[1], blocks);
   __syncthreads();
-  if (tid == 0) { p.hdr->n_prefill = sh[1]; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = sh[0]; }
+  if (tid == 0) { p.hdr->n_prefill = sh[1]; p.hdr->n_decode = 0; p.hdr->chunk_keys = 0; p.hdr->status = sh[0] & ~kBadHeadList; }
   if (p.batch_kind == 1 && p.plan_fresh && p.P > 0)
     for (int i = 0; i < p.num_seqs; ++i)
       if (skip[i])
         for (int e = tid; e < p.P * p.NQ * p.S; e += 256) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
+  if (sh[0] & kBadHeadList) zero_unowned_mass<256>(p);
 }
 
 // PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
@@ -923,7 +925,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     prefill_item<D, KV8, SHARED, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
   } else {
     if (bid == (int)gridDim.x - 1) {
-      settle_chunks(p, reinterpret_cast<int*>(smem));
+      settle_chunks(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
       return;
     }
     ChunkItem it;
