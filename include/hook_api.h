@@ -410,20 +410,24 @@ hook_status hook_kv_write(const hook_kv_write_args* args);
  *   - max_spans may be up to HOOK_MAX_SPANS_WIDE,
  *   - no attention output is computed: out and v_cache are ignored (run hook_attn_probe with
  *     num_probe_heads = 0 for the output),
- *   - workspace is optional scratch: with at least hook_span_mass_workspace_bytes(args) bytes (8-byte
- *     aligned) the two passes run as two kernels split over keys and spans and use the whole chip;
- *     without it one workgroup per (sequence, head, 16 rows) does everything (same results to
- *     rounding, several times slower on long sequences),
+ *   - workspace is optional scratch: with hook_span_mass_workspace_bytes(args) bytes (8-byte
+ *     aligned) the two passes run as two kernels split over keys and spans and use the whole chip.
+ *     From one key split per 2048 keys of max_blocks_per_seq on (about half of those bytes) a smaller
+ *     one is used as well, with fewer splits.  What it held is destroyed, and the number of splits
+ *     changes the order of the sums: results are reproducible bit for bit at the same workspace_bytes.
+ *     A smaller or misaligned workspace is left untouched and one workgroup per (sequence, head,
+ *     16 rows) does everything, as without one (same results to rounding, several times slower on
+ *     long sequences),
  *   - only HOOK_BF16 inputs are supported (HOOK_ERR_UNSUPPORTED otherwise); the key cache may be
  *     8-bit (kv_dtype, k_scale; v_scale is not read),
  * Two passes over the keys of each (sequence, probed head, 16-row block): exact softmax maximum
- * and normaliser first, then the span sums; no atomics, results reproducible bit for bit.
+ * and normaliser first, then the span sums; no atomics.
  * A content-free calibration prompt is a second call; hook_reduce_mass with negated weights
  * subtracts it.
  */
 hook_status hook_span_mass(const hook_attn_probe_args* args);
 
-/* Scratch bytes that let hook_span_mass take its split path (0: not available for these shapes). */
+/* Scratch bytes that let hook_span_mass split its work as finely as pays (0: not available for these shapes). */
 size_t hook_span_mass_workspace_bytes(const hook_attn_probe_args* args);
 
 /*

@@ -464,7 +464,11 @@ __global__ __launch_bounds__(kSumWaves * 64) void k_span_sums(const SpanParams p
 }
 
 // geometry of the split path from host scalars only
-struct SplitGeom { int nsplit, sgroups, nq_pad; size_t bytes; bool usable; };
+struct SplitGeom { int nsplit, least, sgroups, nq_pad; size_t bytes; bool usable; };
+
+// Scratch memory for fewer key splits than one per this many keys is not used (nor touched): pass 1 would run on a small
+// part of the chip.
+constexpr int kLeastSplitKeys = 2 * kSplitKeys;
 
 inline SplitGeom split_geometry(const hook_attn_probe_args* a) {
   SplitGeom g{};
@@ -472,8 +476,12 @@ inline SplitGeom split_geometry(const hook_attn_probe_args* a) {
   g.nsplit = (int)((max_ctx + kSplitKeys - 1) / kSplitKeys);
   if (g.nsplit < 1) g.nsplit = 1;
   if (g.nsplit > kMaxSplits) g.nsplit = kMaxSplits;
-  if ((long long)a->num_seqs * g.nsplit > 65535) g.nsplit = 65535 / a->num_seqs;   // likewise
-  // one span per wave, as long as the launch grid's third dimension (65535) holds the groups
+  g.least = (int)((max_ctx + kLeastSplitKeys - 1) / kLeastSplitKeys);
+  if (g.least > kMaxSplits) g.least = kMaxSplits;
+  // as many as the launch grid's third dimension (65535) holds
+  if ((long long)a->num_seqs * g.nsplit > 65535) g.nsplit = 65535 / a->num_seqs;
+  if (g.least > g.nsplit) g.least = g.nsplit;
+  // one span per wave, as long as that dimension holds the groups
   g.sgroups = (a->max_spans + kSumWaves - 1) / kSumWaves;
   if (g.sgroups < 1) g.sgroups = 1;
   if (a->num_seqs > 0 && g.sgroups > 65535 / a->num_seqs) g.sgroups = 65535 / a->num_seqs;
@@ -523,11 +531,11 @@ extern "C" hook_status hook_span_mass(const hook_attn_probe_args* a) {
   hipStream_t st = static_cast<hipStream_t>(a->stream);
 
   // with enough scratch memory: pass 1 split over the keys, pass 2 over the spans
-  // (as many key splits as the scratch memory holds, at least one)
+  // (as many key splits as the scratch memory holds; below the least number it is left alone)
   SplitGeom geo = split_geometry(a);
   const size_t per_split = geo.bytes / (size_t)geo.nsplit;
   if (a->workspace_bytes < geo.bytes) geo.nsplit = (int)(a->workspace_bytes / per_split);
-  if (geo.usable && a->workspace && geo.nsplit >= 1 && (reinterpret_cast<uintptr_t>(a->workspace) % 8) == 0) {
+  if (geo.usable && a->workspace && geo.nsplit >= geo.least && (reinterpret_cast<uintptr_t>(a->workspace) % 8) == 0) {
     p.stats = static_cast<float2*>(a->workspace);
     p.nsplit = geo.nsplit; p.sgroups = geo.sgroups; p.nq_pad = geo.nq_pad;
     const unsigned gx = (unsigned)((geo.nq_pad / kSmRows + kSplitBlocks - 1) / kSplitBlocks);

@@ -133,3 +133,30 @@ def test_span_mass_over_an_8_bit_cache(d):
     wide = binding.hook_span_mass_batch(few8)
     torch.cuda.synchronize()
     assert (call.mass - wide).abs().max().item() <= 2e-5
+
+
+@pytest.mark.parametrize("seqs,ctx", [(2, 9000), (1, 40000), (3, 500)])
+def test_span_mass_with_scratch_for_some_of_the_splits(seqs, ctx):
+    """Scratch for the full number of splits, for one per 2048 keys (at most 16) and for one in between is used; below
+    that it is left as it was.  All give the oracle's masses."""
+    from paper_2603_06588_amd import binding
+    lens = [ctx - 37 * i for i in range(seqs)]
+    b = W.random_batch(580 + seqs, lens, [20] * seqs, 4, 2, 64, torch.bfloat16, std=1.0, num_probe_heads=2, max_sel_q=20, max_spans=12)
+    b.query_sel[:, 0], b.query_sel[:, 1] = 3, 20
+    _, want = oracle.attn_probe_batch(b, rows=_selected_rows(b))
+    bd = b.to(DEV)
+    per_split = seqs * 2 * 32 * 8                       # (max, sum) of every head and row slot, rows in whole blocks of 16
+    keys = 16 * b.max_blocks_per_seq
+    full, least = min(-(-keys // 1024), 16), min(-(-keys // 2048), 16)
+    for splits in sorted({full, (full + least) // 2, least, least - 1, 0}):
+        for short in (0, 1):                            # and one byte less: the next smaller number of splits
+            room = splits * per_split - short
+            if room <= 0:
+                continue
+            ws = torch.full((full * per_split,), 0x5A, dtype=torch.uint8, device=DEV)
+            got = binding.hook_span_mass_batch(bd, workspace=ws[:room])
+            torch.cuda.synchronize()
+            used = room // per_split if room // per_split >= least else 0
+            assert bool((ws[used * per_split:] == 0x5A).all()), (splits, short)
+            assert bool((ws == 0x5A).all()) == (used == 0), (splits, short)
+            assert (got.cpu().double() - want).abs().max().item() <= MASS_TOL, (splits, short)
