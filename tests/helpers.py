@@ -24,28 +24,37 @@ def run_hip(b, probe: bool = True):
     return out, mass
 
 
-def planned_reference(b_cpu, **kw):
-    """The call with empty sequences appended until there are too many of them for the kernels to plan the batch
-    themselves: its work lists come from the planning kernel.  `out` and `mass` are cut back to the batch's sequences."""
-    from paper_2603_06588_amd import binding
+def beyond_self_planning(b_cpu):
+    """The batch on the GPU with empty sequences appended until there are too many of them for the kernels to find their
+    work themselves: its work lists come from the planning kernel."""
     b = b_cpu.to("cuda:0")
     more = max(513 - b.num_seqs, 0)
 
-    def grow(t, rows):
-        return torch.cat([t, t[-1:].expand(rows, *t.shape[1:])]).contiguous()
+    def grow(t):
+        return torch.cat([t, t[-1:].expand(more, *t.shape[1:])]).contiguous()
 
-    n, b.num_seqs = b.num_seqs, b.num_seqs + more
-    b.seq_lens, b.block_table, b.cu_q_lens = grow(b.seq_lens, more), grow(b.block_table, more), grow(b.cu_q_lens, more)
-    b.query_sel, b.key_spans = grow(b.query_sel, more), grow(b.key_spans, more)
-    call = binding.call_from_batch(b, **kw)
+    b.num_seqs += more
+    b.seq_lens, b.block_table, b.cu_q_lens = grow(b.seq_lens), grow(b.block_table), grow(b.cu_q_lens)
+    b.query_sel, b.key_spans = grow(b.query_sel), grow(b.key_spans)
+    return b
+
+
+def plan_header(call):
+    """[row blocks, single-row items, keys per item, status]; a batch without a planner has 0 keys per item."""
+    return call.workspace[:16].view(torch.int32).tolist()
+
+
+def planned_reference(b_cpu, **kw):
+    """The call by way of the planning kernel; `mass` is cut back to the batch's own sequences."""
+    from paper_2603_06588_amd import binding
+    call = binding.call_from_batch(beyond_self_planning(b_cpu), **kw)
     call.workspace.fill_(0xFF)
     call.out.fill_(float("nan"))
     call.mass.fill_(float("nan"))
     call.launch()
     torch.cuda.synchronize()
-    header = call.workspace[:16].view(torch.int32).tolist()       # prefill items, decode items, chunk keys, status
-    assert header[2] >= 256, f"no planner ran: {header}"
-    call.mass = call.mass[:n]
+    assert plan_header(call)[2] >= 256, f"no planner ran: {plan_header(call)}"
+    call.mass = call.mass[:b_cpu.num_seqs]
     return call
 
 

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import bits, compare_with_oracle
+from helpers import beyond_self_planning, bits, compare_with_oracle, plan_header
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -160,9 +160,10 @@ def test_fp8_cache_c2_shape_shrunk():
     print(compare_with_oracle(b8, call.out, call.mass, label="c2_kv8_shrunk"), flush=True)
 
 
-def test_fp8_cache_chunk_call_writes_its_new_rows_quantised():
-    """k_new / v_new with an 8-bit cache and query chunks: the planning launch quantises the rows into
-    the cache, the chunk kernel then reads them back."""
+@pytest.mark.parametrize("planned", [False, True])
+def test_fp8_cache_chunk_call_writes_its_new_rows_quantised(planned):
+    """k_new / v_new with an 8-bit cache and query chunks: the planning launch (a launch of its own in a batch that
+    needs no planner) quantises the rows into the cache, the chunk kernel then reads them back."""
     from oracle.capture import kv_write
     b = W.random_batch(995, [300, 64], [100, 64], 8, 2, 128, torch.bfloat16, num_probe_heads=3, max_sel_q=2,
                        poison=False)
@@ -176,9 +177,11 @@ def test_fp8_cache_chunk_call_writes_its_new_rows_quantised():
     kw = dict(after.__dict__)
     kw.update(k_cache=want_k, v_cache=want_v)
     after = type(after)(**kw)
-    bd = b8.to(DEV)
+    bd = beyond_self_planning(b8) if planned else b8.to(DEV)
     call = binding.call_from_batch(bd, k_new=k_new.to(DEV), v_new=v_new.to(DEV))
     call.launch()
     torch.cuda.synchronize()
+    assert (plan_header(call)[2] >= 256) == planned
+    call.mass = call.mass[:b.num_seqs]
     assert torch.equal(bd.k_cache.cpu(), want_k) and torch.equal(bd.v_cache.cpu(), want_v)
     print(compare_with_oracle(after, call.out, call.mass, label="kv8_chunks_in_call_write"), flush=True)

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import bits, compare_with_oracle
+from helpers import bits, compare_with_oracle, planned_reference
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -45,7 +45,9 @@ def test_attention_with_block_offsets_beyond_4_gib():
     torch.cuda.synchronize()
     assert call.device_status() == 0
     print(compare_with_oracle(b_cpu, call.out, call.mass, label="large_pool_mixed"), flush=True)
-    # the decode-only part once more through the self-planned path
+    call = planned_reference(big)
+    print(compare_with_oracle(b_cpu, call.out, call.mass, label="large_pool_planned"), flush=True)
+    # the decode-only part once more with the hint
     d_cpu = W.random_batch(1302, [2100, 90, 1300, 260], [1, 1, 1, 1], 32, 8, 128, torch.bfloat16, num_probe_heads=6,
                            max_sel_q=1, max_spans=3)
     d_cpu.query_sel[:, 0], d_cpu.query_sel[:, 1] = 0, 1

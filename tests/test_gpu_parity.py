@@ -4,7 +4,7 @@ import torch
 
 from paper_2603_06588_amd import workloads as W
 import oracle
-from helpers import MASS_ATOL as MASS_TOL, bits, compare_with_oracle, run_hip
+from helpers import MASS_ATOL as MASS_TOL, beyond_self_planning, bits, compare_with_oracle, plan_header, planned_reference, run_hip
 
 pytestmark = pytest.mark.gpu
 
@@ -414,8 +414,8 @@ def test_plan_reuse_across_layers():
     entries of `mass` that no selected row maps to are left as they were."""
     from paper_2603_06588_amd import binding as B
     lens, qlens = [300, 77, 1500, 150, 40, 9], [300, 1, 1, 90, 0, 9]
-    layer0 = W.random_batch(196, lens, qlens, 8, 2, 128, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=2).to(DEV)
-    layer1 = W.random_batch(197, lens, qlens, 8, 2, 128, torch.bfloat16, num_probe_heads=5, max_sel_q=4, max_spans=2).to(DEV)
+    layer0 = beyond_self_planning(W.random_batch(196, lens, qlens, 8, 2, 128, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=2))
+    layer1 = beyond_self_planning(W.random_batch(197, lens, qlens, 8, 2, 128, torch.bfloat16, num_probe_heads=5, max_sel_q=4, max_spans=2))
     fresh0 = B.call_from_batch(layer0)
     fresh0.launch()
     want1_out, want1_mass = run_hip(layer1)
@@ -424,10 +424,10 @@ def test_plan_reuse_across_layers():
     mass1 = torch.full_like(want1_mass, marker)
     reuse1 = B.call_from_batch(layer1, workspace=fresh0.workspace, mass=mass1, plan_mode=B.PLAN_REUSE)
     reuse1.out.fill_(float("nan"))
-    from paper_2603_06588_amd import benchlib
-    times = benchlib.launch_timed(reuse1)
+    lists = plan_header(fresh0)
+    assert lists == [10 + 3 + 1, 1 + 6, 256, 0]                # chunks in blocks of 32 rows; 77 and 1500 keys by 256
+    reuse1.launch()
     torch.cuda.synchronize()
-    assert times[0] == 0.0                                     # no planner
     assert torch.equal(bits(reuse1.out[:300]), bits(want1_out[:300]))
     valid_rows = torch.ones(layer1.total_q, dtype=torch.bool)
     assert torch.equal(bits(reuse1.out[valid_rows]), bits(want1_out[valid_rows]))
@@ -436,6 +436,12 @@ def test_plan_reuse_across_layers():
     assert (want1_mass[~written] == 0).all()                   # what was left alone is what a fresh call zero-fills
     assert written.any() and (~written).any()
     assert reuse1.device_status() == 0
+    # no planner wrote the lists again: without the row blocks in them no chunk is computed
+    reuse1.workspace[:4] = 0
+    reuse1.out.fill_(float("nan"))
+    reuse1.launch()
+    torch.cuda.synchronize()
+    assert torch.isnan(reuse1.out[:300].float()).all() and plan_header(reuse1) == [0] + lists[1:]
 
 
 def test_batch_kind_hint():
@@ -447,7 +453,8 @@ def test_batch_kind_hint():
     dec = W.random_batch(191, [300, 77, 1500], [1, 1, 1], 8, 2, 128, torch.bfloat16, num_probe_heads=3, max_sel_q=1,
                          max_spans=2).to(DEV)
     for b, kind in ((pre, binding.BATCH_PREFILL_ONLY), (dec, binding.BATCH_DECODE_ONLY)):
-        ref_out, ref_mass = run_hip(b)
+        ref = planned_reference(b)
+        ref_out, ref_mass = ref.out, ref.mass
         call = binding.call_from_batch(b, batch_kind=kind)
         call.out.fill_(float("nan"))
         call.launch()
@@ -455,7 +462,7 @@ def test_batch_kind_hint():
         if kind == binding.BATCH_PREFILL_ONLY:
             assert torch.equal(bits(call.out), bits(ref_out)) and torch.equal(bits(call.mass), bits(ref_mass))
         else:
-            # a small batch of single rows cuts its contexts into equal parts instead of planned chunks:
+            # single rows without a planner are cut into equal ranges instead of planned chunks:
             # the same sums in another order
             assert torch.allclose(call.out.float(), ref_out.float(), atol=2e-2, rtol=2e-2)
             assert torch.allclose(call.mass, ref_mass, atol=1e-3)

@@ -1,12 +1,11 @@
-"""Small batches of single rows plan themselves: every sequence is cut into equally many parts by the
-workgroups, and no planning launch runs.  These cases pin that path against the CPU oracle through the
-C ABI (needs an MI355X); each has at most 512 (sequence, kv head, head group) triples, which is what
-selects it."""
+"""Batches of at most 512 single rows plan themselves: the workgroups find their equal ranges of the contexts from the
+lengths, and no planning launch runs.  These cases pin that path against the CPU oracle through the C ABI (needs an
+MI355X)."""
 import pytest
 import torch
 
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import bits, compare_with_oracle, run_hip
+from helpers import bits, compare_with_oracle, planned_reference
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -90,8 +89,8 @@ def test_self_planned_decode_skips_and_flags_what_the_planner_would():
     st = call.device_status()
     assert st == (2 | 4 | 8), st
     # the planned path (no hint) on the same, valid part of the batch
-    good = b_cpu.to(DEV)
-    ref_out, ref_mass = run_hip(good)
+    ref = planned_reference(b_cpu)
+    ref_out, ref_mass = ref.out, ref.mass
     cu = b_cpu.cu_q_lens.tolist()
     for i in range(16):
         rows = slice(cu[i], cu[i + 1])

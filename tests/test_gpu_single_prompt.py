@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import bits, compare_with_oracle
+from helpers import bits, compare_with_oracle, plan_header, planned_reference
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -48,8 +48,8 @@ def test_single_prompt_equals_planned_path_and_oracle(seed, L, n, Hq, Hkv, sel, 
     # the words a planner would have left: [row blocks, 0, 0, status]
     hdr = own.workspace[:16].view(torch.int32).tolist()
     assert hdr[1:4] == [0, 0, 0] and hdr[0] > 0, hdr
-    planned = _run(b, binding.BATCH_MIXED)
-    assert planned.workspace[:16].view(torch.int32).tolist()[0] == hdr[0]
+    planned = planned_reference(b, batch_kind=binding.BATCH_PREFILL_ONLY)
+    assert plan_header(planned)[0] == hdr[0]
     assert torch.equal(bits(own.out), bits(planned.out))
     assert torch.equal(bits(own.mass), bits(planned.mass))          # also: no entry left at the NaN it started with
     print("      ", compare_with_oracle(b, own.out, own.mass, label=label), flush=True)
@@ -122,7 +122,7 @@ def test_single_prompt_other_head_size_and_cache_type(d, kv8):
     b = W.random_batch(1440 + d, [777], [300], 8, 2, d, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=3)
     if kv8:
         b = W.fp8_cache_variant(b, 1441)
-    own, planned = _run(b, binding.BATCH_PREFILL_ONLY), _run(b, binding.BATCH_MIXED)
+    own, planned = _run(b, binding.BATCH_PREFILL_ONLY), planned_reference(b)
     assert torch.equal(bits(own.out), bits(planned.out)) and torch.equal(bits(own.mass), bits(planned.mass))
     print("      ", compare_with_oracle(b, own.out, own.mass, label="single"), flush=True)
 
