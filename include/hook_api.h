@@ -82,9 +82,10 @@ typedef enum { HOOK_KV_SAME = 0, HOOK_KV_FP8_E4M3 = 1 } hook_kv_dtype;
  * batch).  A sequence that contradicts the hint is NOT computed: its rows of `out` stay untouched,
  * its `mass` entries are zero and bit 3 of the device status word is set.
  * In a batch of at most 512 sequences (HOOK_BF16) single rows need no planning launch: the contexts
- * are cut into equal ranges and the workgroups find theirs from the lengths.  Query chunks need none
- * either when there is one sequence or when they are few; results are bit for bit those of the planned
- * call.  The status word is written as always.
+ * are cut into equal ranges and the workgroups find theirs from the lengths; results are those of a
+ * planned call up to the order of the sums.  Query chunks need none either when there is one sequence
+ * or when they are few; their results are bit for bit those of the planned call.  The status word is
+ * written as always.
  */
 typedef enum hook_batch_kind {
   HOOK_BATCH_MIXED = 0,         /* anything (default) */
@@ -98,9 +99,10 @@ typedef enum hook_batch_kind {
  * model step sees the same batch.  HOOK_PLAN_REUSE tells a call that the workspace still holds the
  * lists a HOOK_PLAN_FRESH call wrote for exactly this batch (and was given as `workspace_bytes` what
  * this call is given): the planning kernel is left out.
- * Because that kernel is also what zero-fills `mass`, a reusing call writes only the entries of
- * valid selected rows and leaves every other entry of `mass` as it is (give it a zeroed buffer
- * once; those entries are never written afterwards).  Reusing lists of a different batch is a
+ * Zeros for the entries of `mass` that hold no row are written by HOOK_PLAN_FRESH calls alone (with
+ * or without a planning kernel): a reusing call writes only the entries of valid selected rows and
+ * leaves every other entry of `mass` as it is (give it a zeroed buffer once; those entries are never
+ * written afterwards).  Reusing lists of a different batch is a
  * caller error that is not detected.
  */
 typedef enum hook_plan_mode {

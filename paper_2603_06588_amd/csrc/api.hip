@@ -12,9 +12,9 @@ using namespace hook;
 
 constexpr size_t kAlign = 256;
 // Row blocks find their work themselves up to this many workgroups (two resident rounds).  Finding it costs every
-// workgroup about a thousand cycles, the planning launch costs the call 4-5 us and sorts better: 2 prompts of 200
-// tokens 16.2 us planned, 11.6 by themselves; 8 of 200-600 (800 workgroups) 31.6 and 29.3; 3 of 1500-2048 (1350
-// workgroups) 81.1 and 82.7.
+// workgroup about a thousand cycles; the planning launch (8 us in a kernel trace of 16 prompts) costs a small call less
+// than that and sorts better: 2 prompts of 200 tokens 16.2 us planned, 11.6 by themselves; 8 of 200-600 (800
+// workgroups) 31.6 and 29.3; 3 of 1500-2048 (1350 workgroups) 81.1 and 82.7.
 constexpr long long kSelfPlanMaxWgs = 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -53,9 +53,10 @@ int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_p
 }
 
 // Ranges of a self-planned batch of single rows (decode.hip): one resident
-// round of workgroups (256 compute units times the 3 workgroups each holds, 2 for groups of 8 heads) - a
-// second, partial round costs more than its finer balance gains - but no range shorter than
-// kStreamMinBlocks.
+// round of workgroups - a second, partial round costs more than its finer balance gains - but no range shorter than
+// kStreamMinBlocks.  A round is taken as 3 workgroups for each of 256 compute units, 2 for groups of 8 heads: what the
+// kernel's launch bounds promise and head size 128 over a 16-bit cache holds.  (Instantiations with fewer registers,
+// at head size 64 or over an 8-bit cache, hold 4 in some cases; a finer cut for them has not been measured.)
 int stream_ranges(const hook_attn_probe_args* a, const Layout& l, int num_seqs) {
   const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3), wgs = (long long)a->num_kv_heads * l.dec_hgroups;
   // (and one range per sequence more, for ranges that end with their sequence)

@@ -12,7 +12,7 @@
 //
 // What bounds it: small batches are all this path sees, so latency - the length of one wave's chain of
 // dependent loads and the number of launches.  256 rows x 8 heads, d 64: one row per wave on the vector ALUs
-// behind a clearing launch took 2.8 + 34 us, this takes one launch of 7.5 us.
+// behind a clearing launch took 2.8 + 34 us, this takes one launch of 8.7 us (kernel trace).
 #include "hook_device.h"
 
 namespace hook {

@@ -2,8 +2,8 @@
 // per-chunk partial results.
 //
 // The path is bound by HBM: every live K and V element of a kv head is read exactly once
-// and shared by the HP query heads of its group.  A workgroup owns one (sequence, key chunk,
-// kv head); each of its 4 waves streams a contiguous run of 16-key cache blocks straight
+// and shared by the HP query heads of its group.  A workgroup owns one (range of the contexts, or
+// sequence and key chunk; kv head); each of its 4 waves streams a contiguous run of 16-key cache blocks straight
 // from global memory into registers (16-byte loads, one block ahead):
 //   - the K block is the A operand of S^T = K Q^T (16x16x32 bf16 MFMA, keys = M, heads = N),
 //     whose accumulator gives lane (head j, key group kq) the scores of 4 keys;
@@ -469,7 +469,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
 // workgroup streams the same number of blocks however ragged the contexts are; a range may cover the end of
 // one sequence and the beginning of the next.  A workgroup finds its range by a scan over the lengths (each
 // wave on its own, lane l takes sequences l K .. l K + K - 1), which costs about a microsecond instead of a
-// planning launch (8 us).  Range g and sequence i share at most one piece and the path through the pairs is a
+// planning launch (8 us in a kernel trace).  Range g and sequence i share at most one piece and the path through the pairs is a
 // staircase, so g + i numbers the partial records without gaps between the records of one sequence.
 // A piece costs a workgroup its start-up (ids, query, first keys, merge), so where whole sequences can be dealt
 // out to the ranges with hardly more blocks each, no range covers two: a sequence then takes its blocks divided by

@@ -27,8 +27,8 @@ constexpr int kPlanBuckets = 2048;  // counting-sort buckets (tile counts) of th
 constexpr int kChunkSizes = 5;
 constexpr int kMaxChunkKeys = 512 << (kChunkSizes - 1);
 constexpr int kDecodeFillWgs = 2048;
-// Batches of single rows with at most this many sequences plan themselves (decode.hip); a range of
-// blocks is never shorter than one block per wave of a workgroup.
+// Batches of single rows with at most this many sequences plan themselves (decode.hip); ranges are cut no shorter than
+// one block per wave of a workgroup (the last one of a batch, or of a sequence, may hold fewer).
 constexpr int kStreamMaxSeqs = 512;
 constexpr int kStreamMinBlocks = 4;
 // A running maximum is only raised when a tile's maximum exceeds it by more than this many

@@ -775,7 +775,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
 // into kDepthParts equal parts and the order is: the deepest part of every sequence, the next part of every sequence, ...
 // with descending blocks inside.  An item's block then follows from sums over the sequences, which every wave forms
 // for itself (lane l takes sequences l K .. l K + K - 1): one trip to memory for the lengths instead of a planning
-// launch (7-9 us) and two trips for its record.  It costs a workgroup about a thousand cycles, so launches of many
+// launch (8 us in a kernel trace of 16 prompts) and two trips for its record.  It costs a workgroup about a thousand cycles, so launches of many
 // rounds keep the planner (kSelfPlanMaxWgs).  (2 or 8 parts: 1-3 % slower on 16 ragged prompts; 16: 7 %, as
 // neighbouring workgroups then share fewer tiles in L2.)
 constexpr int kSeqsPerLane = kStreamMaxSeqs / 64;
