@@ -27,10 +27,10 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 # until the counters are taken again.
 TRAFFIC = {
     # key: (bytes per launch, source files, hash of those files when the counters were taken)
-    "k_prefill128/c2": (797424994, ("prefill.hip", "hook_device.h"), "2a8a49143a6fb91c"),
-    "k_prefill128/c4": (5191965184, ("prefill.hip", "hook_device.h"), "2a8a49143a6fb91c"),
-    "k_decode/c3": (4910675161, ("decode.hip", "hook_device.h"), "6a4b00fc927a5ed1"),
-    "k_decode/c3_fp8": (2440025513, ("decode.hip", "hook_device.h"), "6a4b00fc927a5ed1"),
+    "k_prefill/c2": (830335268, ("prefill.hip", "hook_device.h"), "be5639f65c28c6ed"),
+    "k_prefill/c4": (5259019640, ("prefill.hip", "hook_device.h"), "be5639f65c28c6ed"),
+    "k_decode_stream/c3": (4888511690, ("decode.hip", "hook_device.h"), "d2072dade17a78a2"),
+    "k_decode_stream/c3_fp8": (2477001254, ("decode.hip", "hook_device.h"), "d2072dade17a78a2"),
 }
 
 
@@ -260,7 +260,7 @@ def main() -> int:
     flops2 = attn_flops(b2)
     ov2 = interleaved_overhead(call2, call2_off, max(10, K // 2), 3)
     value = flops2 / (t2["mean_ms"] * 1e-3) / 1e12
-    roofline = roofline_obj("mfma", "k_prefill<128>", flops2, k2["prefill_ms"], "k_prefill128/c2")
+    roofline = roofline_obj("mfma", "k_prefill<128>", flops2, k2["prefill_ms"], "k_prefill/c2")
     pre_tflops = roofline["achieved"]
     cpu_baseline = None
     if not args.no_cpu_baseline:
@@ -280,7 +280,7 @@ def main() -> int:
         extra["decode_c3"] = {
             "workload": "c3_decode_8b", "value": by3 / (t3["mean_ms"] * 1e-3) / 1e9, "unit": "GB/s",
             "ms_per_step": t3["mean_ms"], "median_ms": t3["median_ms"], "min_ms": t3["min_ms"], "kernels_ms": k3,
-            "roofline": roofline_obj("hbm", "k_decode<128,4>", by3, k3["decode_ms"], "k_decode/c3"),
+            "roofline": roofline_obj("hbm", "k_decode_stream<128,4>", by3, k3["decode_ms"], "k_decode_stream/c3"),
             "probe_overhead_pct": ov3["overhead_pct"],
             "workspace_mb": call3.workspace_needed / 2**20,
         }
@@ -294,7 +294,7 @@ def main() -> int:
             "workload": "c3_decode_8b with 8-bit E4M3 key/value caches (one scale per kv head)",
             "value": by3q / (t3q["mean_ms"] * 1e-3) / 1e9, "unit": "GB/s", "ms_per_step": t3q["mean_ms"],
             "kernels_ms": k3q, "speedup_vs_bf16_cache": t3["mean_ms"] / t3q["mean_ms"],
-            "roofline": roofline_obj("hbm", "k_decode<128,4,fp8>", by3q, k3q["decode_ms"], "k_decode/c3_fp8")}
+            "roofline": roofline_obj("hbm", "k_decode_stream<128,4,kv8>", by3q, k3q["decode_ms"], "k_decode_stream/c3_fp8")}
         del b3q, call3q
         torch.cuda.empty_cache()
         # compact q/k capture on the same batch: every key of every kv head, the probed heads' queries
@@ -334,7 +334,7 @@ def main() -> int:
             "us_per_call": ts["mean_ms"] * 1e3, "us_per_call_plan_reused": ts_reuse["mean_ms"] * 1e3,
             "us_per_call_back_to_back": ts_b2b * 1e3,
             "kernels_ms": kernel_times(calls, K),
-            "roofline": roofline_obj("hbm", "whole call back to back (k_decode + k_combine)", kv_bytes(bs), ts_b2b)}
+            "roofline": roofline_obj("hbm", "whole call back to back (k_decode_stream + k_combine)", kv_bytes(bs), ts_b2b)}
         del bs, calls, calls_reuse
         torch.cuda.empty_cache()
 
@@ -379,7 +379,7 @@ def main() -> int:
         extra["long_prefill_c4"] = {
             "workload": "c4_long_prefill_70b", "value": fl4 / (t4["mean_ms"] * 1e-3) / 1e12, "unit": "TFLOP/s",
             "ms_per_step": t4["mean_ms"], "kernels_ms": k4,
-            "roofline": roofline_obj("mfma", "k_prefill<128>", fl4, k4["prefill_ms"], "k_prefill128/c4"),
+            "roofline": roofline_obj("mfma", "k_prefill<128>", fl4, k4["prefill_ms"], "k_prefill/c4"),
             "probe_overhead_pct": ov4["overhead_pct"],
         }
         if not args.no_cpu_baseline:
@@ -432,7 +432,7 @@ def main() -> int:
             "workload": "c5_mixed", "attn_plus_steer_ms": t5["mean_ms"], "attn_ms": t5a["mean_ms"],
             "kernels_ms": k5,
             "roofline_prefill": roofline_obj("mfma", "k_prefill<128>", fl5, k5["prefill_ms"]) if k5["prefill_ms"] > 0 else None,
-            "roofline_decode": roofline_obj("hbm", "k_decode<128,4>", by5, k5["decode_ms"]) if k5["decode_ms"] > 0 else None,
+            "roofline_decode": roofline_obj("hbm", "k_decode_stream<128,4>", by5, k5["decode_ms"]) if k5["decode_ms"] > 0 else None,
             "roofline_max_ms": t_roof_ms, "roofline_sum_ms": t_sum_ms,
             "probe_overhead_pct": ov5["overhead_pct"],
             "steer": {"ms_single_call": t5s["mean_ms"], "ms": t5s_b, "buffers_rotated": 4,
@@ -549,7 +549,7 @@ def main() -> int:
                         "roofline": roofline_obj("mfma", "k_prefill<64>", attn_flops(bp), kp["prefill_ms"])},
             "decode": {"workload": "128 single rows at 1024-8192 tokens of context, 32 q / 8 kv heads, d 64, bf16",
                        "ms_per_step": td["mean_ms"], "kernels_ms": kd,
-                       "roofline": roofline_obj("hbm", "k_decode<64,4>", kv_bytes(bd), kd["decode_ms"])}}
+                       "roofline": roofline_obj("hbm", "k_decode_stream<64,4>", kv_bytes(bd), kd["decode_ms"])}}
         del bp, bd, callp, calld
         torch.cuda.empty_cache()
 
