@@ -21,9 +21,10 @@ extern "C" {
 /*
  * The same launches as hook_attn_probe, bracketed by HIP events on args->stream, then WAITS for
  * them.  kernel_ms (HOST pointer, 4 floats) receives the durations in milliseconds of the plan,
- * prefill, decode and combine kernels (fp32 inputs: the zero-fill and attention kernels together
- * in kernel_ms[0], the rest 0; kernels left out by batch_kind or a reused plan read 0).  Creates
- * and destroys HIP events; not for graph capture.
+ * prefill, decode and combine kernels (fp32 inputs: the one attention kernel in kernel_ms[0], the
+ * rest 0; kernels left out by batch_kind, a reused plan or a batch that plans itself read 0, and a
+ * cache write without a planning launch reads as kernel_ms[0]).  Creates and destroys HIP events;
+ * not for graph capture.
  */
 hook_status hook_bench_attn_probe_timed(const hook_attn_probe_args* args, float* kernel_ms);
 

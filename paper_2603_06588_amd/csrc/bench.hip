@@ -73,10 +73,14 @@ __global__ __launch_bounds__(256) void k_probe_read(const uint4* __restrict__ sr
   if (acc == 0x9E3779B9u) sink[0] = acc;
 }
 
-// kernels that the batch_kind hint or a reused plan left out took no time (two events in a row still differ)
+// kernels that the batch_kind hint, a reused plan or a batch that plans itself left out took no time (two events in a
+// row still differ)
 void zero_skipped(const hook_attn_probe_args* a, float* kernel_ms) {
   if (a->dtype != HOOK_BF16) return;
   if (a->plan_mode == HOOK_PLAN_REUSE) kernel_ms[0] = 0.0f;
+  PlanHeader h{};       // keys per item: 0 unless a planner ran (a cache write of its own stands in the planner's place)
+  if (!a->k_new && hipMemcpy(&h, a->workspace, sizeof h, hipMemcpyDeviceToHost) == hipSuccess && h.chunk_keys == 0)
+    kernel_ms[0] = 0.0f;
   if (a->batch_kind == HOOK_BATCH_DECODE_ONLY) kernel_ms[1] = 0.0f;
   if (a->batch_kind == HOOK_BATCH_PREFILL_ONLY) kernel_ms[2] = kernel_ms[3] = 0.0f;
 }

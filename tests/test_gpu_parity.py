@@ -470,6 +470,8 @@ def test_batch_kind_hint():
         from paper_2603_06588_amd import benchlib
         ms = benchlib.launch_timed(call)
         assert ms[1 if kind == binding.BATCH_DECODE_ONLY else 2] == 0.0     # the other side was not launched
+        assert ms[0] == 0.0                                                 # nor a planner
+        assert benchlib.launch_timed(ref)[0] > 0.0
     mixed = W.random_batch(192, [300, 77, 150, 40], [300, 1, 90, 1], 8, 2, 128, torch.bfloat16, num_probe_heads=3,
                            max_sel_q=3, max_spans=2).to(DEV)
     ref_out, ref_mass = run_hip(mixed)
