@@ -280,7 +280,7 @@ def main() -> int:
         extra["decode_c3"] = {
             "workload": "c3_decode_8b", "value": by3 / (t3["mean_ms"] * 1e-3) / 1e9, "unit": "GB/s",
             "ms_per_step": t3["mean_ms"], "median_ms": t3["median_ms"], "min_ms": t3["min_ms"], "kernels_ms": k3,
-            "roofline": roofline_obj("hbm", "k_decode_stream<128,4>", by3, k3["decode_ms"], "k_decode_stream/c3"),
+            "roofline": roofline_obj("hbm", "k_decode<128,4>", by3, k3["decode_ms"], "k_decode_stream/c3"),
             "probe_overhead_pct": ov3["overhead_pct"],
             "workspace_mb": call3.workspace_needed / 2**20,
         }
@@ -294,7 +294,7 @@ def main() -> int:
             "workload": "c3_decode_8b with 8-bit E4M3 key/value caches (one scale per kv head)",
             "value": by3q / (t3q["mean_ms"] * 1e-3) / 1e9, "unit": "GB/s", "ms_per_step": t3q["mean_ms"],
             "kernels_ms": k3q, "speedup_vs_bf16_cache": t3["mean_ms"] / t3q["mean_ms"],
-            "roofline": roofline_obj("hbm", "k_decode_stream<128,4,kv8>", by3q, k3q["decode_ms"], "k_decode_stream/c3_fp8")}
+            "roofline": roofline_obj("hbm", "k_decode<128,4,kv8>", by3q, k3q["decode_ms"], "k_decode_stream/c3_fp8")}
         del b3q, call3q
         torch.cuda.empty_cache()
         # compact q/k capture on the same batch: every key of every kv head, the probed heads' queries

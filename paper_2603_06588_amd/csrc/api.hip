@@ -77,12 +77,12 @@ size_t place(const hook_attn_probe_args* a, Layout& l) {
   return off;
 }
 
-// The layout for a workspace of `bytes`.  Single rows of up to kStreamMaxSeqs sequences, whose lengths every
+// The layout for a workspace of `bytes`.  Single rows of up to kStreamSeqs sequences, whose lengths every
 // workgroup can afford to scan, plan themselves where their records fit; those are numbered by range + sequence, which
 // can take more slots than the planner's items.  A smaller workspace keeps the planner, so every size that holds the
 // planner's items is accepted.
 // The size reported is no smaller for a larger batch (one buffer, asked for once, serves every batch up to that one with
-// the kernels that its own size would have got it): beyond kStreamMaxSeqs it still holds the records of that many, and
+// the kernels that its own size would have got it): beyond kStreamSeqs it still holds the records of that many, and
 // up to the static scratch's size it asks for no more than that.
 Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
   Layout l{};
@@ -98,7 +98,7 @@ Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
     l.needed = l.reported = place(a, l);
     if (a->num_seqs > 0) {
-      const int planned_cap = l.dec_cap, n = a->num_seqs < kStreamMaxSeqs ? a->num_seqs : kStreamMaxSeqs;
+      const int planned_cap = l.dec_cap, n = a->num_seqs < kStreamSeqs ? a->num_seqs : kStreamSeqs;
       const int ranges = stream_ranges(a, l, n);
       if (l.dec_cap < ranges + n) l.dec_cap = ranges + n;
       const size_t streaming = place(a, l), fixed = (size_t)HOOK_STATIC_SCRATCH_BYTES;
@@ -219,17 +219,17 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.hpw = l.hpw; p.rows_per_wg = l.rows_per_wg; p.hgroups = l.hgroups;
   p.dec_hp = l.dec_hp; p.dec_hgroups = l.dec_hgroups;
   p.batch_kind = a->batch_kind;
-  // up to kStreamMaxSeqs sequences single rows find their work themselves, and so do row blocks while there are
+  // single rows of few sequences find their work themselves (make_layout), and so do row blocks while there are
   // few of them (or the planner would have nothing to sort)
-  const bool self = a->dtype == HOOK_BF16 && a->num_seqs <= kStreamMaxSeqs &&
-                    (l.ranges > 0 || a->batch_kind == HOOK_BATCH_PREFILL_ONLY);
-  p.dec_ranges = self && a->batch_kind != HOOK_BATCH_PREFILL_ONLY ? l.ranges : 0;
-  p.pf_self = self && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
+  const bool streams = a->dtype == HOOK_BF16 && l.ranges > 0 && a->batch_kind != HOOK_BATCH_PREFILL_ONLY;
+  p.dec_ranges = streams ? l.ranges : 0;
+  p.pf_self = a->dtype == HOOK_BF16 && a->num_seqs <= kScanMaxSeqs && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
+              (streams || a->batch_kind == HOOK_BATCH_PREFILL_ONLY) &&
               (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups <= kSelfPlanMaxWgs);
   // The streaming kernel can do without a write ahead of it while a wave can hold every new row's place, one per lane.
   // (A launch ahead costs a call 4 us: 1 x 1237 tokens 16.6 us against 11.7, 8 x 4096 30.2 against 26.3, 64 x 2048 77.2
   // against 72.8.  Where to look would take more registers for more sequences, and the loop has none to spare.)
-  p.dec_write = writes_kv && self && a->batch_kind == HOOK_BATCH_DECODE_ONLY && a->num_seqs <= 64 && a->total_q <= a->num_seqs;
+  p.dec_write = writes_kv && streams && a->batch_kind == HOOK_BATCH_DECODE_ONLY && a->num_seqs <= 64 && a->total_q <= a->num_seqs;
   p.plan_fresh = a->plan_mode == HOOK_PLAN_FRESH;
 
   hipStream_t st = static_cast<hipStream_t>(a->stream);
@@ -238,7 +238,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   // a small batch of single rows writes its rows while streaming, the planning launch carries the cache write where
   // there is one, else it gets a launch of its own
   const bool plans = a->dtype == HOOK_BF16 && a->plan_mode == HOOK_PLAN_FRESH &&
-                     !(a->batch_kind == HOOK_BATCH_DECODE_ONLY ? self : p.pf_self != 0);
+                     !(a->batch_kind == HOOK_BATCH_DECODE_ONLY ? streams : p.pf_self != 0);
   if (writes_kv && !p.dec_write && !plans && launch_kv_write(p.kvw, st) != hipSuccess)
     return HOOK_ERR_LAUNCH;
   if (a->dtype == HOOK_F32) {

@@ -14,6 +14,7 @@
 //   - the key-group streams of a wave, the waves of a workgroup and finally the chunks of a
 //     sequence are merged with the usual (max, sum) weights; probe span sums ride along with
 //     the normaliser in every merge.
+#include "fp8_device.h"
 #include "kv_write_device.h"
 
 #include <type_traits>
@@ -30,16 +31,6 @@ struct DecodeCfg {
   static constexpr int KPL = kBlock / VK;      // keys per V lane per block (4 or 2)
   static constexpr int PSTR = D + kPartialPad; // floats per partial record
 };
-
-// 8-bit cache: two fp8 values of one 16-bit half of `w` as bf16 (exact: 3 mantissa bits)
-__device__ __forceinline__ uint32_t fp8x2_to_bf16x2(uint32_t w, bool upper_half) {
-  bf16x2 v;
-  if (upper_half) v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true);
-  else v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false);
-  uint32_t u;
-  __builtin_memcpy(&u, &v, 4);
-  return u;
-}
 
 // A pointer read through it is not known to point to global memory unless this says so.
 template <typename T>
@@ -74,25 +65,43 @@ struct NewRows {
   int at;       // 16 * row of k_new / v_new + place in the block
   bool store;
 };
+// WHOLE_LINES: how K rows of 128 bytes and more are fetched (below).  The one kind of batch that is better off without is
+// large and of 256-byte rows for up to four heads: 8 rows 26.9 -> 25.5 us, 24 49.8 -> 49.1, but 64 of 1000-8000 tokens
+// 190 -> 192 and 200 of 1000-4000 (planned) 331 -> 337.
+constexpr int kLineSeqs = 32;
 template <int D, int HP, bool KV8>
+constexpr bool lines_always() { return HP == 8 || KV8 || D == 64; }
+template <int D, int HP, bool KV8, bool WHOLE_LINES>
 __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4][HP][DecodeCfg<D>::PSTR], int tid, int lane,
                                              int w, int kvh, int head0, int seq, int qrow, int kstart, int kend,
                                              int item, const NewRows& fresh) {
   using C = DecodeCfg<D>;
   constexpr int NW = 4;
+  constexpr int ESZ = KV8 ? 1 : 2;                      // bytes per cache element
   const int blk0 = kstart >> 4;                         // first block of the range inside the sequence
   const int nblk = (kend - kstart + kBlock - 1) / kBlock;
   const int bpw = (nblk + NW - 1) / NW;
   const int b0 = min(w * bpw, nblk), b1 = min(b0 + bpw, nblk);
 
   const int* const bt = in_global(p.block_table) + (size_t)seq * p.max_blocks + blk0;
-  constexpr int ESZ = KV8 ? 1 : 2;                      // bytes per cache element
   const char* const kbase = static_cast<const char*>(in_global(p.k_cache)) + (size_t)kvh * kBlock * D * ESZ;
   const char* const vbase = static_cast<const char*>(in_global(p.v_cache)) + (size_t)kvh * kBlock * D * ESZ;
   const unsigned blk_bytes = (unsigned)p.Hkv * kBlock * D * ESZ;
 
   // score-lane role: head j = lane % 16 (real if j < HP), key group kq = lane / 16
   const int j = lane & 15, kq = lane >> 4;
+  // K rows of at least a memory line (128 bytes) are fetched a line of eight rows at a time, lane (row lane % 8, 16-byte
+  // piece lane / 8).  As the A operand of the score MFMA such a load holds the even pieces of its rows in operand rows
+  // 0 .. 7 and the odd ones in 8 .. 15, so Q comes as two sets of columns, 0 .. 7 against the even pieces of a line and
+  // 8 .. 15 against the odd ones, and a score is the sum of two accumulator entries (compute_block).  Otherwise operand
+  // rows are key rows, and a load takes 64 bytes, half a line, of each of 16 rows.  Whole lines are 2-6 % faster (8 x 2500-4096
+  // tokens 26.9 -> 25.5 us, 8-bit 20.5 -> 19.6, 256 x 1000-8192 of 8-bit 431 -> 425, 128 x 1000-4000 at d 64 121 -> 119) but
+  // for large streams of 256-byte rows and up to four heads (kLineSeqs), where 1 KB in one piece (4 rows, four classes of
+  // pieces) is slower still (64 x 1000-8000 190 -> 194).
+  constexpr int ROWB = D * ESZ;
+  constexpr bool LINES = WHOLE_LINES && ROWB >= 128;
+  const int krow = LINES ? lane & 7 : j, kpiece = LINES ? lane >> 3 : kq;
+  const int qhead = LINES ? j & 7 : j;
   // value-lane role: key group vk, 16-byte chunk ch; its keys KPL*vk .. KPL*vk+KPL-1 all
   // belong to score key group (KPL*vk)/4 = lane / 16, so exponentials only move inside a group of 16 lanes
   const int vk = lane / C::CHV, ch = lane % C::CHV;
@@ -111,23 +120,27 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     qe = min(cload(p.query_sel, 2 * seq + 1), qb + p.NQ);
     if (lane < p.P) ph0 = in_global(p.probe_heads)[lane];
   }
-  bf16x8 qf[C::KSTEPS];
+  // the contraction may take the dimensions in any order as long as both operands agree: a 16-bit piece is one k-step of
+  // eight dimensions, an 8-bit one (16 dimensions) two
+  constexpr int NQF = LINES ? D / 64 : C::KSTEPS;
+  bf16x8 qf[NQF];
 #pragma unroll
-  for (int s = 0; s < C::KSTEPS; ++s) {
+  for (int s = 0; s < NQF; ++s) {
     uint4 v = make_uint4(0, 0, 0, 0);
-    // the contraction may take the dimensions in any order as long as both operands agree: with the
-    // 8-bit cache a lane's key bytes are the 16-byte piece (s / 2) of its row, so k-step s covers
-    // dimensions 64 (s / 2) + 16 kq + 8 (s % 2) + 0..7 instead of 32 s + 8 kq + 0..7
-    const int dim0 = KV8 ? 64 * (s >> 1) + 16 * kq + 8 * (s & 1) : 32 * s + 8 * kq;
-    if (j < HP)
-      v = *reinterpret_cast<const uint4*>(static_cast<const __bf16*>(in_global(p.q)) + ((size_t)qrow * p.Hq + head0 + j) * D + dim0);
+    const int dim0 = KV8 ? 16 * (LINES ? 2 * kq + (j >> 3) : kq) + 8 * s
+                         : LINES ? 64 * s + 16 * kq + 8 * (j >> 3) : 32 * s + 8 * kq;
+    if (qhead < HP)
+      v = *reinterpret_cast<const uint4*>(static_cast<const __bf16*>(in_global(p.q)) + ((size_t)qrow * p.Hq + head0 + qhead) * D + dim0);
     __builtin_memcpy(&qf[s], &v, 16);
   }
 
   // 16-byte pieces per lane and block: K rows for the score MFMA, V rows for P V (8-bit V: 8 bytes)
-  constexpr int kKr = KV8 ? C::KSTEPS / 2 : C::KSTEPS;
+  constexpr int kKr = kBlock * ROWB / 1024;
   struct Block { uint4 k[kKr]; uint4 v[C::KPL]; int id; };
-  const unsigned koff = (unsigned)j * D * ESZ + 16 * kq;
+  const unsigned koff = (unsigned)krow * ROWB + 16 * kpiece;
+  // load s: rows 8 (s / LPR) .., line s % LPR (the lines of a row one after the other); or 64 bytes of all rows
+  constexpr int LPR = LINES ? ROWB / 128 : kKr;
+  auto k_at = [](int s) { return (unsigned)(LINES ? 8 * (s / LPR) * ROWB + 128 * (s % LPR) : 64 * s); };
   const unsigned voff = (unsigned)(C::KPL * vk) * D * ESZ + 8 * ESZ * ch;
   // Rows past the last token lie in a block the sequence owns, and what they hold (anything, NaN included) is
   // replaced before use in the range's last block.  Loads are always issued, so that the compiler knows how
@@ -139,7 +152,7 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     unsigned ko = b < b1 ? koff : 0, vo = b < b1 ? voff : 0;     // (opaque, so that the loads take a scalar base and a 32-bit lane offset)
     asm("" : "+v"(ko), "+v"(vo));
 #pragma unroll
-    for (int s = 0; s < kKr; ++s) d.k[s] = load_stream16(kb + ko + 64 * s);
+    for (int s = 0; s < kKr; ++s) d.k[s] = load_stream16(kb + ko + k_at(s));
 #pragma unroll
     for (int i = 0; i < C::KPL; ++i) {
       if constexpr (KV8) {
@@ -197,16 +210,16 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
       char* kdst = const_cast<char*>(kbase) + off;
       char* vdst = const_cast<char*>(vbase) + off;
       // 16-bit rows are requested straight into the block's registers and stored once all of them are there
-      if (j == r) {
 #pragma unroll
-        for (int s = 0; s < kKr; ++s) {
+      for (int s = 0; s < kKr; ++s) {
+        if (krow + 8 * (s / LPR) == r) {
           if constexpr (KV8) {
-            const uint4 a = load_global16(kn + 128 * s + 32 * kq), b = load_global16(kn + 128 * s + 32 * kq + 16);
+            const uint4 a = load_global16(kn + 32 * kpiece), b = load_global16(kn + 32 * kpiece + 16);
             const float sc = cloadf(p.k_scale, kvh);
             const uint2 lo = quantize_chunk_e4m3(a, sc), hi = quantize_chunk_e4m3(b, sc);
             d.k[s] = make_uint4(lo.x, lo.y, hi.x, hi.y);
           } else {
-            d.k[s] = load_global16(kn + 64 * s + 16 * kq);
+            d.k[s] = load_global16(kn + (LINES ? 128 : 64) * (s % LPR) + 16 * kpiece);
           }
         }
       }
@@ -225,10 +238,9 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
       __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
       __builtin_amdgcn_sched_barrier(0);
       if (store) {
-        if (j == r) {
 #pragma unroll
-          for (int s = 0; s < kKr; ++s) *reinterpret_cast<uint4*>(kdst + koff + 64 * s) = d.k[s];
-        }
+        for (int s = 0; s < kKr; ++s)
+          if (krow + 8 * (s / LPR) == r) *reinterpret_cast<uint4*>(kdst + koff + k_at(s)) = d.k[s];
 #pragma unroll
         for (int i = 0; i < C::KPL; ++i) {
           if (C::KPL * vk + i == r) {
@@ -243,27 +255,34 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
       for (int i = 0; i < C::KPL; ++i)           // 0 * NaN would poison the output
         if (key0 + C::KPL * vk + i >= kend) d.v[i] = make_uint4(0, 0, 0, 0);
     }
-    f32x4 sacc = {0.0f, 0.0f, 0.0f, 0.0f};
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    f32x4 sacc[2] = {zero, zero};          // rows 0 .. 7 and 8 .. 15 (LINES)
 #pragma unroll
-    for (int s = 0; s < C::KSTEPS; ++s) {
+    for (int s = 0; s < kKr * (KV8 ? 2 : 1); ++s) {
+      const uint4& w = d.k[KV8 ? s >> 1 : s];
       bf16x8 a;
       if constexpr (KV8) {
         // bytes 8 (s % 2) .. 8 (s % 2) + 7 of piece s / 2
-        const uint32_t w0 = (s & 1) ? d.k[s >> 1].z : d.k[s >> 1].x;
-        const uint32_t w1 = (s & 1) ? d.k[s >> 1].w : d.k[s >> 1].y;
-        const uint4 cv = make_uint4(fp8x2_to_bf16x2(w0, false), fp8x2_to_bf16x2(w0, true),
-                                    fp8x2_to_bf16x2(w1, false), fp8x2_to_bf16x2(w1, true));
+        const uint4 cv = e4m3x8_to_bf16x8((s & 1) ? make_uint2(w.z, w.w) : make_uint2(w.x, w.y));
         __builtin_memcpy(&a, &cv, 16);
       } else {
-        __builtin_memcpy(&a, &d.k[s], 16);
+        __builtin_memcpy(&a, &w, 16);
       }
-      sacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[s], sacc, 0, 0, 0);
+      const int half = !LINES ? 0 : KV8 ? s >> 1 : s / LPR;
+      sacc[half] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[KV8 ? s & 1 : s % LPR], sacc[half], 0, 0, 0);
     }
-    // lane (j, kq): sacc[r] = score of head j with key key0 + 4 kq + r
+    // lane (j, kq): tt[r] = score of head j with key key0 + 4 kq + r.  LINES: entry (row i, column n) of a half holds the
+    // even pieces of row i where i < 8 and n < 8 and the odd ones of row i - 8 where both are 8 or more; one swap of lane
+    // halves brings the rows of both halves into place, and the odd pieces come from eight columns on.
     float tt[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      tt[r] = sacc[r] * c;
+      float score = sacc[0][r];
+      if constexpr (LINES) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_uint(sacc[0][r]), __float_as_uint(sacc[1][r]), false, false);
+        score = __uint_as_float(x[0]) + __uint_as_float(__builtin_amdgcn_update_dpp(0u, x[1], 0x128, 0xf, 0xf, false));   // row_ror:8
+      }
+      tt[r] = score * c;
     }
     if (last) {
 #pragma unroll
@@ -440,9 +459,10 @@ __device__ __forceinline__ DecodeSeq decode_seq(const AttnParams& p, int Lraw, i
   return s;
 }
 
-// The planner's items: one (sequence, chunk) per workgroup, longest first.
+// The planner's items: one (sequence, chunk) per workgroup, longest first.  Four workgroups to a compute unit over an
+// 8-bit cache and at head size 64, where a wave has half the bytes in flight (three for groups of 8 heads).
 template <int D, int HP, bool KV8>
-__global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParams p) {
+__global__ __launch_bounds__(256, (HP == 8 ? 2 : 3) + (KV8 || D == 64 ? 1 : 0)) void k_decode(const AttnParams p) {
   __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
   const int tid = threadIdx.x;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -460,7 +480,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
   const int item = min(max(slot, 0), p.dec_cap - 1);
   const int CH = p.hdr->chunk_keys;
   const int kstart = it.y * CH;
-  decode_range<D, HP, KV8>(p, red, tid, tid & 63, w, kvh, kvh * p.G + hg * HP, it.x, it.w, kstart, min(it.z, kstart + CH),
+  decode_range<D, HP, KV8, lines_always<D, HP, KV8>()>(p, red, tid, tid & 63, w, kvh, kvh * p.G + hg * HP, it.x, it.w, kstart, min(it.z, kstart + CH),
                            item, NewRows{-1, 0, false});
 }
 
@@ -475,7 +495,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode(const AttnParam
 // out to the ranges with hardly more blocks each, no range covers two: a sequence then takes its blocks divided by
 // `bpr` ranges, rounded up, which fits while bpr is at least total / (ranges - sequences).  kPieceBlocks is about
 // what a second piece costs in blocks.
-constexpr int kScanPerLane = kStreamMaxSeqs / 64;
+constexpr int kScanPerLane = kStreamSeqs / 64;
 constexpr int kPieceBlocks = 4;
 
 struct BlockScan {
@@ -518,7 +538,7 @@ __device__ __forceinline__ BlockScan scan_blocks(const AttnParams& p, int lane) 
   return sc;
 }
 
-template <int D, int HP, bool KV8>
+template <int D, int HP, bool KV8, bool WHOLE_LINES>
 __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const AttnParams p) {
   __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -600,7 +620,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
     const AttnParams& pp = reread_arguments();
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    decode_range<D, HP, KV8>(pp, red, w * 64 + ln, ln, w, kvh, head0, seq, qrow, o * kBlock, kend, g + seq, fresh);
+    decode_range<D, HP, KV8, WHOLE_LINES>(pp, red, w * 64 + ln, ln, w, kvh, head0, seq, qrow, o * kBlock, kend, g + seq, fresh);
     // where the merge kernel finds the sequence's records
     if (o == 0 && kvh == 0 && hg == 0 && tid == 0)
       p.seq_dec[seq] = make_int2(g + seq, sc.whole ? ((L + kBlock - 1) / kBlock + sc.bpr - 1) / sc.bpr
@@ -777,8 +797,10 @@ hipError_t launch_decode_dh(const AttnParams& p, hipStream_t st) {
   if (p.dec_ranges > 0) {
     const long long grid = (long long)p.dec_ranges * p.Hkv * p.dec_hgroups;
     if (!grid_fits(grid)) return hipErrorInvalidValue;
-    if (p.kv8) hipLaunchKernelGGL((k_decode_stream<D, HP, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((k_decode_stream<D, HP, false>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    if (p.kv8) hipLaunchKernelGGL((k_decode_stream<D, HP, true, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    else if (lines_always<D, HP, false>() || p.num_seqs <= kLineSeqs)
+      hipLaunchKernelGGL((k_decode_stream<D, HP, false, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((k_decode_stream<D, HP, false, lines_always<D, HP, false>()>), dim3((unsigned)grid), dim3(256), 0, st, p);
     return hipGetLastError();
   }
   const long long grid = (long long)p.dec_cap * p.Hkv * p.dec_hgroups;

@@ -27,9 +27,14 @@ constexpr int kPlanBuckets = 2048;  // counting-sort buckets (tile counts) of th
 constexpr int kChunkSizes = 5;
 constexpr int kMaxChunkKeys = 512 << (kChunkSizes - 1);
 constexpr int kDecodeFillWgs = 2048;
-// Batches of single rows with at most this many sequences plan themselves (decode.hip); ranges are cut no shorter than
-// one block per wave of a workgroup (the last one of a batch, or of a sequence, may hold fewer).
-constexpr int kStreamMaxSeqs = 512;
+// Batches of single rows with at most kStreamSeqs sequences plan themselves (decode.hip); ranges are cut no shorter than
+// one block per wave of a workgroup (the last one of a batch, or of a sequence, may hold fewer).  More rows than that
+// are worth the planning launch: the hardware deals its items out one by one, longest first, whereas equal ranges that
+// start together do not end together (256 x 1000-8192 tokens: the first after 370, the last after 770 us).  Streamed and
+// planned: 128 x 1000-8192 tokens 408 and 407 us, 200 x 300-1000 with new rows 109 and 106, 256 x 300-1000 130 and 124, 500 x
+// 200-2000 414 and 391; 256 x 1000-8192 for groups of 8 heads 796 and 782, over an 8-bit cache 546 and 480.
+constexpr int kStreamSeqs = 192;
+constexpr int kScanMaxSeqs = 512;   // query chunks of at most this many sequences can plan themselves (prefill.hip)
 constexpr int kStreamMinBlocks = 4;
 // A running maximum is only raised when a tile's maximum exceeds it by more than this many
 // powers of two; exponentials then stay below 2^kLazyTau, far inside fp32 range, and the

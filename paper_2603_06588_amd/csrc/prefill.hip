@@ -778,7 +778,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
 // launch (8 us in a kernel trace of 16 prompts) and two trips for its record.  It costs a workgroup about a thousand cycles, so launches of many
 // rounds keep the planner (kSelfPlanMaxWgs).  (2 or 8 parts: 1-3 % slower on 16 ragged prompts; 16: 7 %, as
 // neighbouring workgroups then share fewer tiles in L2.)
-constexpr int kSeqsPerLane = kStreamMaxSeqs / 64;
+constexpr int kSeqsPerLane = kScanMaxSeqs / 64;
 
 struct ChunkSeq { int L, n, qbase, bits; bool valid; };
 
@@ -878,7 +878,7 @@ __device__ __forceinline__ bool find_item(const AttnParams& p, int item, int lan
 // entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those) and of elements
 // of the head list that no head owns.
 __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
-  int* const skip = sh + 2;     // [kStreamMaxSeqs]
+  int* const skip = sh + 2;     // [kScanMaxSeqs]
   const int tid = threadIdx.x;
   if (tid < 2) sh[tid] = 0;
   __syncthreads();

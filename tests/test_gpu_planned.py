@@ -71,3 +71,29 @@ def test_more_single_rows_than_plan_themselves_with_long_contexts_among_them(kv8
     torch.cuda.synchronize()
     assert plan_header(call) == [0, 522, 8192, 0]
     print("      ", compare_with_oracle(b, call.out, call.mass, label="long items"), flush=True)
+
+
+@pytest.mark.parametrize("kv8", [False, True])
+@pytest.mark.parametrize("n,planned", [(192, False), (193, True)])
+def test_batches_on_both_sides_of_the_planner(n, planned, kv8):
+    """The largest batch that streams in equal ranges and the smallest that is planned, with new rows, over every head
+    size and group size of the two kernels' key layouts."""
+    for Hq, Hkv, d in ((8, 2, 128), (16, 2, 128), (8, 2, 64), (2, 2, 128)):
+        lens = [1 + (i * 29) % 180 for i in range(n)]
+        print(f"[case] n={n} Hq={Hq} d={d} kv8={kv8}", flush=True)
+        b = W.random_batch(2720 + n, lens, [1] * n, Hq, Hkv, d, torch.bfloat16, num_probe_heads=2, max_sel_q=1, max_spans=2)
+        if kv8:
+            b = W.fp8_cache_variant(b, 2721)
+        gen = torch.Generator().manual_seed(2722)
+        k_new, v_new = (torch.randn((n, Hkv, d), generator=gen).to(torch.bfloat16) for _ in range(2))
+        after = b.to("cpu")
+        after.k_cache, after.v_cache = kv_write(k_new, v_new, b.block_table, b.seq_lens, b.cu_q_lens, b.k_cache, b.v_cache,
+                                                *((b.k_scale, b.v_scale) if kv8 else ()))
+        call = binding.call_from_batch(b.to(DEV), batch_kind=binding.BATCH_DECODE_ONLY, k_new=k_new.to(DEV), v_new=v_new.to(DEV))
+        call.workspace.fill_(0xFF)
+        call.out.fill_(float("nan"))
+        call.mass.fill_(float("nan"))
+        call.launch()
+        torch.cuda.synchronize()
+        assert plan_header(call) == [0, n if planned else 0, 256 if planned else 0, 0]
+        print("      ", compare_with_oracle(after, call.out, call.mass, label="n=%d" % n), flush=True)
