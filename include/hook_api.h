@@ -413,7 +413,7 @@ hook_status hook_kv_write(const hook_kv_write_args* args);
  *   - no attention output is computed: out and v_cache are ignored (run hook_attn_probe with
  *     num_probe_heads = 0 for the output),
  *   - workspace is optional scratch: with hook_span_mass_workspace_bytes(args) bytes (8-byte
- *     aligned) the two passes run as two kernels split over keys and spans and use the whole chip.
+ *     aligned) the work runs as two kernels split over keys and spans and uses the whole chip.
  *     From one key split per 2048 keys of max_blocks_per_seq on (about half of those bytes) a smaller
  *     one is used as well, with fewer splits.  What it held is destroyed, and the number of splits
  *     changes the order of the sums: results are reproducible bit for bit at the same workspace_bytes.
@@ -422,8 +422,9 @@ hook_status hook_kv_write(const hook_kv_write_args* args);
  *     long sequences),
  *   - only HOOK_BF16 inputs are supported (HOOK_ERR_UNSUPPORTED otherwise); the key cache may be
  *     8-bit (kv_dtype, k_scale; v_scale is not read),
- * Two passes over the keys of each (sequence, probed head, 16-row block): exact softmax maximum
- * and normaliser first, then the span sums; no atomics.
+ * Without scratch two passes over the keys of each (sequence, probed head, 16-row block): exact softmax
+ * maximum and normaliser first, then the span sums.  With it one pass that sums disjoint spans in
+ * increasing order on the way; others are walked once more.  No atomics.
  * A content-free calibration prompt is a second call; hook_reduce_mass with negated weights
  * subtracts it.
  */

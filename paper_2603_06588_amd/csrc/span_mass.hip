@@ -241,10 +241,23 @@ __global__ __launch_bounds__(kSmWaves * 64) void k_span_mass(const SpanParams p)
   }
 }
 
-// ---- the same two passes as two kernels, for callers that provide scratch memory: a single
-// workgroup per row block has to pull a long sequence's keys through one CU (about 100 us per
-// 10 k keys and pass); here pass 1 is split over the keys and pass 2 over the spans, so the
-// work spreads over the chip.
+// ---- the same as two kernels, for callers that provide scratch memory: a single workgroup per row block has to pull a
+// long sequence's keys through one CU (about 100 us per 10 k keys and pass); here the keys are split over the chip, and
+// most spans are summed in the pass that finds the statistics, against the reference of their split.
+
+// Sum and maximum over the four lanes of a row (l, l ^ 16, l ^ 32, l ^ 48), in all of them, without a trip through LDS.
+__device__ __forceinline__ float row_sum(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float row_max(float v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
 
 // What both kernels need to know about their row block; false if there is nothing to do.
 struct RowBlock {
@@ -282,17 +295,24 @@ __device__ __forceinline__ void load_q(const SpanParams& p, const RowBlock& r, i
   for (int s = 0; s < D / 32; ++s) qf[s] = qp[4 * s + quarter];
 }
 
-// Both kernels are bound by latency, not by the bytes (4 prompts of 6-14 k tokens, 8 heads: 84 MB of keys
-// per pass): a wave spends most of its time in the chain lengths -> rows -> block ids -> keys.  So the work
-// is cut fine and the workgroups are small, which lets the chip start them all at once and even out
-// sequences of unequal length: pass 1 takes 1024 keys with 4 waves (2048 keys: 4 waves 38 us, 16 waves 40;
-// 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27), pass 2 gives every span a wave of its own, two to a
-// workgroup (two spans per wave in turn, four waves: 45 us; one span: 8 waves 38 us, 4 waves 32, 2 waves 30).
+// Both kernels are bound by latency, not by the bytes (4 prompts of 6-14 k tokens, 8 heads: 84 MB of keys): a wave spends
+// most of its time in the chain lengths -> rows -> block ids -> keys.  So the work is cut fine and the workgroups are small,
+// which lets the chip start them all at once and even out sequences of unequal length: pass 1 takes 1024 keys with 4
+// waves (2048 keys: 4 waves 38 us, 16 waves 40; 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27), and the second kernel
+// gives every span a wave of its own, two to a workgroup.
 constexpr int kStatWaves = 4;     // waves per workgroup of pass 1
-constexpr int kSumWaves = 2;      // waves (spans at a time) per workgroup of pass 2
+constexpr int kSumWaves = 2;      // waves (spans at a time) per workgroup of the second kernel
 constexpr int kSplitBlocks = 2;   // blocks of 16 rows per workgroup: they share every K fetch
+constexpr int kSplitRows = kSplitBlocks * kSmRows;
 constexpr int kSplitKeys = 1024;  // keys of one workgroup of pass 1 (until kMaxSplits is reached)
 constexpr int kMaxSplits = 16;    // key splits of pass 1
+// A span is summed by the workgroup whose split it begins in, which reads on behind its split to the end of its last span.
+// The spans of a split have to be disjoint and in order for that, and at most kListSpans; where they are not, the split's
+// sum of exponentials carries a minus sign, and every span that begins in it gets its own walk over its keys in the
+// second kernel.  So does a span that ends behind its split in a sequence with a span of more than kOverhang keys (a mark, -1, in
+// `mass` says so): one such walk takes as long as many, and reading on would come on top.
+constexpr int kListSpans = 64;
+constexpr int kOverhang = 512;
 
 // The kSplitBlocks row blocks of workgroup column `bx`.  A block without rows shadows the other one
 // (same loads and arithmetic, nothing written); false if no block has rows.
@@ -314,21 +334,30 @@ __device__ __forceinline__ bool row_blocks(const SpanParams& p, int i, int ps, i
   return true;
 }
 
+// 16-key tiles per split of a row block whose last row sits at pos_max
+__device__ __forceinline__ int split_tiles(int pos_max, int nsplit) { return (pos_max / 16 + nsplit) / nsplit; }
+
+// Pass 1, a workgroup per (sequence, probed head, 32 rows, split): the split's statistics - a reference near the
+// maximum and the sum of exponentials against it, per row - and, into `mass`, the sums of the spans that begin in it against
+// the same reference.  The waves take runs of tiles one behind the other, so a wave meets the spans in order and
+// keeps the sum of the one it is in, in registers; a finished span's sum goes to LDS, where the waves are merged.
+// 4 prompts of 7-16 k tokens, 8 heads, 32 rows, documents of 64-256 keys: 27 us and 8 for the second kernel (24 and 30 when the
+// second one read all documents again); 7 documents of 20-40 keys 9.1 + 3.6 (7.6 + 5.0).
 template <int D, bool KV8>
 __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams p) {
-  __shared__ float sh_m[kStatWaves][kSplitBlocks][kSmRows];
-  __shared__ float sh_l[kStatWaves][kSplitBlocks][kSmRows];
-  // every workgroup helps zero-filling mass (the second kernel writes only entries with a row and a span)
-  {
-    const size_t nmass = (size_t)p.num_seqs * p.P * p.NQ * p.S;
-    const size_t nthreads = (size_t)gridDim.x * gridDim.y * gridDim.z * blockDim.x;
-    const size_t me = (((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
-    for (size_t x = me; x < nmass; x += nthreads) p.mass[x] = 0.0f;
-  }
+  __shared__ float sh_m[kStatWaves][kSplitRows];
+  __shared__ float sh_l[kStatWaves][kSplitRows];
+  __shared__ float sh_part[kStatWaves][kListSpans][kSplitRows];
+  __shared__ int sh_list[kStatWaves][3][kListSpans];
   const int i = blockIdx.z / p.nsplit, sp = blockIdx.z % p.nsplit, ps = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, quarter = lane >> 4;
+  const int2* const spans = reinterpret_cast<const int2*>(p.key_spans) + (size_t)i * p.S;
+  constexpr int kSpanLoads = 8;                    // the first 512 spans are requested with the lengths
+  int2 coming[kSpanLoads];
+#pragma unroll
+  for (int u = 0; u < kSpanLoads; ++u) coming[u] = spans[min(64 * u + lane, p.S - 1)];
   RowBlock r[kSplitBlocks];
   bool has[kSplitBlocks];
   int pos_max;
@@ -338,128 +367,249 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) load_q<D>(p, r[nb], quarter, qf[nb]);
   const float c = KV8 ? p.scale_log2 * p.k_scale[r[0].g] : p.scale_log2;
-  const int ntile = pos_max / 16 + 1;
-  const int per = (ntile + p.nsplit - 1) / p.nsplit;           // tiles per split
+  const int ntile = pos_max / 16 + 1, per = split_tiles(pos_max, p.nsplit);
   const int lo = 16 * per * sp, hi = min(16 * per * (sp + 1), 16 * ntile);
-  float m[kSplitBlocks], l[kSplitBlocks];
+
+  // The spans that begin in this split, found by every wave for itself; lane k keeps the k-th.
+  int count = 0;
+  bool any_long = false;
+  for (int s0 = 0; s0 < p.S && count <= kListSpans; s0 += 64 * kSpanLoads) {
 #pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) { m[nb] = -INFINITY; l[nb] = 0.0f; }
-  stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, lo + 16 * kSmGroup * wave, 16 * kSmGroup * kStatWaves,
-                               hi, pos_max, [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+    for (int u = 0; u < kSpanLoads; ++u) {
+      if (s0 + 64 * u >= p.S) break;
+      const int s = s0 + 64 * u + lane;
+      const int a = max(coming[u].x, 0), e = min(coming[u].y, pos_max + 1);
+      const unsigned long long hit = __builtin_amdgcn_ballot_w64(s < p.S && e > a && a >= lo && a < hi);
+      any_long = any_long || __builtin_amdgcn_ballot_w64(s < p.S && e - a > kOverhang) != 0;
+      const int at = count + __builtin_amdgcn_mbcnt_hi((unsigned)(hit >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hit, 0));
+      if (((hit >> lane) & 1) && at < kListSpans) {
+        sh_list[wave][0][at] = a;
+        sh_list[wave][1][at] = e;
+        sh_list[wave][2][at] = s;
+      }
+      count += __builtin_popcountll(hit);
+    }
+    if (s0 + 64 * kSpanLoads < p.S) {
+#pragma unroll
+      for (int u = 0; u < kSpanLoads; ++u) coming[u] = spans[min(s0 + 64 * (kSpanLoads + u) + lane, p.S - 1)];
+    }
+  }
+  const int span_a = sh_list[wave][0][lane], span_e = sh_list[wave][1][lane];      // (lane < count)
+  const bool listed = count <= kListSpans &&
+                      __builtin_amdgcn_ballot_w64(lane > 0 && lane < count && span_a < sh_list[wave][1][max(lane - 1, 0)]) == 0;
+  int summed = listed ? count : 0, stop = hi;      // stop: end of the keys to read
+  if (summed > 0) {
+    const int last_e = __builtin_amdgcn_readlane(span_e, summed - 1);
+    if (any_long && last_e > hi) --summed;
+    else stop = max(hi, last_e);
+  }
+  for (int e = lane; e < summed * kSplitRows; e += 64) sh_part[wave][e / kSplitRows][e % kSplitRows] = 0.0f;
+
+  // this wave's run of tiles, and its first span
+  const int run = ((stop - lo + 15) / 16 + kStatWaves - 1) / kStatWaves;
+  const int w_lo = lo + 16 * run * wave, w_hi = min(w_lo + 16 * run, stop);
+  const unsigned long long ahead = __builtin_amdgcn_ballot_w64(lane < summed && span_e > w_lo);
+  int k = ahead ? __builtin_ctzll(ahead) : summed;
+  const int k_first = k;
+  int sa = __builtin_amdgcn_readlane(span_a, k & 63), se = __builtin_amdgcn_readlane(span_e, k & 63);
+
+  float m[kSplitBlocks], l[kSplitBlocks], acc[kSplitBlocks];      // m: one reference for the four lanes of a row
+#pragma unroll
+  for (int nb = 0; nb < kSplitBlocks; ++nb) { m[nb] = -INFINITY; l[nb] = 0.0f; acc[nb] = 0.0f; }
+  auto flush = [&]() {
 #pragma unroll
     for (int nb = 0; nb < kSplitBlocks; ++nb) {
-      float sv[4];
+      const float v = row_sum(acc[nb]);
+      if (quarter == 0) sh_part[wave][k][kSmRows * nb + j] = v;
+      acc[nb] = 0.0f;
+    }
+  };
+  stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, w_lo, 16 * kSmGroup, w_hi, pos_max,
+                                    [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+    float ex[kSplitBlocks][4], sum[kSplitBlocks];
+#pragma unroll
+    for (int nb = 0; nb < kSplitBlocks; ++nb) {
       float mt = -INFINITY;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int key = key0 + 4 * quarter + q;
-        sv[q] = key <= r[nb].pos ? sc[nb][q] * c : -INFINITY;
-        mt = fmaxf(mt, sv[q]);
+        ex[nb][q] = key0 + 4 * quarter + q <= r[nb].pos ? sc[nb][q] * c : -INFINITY;
+        mt = fmaxf(mt, ex[nb][q]);
       }
-      const float mn = fmaxf(m[nb], mt);
-      const float ref = (mn == -INFINITY) ? 0.0f : mn;
-      l[nb] *= fast_exp2(m[nb] - ref);
+      // the reference is raised by what exceeds it by kLazyTau, with the sums that refer to it
+      if (__builtin_amdgcn_ballot_w64(mt > m[nb] + kLazyTau) != 0) {
+        mt = row_max(mt);
+        const float mn = mt > m[nb] + kLazyTau ? mt : m[nb];
+        const float alpha = mn > m[nb] ? fast_exp2(m[nb] - mn) : 1.0f;
+        l[nb] *= alpha;
+        acc[nb] *= alpha;
+        if (quarter == 0)
+          for (int kk = k_first; kk < k; ++kk) sh_part[wave][kk][kSmRows * nb + j] *= alpha;
+        m[nb] = mn;
+      }
+      const float ref = m[nb] == -INFINITY ? 0.0f : m[nb];
+      sum[nb] = 0.0f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) l[nb] += fast_exp2(sv[q] - ref);
-      m[nb] = mn;
+      for (int q = 0; q < 4; ++q) {
+        ex[nb][q] = fast_exp2(ex[nb][q] - ref);
+        sum[nb] += ex[nb][q];
+      }
+      if (key0 < hi) l[nb] += sum[nb];
+    }
+    while (k < summed && sa < key0 + 16) {         // (se > key0)
+      if (sa <= key0 && se >= key0 + 16) {
+#pragma unroll
+        for (int nb = 0; nb < kSplitBlocks; ++nb) acc[nb] += sum[nb];
+      } else {
+#pragma unroll
+        for (int nb = 0; nb < kSplitBlocks; ++nb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int key = key0 + 4 * quarter + q;
+            acc[nb] += key >= sa && key < se ? ex[nb][q] : 0.0f;
+          }
+      }
+      if (se > key0 + 16) break;
+      flush();
+      ++k;
+      sa = __builtin_amdgcn_readlane(span_a, k & 63);
+      se = __builtin_amdgcn_readlane(span_e, k & 63);
     }
   });
+  if (k < summed) flush();                         // the span that the next wave goes on with
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) {
-#pragma unroll
-    for (int off = 16; off <= 32; off <<= 1) {
-      const float mo = __shfl_xor(m[nb], off), lo2 = __shfl_xor(l[nb], off);
-      const float mn = fmaxf(m[nb], mo);
-      if (mn != -INFINITY) l[nb] = l[nb] * fast_exp2(m[nb] - mn) + lo2 * fast_exp2(mo - mn);
-      m[nb] = mn;
-    }
-    if (quarter == 0) { sh_m[wave][nb][j] = m[nb]; sh_l[wave][nb][j] = l[nb]; }
+    l[nb] = row_sum(l[nb]);
+    if (quarter == 0) { sh_m[wave][kSmRows * nb + j] = m[nb]; sh_l[wave][kSmRows * nb + j] = l[nb]; }
   }
   __syncthreads();
-  if (threadIdx.x < kSplitBlocks * kSmRows) {
-    const int nb = threadIdx.x / kSmRows, jj = threadIdx.x % kSmRows;
-    float M = -INFINITY;
+  // thread: row, and every eighth span
+  constexpr int kSpanStep = kStatWaves * 64 / kSplitRows;
+  const int row = threadIdx.x % kSplitRows, slot = kSplitRows * blockIdx.x + row;
+  float M = -INFINITY, wgt[kStatWaves], Ls = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kStatWaves; ++w) M = fmaxf(M, sh_m[w][nb][jj]);
-    float Ls = 0.0f;
+  for (int w = 0; w < kStatWaves; ++w) M = fmaxf(M, sh_m[w][row]);
 #pragma unroll
-    for (int w = 0; w < kStatWaves; ++w) {
-      const float mw = sh_m[w][nb][jj];
-      if (mw != -INFINITY) Ls += sh_l[w][nb][jj] * fast_exp2(mw - M);
-    }
-    const int slot = kSmRows * (kSplitBlocks * blockIdx.x + nb) + jj;
-    if (slot < p.nq_pad) p.stats[(((size_t)i * p.P + ps) * p.nq_pad + slot) * p.nsplit + sp] = make_float2(M, Ls);
+  for (int w = 0; w < kStatWaves; ++w) {
+    wgt[w] = sh_m[w][row] == -INFINITY ? 0.0f : fast_exp2(sh_m[w][row] - M);
+    Ls += sh_l[w][row] * wgt[w];
   }
+  if (threadIdx.x < kSplitRows && slot < p.nq_pad)
+    p.stats[(((size_t)i * p.P + ps) * p.nq_pad + slot) * p.nsplit + sp] = make_float2(M, listed ? Ls : -Ls);
+  if (slot >= p.NQ) return;
+  float* const mass = p.mass + (((size_t)i * p.P + ps) * p.NQ + slot) * p.S;
+  for (int kk = threadIdx.x / kSplitRows; kk < summed; kk += kSpanStep) {
+    float v = 0.0f;
+#pragma unroll
+    for (int w = 0; w < kStatWaves; ++w) v += sh_part[w][kk][row] * wgt[w];
+    mass[sh_list[0][2][kk]] = v;
+  }
+  if (listed && summed < count && threadIdx.x < kSplitRows) mass[sh_list[0][2][summed]] = -1.0f;
 }
 
+// The second kernel: from the splits' references to the row's, divided by its normaliser; zeros where there is no row or
+// no key; and the walk over the keys of spans that the first kernel left out.
 template <int D, bool KV8>
 __global__ __launch_bounds__(kSumWaves * 64) void k_span_sums(const SpanParams p) {
   const int i = blockIdx.z / p.sgroups, sg = blockIdx.z % p.sgroups, ps = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, quarter = lane >> 4;
+  float* const mass = p.mass + ((size_t)i * p.P + ps) * p.NQ * p.S;
+  const int slot0 = kSplitRows * blockIdx.x;
   RowBlock r[kSplitBlocks];
   bool has[kSplitBlocks];
   int pos_max;
-  if (!row_blocks(p, i, ps, blockIdx.x, j, r, has, pos_max)) return;   // uniform
-  const int* bt = p.block_table + (size_t)i * p.max_blocks;
-  bf16x8 qf[kSplitBlocks][D / 32];
-#pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) load_q<D>(p, r[nb], quarter, qf[nb]);
-  const float c = KV8 ? p.scale_log2 * p.k_scale[r[0].g] : p.scale_log2;
-  // each row's softmax maximum and normaliser from the key splits of the first kernel
+  if (!row_blocks(p, i, ps, blockIdx.x, j, r, has, pos_max)) {   // uniform
+    for (int s = sg * kSumWaves + wave; s < p.S; s += p.sgroups * kSumWaves)
+      if (lane < kSplitRows && slot0 + lane < p.NQ) mass[(size_t)(slot0 + lane) * p.S + s] = 0.0f;
+    return;
+  }
+  const int per = split_tiles(pos_max, p.nsplit);
+  // each row's reference and normaliser from the key splits of the first kernel
   float M[kSplitBlocks], inv[kSplitBlocks];
+  float2 v[kSplitBlocks][kMaxSplits / 4];
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) {
-    M[nb] = 0.0f;
-    inv[nb] = 0.0f;
-    if (has[nb]) {   // uniform; a shadow block has no statistics of its own and writes nothing
-      // the four lanes of a row take a quarter of the splits each
-      const float2* st = p.stats + (((size_t)i * p.P + ps) * p.nq_pad + r[nb].slot0 + j) * p.nsplit;
-      float2 v[kMaxSplits / 4];
+    // the four lanes of a row take a quarter of the splits each (a block without rows reads the other one's)
+    const int block = has[nb] ? nb : 1 - nb;
+    const float2* st = p.stats + (((size_t)i * p.P + ps) * p.nq_pad + slot0 + kSmRows * block + j) * p.nsplit;
 #pragma unroll
-      for (int u = 0; u < kMaxSplits / 4; ++u) {
-        const int sp = kMaxSplits / 4 * quarter + u;
-        v[u] = sp < p.nsplit ? st[sp] : make_float2(-INFINITY, 0.0f);
-      }
-      float mx = -INFINITY, Lsum = 0.0f;
-#pragma unroll
-      for (int u = 0; u < kMaxSplits / 4; ++u) mx = fmaxf(mx, v[u].x);
-      mx = fmaxf(mx, __shfl_xor(mx, 16));
-      mx = fmaxf(mx, __shfl_xor(mx, 32));
-#pragma unroll
-      for (int u = 0; u < kMaxSplits / 4; ++u) Lsum += v[u].y * fast_exp2(v[u].x - mx);   // an empty split adds 0
-      Lsum += __shfl_xor(Lsum, 16);
-      Lsum += __shfl_xor(Lsum, 32);
-      M[nb] = mx;
-      inv[nb] = 1.0f / Lsum;
+    for (int u = 0; u < kMaxSplits / 4; ++u) {
+      const int sp = kMaxSplits / 4 * quarter + u;
+      v[nb][u] = sp < p.nsplit ? st[sp] : make_float2(-INFINITY, 0.0f);
     }
   }
-  for (int s = sg * kSumWaves + wave; s < p.S; s += p.sgroups * kSumWaves) {
-    const int a = max(p.key_spans[((size_t)i * p.S + s) * 2], 0);
-    const int e = min(p.key_spans[((size_t)i * p.S + s) * 2 + 1], pos_max + 1);
-    if (e <= a) continue;                          // uniform; mass was zero-filled
-    float acc[kSplitBlocks];
+  const int2* const spans = reinterpret_cast<const int2*>(p.key_spans) + (size_t)i * p.S;
+  int s = sg * kSumWaves + wave;
+  if (s >= p.S) return;
+  int2 span = spans[s];
+  float out[kSplitBlocks];
 #pragma unroll
-    for (int nb = 0; nb < kSplitBlocks; ++nb) acc[nb] = 0.0f;
-    stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, a, 16 * kSmGroup, e, pos_max,
-                                 [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+  for (int nb = 0; nb < kSplitBlocks; ++nb) out[nb] = r[nb].row_ok ? mass[(size_t)(r[nb].slot0 + j) * p.S + s] : 0.0f;
 #pragma unroll
-      for (int nb = 0; nb < kSplitBlocks; ++nb)
+  for (int nb = 0; nb < kSplitBlocks; ++nb) {
+    float mx = -INFINITY, Lsum = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int key = key0 + 4 * quarter + q;
-          acc[nb] += (key < e && key <= r[nb].pos) ? fast_exp2(sc[nb][q] * c - M[nb]) : 0.0f;
+    for (int u = 0; u < kMaxSplits / 4; ++u) mx = fmaxf(mx, v[nb][u].x);
+    mx = row_max(mx);
+#pragma unroll
+    for (int u = 0; u < kMaxSplits / 4; ++u) Lsum += fabsf(v[nb][u].y) * fast_exp2(v[nb][u].x - mx);   // an empty split adds 0
+    M[nb] = mx;
+    inv[nb] = 1.0f / row_sum(Lsum);
+  }
+  for (;;) {
+    const int a = max(span.x, 0), e = min(span.y, pos_max + 1);
+    bool walk = false;
+    if (e > a) {                                   // uniform
+      const int sp = a / 16 / per, from = sp / (kMaxSplits / 4) * 16 + j;
+#pragma unroll
+      for (int nb = 0; nb < kSplitBlocks; ++nb) {
+        float ref = v[nb][0].x, sum = v[nb][0].y;
+#pragma unroll
+        for (int u = 1; u < kMaxSplits / 4; ++u) {
+          ref = sp % (kMaxSplits / 4) == u ? v[nb][u].x : ref;
+          sum = sp % (kMaxSplits / 4) == u ? v[nb][u].y : sum;
         }
-    });
+        ref = __shfl(ref, from);                   // -inf: the row sees no key of this split
+        walk = walk || out[nb] < 0.0f || __float_as_int(__shfl(sum, from)) < 0;
+        out[nb] *= ref == -INFINITY ? 0.0f : fast_exp2(ref - M[nb]) * inv[nb];
+      }
+      walk = __builtin_amdgcn_ballot_w64(walk) != 0;
+    }
+    if (walk) {
+      const int* bt = p.block_table + (size_t)i * p.max_blocks;
+      bf16x8 qf[kSplitBlocks][D / 32];
+#pragma unroll
+      for (int nb = 0; nb < kSplitBlocks; ++nb) load_q<D>(p, r[nb], quarter, qf[nb]);
+      const float c = KV8 ? p.scale_log2 * p.k_scale[r[0].g] : p.scale_log2;
+      float acc[kSplitBlocks];
+#pragma unroll
+      for (int nb = 0; nb < kSplitBlocks; ++nb) acc[nb] = 0.0f;
+      stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, a, 16 * kSmGroup, e, pos_max,
+                                        [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+#pragma unroll
+        for (int nb = 0; nb < kSplitBlocks; ++nb)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int key = key0 + 4 * quarter + q;
+            acc[nb] += (key < e && key <= r[nb].pos) ? fast_exp2(sc[nb][q] * c - M[nb]) : 0.0f;
+          }
+      });
+#pragma unroll
+      for (int nb = 0; nb < kSplitBlocks; ++nb) {
+        out[nb] = row_sum(acc[nb]) * inv[nb];
+      }
+    }
 #pragma unroll
     for (int nb = 0; nb < kSplitBlocks; ++nb) {
-      float v = acc[nb];
-      v += __shfl_xor(v, 16);
-      v += __shfl_xor(v, 32);
-      if (quarter == 0 && r[nb].row_ok)
-        p.mass[(((size_t)i * p.P + ps) * p.NQ + (r[nb].slot0 + j)) * p.S + s] = v * inv[nb];
+      const int slot = slot0 + kSmRows * nb + j;
+      if (quarter == 0 && slot < p.NQ) mass[(size_t)slot * p.S + s] = r[nb].row_ok && e > a ? out[nb] : 0.0f;
     }
+    s += p.sgroups * kSumWaves;
+    if (s >= p.S) break;
+    span = spans[s];
+#pragma unroll
+    for (int nb = 0; nb < kSplitBlocks; ++nb) out[nb] = r[nb].row_ok ? mass[(size_t)(r[nb].slot0 + j) * p.S + s] : 0.0f;
   }
 }
 

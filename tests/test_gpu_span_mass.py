@@ -160,3 +160,38 @@ def test_span_mass_with_scratch_for_some_of_the_splits(seqs, ctx):
             assert bool((ws[used * per_split:] == 0x5A).all()), (splits, short)
             assert bool((ws == 0x5A).all()) == (used == 0), (splits, short)
             assert (got.cpu().double() - want).abs().max().item() <= MASS_TOL, (splits, short)
+
+
+def _layouts(L):
+    """Lists of spans that fall on both sides of what the first kernel sums: splits hold 16 * ceil(tiles / splits) keys."""
+    yield "abutting", [(a, a + 100) for a in range(0, L, 100)]
+    yield "abutting from the middle of a tile", [(a, a + 37) for a in range(5, L, 37)][:120]
+    yield "empty ones between", [(a, a + n) for a in range(40, L, 90) for n in (0, 60, -3)]
+    yield "64 in a split", [(8 + 12 * k, 8 + 12 * k + 11) for k in range(64)]
+    yield "65 in a split", [(8 + 12 * k, 8 + 12 * k + 11) for k in range(65)]
+    yield "single keys", [(k, k + 1) for k in range(L - 60, L)]
+    yield "across a split, 512 keys at most", [(900, 1412), (1412, 1413), (1900, 2400)]
+    yield "across a split, 513 keys", [(900, 1413), (1413, 1500), (1900, 2400)]
+    yield "across several splits", [(10, 3000), (3000, 3010), (3010, L)]
+    yield "overlapping", [(0, 700), (100, 200), (600, 1500), (1490, 1491)]
+    yield "out of order", [(2000, 2100), (100, 300), (300, 310), (1500, 1600)]
+    yield "the same one many times", [(50, 1100)] * 70
+    yield "beyond the context", [(-20, 30), (30, 40), (L - 10, L + 50), (L + 50, L + 60)]
+
+
+@pytest.mark.parametrize("d,kv8", [(128, False), (64, True)])
+def test_span_layouts(d, kv8):
+    """Every layout on two contexts of several splits and one of a single tile, rows in two blocks of 32."""
+    lens, qlens = [4100, 2573, 12], [50, 40, 12]
+    b = W.random_batch(530 + d, lens, qlens, 8, 2, d, torch.bfloat16, std=1.0, num_probe_heads=2, max_sel_q=50, max_spans=4)
+    if kv8:
+        b = W.fp8_cache_variant(b, 531)
+    for i, n in enumerate(qlens):
+        b.query_sel[i, 0], b.query_sel[i, 1] = 0, n
+    lists = [dict(_layouts(L)) for L in lens]
+    for name in lists[0]:
+        print("[case]", name, flush=True)
+        S = max(len(x[name]) for x in lists)
+        b.max_spans = S
+        b.key_spans = torch.tensor([x[name] + [(0, 0)] * (S - len(x[name])) for x in lists], dtype=torch.int32)
+        _check(b)
