@@ -150,3 +150,22 @@ def test_several_prompts_find_their_row_blocks(nseq, lo, hi, rows, kind):
     cu = b.cu_q_lens.tolist()
     assert hit.device_status() == 4 and (hit.mass[1] == 0).all() and (hit.out[cu[1]:cu[2]] == 7.0).all()
     assert torch.equal(bits(hit.out[:cu[1]]), bits(call.out[:cu[1]])) and torch.equal(bits(hit.mass[0]), bits(call.mass[0]))
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,kv8", [(8, 2, 128, False), (16, 2, 64, False), (4, 1, 128, True), (8, 2, 64, True)])
+def test_row_blocks_whose_keys_are_shared(Hq, Hkv, d, kv8):
+    """Few row blocks: two groups of waves take half of the key tiles each.  Lengths around the tile borders (one to five
+    tiles, halves of unequal length, a second half that some rows do not reach), spans across the middle, several
+    sequences of unlike depth in one call; against the oracle and the planned call."""
+    for lens, qlens in (([129], [129]), ([192], [2]), ([193], [193]), ([256], [33]), ([257], [257]), ([320, 40, 150], [320, 40, 31]),
+                        ([1000, 65, 64], [40, 65, 64])):
+        print(f"[case] shared keys Hq={Hq} d={d} kv8={kv8} L={lens} n={qlens}", flush=True)
+        b = W.random_batch(1460 + lens[0], lens, qlens, Hq, Hkv, d, torch.bfloat16, num_probe_heads=3, max_sel_q=8, max_spans=3)
+        for i, (L, n) in enumerate(zip(lens, qlens)):
+            b.query_sel[i, 0], b.query_sel[i, 1] = max(0, n - 5), n
+            b.key_spans[i] = torch.tensor([(0, L), (L // 2 - 5, L // 2 + 70), (60, 68)], dtype=torch.int32)
+        if kv8:
+            b = W.fp8_cache_variant(b, 1461)
+        own, planned = _run(b, binding.BATCH_PREFILL_ONLY), planned_reference(b, batch_kind=binding.BATCH_PREFILL_ONLY)
+        assert torch.equal(bits(own.out), bits(planned.out)) and torch.equal(bits(own.mass), bits(planned.mass))
+        print("      ", compare_with_oracle(b, own.out, own.mass, label="shared"), flush=True)
