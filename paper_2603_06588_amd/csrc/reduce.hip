@@ -1,4 +1,4 @@
-// Score reductions over the mass tensor: one workgroup per sequence (and per 64 spans), fp32 sums in a
+// Score reductions over the mass tensor: one workgroup per sequence (and per 16 spans), fp32 sums in a
 // fixed order (strided partial sums per thread, a butterfly inside the wave, the waves in turn), so the
 // result does not depend on anything but the inputs.
 #include "../../include/hook_api.h"
@@ -46,29 +46,36 @@ __device__ __forceinline__ SeqRows selected_slots(const ReduceParams& p, int i) 
 
 // Scores per span.  A row's spans are neighbours in memory, so neighbouring threads take neighbouring
 // spans of one row and the groups of threads share the (head, row) pairs: every load is coalesced.
-// (One wave per sequence, eight spans per pass over the pairs, read 4 x 8 heads x 32 rows x 88 spans in
-// 96 us; this form takes 6.6 in a kernel trace.)
+// (One wave per sequence, eight spans per pass over the pairs, read 4 x 8 heads x 32 rows x 88 spans in 96 us.  With 64
+// spans to a workgroup, two batches of loads per thread and a division for each load 4 x 8 x 32 x 100 took 6.3 us in a
+// kernel trace; with one batch and the pair counted on from load to load it takes 4.6 at 32 spans and 3.9 at 16, where a
+// row's share is 64 bytes still.)
+constexpr int kReduceSpansLog2 = 4;
 template <int NT>
 __global__ __launch_bounds__(NT) void k_reduce_spans(const ReduceParams p) {
-  __shared__ float red[NT / 64][64];
+  __shared__ float red[NT / 64][1 << kReduceSpansLog2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i = blockIdx.x;
   const int lanes = 1 << p.lanes_log2;
-  const int r = blockIdx.y * 64 + (tid & (lanes - 1));
+  const int r = (blockIdx.y << kReduceSpansLog2) + (tid & (lanes - 1));
   const int sub = tid >> p.lanes_log2, nsub = NT >> p.lanes_log2;
   const SeqRows rows = selected_slots(p, i);
   const float* m = p.mass + (size_t)i * p.P * p.NQ * p.S + r;
   const int npairs = p.P * rows.nv;
   float acc = 0.0f;
-  if (r < p.S) {
+  if (r < p.S && npairs > 0) {
+    int ph = sub / rows.nv, t = sub - ph * rows.nv;               // the next pair, and how far it is to the one after
+    const int dph = nsub / rows.nv, dt = nsub - dph * rows.nv;
     for (int e0 = sub; e0 < npairs; e0 += kInFlight * nsub) {
       float v[kInFlight], wp[kInFlight];
 #pragma unroll
       for (int u = 0; u < kInFlight; ++u) {
-        const int e = min(e0 + u * nsub, npairs - 1);   // past the end: a repeated load with weight 0
-        const int ph = e / rows.nv, t = rows.skip + e - ph * rows.nv;
-        v[u] = m[((size_t)ph * p.NQ + t) * p.S];
-        wp[u] = p.w ? p.w[ph] : 1.0f / (float)p.P;
+        const int h = min(ph, p.P - 1);                           // past the end: some load with weight 0
+        v[u] = m[((size_t)h * p.NQ + rows.skip + t) * p.S];
+        wp[u] = p.w ? p.w[h] : 1.0f / (float)p.P;
+        ph += dph;
+        t += dt;
+        if (t >= rows.nv) { t -= rows.nv; ++ph; }
       }
 #pragma unroll
       for (int u = 0; u < kInFlight; ++u) acc += (e0 + u * nsub < npairs) ? wp[u] * v[u] : 0.0f;
@@ -148,8 +155,8 @@ extern "C" hook_status hook_reduce_mass(const hook_reduce_args* a) {
   hipStream_t st = static_cast<hipStream_t>(a->stream);
   const bool many = (long long)p.P * p.NQ >= kManyPairs;
   if (p.mode == HOOK_REDUCE_SPAN_MEAN) {
-    while ((1 << p.lanes_log2) < p.S && p.lanes_log2 < 6) ++p.lanes_log2;
-    const dim3 grid((unsigned)p.num_seqs, (unsigned)((p.S + 63) / 64));
+    while ((1 << p.lanes_log2) < p.S && p.lanes_log2 < kReduceSpansLog2) ++p.lanes_log2;
+    const dim3 grid((unsigned)p.num_seqs, (unsigned)((p.S + (1 << kReduceSpansLog2) - 1) >> kReduceSpansLog2));
     if (many) hipLaunchKernelGGL(k_reduce_spans<1024>, grid, dim3(1024), 0, st, p);
     else hipLaunchKernelGGL(k_reduce_spans<256>, grid, dim3(256), 0, st, p);
   } else if (many) {

@@ -64,3 +64,19 @@ def test_reduce_large_many_rows():
     mass = torch.rand((3, 16, 512, 8), generator=g) / 512
     for mode in (SPAN_MEAN, RATIO_MEAN, RATIO_OF_SUMS):
         _check(mass, mode, a=7, b=0)
+
+
+@pytest.mark.parametrize("S", [1, 3, 16, 17, 40])
+@pytest.mark.parametrize("P,NQ", [(1, 1), (3, 43), (2, 700), (11, 12)])
+def test_reduce_spans_at_group_borders(P, NQ, S):
+    """Spans on both sides of a workgroup's 16, (head, row) pairs fewer and more than a step of its threads, rows that do
+    not divide that step, sequences without a row."""
+    g = torch.Generator().manual_seed(100 * P + S)
+    mass = torch.rand((5, P, NQ, S), generator=g) * 0.2
+    sel = torch.tensor([[0, NQ], [-1, NQ // 2], [0, 0], [NQ - 1, NQ + 5], [1, 2]], dtype=torch.int32)
+    mass[1, :, 0] = 0.0                     # slots of rows in front of the chunk hold zeros
+    n = torch.tensor([NQ, NQ, 7, 2 * NQ, 1], dtype=torch.int32)
+    cu = torch.zeros(6, dtype=torch.int32)
+    cu[1:] = torch.cumsum(n, 0)
+    _check(mass, SPAN_MEAN, sel, cu, torch.rand(P, generator=g) + 0.5)
+    _check(mass, SPAN_MEAN)
