@@ -173,6 +173,15 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const AttnParams p) {
 #pragma unroll
   for (int k = 0; k < kChunkSizes; ++k)
     if ((long long)sh_cnt[k] * wg_per_item >= kDecodeFillWgs) chunk = 512 << k;
+  // Few long contexts among many short ones: an item of several times a workgroup's share (all contexts in pieces of 512 keys
+  // over 768 resident workgroups) would outlast the rest.  As far as the records reach (1 x 32768 + 400 x 300 tokens
+  // 224 us with 8192 keys per item, 132 so); batches beyond kScanMaxSeqs have short items by their number.
+  if (p.num_seqs <= kScanMaxSeqs) {
+    const long long share = (long long)sh_cnt[0] * 512 * wg_per_item / 768;
+#pragma unroll
+    for (int k = kChunkSizes - 1; k >= 1; --k)
+      if (chunk == (512 << k) && chunk > share && sh_cnt[k - 1] <= p.dec_cap) chunk >>= 1;
+  }
   __syncthreads();
 
   // pass 2: scatter.  What the ordering pass below needs about a thread's first sequence stays

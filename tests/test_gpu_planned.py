@@ -97,3 +97,21 @@ def test_batches_on_both_sides_of_the_planner(n, planned, kv8):
         torch.cuda.synchronize()
         assert plan_header(call) == [0, n if planned else 0, 256 if planned else 0, 0]
         print("      ", compare_with_oracle(after, call.out, call.mass, label="n=%d" % n), flush=True)
+
+
+@pytest.mark.parametrize("kv8", [False, True])
+def test_one_long_context_among_many_short_ones(kv8):
+    """Items are cut to a workgroup's share where the largest that fill the chip would be much longer."""
+    lens = [1 + (i * 37) % 90 for i in range(300)]
+    lens[7] = 16000
+    b = W.random_batch(2730, lens, [1] * 300, 16, 8, 64, torch.bfloat16, num_probe_heads=2, max_sel_q=1, max_spans=2)
+    if kv8:
+        b = W.fp8_cache_variant(b, 2731)
+    call = binding.call_from_batch(b.to(DEV), batch_kind=binding.BATCH_DECODE_ONLY)
+    call.workspace.fill_(0xFF)
+    call.out.fill_(float("nan"))
+    call.mass.fill_(float("nan"))
+    call.launch()
+    torch.cuda.synchronize()
+    assert plan_header(call) == [0, 299 + 16000 // 1024 + 1, 1024, 0]      # 331 pieces of 512 keys * 8 / 768 = 1765 keys
+    print("      ", compare_with_oracle(b, call.out, call.mass, label="one long"), flush=True)
