@@ -18,20 +18,6 @@ constexpr size_t kAlign = 256;
 constexpr long long kSelfPlanMaxWgs = 1024;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
-// Whether a row block's keys are shared by two groups of four waves (prefill.hip, groups of a multiple of four heads).  The
-// walk over its tiles is half as long then, but the eight waves fill a compute unit, so it pays where there is at most
-// one row block to each of 256 of them, unless contexts are short: 1024 tokens at 32 / 8 heads 24.7 -> 22.1 us, 300 rows
-// behind 7900 134 -> 101, 700 tokens 19.8 -> 18.1, 512 (128 row blocks) 14.5 -> 14.4, but 65 (24) 8.2 -> 8.8 and 512 at
-// 64 / 8 heads (256) 14.9 -> 15.3.  With up to two row blocks to a
-// compute unit they would wait for each other (2 x 1024 tokens 33 -> 37 us, 1096 rows behind 3000 89 -> 93), except those of one
-// prompt alone, which are half as long on average as its longest: 1500 tokens 36.5 -> 30.2, 2048 51.6 -> 47.6, 2048 over an
-// 8-bit cache 58.5 -> 53.2.  The rule reads nothing but sizes that planned and self-planned calls share.
-bool splits_keys(const hook_attn_probe_args* a, long long workgroups) {
-  const long long context = (long long)a->max_blocks_per_seq * kBlock, rows = a->total_q;
-  if (workgroups <= 256) return context > (workgroups <= 128 ? 2 : 8) * kTileKeys;
-  return workgroups <= 512 && 4 * context <= 5 * rows && 5 * context >= 4 * rows;
-}
-
 struct Layout {
   size_t off_hdr, off_pf, off_dec, off_seq, off_part;
   size_t needed, reported;      // smallest workspace that is accepted; size to ask for
@@ -240,7 +226,6 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.pf_self = a->dtype == HOOK_BF16 && a->num_seqs <= kScanMaxSeqs && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
               (streams || a->batch_kind == HOOK_BATCH_PREFILL_ONLY) &&
               (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups <= kSelfPlanMaxWgs);
-  p.pf_split = l.rows_per_wg == kWaveRows && splits_keys(a, (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups);
   // The streaming kernel can do without a write ahead of it while a wave can hold every new row's place, one per lane.
   // (A launch ahead costs a call 4 us: 1 x 1237 tokens 16.6 us against 11.7, 8 x 4096 30.2 against 26.3, 64 x 2048 77.2
   // against 72.8.  Where to look would take more registers for more sequences, and the loop has none to spare.)

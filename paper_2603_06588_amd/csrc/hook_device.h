@@ -117,7 +117,6 @@ struct AttnParams {
   int hgroups;                      // G / hpw
   int dec_hp;                       // q heads per decode workgroup (8, 4, 2 or 1)
   int dec_hgroups;                  // G / dec_hp
-  int pf_split;                     // chunk workgroups are two groups of waves that share the keys
 };
 
 // The kernel's argument block, through a pointer whose origin the compiler cannot see.

@@ -30,10 +30,6 @@
 // above, so the rest of the loop is the 16-bit one and every byte is widened once for the four heads
 // that share it.  The key scale goes into the softmax scale, the value scale into the normalisation of `out`.
 //
-// Calls with few row blocks (splits_keys in api.hip) put two such groups of four waves on one: each takes half of the
-// key tiles through buffers of its own, and they merge through LDS at the end.  (Half a tile out of step, with a barrier
-// between the two stages, so that one group's exponentials meet the other's P V: 2048 tokens 47.6 -> 50.8 us.)
-//
 // Probe span sums are taken from the fp32 exponentials under the same running reference
 // as the normaliser and divided by it at the end: the captured mass is the exact softmax
 // mass of the row.  Waves that probe run a second instantiation of the same loop whose
@@ -67,8 +63,6 @@ struct Cfg {
 // all of them at D = 128 and half of them at D = 64).
 template <int D> __device__ __forceinline__ int k_swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 template <int D> __device__ __forceinline__ int v_swizzle(int r) { return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); }
-// the same for the rows of the output on their way out (half rows where two groups of waves share them)
-template <int D, bool HALF> __device__ __forceinline__ int out_swizzle(int r) { return !HALF ? k_swizzle<D>(r) : D == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -611,34 +605,26 @@ __device__ __forceinline__ void rest_of_first_tiles(const WaveCtx& cx, unsigned 
 // qbase) for the heads of (kvh, hg).  ZERO_REST (self-planned calls): the wave that owns a probed
 // head in the item of row 0 also writes zeros to that head's `mass` slots that hold no row, so that
 // every entry of `mass` is written exactly once without a planner's zero-fill.
-// SPLIT: two groups of four waves with buffers of their own take the first and the second half of the key tiles, and are
-// merged at the end, each normalising and storing half of the dimensions.  (The groups meet at the same number of barriers.)
-template <int D, bool KV8, bool SHARED, bool ZERO_REST, bool SPLIT>
-__device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem0, int kvh, int hg, int seq,
-                                             int row0, int Lall, int n, int qbase) {
+template <int D, bool KV8, bool SHARED, bool ZERO_REST>
+__device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem, int kvh, int hg, int seq,
+                                             int row0, int L, int n, int qbase) {
   using C = Cfg<D, KV8>;
-  static_assert(!(SPLIT && SHARED), "split workgroups take one row block");
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), w = SPLIT ? wave & 3 : wave, grp = SPLIT ? wave >> 2 : 0;
-  unsigned char* const smem = SPLIT ? smem0 + grp * C::LDS : smem0;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hh = w % p.hpw, rb = w / p.hpw;
   const int head = kvh * p.G + hg * p.hpw + hh;
   const int wrow0 = row0 + rb * kWaveRows;
   const bool wave_active = wrow0 < n;
   const int qi = lane & 31, hf = lane >> 5;
   const int t = max(min(wrow0 + qi, n - 1), 0);
-  const int wave_pos_min = Lall - n + min(wrow0, n - 1);
-  const int wg_pos_max = Lall - n + min(row0 + p.rows_per_wg, n) - 1;
-  const int all_tiles = wg_pos_max / kTileKeys + 1;
-  // this group's tiles; from here on keys and blocks count from its first tile
-  const int longer = SPLIT ? (all_tiles + 1) / 2 : all_tiles, tile0 = grp ? longer : 0;
-  const int ntiles = grp ? all_tiles - longer : longer;
-  const int L = Lall - kTileKeys * tile0;
-  const int n_nomask = (wave_pos_min + 1) / kTileKeys - tile0;   // tiles whose last key is within every row's horizon
-  const int mine = (Lall - n + min(wrow0 + kWaveRows, n) - 1) / kTileKeys + 1;     // tiles with a key within some row's
+  const int wave_pos_min = L - n + min(wrow0, n - 1);
+  const int wg_pos_max = L - n + min(row0 + p.rows_per_wg, n) - 1;
+  const int ntiles = wg_pos_max / kTileKeys + 1;
+  const int n_nomask = (wave_pos_min + 1) / kTileKeys;   // tiles whose last key is within every row's horizon
+  const int mine = (L - n + min(wrow0 + kWaveRows, n) - 1) / kTileKeys + 1;     // tiles with a key within some row's
 
-  const int* const bt = p.block_table + (size_t)seq * p.max_blocks + 4 * tile0;
+  const int* const bt = p.block_table + (size_t)seq * p.max_blocks;
   WaveCtx cx;
   cx.L = L;
   cx.last_blk = (L - 1) >> 4;
@@ -705,10 +691,6 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
     qsel_b = cload(p.query_sel, 2 * seq);
     qsel_e = min(cload(p.query_sel, 2 * seq + 1), qsel_b + p.NQ);
     load_spans_uniform(p.key_spans, seq, p.S, sp_a, sp_b);
-    if constexpr (SPLIT) {
-#pragma unroll
-      for (int s = 0; s < kMaxSpans; ++s) { sp_a[s] -= kTileKeys * tile0; sp_b[s] -= kTileKeys * tile0; }
-    }
   }
   const bool wave_probe = wave_active && pslot >= 0 && qsel_b < min(wrow0 + kWaveRows, n) && qsel_e > wrow0;
 
@@ -727,108 +709,44 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NI) : "memory");
   __syncthreads();
 
-  if (SPLIT && ntiles == 0) {      // a row block of one tile
-    m_run = -INFINITY;
-    l_run = 0.0f;
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) O[mb][r] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < kMaxSpans; ++s) am[s] = 0.0f;
-  } else if (wave_probe) {
+  if (wave_probe)
     run_tiles<D, KV8, SHARED, true>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
-  } else {
+  else
     run_tiles<D, KV8, SHARED, false>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
-  }
-  if (SPLIT && ntiles < longer) __syncthreads();
 
-  // epilogue: (split: merge,) normalise, transpose through LDS (16-byte chunks swizzled by row), coalesced stores
-  float l_tot = l_run + __shfl_xor(l_run, 32);
-  float inv_l = 1.0f / l_tot;
-  float inv = KV8 ? inv_l * p.v_scale[kvh] : inv_l;     // `out` carries the value scale, `mass` does not
+  // epilogue: normalise, transpose through LDS (16-byte chunks swizzled by row), coalesced stores
+  const float l_tot = l_run + __shfl_xor(l_run, 32);
+  const float inv_l = 1.0f / l_tot;
+  const float inv = KV8 ? inv_l * p.v_scale[kvh] : inv_l;     // `out` carries the value scale, `mass` does not
   wait_vmem();   // the clamped fetches of the last iterations must have landed before LDS is reused
   __syncthreads();
-  constexpr int OC = SPLIT ? C::CH / 2 : C::CH, RBO = 16 * OC, MBO = SPLIT ? C::MB / 2 : C::MB;   // chunks, row bytes, blocks stored
-  const int ch0 = SPLIT ? grp * OC : 0;
-  unsigned char* ot = smem + w * (kWaveRows * C::RB);
-  if constexpr (SPLIT) {
-    // per wave: the half of the output that the other group stores, then reference, normaliser and span sums by lane
-    constexpr int kHalf = MBO * 4 * 1024, kWaveArea = kHalf + (2 + kMaxSpans) * 256;
-    static_assert(4 * kWaveArea <= C::LDS, "the exchange fits the buffers");
-    unsigned char* const mine_x = smem + w * kWaveArea;
-    unsigned char* const other_x = smem0 + (1 - grp) * C::LDS + w * kWaveArea;
-#pragma unroll
-    for (int mb = 0; mb < MBO; ++mb)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        float4 v;
-        v.x = grp ? O[mb][4 * g4] : O[MBO + mb][4 * g4];
-        v.y = grp ? O[mb][4 * g4 + 1] : O[MBO + mb][4 * g4 + 1];
-        v.z = grp ? O[mb][4 * g4 + 2] : O[MBO + mb][4 * g4 + 2];
-        v.w = grp ? O[mb][4 * g4 + 3] : O[MBO + mb][4 * g4 + 3];
-        *reinterpret_cast<float4*>(mine_x + (4 * mb + g4) * 1024 + 16 * lane) = v;
-      }
-    float* const mine_s = reinterpret_cast<float*>(mine_x + kHalf) + lane;
-    mine_s[0] = m_run;
-    mine_s[64] = l_tot;
-    if (wave_probe) {
-#pragma unroll
-      for (int s = 0; s < kMaxSpans; ++s) mine_s[64 * (2 + s)] = am[s];
-    }
-    __syncthreads();
-    const float* const other_s = reinterpret_cast<const float*>(other_x + kHalf) + lane;
-    const float m_o = other_s[0], l_o = other_s[64], m_all = fmaxf(m_run, m_o);
-    // (a group without a key for a row counts for nothing there, whatever its values were)
-    const bool use_own = m_run != -INFINITY, use_other = m_o != -INFINITY;
-    const float w_own = use_own ? fast_exp2(m_run - m_all) : 0.0f, w_o = use_other ? fast_exp2(m_o - m_all) : 0.0f;
-    l_tot = l_tot * w_own + l_o * w_o;
-    if (wave_probe) {
-#pragma unroll
-      for (int s = 0; s < kMaxSpans; ++s) am[s] = am[s] * w_own + other_s[64 * (2 + s)] * w_o;
-    }
-#pragma unroll
-    for (int mb = 0; mb < MBO; ++mb)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const float4 x = *reinterpret_cast<const float4*>(other_x + (4 * mb + g4) * 1024 + 16 * lane);
-        const float xs[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float own = grp ? O[MBO + mb][4 * g4 + e] : O[mb][4 * g4 + e];
-          O[mb][4 * g4 + e] = (use_own ? own * w_own : 0.0f) + (use_other ? xs[e] * w_o : 0.0f);
-        }
-      }
-    ot = other_x;      // (nobody else reads it)
-    inv_l = 1.0f / l_tot;
-    inv = KV8 ? inv_l * p.v_scale[kvh] : inv_l;
-  }
+  unsigned char* const ot = smem + w * (kWaveRows * C::RB);
   if (wave_active) {
 #pragma unroll
-    for (int mb = 0; mb < MBO; ++mb)
+    for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
       for (int g4 = 0; g4 < 4; ++g4) {
         uint2 v;
         v.x = pack_bf16(O[mb][4 * g4] * inv, O[mb][4 * g4 + 1] * inv);
         v.y = pack_bf16(O[mb][4 * g4 + 2] * inv, O[mb][4 * g4 + 3] * inv);
         const int ch = 4 * mb + g4;
-        *reinterpret_cast<uint2*>(ot + qi * RBO + ((ch ^ out_swizzle<D, SPLIT>(qi)) << 4) + 8 * hf) = v;
+        *reinterpret_cast<uint2*>(ot + qi * C::RB + ((ch ^ k_swizzle<D>(qi)) << 4) + 8 * hf) = v;
       }
   }
   __syncthreads();
   if (wave_active) {
     __bf16* const og = static_cast<__bf16*>(p.out);
 #pragma unroll
-    for (int j = 0; j < OC / 2; ++j) {
-      const int rr = lane / OC + (64 / OC) * j;
-      const int ch = lane % OC;
+    for (int j = 0; j < C::CH / 2; ++j) {
+      const int rr = lane / C::CH + (64 / C::CH) * j;
+      const int ch = lane % C::CH;
       const int tr = wrow0 + rr;
       if (tr < n) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ot + rr * RBO + ((ch ^ out_swizzle<D, SPLIT>(rr)) << 4));
-        *reinterpret_cast<uint4*>(og + ((size_t)(qbase + tr) * p.Hq + head) * D + 8 * (ch0 + ch)) = v;
+        const uint4 v = *reinterpret_cast<const uint4*>(ot + rr * C::RB + ((ch ^ k_swizzle<D>(rr)) << 4));
+        *reinterpret_cast<uint4*>(og + ((size_t)(qbase + tr) * p.Hq + head) * D + 8 * ch) = v;
       }
     }
-    if (wave_probe && grp == 0) {
+    if (wave_probe) {
 #pragma unroll
       for (int s = 0; s < kMaxSpans; ++s) {
         if (s < p.S) {
@@ -841,7 +759,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
     }
   }
   if constexpr (ZERO_REST) {
-    if (row0 == 0 && rb == 0 && grp == 0 && pslot >= 0 && p.plan_fresh) {
+    if (row0 == 0 && rb == 0 && pslot >= 0 && p.plan_fresh) {
       const int lo = max(qsel_b, 0), hi = min(qsel_e, n);     // slots lo - qsel_b .. hi - qsel_b - 1 hold rows
       for (int e = lane; e < p.NQ * p.S; e += 64) {
         const int tr = qsel_b + e / p.S;
@@ -959,14 +877,13 @@ __device__ __forceinline__ bool find_item(const AttnParams& p, int item, int lan
 // What the planner does besides, by a workgroup of its own: the header with the status word, and zeros in the `mass`
 // entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those) and of elements
 // of the head list that no head owns.
-template <int NT>
 __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   int* const skip = sh + 2;     // [kScanMaxSeqs]
   const int tid = threadIdx.x;
   if (tid < 2) sh[tid] = 0;
   __syncthreads();
-  int bits = p.plan_fresh && bad_head_list<NT>(p) ? kBadHeadList : 0, blocks = 0;
-  for (int i = tid; i < p.num_seqs; i += NT) {
+  int bits = p.plan_fresh && bad_head_list<256>(p) ? kBadHeadList : 0, blocks = 0;
+  for (int i = tid; i < p.num_seqs; i += 256) {
     const ChunkSeq s = chunk_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
     bits |= s.bits;
     if (s.valid) blocks += (s.n + p.rows_per_wg - 1) / p.rows_per_wg;
@@ -979,16 +896,16 @@ __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   if (p.batch_kind == 1 && p.plan_fresh && p.P > 0)
     for (int i = 0; i < p.num_seqs; ++i)
       if (skip[i])
-        for (int e = tid; e < p.P * p.NQ * p.S; e += NT) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
-  if (sh[0] & kBadHeadList) zero_unowned_mass<NT>(p);
+        for (int e = tid; e < p.P * p.NQ * p.S; e += 256) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
+  if (sh[0] & kBadHeadList) zero_unowned_mass<256>(p);
 }
 
 // PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
 // of the grid settles the rest, and `mass` is written entry by entry by the waves that own the entries.
 // SHARED: several row blocks to a workgroup (groups of fewer than four heads).  An instantiation of its own, because the
 // spills that the fetch-only iterations bring cost a prompt of 2048 tokens at 32 / 8 heads 1.5 of its 49.5 us.
-template <int D, bool KV8, bool SHARED, bool PLANNED, bool SPLIT>
-__global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void k_prefill(const AttnParams p) {
+template <int D, bool KV8, bool SHARED, bool PLANNED>
+__global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int bid = blockIdx.x;
@@ -1005,37 +922,35 @@ __global__ __launch_bounds__(SPLIT ? 512 : 256, SPLIT ? 1 : 2) void k_prefill(co
     asm volatile("" :: "s"(it.x), "s"(it.y), "s"(it.z), "s"(it.w), "s"(qbase), "s"(nitems), "s"(p.block_table), "s"(p.q),
                  "s"(p.k_cache), "s"(p.v_cache));
     if (item >= nitems) return;
-    prefill_item<D, KV8, SHARED, false, SPLIT>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
+    prefill_item<D, KV8, SHARED, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
   } else {
     if (bid == (int)gridDim.x - 1) {
-      settle_chunks<SPLIT ? 512 : 256>(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
+      settle_chunks(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
       return;
     }
     ChunkItem it;
     const bool some = find_item(p, item, threadIdx.x & 63, it);
     asm volatile("" :: "s"(p.block_table), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache));
     if (!some) return;
-    prefill_item<D, KV8, SHARED, true, SPLIT>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
+    prefill_item<D, KV8, SHARED, true>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
   }
 }
 
-template <int D, bool KV8, bool SHARED, bool PLANNED, bool SPLIT>
+template <int D, bool KV8, bool SHARED, bool PLANNED>
 hipError_t launch_kernel(const AttnParams& p, long long grid, hipStream_t st) {
   static std::atomic<unsigned long long> configured{0};
-  constexpr int lds = Cfg<D, KV8>::LDS * (SPLIT ? 2 : 1);
-  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, SHARED, PLANNED, SPLIT>), lds, configured);
+  constexpr int lds = Cfg<D, KV8>::LDS;
+  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, SHARED, PLANNED>), lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_prefill<D, KV8, SHARED, PLANNED, SPLIT>), dim3((unsigned)grid), dim3(SPLIT ? 512 : 256), lds, st, p);
+  hipLaunchKernelGGL((k_prefill<D, KV8, SHARED, PLANNED>), dim3((unsigned)grid), dim3(256), lds, st, p);
   return hipGetLastError();
 }
 
 template <int D, bool KV8>
 hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
-  if (p.rows_per_wg != kWaveRows)
-    return p.pf_self ? launch_kernel<D, KV8, true, false, false>(p, grid, st) : launch_kernel<D, KV8, true, true, false>(p, grid, st);
-  if (p.pf_split)
-    return p.pf_self ? launch_kernel<D, KV8, false, false, true>(p, grid, st) : launch_kernel<D, KV8, false, true, true>(p, grid, st);
-  return p.pf_self ? launch_kernel<D, KV8, false, false, false>(p, grid, st) : launch_kernel<D, KV8, false, true, false>(p, grid, st);
+  if (p.rows_per_wg == kWaveRows)
+    return p.pf_self ? launch_kernel<D, KV8, false, false>(p, grid, st) : launch_kernel<D, KV8, false, true>(p, grid, st);
+  return p.pf_self ? launch_kernel<D, KV8, true, false>(p, grid, st) : launch_kernel<D, KV8, true, true>(p, grid, st);
 }
 
 }  // namespace

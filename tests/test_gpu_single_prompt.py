@@ -154,9 +154,9 @@ def test_several_prompts_find_their_row_blocks(nseq, lo, hi, rows, kind):
 
 @pytest.mark.parametrize("Hq,Hkv,d,kv8", [(8, 2, 128, False), (16, 2, 64, False), (4, 1, 128, True), (8, 2, 64, True)])
 def test_row_blocks_whose_keys_are_shared(Hq, Hkv, d, kv8):
-    """Few row blocks: two groups of waves take half of the key tiles each.  Lengths around the tile borders (one to five
-    tiles, halves of unequal length, a second half that some rows do not reach), spans across the middle, several
-    sequences of unlike depth in one call; against the oracle and the planned call."""
+    """Few row blocks, whose waves share the keys they fetch.  Lengths around the tile borders (one to five tiles, a last
+    tile that some rows do not reach), spans across the middle, several sequences of unlike depth in one call; against the
+    oracle and the planned call."""
     for lens, qlens in (([129], [129]), ([192], [2]), ([193], [193]), ([256], [33]), ([257], [257]), ([320, 40, 150], [320, 40, 31]),
                         ([1000, 65, 64], [40, 65, 64])):
         print(f"[case] shared keys Hq={Hq} d={d} kv8={kv8} L={lens} n={qlens}", flush=True)
@@ -169,3 +169,56 @@ def test_row_blocks_whose_keys_are_shared(Hq, Hkv, d, kv8):
         own, planned = _run(b, binding.BATCH_PREFILL_ONLY), planned_reference(b, batch_kind=binding.BATCH_PREFILL_ONLY)
         assert torch.equal(bits(own.out), bits(planned.out)) and torch.equal(bits(own.mass), bits(planned.mass))
         print("      ", compare_with_oracle(b, own.out, own.mass, label="shared"), flush=True)
+
+
+def _widened(b, factor):
+    """The same batch behind a block table `factor` times as wide."""
+    v = b.to("cpu")
+    v.block_table = torch.cat([v.block_table] + [torch.full_like(v.block_table, W.PAD_BLOCK_ID)] * (factor - 1), dim=1).contiguous()
+    v.max_blocks_per_seq *= factor
+    return v
+
+
+@pytest.mark.parametrize("lens,qlens,Hq,Hkv,d,kv8", [([1500], [1500], 32, 8, 128, False), ([1024], [1024], 32, 8, 128, False),
+                                                    ([700], [300], 32, 8, 64, False), ([1100], [1100], 32, 8, 128, True),
+                                                    ([512] * 4, [512] * 4, 16, 4, 128, False)])
+def test_results_depend_on_neither_the_table_width_nor_the_rest_of_the_batch(lens, qlens, Hq, Hkv, d, kv8):
+    """A row block's result is a matter of its rows and keys: bit for bit the same behind a wider block table and in a
+    batch with more sequences than it was alone."""
+    b = W.random_batch(1480 + lens[0], lens, qlens, Hq, Hkv, d, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=2)
+    for i, n in enumerate(qlens):
+        b.query_sel[i, 0], b.query_sel[i, 1] = n - 4, n
+    if kv8:
+        b = W.fp8_cache_variant(b, 1481)
+    ref = _run(b, binding.BATCH_PREFILL_ONLY)
+    print("      ", compare_with_oracle(b, ref.out, ref.mass, label="alone"), flush=True)
+    for factor in (2, 8):
+        got = _run(_widened(b, factor), binding.BATCH_PREFILL_ONLY)
+        assert torch.equal(bits(got.out), bits(ref.out)) and torch.equal(bits(got.mass), bits(ref.mass)), f"table x {factor}"
+    times = 4                                  # the same sequences several times over (their caches are only read)
+    v = b.to("cpu")
+    for name in ("seq_lens", "block_table", "query_sel", "key_spans", "q"):
+        t = getattr(v, name)
+        setattr(v, name, torch.cat([t] * times).contiguous())
+    n = v.cu_q_lens[1:] - v.cu_q_lens[:-1]
+    v.cu_q_lens = torch.cat([v.cu_q_lens[:1], torch.cumsum(torch.cat([n] * times), 0).to(torch.int32)])
+    v.num_seqs, v.total_q = times * b.num_seqs, times * b.total_q
+    got = _run(v, binding.BATCH_PREFILL_ONLY)
+    for k in range(times):
+        rows, seqs = slice(k * b.total_q, (k + 1) * b.total_q), slice(k * b.num_seqs, (k + 1) * b.num_seqs)
+        assert torch.equal(bits(got.out[rows]), bits(ref.out)) and torch.equal(bits(got.mass[seqs]), bits(ref.mass)), f"copy {k}"
+
+
+@pytest.mark.parametrize("d,kv8", [(128, False), (64, False), (128, True)])
+def test_spans_that_end_at_the_integers_limits(d, kv8):
+    """An end near the lowest integer makes an empty span, one near the largest reaches to the row's own key."""
+    lo, hi = -2**31, 2**31 - 1
+    for L, n in ((200, 200), (700, 40), (65, 2)):
+        b = W.random_batch(1490 + L, [L], [n], 8, 2, d, torch.bfloat16, num_probe_heads=3, max_sel_q=4, max_spans=4)
+        b.query_sel[0, 0], b.query_sel[0, 1] = max(0, n - 4), n
+        b.key_spans[0] = torch.tensor([(0, lo), (lo, hi), (lo, lo + 1), (40, hi)], dtype=torch.int32)
+        if kv8:
+            b = W.fp8_cache_variant(b, 1491)
+        got = _run(b, binding.BATCH_PREFILL_ONLY)
+        assert (got.mass[:, :, :, 0] == 0).all() and (got.mass[:, :, :, 2] == 0).all()
+        print("      ", compare_with_oracle(b, got.out, got.mass, label="limits"), flush=True)
