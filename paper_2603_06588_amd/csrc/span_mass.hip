@@ -311,7 +311,10 @@ constexpr int kMaxSplits = 16;    // key splits of pass 1
 // sum of exponentials carries a minus sign, and every span that begins in it gets its own walk over its keys in the
 // second kernel.  So does a span that ends behind its split in a sequence with a span of more than kOverhang keys (a mark, -1, in
 // `mass` says so): one such walk takes as long as many, and reading on would come on top.
-constexpr int kListSpans = 64;
+// The list holds as many spans as leave four workgroups to a compute unit their LDS: 4 keys each in 1024 keys, 16 each in the
+// 4096 keys that a split of a 64 k context has.  (64 spans: 654 documents of 5-20 keys in each of 4 prompts of 8200 tokens 106.8
+// us, 48.0 so; 1024 of 30-50 in 65536 76.7 and 57.3; all walked, without the list in the first kernel, 105.4 and 72.7.)
+constexpr int kListSpans = 256;
 constexpr int kOverhang = 512;
 
 // The kSplitBlocks row blocks of workgroup column `bx`.  A block without rows shadows the other one
@@ -340,15 +343,16 @@ __device__ __forceinline__ int split_tiles(int pos_max, int nsplit) { return (po
 // Pass 1, a workgroup per (sequence, probed head, 32 rows, split): the split's statistics - a reference near the
 // maximum and the sum of exponentials against it, per row - and, into `mass`, the sums of the spans that begin in it against
 // the same reference.  The waves take runs of tiles one behind the other, so a wave meets the spans in order and
-// keeps the sum of the one it is in, in registers; a finished span's sum goes to LDS, where the waves are merged.
+// keeps the sum of the one it is in, in registers; a finished span's sum goes to LDS, where the waves are merged.  Two waves
+// have at most one span in common, so slot k + w is written by no other wave than w.
 // 4 prompts of 7-16 k tokens, 8 heads, 32 rows, documents of 64-256 keys: 27 us and 8 for the second kernel (24 and 30 when the
 // second one read all documents again); 7 documents of 20-40 keys 9.1 + 3.6 (7.6 + 5.0).
 template <int D, bool KV8>
 __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams p) {
   __shared__ float sh_m[kStatWaves][kSplitRows];
   __shared__ float sh_l[kStatWaves][kSplitRows];
-  __shared__ float sh_part[kStatWaves][kListSpans][kSplitRows];
-  __shared__ int sh_list[kStatWaves][3][kListSpans];
+  __shared__ float sh_part[kListSpans + kStatWaves - 1][kSplitRows];     // wave w's sum of span k in slot k + w
+  __shared__ int sh_a[kListSpans], sh_e[kListSpans], sh_s[kListSpans];   // begin, end and number of the split's spans
   const int i = blockIdx.z / p.nsplit, sp = blockIdx.z % p.nsplit, ps = blockIdx.y;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -370,7 +374,7 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
   const int ntile = pos_max / 16 + 1, per = split_tiles(pos_max, p.nsplit);
   const int lo = 16 * per * sp, hi = min(16 * per * (sp + 1), 16 * ntile);
 
-  // The spans that begin in this split, found by every wave for itself; lane k keeps the k-th.
+  // The spans that begin in this split: every wave counts them, the first one writes the list.
   int count = 0;
   bool any_long = false;
   for (int s0 = 0; s0 < p.S && count <= kListSpans; s0 += 64 * kSpanLoads) {
@@ -382,10 +386,10 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
       const unsigned long long hit = __builtin_amdgcn_ballot_w64(s < p.S && e > a && a >= lo && a < hi);
       any_long = any_long || __builtin_amdgcn_ballot_w64(s < p.S && e - a > kOverhang) != 0;
       const int at = count + __builtin_amdgcn_mbcnt_hi((unsigned)(hit >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)hit, 0));
-      if (((hit >> lane) & 1) && at < kListSpans) {
-        sh_list[wave][0][at] = a;
-        sh_list[wave][1][at] = e;
-        sh_list[wave][2][at] = s;
+      if (wave == 0 && ((hit >> lane) & 1) && at < kListSpans) {
+        sh_a[at] = a;
+        sh_e[at] = e;
+        sh_s[at] = s;
       }
       count += __builtin_popcountll(hit);
     }
@@ -394,24 +398,38 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
       for (int u = 0; u < kSpanLoads; ++u) coming[u] = spans[min(s0 + 64 * (kSpanLoads + u) + lane, p.S - 1)];
     }
   }
-  const int span_a = sh_list[wave][0][lane], span_e = sh_list[wave][1][lane];      // (lane < count)
-  const bool listed = count <= kListSpans &&
-                      __builtin_amdgcn_ballot_w64(lane > 0 && lane < count && span_a < sh_list[wave][1][max(lane - 1, 0)]) == 0;
+  __syncthreads();
+  // lane i holds span 64 * window + i; most lists fit one window
+  int window = 0, span_a = sh_a[lane], span_e = sh_e[lane];
+  bool listed = count <= kListSpans &&
+                __builtin_amdgcn_ballot_w64(lane > 0 && lane < count && span_a < sh_e[max(lane - 1, 0)]) == 0;
+  for (int k0 = 64; k0 < count && listed; k0 += 64)
+    listed = __builtin_amdgcn_ballot_w64(k0 + lane < count && sh_a[k0 + lane] < sh_e[k0 + lane - 1]) == 0;
   int summed = listed ? count : 0, stop = hi;      // stop: end of the keys to read
   if (summed > 0) {
-    const int last_e = __builtin_amdgcn_readlane(span_e, summed - 1);
+    const int last_e = __builtin_amdgcn_readfirstlane(sh_e[summed - 1]);
     if (any_long && last_e > hi) --summed;
     else stop = max(hi, last_e);
   }
-  for (int e = lane; e < summed * kSplitRows; e += 64) sh_part[wave][e / kSplitRows][e % kSplitRows] = 0.0f;
 
   // this wave's run of tiles, and its first span
   const int run = ((stop - lo + 15) / 16 + kStatWaves - 1) / kStatWaves;
   const int w_lo = lo + 16 * run * wave, w_hi = min(w_lo + 16 * run, stop);
-  const unsigned long long ahead = __builtin_amdgcn_ballot_w64(lane < summed && span_e > w_lo);
-  int k = ahead ? __builtin_ctzll(ahead) : summed;
+  int k = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane < summed && span_e <= w_lo));
+  for (int k0 = 64; k0 < summed; k0 += 64)
+    k += __builtin_popcountll(__builtin_amdgcn_ballot_w64(k0 + lane < summed && sh_e[k0 + lane] <= w_lo));
   const int k_first = k;
-  int sa = __builtin_amdgcn_readlane(span_a, k & 63), se = __builtin_amdgcn_readlane(span_e, k & 63);
+  int sa, se;
+  auto find_span = [&]() {                         // (what it finds behind the last span is not used)
+    if (k >> 6 != window) {
+      window = k >> 6;
+      span_a = sh_a[min(64 * window + lane, kListSpans - 1)];
+      span_e = sh_e[min(64 * window + lane, kListSpans - 1)];
+    }
+    sa = __builtin_amdgcn_readlane(span_a, k & 63);
+    se = __builtin_amdgcn_readlane(span_e, k & 63);
+  };
+  find_span();
 
   float m[kSplitBlocks], l[kSplitBlocks], acc[kSplitBlocks];      // m: one reference for the four lanes of a row
 #pragma unroll
@@ -420,7 +438,7 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
 #pragma unroll
     for (int nb = 0; nb < kSplitBlocks; ++nb) {
       const float v = row_sum(acc[nb]);
-      if (quarter == 0) sh_part[wave][k][kSmRows * nb + j] = v;
+      if (quarter == 0) sh_part[k + wave][kSmRows * nb + j] = v;
       acc[nb] = 0.0f;
     }
   };
@@ -443,7 +461,7 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
         l[nb] *= alpha;
         acc[nb] *= alpha;
         if (quarter == 0)
-          for (int kk = k_first; kk < k; ++kk) sh_part[wave][kk][kSmRows * nb + j] *= alpha;
+          for (int kk = k_first; kk < k; ++kk) sh_part[kk + wave][kSmRows * nb + j] *= alpha;
         m[nb] = mn;
       }
       const float ref = m[nb] == -INFINITY ? 0.0f : m[nb];
@@ -471,11 +489,10 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
       if (se > key0 + 16) break;
       flush();
       ++k;
-      sa = __builtin_amdgcn_readlane(span_a, k & 63);
-      se = __builtin_amdgcn_readlane(span_e, k & 63);
+      find_span();
     }
   });
-  if (k < summed) flush();                         // the span that the next wave goes on with
+  if (k < summed && sa < w_hi) flush();            // the span that the next wave goes on with
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) {
     l[nb] = row_sum(l[nb]);
@@ -498,12 +515,14 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
   if (slot >= p.NQ) return;
   float* const mass = p.mass + (((size_t)i * p.P + ps) * p.NQ + slot) * p.S;
   for (int kk = threadIdx.x / kSplitRows; kk < summed; kk += kSpanStep) {
+    const int a = sh_a[kk], e = sh_e[kk];
     float v = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kStatWaves; ++w) v += sh_part[w][kk][row] * wgt[w];
-    mass[sh_list[0][2][kk]] = v;
+    for (int w = 0; w < kStatWaves; ++w)           // the waves whose runs the span meets
+      v += a < lo + 16 * run * (w + 1) && e > lo + 16 * run * w ? sh_part[kk + w][row] * wgt[w] : 0.0f;
+    mass[sh_s[kk]] = v;
   }
-  if (listed && summed < count && threadIdx.x < kSplitRows) mass[sh_list[0][2][summed]] = -1.0f;
+  if (listed && summed < count && threadIdx.x < kSplitRows) mass[sh_s[summed]] = -1.0f;
 }
 
 // The second kernel: from the splits' references to the row's, divided by its normaliser; zeros where there is no row or

@@ -169,6 +169,10 @@ def _layouts(L):
     yield "empty ones between", [(a, a + n) for a in range(40, L, 90) for n in (0, 60, -3)]
     yield "64 in a split", [(8 + 12 * k, 8 + 12 * k + 11) for k in range(64)]
     yield "65 in a split", [(8 + 12 * k, 8 + 12 * k + 11) for k in range(65)]
+    yield "128 in a split", [(4 * k, 4 * k + 3) for k in range(128)]
+    yield "129 in a split", [(4 * k, 4 * k + 4) for k in range(129)]
+    yield "256 in a split", [(2 * k, 2 * k + 2) for k in range(256)]
+    yield "257 in a split", [(2 * k, 2 * k + 2) for k in range(257)]
     yield "single keys", [(k, k + 1) for k in range(L - 60, L)]
     yield "across a split, 512 keys at most", [(900, 1412), (1412, 1413), (1900, 2400)]
     yield "across a split, 513 keys", [(900, 1413), (1413, 1500), (1900, 2400)]
@@ -195,3 +199,29 @@ def test_span_layouts(d, kv8):
         b.max_spans = S
         b.key_spans = torch.tensor([x[name] + [(0, 0)] * (S - len(x[name])) for x in lists], dtype=torch.int32)
         _check(b)
+
+
+def _relative_error(b, workspace=None):
+    """Largest relative error over the masses of selected rows, of the form that is split over the chip."""
+    from paper_2603_06588_amd import binding
+    _, want = oracle.attn_probe_batch(b, rows=_selected_rows(b))
+    got = binding.hook_span_mass_batch(b.to(DEV), workspace=workspace).cpu().double()
+    some = want > 1e-30
+    assert some.any() and bool((got[~some].abs() <= 1e-30).all())
+    return ((got - want).abs()[some] / want[some]).max().item()
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("count", [64, 65, 192, 193, 255, 256, 257])
+def test_spans_of_a_split_up_to_the_lists_length(d, count):
+    """Short spans by relative error (scores of unit spread: their fp32 sums are off by at most (d + 3) 2^-24 sum |q k| / sqrt(d),
+    about 6e-5, in a span and in the normaliser).  Up to 256 spans of a split are summed with the statistics, more are walked:
+    the split's sum of exponentials then carries a minus sign."""
+    L, n = 2048, 40
+    b = W.random_batch(540 + d + count, [L], [n], 8, 2, d, torch.bfloat16, std=1.0, num_probe_heads=2, max_sel_q=n, max_spans=count + 2)
+    b.query_sel[0, 0], b.query_sel[0, 1] = 0, n
+    b.key_spans[0] = torch.tensor([(3 * k + k // 3 % 2, 3 * k + 3) for k in range(count)] + [(1100, 1180), (1180, 1500)], dtype=torch.int32)
+    stats = torch.zeros(2 * 48 * 2 * 2, dtype=torch.float32, device=DEV)          # heads, row slots, splits, (reference, sum)
+    assert _relative_error(b, stats.view(torch.uint8)) <= 5e-4
+    sums = stats.view(2, 48, 2, 2)[:, :n, :, 1]
+    assert bool((torch.signbit(sums[:, :, 0]) == (count > 256)).all()) and bool((sums[:, :, 1] > 0).all())
