@@ -225,3 +225,28 @@ def test_spans_of_a_split_up_to_the_lists_length(d, count):
     assert _relative_error(b, stats.view(torch.uint8)) <= 5e-4
     sums = stats.view(2, 48, 2, 2)[:, :n, :, 1]
     assert bool((torch.signbit(sums[:, :, 0]) == (count > 256)).all()) and bool((sums[:, :, 1] > 0).all())
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_scores_that_rise_along_the_context(d):
+    """Scores rise in steps of 12 powers of two every 40 keys, four at a time, and by 6 from one 832-key split to the next, so
+    a wave raises its reference with finished spans behind it, inside an open one and before its first, and waves and
+    splits have references far apart.  Relative error: fp32 sums of scores of up to 70 powers of two are off by (d + 3) 2^-24 * 76
+    ln 2, 4e-4, in a span and in the normaliser alike."""
+    L, n = 4100, 40
+    layouts = {"short": [(a, a + 25) for a in range(5, L, 33)], "abutting": [(a, min(a + 40, L)) for a in range(0, L, 40)],
+               "long": [(10, 400), (400, 900), (950, 1300), (1640, 1700), (1700, 2100), (3300, 3310), (3310, L)],
+               "walked": [(a, a + 100) for a in range(0, L, 70)]}
+    b = W.random_batch(550 + d, [L], [n], 8, 2, d, torch.bfloat16, std=1.0, num_probe_heads=3, max_sel_q=n, max_spans=2)
+    b.query_sel[0, 0], b.query_sel[0, 1] = 0, n
+    pos = torch.arange(L)
+    level = 12.0 * (pos // 40 % 4) + 6.0 * (pos // 832)
+    b.q[:, :, 0] = 1.0
+    b.q[:, :, 1:] *= 0.5
+    b.k_cache[b.block_table[0, pos // 16].long(), :, pos % 16, 0] = (level * d ** 0.5 / 1.4427).to(torch.bfloat16)[:, None]
+    for name, spans in layouts.items():
+        b.max_spans = len(spans)
+        b.key_spans = torch.tensor([spans], dtype=torch.int32)
+        err = _relative_error(b)
+        print("[case]", name, err, flush=True)
+        assert err <= 1e-3, name
