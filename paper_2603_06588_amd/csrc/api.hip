@@ -41,7 +41,8 @@ bool shapes_supported(const hook_attn_probe_args* a) {
 // sequence's item count, so whenever the next larger size was refused (fewer than kDecodeFillWgs
 // workgroups, i.e. at most (kDecodeFillWgs - 1) / wg_per_item items) the chosen size yields at most
 // twice that; and the largest size yields at most one item per kMaxChunkKeys keys of the longest
-// context the block table allows.  (The 256-key tiling of every context is a bound as well.)
+// context the block table allows.  (The 256-key tiling of every context is a bound as well.)  Where the planner halves
+// its choice further, for a few long contexts among short ones, it stops at this bound, which it is given as dec_cap.
 int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_per_item) {
   const long long refused = 2 * ((kDecodeFillWgs - 1) / wg_per_item);
   const long long largest = num_decode_seqs * ((max_context + kMaxChunkKeys - 1) / kMaxChunkKeys);

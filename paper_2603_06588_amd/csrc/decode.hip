@@ -660,13 +660,14 @@ __device__ __forceinline__ void settle_batch(const AttnParams& p) {
 // Merges the partial records of a sequence: WPH waves per q head take its records in turn (a workgroup is
 // max(4, WPH) waves), lane = output columns.  In a self-planned batch the wave that owns a probed head also
 // zero-fills the `mass` slots without a row.  Every first touch of a record is a trip to memory (other
-// workgroups wrote them under other L2s), and trips are all this kernel's time, so a wave requests
-// kInFlight whole records before it waits for any: as long as a sequence has at most WPH * kInFlight records
-// there are two trips, the record count and the records.
+// workgroups wrote them under other L2s), and trips are all this kernel's time, so a wave requests several
+// whole records before it waits for any: 8 where several waves share a head, and where one wave has a head to itself 4,
+// or 16 for a sequence with more than that (one context of 32768 tokens, 64 records, among 199 of 300, by fours 12.0 us in
+// a kernel trace and the call 89.0 us, 85.7 so; over an 8-bit cache 60.9 and 57.4; contexts of up to 200 tokens alike).
 template <int D, int WPH>
 __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const AttnParams p) {
   using C = DecodeCfg<D>;
-  constexpr int kInFlight = WPH == 1 ? 4 : 8, E = D / 64, NWV = WPH > 4 ? WPH : 4;
+  constexpr int E = D / 64, NWV = WPH > 4 ? WPH : 4;
   __shared__ float sh_o[WPH > 1 ? NWV : 1][D + kMaxSpans];
   __shared__ float sh_m[NWV], sh_l[NWV];
   const int seq = blockIdx.x;
@@ -717,35 +718,41 @@ __global__ __launch_bounds__(64 * (WPH > 4 ? WPH : 4)) void k_combine(const Attn
   if (live) {
     const size_t rstride = (size_t)p.Hq * C::PSTR;
     const float* rec0 = p.partials + ((size_t)sd.x * p.Hq + head) * C::PSTR;
-    for (int c = part; c < count; c += kInFlight * WPH) {
-      float v[kInFlight][E], sp[kInFlight], rm[kInFlight], rl[kInFlight];
+    auto merge = [&](auto in_flight) {
+      constexpr int kInFlight = decltype(in_flight)::value;
+      for (int c = part; c < count; c += kInFlight * WPH) {
+        float v[kInFlight][E], sp[kInFlight], rm[kInFlight], rl[kInFlight];
 #pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {
-        const float* r = rec0 + (size_t)min(c + u * WPH, count - 1) * rstride;
+        for (int u = 0; u < kInFlight; ++u) {
+          const float* r = rec0 + (size_t)min(c + u * WPH, count - 1) * rstride;
 #pragma unroll
-        for (int e = 0; e < E; ++e) v[u][e] = r[E * lane + e];
-        sp[u] = (lane < kMaxSpans) ? r[D + 2 + lane] : 0.0f;
-        rm[u] = c + u * WPH < count ? r[D] : -INFINITY;
-        rl[u] = r[D + 1];
+          for (int e = 0; e < E; ++e) v[u][e] = r[E * lane + e];
+          sp[u] = (lane < kMaxSpans) ? r[D + 2 + lane] : 0.0f;
+          rm[u] = c + u * WPH < count ? r[D] : -INFINITY;
+          rl[u] = r[D + 1];
+        }
+        float mn = m;
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) mn = fmaxf(mn, rm[u]);
+        const float keep = fast_exp2(m - mn);        // mn is finite: record c exists
+        m = mn;
+        l *= keep;
+        a *= keep;
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[e] *= keep;
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+          const float wg = fast_exp2(rm[u] - mn);
+          l = __builtin_fmaf(wg, rl[u], l);
+          a = __builtin_fmaf(wg, sp[u], a);
+#pragma unroll
+          for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(wg, v[u][e], o[e]);
+        }
       }
-      float mn = m;
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) mn = fmaxf(mn, rm[u]);
-      const float keep = fast_exp2(m - mn);        // mn is finite: record c exists
-      m = mn;
-      l *= keep;
-      a *= keep;
-#pragma unroll
-      for (int e = 0; e < E; ++e) o[e] *= keep;
-#pragma unroll
-      for (int u = 0; u < kInFlight; ++u) {
-        const float wg = fast_exp2(rm[u] - mn);
-        l = __builtin_fmaf(wg, rl[u], l);
-        a = __builtin_fmaf(wg, sp[u], a);
-#pragma unroll
-        for (int e = 0; e < E; ++e) o[e] = __builtin_fmaf(wg, v[u][e], o[e]);
-      }
-    }
+    };
+    if constexpr (WPH > 1) merge(std::integral_constant<int, 8>{});
+    else if (count <= 4) merge(std::integral_constant<int, 4>{});
+    else merge(std::integral_constant<int, 16>{});
   }
   if constexpr (WPH > 1) {
     if (lane == 0) { sh_m[wave] = m; sh_l[wave] = l; }
@@ -832,8 +839,9 @@ hipError_t launch_decode(const AttnParams& p, int D, hipStream_t st) {
 
 hipError_t launch_combine(const AttnParams& p, int D, hipStream_t st) {
   if (p.dec_cap <= 0 || p.num_seqs <= 0) return hipSuccess;
-  // as many waves per head as let a sequence's records be fetched in one go: the planner's chunks are long, so
-  // its sequences have few records; a self-planned sequence has about ranges / num_seqs + 2
+  // as many waves per head as let most sequences' records be fetched in one go: a planned batch has many sequences, and
+  // the few that are much longer than the rest have no more waves for their many records; a self-planned sequence has
+  // about ranges / num_seqs + 2
   const int per_seq = p.dec_ranges > 0 ? p.dec_ranges / p.num_seqs + 2 : 1;
   const int wph = per_seq > 32 ? 16 : per_seq > 4 ? 4 : 1;
   const int settles = p.dec_ranges > 0 && p.batch_kind == 2 ? 1 : 0;

@@ -23,7 +23,8 @@ constexpr int kPartialPad = 16;     // floats after the D output values of a dec
 constexpr int kPlanBuckets = 2048;  // counting-sort buckets (tile counts) of the prefill work list
 // Decode chunking rule shared by the planner (which applies it) and the host (which bounds the
 // number of items it can produce): the largest chunk of 512 << k keys, up to kMaxChunkKeys, that
-// still yields kDecodeFillWgs decode workgroups; 256 keys when none does.
+// still yields kDecodeFillWgs decode workgroups; 256 keys when none does.  The planner halves it while it is longer than a
+// workgroup's share of the batch and the items still fit the host's bound (plan.hip).
 constexpr int kChunkSizes = 5;
 constexpr int kMaxChunkKeys = 512 << (kChunkSizes - 1);
 constexpr int kDecodeFillWgs = 2048;

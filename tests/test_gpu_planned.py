@@ -115,3 +115,22 @@ def test_one_long_context_among_many_short_ones(kv8):
     torch.cuda.synchronize()
     assert plan_header(call) == [0, 299 + 16000 // 1024 + 1, 1024, 0]      # 331 pieces of 512 keys * 8 / 768 = 1765 keys
     print("      ", compare_with_oracle(b, call.out, call.mass, label="one long"), flush=True)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,kv8", [(8, 2, 128, False), (16, 2, 64, True), (3, 1, 128, False)])
+def test_planned_sequences_of_few_and_many_records(Hq, Hkv, d, kv8):
+    """The merge gives a head one wave, which takes four records at a time, or sixteen where a sequence has more than four:
+    record counts on both sides of those steps, the last record of one key, of one block and whole."""
+    counts = [1, 2, 3, 4, 5, 8, 15, 16, 17, 20, 31, 32, 33, 48, 49]
+    lens = [256 * (c - 1) + (1, 16, 256)[k % 3] for k, c in enumerate(counts)] + [1 + i % 9 for i in range(185)]
+    b = W.random_batch(2740 + Hq, lens, [1] * len(lens), Hq, Hkv, d, torch.bfloat16, num_probe_heads=2, max_sel_q=1, max_spans=2)
+    if kv8:
+        b = W.fp8_cache_variant(b, 2741)
+    call = binding.call_from_batch(b.to(DEV), batch_kind=binding.BATCH_DECODE_ONLY)
+    call.workspace.fill_(0xFF)
+    call.out.fill_(float("nan"))
+    call.mass.fill_(float("nan"))
+    call.launch()
+    torch.cuda.synchronize()
+    assert plan_header(call) == [0, sum(counts) + 185, 256, 0]
+    print("      ", compare_with_oracle(b, call.out, call.mass, label="records"), flush=True)
