@@ -51,11 +51,12 @@ def test_fp32_rows_before_a_value_that_is_not_finite(d, at, what):
     assert torch.equal(bits(_run(bad).out[:at]), bits(clean.out[:at]))
 
 
-@pytest.mark.parametrize("G,d,kv8", [(1, 64, False), (2, 64, False), (3, 64, True), (1, 128, False), (2, 128, True), (1, 128, True), (4, 128, False)])
+@pytest.mark.parametrize("G,d,kv8", [(1, 64, False), (2, 64, False), (3, 64, True), (1, 128, False), (2, 128, True), (1, 128, True), (4, 128, False),
+                                      (4, 64, False), (4, 128, True), (4, 64, True), (8, 128, False)])
 @pytest.mark.parametrize("at", [70, 200])
 def test_row_blocks_before_a_tile_whose_value_is_not_finite(G, d, kv8, at):
     """Row blocks that share a workgroup (groups of fewer than four heads) walk its tiles together, but a block of 32
-    rows never multiplies a tile of 64 keys behind its last row."""
+    rows never multiplies a tile of 64 keys behind its last row; nor does one that has a workgroup of its own (4 and 8 heads)."""
     b = W.random_batch(3200 + d, [300, 140], [300, 140], 2 * G, 2, d, torch.bfloat16, num_probe_heads=2, max_sel_q=300, max_spans=2)
     b.query_sel[:, 0], b.query_sel[:, 1] = 0, 300
     if kv8:

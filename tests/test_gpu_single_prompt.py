@@ -154,7 +154,7 @@ def test_several_prompts_find_their_row_blocks(nseq, lo, hi, rows, kind):
 
 @pytest.mark.parametrize("Hq,Hkv,d,kv8", [(8, 2, 128, False), (16, 2, 64, False), (4, 1, 128, True), (8, 2, 64, True)])
 def test_row_blocks_whose_keys_are_shared(Hq, Hkv, d, kv8):
-    """Few row blocks, whose waves share the keys they fetch.  Lengths around the tile borders (one to five tiles, a last
+    """Few row blocks, whose four waves share the keys they fetch.  Lengths around the tile borders (one to five tiles, a last
     tile that some rows do not reach), spans across the middle, several sequences of unlike depth in one call; against the
     oracle and the planned call."""
     for lens, qlens in (([129], [129]), ([192], [2]), ([193], [193]), ([256], [33]), ([257], [257]), ([320, 40, 150], [320, 40, 31]),

@@ -1,18 +1,19 @@
 """Self-planned batches of single rows: all contexts laid end to end and cut into equal ranges of cache blocks.
 Sizes where that can go wrong - more sequences than lanes, the largest batch that plans itself and the first
-that does not, ranges that hold many short sequences, empty sequences between them - and the new rows that the
+that does not (beyond it the planner's items), ranges that hold many short sequences, empty sequences between them - and the new rows that the
 same kernel stores into the cache on its way (needs an MI355X)."""
 import pytest
 import torch
 
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import bits, compare_with_oracle
+from helpers import bits, compare_with_oracle, plan_header
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("nseq,hi,Hq,Hkv,d", [(64, 300, 8, 2, 128), (65, 300, 8, 2, 128), (512, 90, 8, 2, 64), (513, 90, 8, 2, 64),
+                                              (192, 90, 8, 2, 64), (193, 90, 8, 2, 64), (192, 90, 8, 2, 128), (193, 90, 8, 2, 128),
                                               (200, 40, 32, 8, 128), (3, 5000, 16, 2, 128),
                                               (14, 500, 32, 8, 128), (4, 131, 64, 8, 128), (95, 200, 32, 8, 128)])
 def test_ranges_over_many_sequences(nseq, hi, Hq, Hkv, d):
@@ -30,6 +31,8 @@ def test_ranges_over_many_sequences(nseq, hi, Hq, Hkv, d):
     call.launch()
     torch.cuda.synchronize()
     assert call.device_status() == 0
+    items, keys = plan_header(call)[1:3]
+    assert (items > 0) == (keys > 0) == (nseq > 192)
     print(compare_with_oracle(b, out, mass, label="stream"), flush=True)
 
 
@@ -92,12 +95,14 @@ def test_new_row_in_a_range_of_256_blocks():
 
 
 @pytest.mark.parametrize("nseq,kv8,d,Hq,Hkv", [(3, False, 128, 32, 8), (40, False, 128, 32, 2), (64, True, 128, 32, 8), (17, False, 64, 8, 2),
-                                               (20, True, 64, 16, 4), (65, False, 128, 32, 8)])
+                                               (20, True, 64, 16, 4), (65, False, 128, 32, 8), (32, False, 128, 32, 8), (33, False, 128, 32, 8),
+                                               (64, False, 128, 32, 8), (64, False, 128, 4, 2)])
 @pytest.mark.parametrize("chunk", [False, True])
 def test_new_rows_are_read_by_the_other_sequences_of_the_call(nseq, kv8, d, Hq, Hkv, chunk):
     """Rows of one context at consecutive positions: each reads the rows that those in front of it bring, as if all had
     been written before the call.  (One context also meets the block again further in front; with `chunk` one sequence
-    contradicts the hint, whose rows are written and read all the same.)"""
+    contradicts the hint, whose rows are written and read all the same.)  Up to 32 sequences, over an 8-bit cache, at head size
+    64 and for groups of 8 heads key rows are fetched by whole lines, otherwise by half lines."""
     print(f"[case] shared context nseq={nseq} kv8={kv8} d={d} Hq={Hq} Hkv={Hkv} chunk={chunk}", flush=True)
     lens, qlens = [300 + i for i in range(nseq)], [1] * nseq
     if chunk:

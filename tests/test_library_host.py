@@ -162,7 +162,7 @@ def test_workspace_of_a_larger_batch_serves_the_smaller_ones(binding, hq, hkv, d
         binding, num_seqs=n, total_q=q, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, max_blocks_per_seq=b, num_blocks=n * b)))
     seqs = [size(n, n, blocks) for n in range(1, 1400)]
     assert all(x <= y for x, y in zip(seqs, seqs[1:])) and seqs[0] > 0
-    for n in (1, 7, 300, 512, 513, 900):
+    for n in (1, 7, 192, 193, 300, 512, 513, 900):
         rows = [size(n, q, blocks) for q in range(1, 4 * n + 200, 3)]
         assert all(x <= y for x, y in zip(rows, rows[1:]))
         ctx = [size(n, n, b) for b in range(1, 3000, 7)]
