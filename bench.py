@@ -27,10 +27,10 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 # until the counters are taken again.
 TRAFFIC = {
     # key: (bytes per launch, source files, hash of those files when the counters were taken)
-    "k_prefill/c2": (830775588, ("prefill.hip", "hook_device.h"), "388db5ff38558d4c"),
-    "k_prefill/c4": (5261048560, ("prefill.hip", "hook_device.h"), "388db5ff38558d4c"),
-    "k_decode/c3": (4890974618, ("decode.hip", "hook_device.h"), "fe43ed32bed05fc0"),
-    "k_decode/c3_fp8": (2436535043, ("decode.hip", "hook_device.h"), "fe43ed32bed05fc0"),
+    "k_prefill/c2": (826898527, ("prefill.hip", "hook_device.h"), "0448991fb14f47c9"),
+    "k_prefill/c4": (5255704022, ("prefill.hip", "hook_device.h"), "0448991fb14f47c9"),
+    "k_decode/c3": (4890551339, ("decode.hip", "hook_device.h"), "7f8e2b0b77bcb09e"),
+    "k_decode/c3_fp8": (2436600339, ("decode.hip", "hook_device.h"), "7f8e2b0b77bcb09e"),
 }
 
 

@@ -424,7 +424,7 @@ hook_status hook_kv_write(const hook_kv_write_args* args);
  *     8-bit (kv_dtype, k_scale; v_scale is not read),
  * Without scratch two passes over the keys of each (sequence, probed head, 16-row block): exact softmax
  * maximum and normaliser first, then the span sums.  With it one pass that sums disjoint spans in
- * increasing order on the way; others are walked once more.  No atomics.
+ * increasing order on the way (up to 256 that begin in one split of the keys); others are walked once more.  No atomics.
  * A content-free calibration prompt is a second call; hook_reduce_mass with negated weights
  * subtracts it.
  */

@@ -66,8 +66,8 @@ struct NewRows {
   bool store;
 };
 // WHOLE_LINES: how K rows of 128 bytes and more are fetched (below).  The one kind of batch that is better off without is
-// large and of 256-byte rows for up to four heads: 8 rows 26.9 -> 25.5 us, 24 49.8 -> 49.1, but 64 of 1000-8000 tokens
-// 190 -> 192 and 200 of 1000-4000 (planned) 331 -> 337.
+// large and of 256-byte rows for up to four heads: 8 rows 26.4 -> 24.9 us (on caches not seen before 27.8 -> 27.0), 24
+// 49.6 -> 48.9, but 64 of 1000-8000 tokens 190 -> 192 and 200 of 1000-4000 (planned) 331 -> 337.
 constexpr int kLineSeqs = 32;
 template <int D, int HP, bool KV8>
 constexpr bool lines_always() { return HP == 8 || KV8 || D == 64; }
@@ -95,7 +95,7 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
   // 0 .. 7 and the odd ones in 8 .. 15, so Q comes as two sets of columns, 0 .. 7 against the even pieces of a line and
   // 8 .. 15 against the odd ones, and a score is the sum of two accumulator entries (compute_block).  Otherwise operand
   // rows are key rows, and a load takes 64 bytes, half a line, of each of 16 rows.  Whole lines are 2-6 % faster (8 x 2500-4096
-  // tokens 26.9 -> 25.5 us, 8-bit 20.5 -> 19.6, 256 x 1000-8192 of 8-bit 431 -> 425, 128 x 1000-4000 at d 64 121 -> 119) but
+  // tokens 26.4 -> 24.9 us, 8-bit 20.0 -> 19.3, 256 x 1000-8192 of 8-bit 431 -> 425, 128 x 1000-4000 at d 64 121 -> 119) but
   // for large streams of 256-byte rows and up to four heads (kLineSeqs), where 1 KB in one piece (4 rows, four classes of
   // pieces) is slower still (64 x 1000-8000 190 -> 194).
   constexpr int ROWB = D * ESZ;
@@ -273,7 +273,9 @@ __device__ __forceinline__ void decode_range(const AttnParams& p, float (&red)[4
     }
     // lane (j, kq): tt[r] = score of head j with key key0 + 4 kq + r.  LINES: entry (row i, column n) of a half holds the
     // even pieces of row i where i < 8 and n < 8 and the odd ones of row i - 8 where both are 8 or more; one swap of lane
-    // halves brings the rows of both halves into place, and the odd pieces come from eight columns on.
+    // halves brings the rows of both halves into place, and the odd pieces come from eight columns on.  (Lanes j >= 8 are left with
+    // products of unlike pieces, for which no head asks.  They keep references of their own; one that rises sends the
+    // wave through the raise below, where lanes that do not rise multiply by 1.)
     float tt[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {

@@ -173,9 +173,10 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const AttnParams p) {
 #pragma unroll
   for (int k = 0; k < kChunkSizes; ++k)
     if ((long long)sh_cnt[k] * wg_per_item >= kDecodeFillWgs) chunk = 512 << k;
-  // Few long contexts among many short ones: an item of several times a workgroup's share (all contexts in pieces of 512 keys
-  // over 768 resident workgroups) would outlast the rest.  As far as the records reach (1 x 32768 + 400 x 300 tokens
-  // 224 us with 8192 keys per item, 132 so); batches beyond kScanMaxSeqs have short items by their number.
+  // Few long contexts among many short ones: an item of several times a workgroup's share (all contexts in pieces of 512
+  // keys over 768 workgroups, what head size 128 over a 16-bit cache holds at once; others hold 512 to 1024) would outlast
+  // the rest.  As far as the records reach (1 x 32768 + 400 x 300 tokens 224 us with 8192 keys per item, 132 so); batches
+  // beyond kScanMaxSeqs have short items by their number.
   if (p.num_seqs <= kScanMaxSeqs) {
     const long long share = (long long)sh_cnt[0] * 512 * wg_per_item / 768;
 #pragma unroll
