@@ -81,7 +81,7 @@ typedef enum { HOOK_KV_SAME = 0, HOOK_KV_FP8_E4M3 = 1 } hook_kv_dtype;
  * With a hint the launches that cannot have work are left out (two of four for a prefill-only
  * batch).  A sequence that contradicts the hint is NOT computed: its rows of `out` stay untouched,
  * its `mass` entries are zero and bit 3 of the device status word is set.
- * In a batch of at most 192 sequences (HOOK_BF16) single rows need no planning launch: the contexts
+ * In a batch of at most 192 sequences (up to 512 where there are few heads; HOOK_BF16) single rows need no planning launch: the contexts
  * are cut into equal ranges and the workgroups find theirs from the lengths; results are those of a
  * planned call up to the order of the sums.  Query chunks need none either when there is one sequence
  * or when they are few; their results are bit for bit those of the planned call.  The status word is

@@ -66,6 +66,24 @@ int stream_ranges(const hook_attn_probe_args* a, const Layout& l, int num_seqs) 
   return (int)(ranges < finest ? ranges : finest);
 }
 
+// Sequences up to which single rows plan themselves; up to kStreamSeqs of them do in any case (why there: hook_device.h).
+// Where an item is few workgroups the planner cuts contexts down to 256 keys to fill the chip, so more sequences are
+// better off in equal ranges.  Streamed and planned, contexts of 100-1000, 500-4000 and 2000-8000 tokens: 4 / 1 heads, 200
+// rows 23 / 51 / 91 and 27 / 60 / 103 us, 500 rows 43 / 102 / 202 and 40 / 111 / 218; 8 / 2 heads, 300 rows 43 / 121 / 252 and
+// 45 / 134 / 272, 500 rows 67 / 192 / 409 and 65 / 201 / 422; 16 / 4 heads, 200 rows 52 / 163 / 341 and 56 / 172 / 354.
+// Contexts shorter than a range are the planner's (8 / 2 heads, 500 rows of 20-200 tokens 34 and 30).
+// Groups of 8 heads have fewer ranges and pass earlier: 8 / 1 heads, 300 rows 37 / 75 / 140 and 37 / 90 / 159, 500 rows 54 / 113 /
+// 222 and 49 / 123 / 232; 16 / 2, 300 rows 53 / 137 / 270 and 55 / 147 / 289; 32 / 4, 200 rows 63 / 181 / 360 and 68 / 185 / 361, but 44
+// and 33 of 20-200 tokens.  So do key rows of half the bytes, where more planned workgroups are resident: 8 / 2 heads over an 8-bit
+// cache, 300 rows 33 / 73 / 145 and 33 / 78 / 145; 16 / 4 heads at head size 64, 200 rows 32 / 62 / 115 and 34 / 58 / 103.
+int stream_seqs(const hook_attn_probe_args* a, const Layout& l) {
+  const int wgs = a->num_kv_heads * l.dec_hgroups;
+  int n = wgs == 1 ? kScanMaxSeqs : wgs == 2 ? 384 : wgs <= 4 ? 288 : kStreamSeqs;
+  if (l.dec_hp == 8) n = wgs <= 2 ? 5 * n / 6 : kStreamSeqs;
+  if (a->head_dim == 64 || a->kv_dtype == HOOK_KV_FP8_E4M3) n = 2 * n / 3;
+  return n > kStreamSeqs ? n : kStreamSeqs;
+}
+
 // Carves the workspace up for the layout's capacities; returns its size.
 size_t place(const hook_attn_probe_args* a, Layout& l) {
   size_t off = 0;
@@ -78,12 +96,12 @@ size_t place(const hook_attn_probe_args* a, Layout& l) {
   return off;
 }
 
-// The layout for a workspace of `bytes`.  Single rows of up to kStreamSeqs sequences, whose lengths every
+// The layout for a workspace of `bytes`.  Single rows of up to stream_seqs() sequences, whose lengths every
 // workgroup can afford to scan, plan themselves where their records fit; those are numbered by range + sequence, which
 // can take more slots than the planner's items.  A smaller workspace keeps the planner, so every size that holds the
 // planner's items is accepted.
 // The size reported is no smaller for a larger batch (one buffer, asked for once, serves every batch up to that one with
-// the kernels that its own size would have got it): beyond kStreamSeqs it still holds the records of that many, and
+// the kernels that its own size would have got it): beyond stream_seqs() it still holds the records of that many, and
 // up to the static scratch's size it asks for no more than that.
 Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
   Layout l{};
@@ -99,7 +117,7 @@ Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
     l.needed = l.reported = place(a, l);
     if (a->num_seqs > 0) {
-      const int planned_cap = l.dec_cap, n = a->num_seqs < kStreamSeqs ? a->num_seqs : kStreamSeqs;
+      const int planned_cap = l.dec_cap, most = stream_seqs(a, l), n = a->num_seqs < most ? a->num_seqs : most;
       const int ranges = stream_ranges(a, l, n);
       if (l.dec_cap < ranges + n) l.dec_cap = ranges + n;
       const size_t streaming = place(a, l), fixed = (size_t)HOOK_STATIC_SCRATCH_BYTES;

@@ -65,9 +65,10 @@ struct NewRows {
   int at;       // 16 * row of k_new / v_new + place in the block
   bool store;
 };
-// WHOLE_LINES: how K rows of 128 bytes and more are fetched (below).  The one kind of batch that is better off without is
+// WHOLE_LINES: how K rows of 128 bytes and more are fetched (below).  Batches that are better off without are
 // large and of 256-byte rows for up to four heads: 8 rows 26.4 -> 24.9 us (on caches not seen before 27.8 -> 27.0), 24
-// 49.6 -> 48.9, but 64 of 1000-8000 tokens 190 -> 192 and 200 of 1000-4000 (planned) 331 -> 337.
+// 49.6 -> 48.9, but 64 of 1000-8000 tokens 190 -> 192 and 200 of 1000-4000 (planned) 331 -> 337.  Large ones for groups of 8 go
+// either way and keep whole lines: 150 x 100-1000 tokens 85 -> 80, x 500-3000 212 -> 213, x 1000-8000 488 -> 500.
 constexpr int kLineSeqs = 32;
 template <int D, int HP, bool KV8>
 constexpr bool lines_always() { return HP == 8 || KV8 || D == 64; }
@@ -497,13 +498,15 @@ __global__ __launch_bounds__(256, (HP == 8 ? 2 : 3) + (KV8 || D == 64 ? 1 : 0)) 
 // out to the ranges with hardly more blocks each, no range covers two: a sequence then takes its blocks divided by
 // `bpr` ranges, rounded up, which fits while bpr is at least total / (ranges - sequences).  kPieceBlocks is about
 // what a second piece costs in blocks.
-constexpr int kScanPerLane = kStreamSeqs / 64;
+// PER_LANE: sequences that a lane has room for (with room for kScanMaxSeqs in every batch 1 x 1237 tokens take 11.13 instead
+// of 10.98 us).
 constexpr int kPieceBlocks = 4;
 
+template <int PER_LANE>
 struct BlockScan {
   int K;                        // sequences per lane
-  int nblk[kScanPerLane];       // blocks of this lane's sequences
-  int L[kScanPerLane], qrow[kScanPerLane];
+  int nblk[PER_LANE];           // blocks of this lane's sequences
+  int L[PER_LANE], qrow[PER_LANE];
   int excl;                     // blocks in front of this lane's first sequence
   int total;                    // blocks of the batch
   int bpr;                      // blocks per range
@@ -511,13 +514,14 @@ struct BlockScan {
   int bits;                     // status bits of this lane's sequences
 };
 
-__device__ __forceinline__ BlockScan scan_blocks(const AttnParams& p, int lane) {
-  BlockScan sc;
+template <int PER_LANE>
+__device__ __forceinline__ BlockScan<PER_LANE> scan_blocks(const AttnParams& p, int lane) {
+  BlockScan<PER_LANE> sc;
   sc.K = (p.num_seqs + 63) >> 6;
   sc.bits = 0;
   int sum = 0;
 #pragma unroll
-  for (int u = 0; u < kScanPerLane; ++u) {
+  for (int u = 0; u < PER_LANE; ++u) {
     sc.nblk[u] = sc.L[u] = sc.qrow[u] = 0;
     const int i = lane * sc.K + u;
     if (u < sc.K && i < p.num_seqs) {
@@ -540,7 +544,7 @@ __device__ __forceinline__ BlockScan scan_blocks(const AttnParams& p, int lane) 
   return sc;
 }
 
-template <int D, int HP, bool KV8, bool WHOLE_LINES>
+template <int D, int HP, bool KV8, bool WHOLE_LINES, int PER_LANE>
 __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const AttnParams p) {
   __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -551,7 +555,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   const int hg = rest % p.dec_hgroups;
   const int g = rest / p.dec_hgroups;
 
-  const BlockScan sc = scan_blocks(p, lane);
+  const BlockScan<PER_LANE> sc = scan_blocks<PER_LANE>(p, lane);
 
   // where the new rows go (at most one sequence per lane: dec_write).  A length beyond the block table is clamped, so
   // its new row has no place in the cache.
@@ -575,13 +579,13 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   // the sequence that the range begins in, and its place there: by blocks, or by ranges where those end with
   // their sequence
   int at = g * sc.bpr, excl = sc.excl, total = sc.total;
-  int size[kScanPerLane];
+  int size[PER_LANE];
 #pragma unroll
-  for (int u = 0; u < kScanPerLane; ++u) size[u] = sc.nblk[u];
+  for (int u = 0; u < PER_LANE; ++u) size[u] = sc.nblk[u];
   if (sc.whole) {
     int sum = 0;
 #pragma unroll
-    for (int u = 0; u < kScanPerLane; ++u) {
+    for (int u = 0; u < PER_LANE; ++u) {
       if (u < sc.K) size[u] = (sc.nblk[u] + sc.bpr - 1) / sc.bpr;      // (uniform: few sequences, few divisions)
       sum += size[u];
     }
@@ -595,7 +599,7 @@ __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const At
   {
     int my_seq = 0, my_o = 0, my_L = 0, my_row = 0, start = excl;
 #pragma unroll
-    for (int u = 0; u < kScanPerLane; ++u) {
+    for (int u = 0; u < PER_LANE; ++u) {
       if (at >= start && at < start + size[u]) {
         my_seq = lane * sc.K + u;
         my_o = (at - start) * (sc.whole ? sc.bpr : 1);
@@ -806,10 +810,18 @@ hipError_t launch_decode_dh(const AttnParams& p, hipStream_t st) {
   if (p.dec_ranges > 0) {
     const long long grid = (long long)p.dec_ranges * p.Hkv * p.dec_hgroups;
     if (!grid_fits(grid)) return hipErrorInvalidValue;
-    if (p.kv8) hipLaunchKernelGGL((k_decode_stream<D, HP, true, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
-    else if (lines_always<D, HP, false>() || p.num_seqs <= kLineSeqs)
-      hipLaunchKernelGGL((k_decode_stream<D, HP, false, true>), dim3((unsigned)grid), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((k_decode_stream<D, HP, false, lines_always<D, HP, false>()>), dim3((unsigned)grid), dim3(256), 0, st, p);
+    constexpr int kFew = kStreamSeqs / 64, kMany = kScanMaxSeqs / 64;
+    const dim3 g((unsigned)grid);
+    if (p.num_seqs > kStreamSeqs) {
+      if (p.kv8) hipLaunchKernelGGL((k_decode_stream<D, HP, true, true, kMany>), g, dim3(256), 0, st, p);
+      else hipLaunchKernelGGL((k_decode_stream<D, HP, false, lines_always<D, HP, false>(), kMany>), g, dim3(256), 0, st, p);
+    } else if (p.kv8) {
+      hipLaunchKernelGGL((k_decode_stream<D, HP, true, true, kFew>), g, dim3(256), 0, st, p);
+    } else if (lines_always<D, HP, false>() || p.num_seqs <= kLineSeqs) {
+      hipLaunchKernelGGL((k_decode_stream<D, HP, false, true, kFew>), g, dim3(256), 0, st, p);
+    } else {
+      hipLaunchKernelGGL((k_decode_stream<D, HP, false, lines_always<D, HP, false>(), kFew>), g, dim3(256), 0, st, p);
+    }
     return hipGetLastError();
   }
   const long long grid = (long long)p.dec_cap * p.Hkv * p.dec_hgroups;

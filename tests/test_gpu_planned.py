@@ -74,11 +74,14 @@ def test_more_single_rows_than_plan_themselves_with_long_contexts_among_them(kv8
 
 
 @pytest.mark.parametrize("kv8", [False, True])
-@pytest.mark.parametrize("n,planned", [(192, False), (193, True)])
-def test_batches_on_both_sides_of_the_planner(n, planned, kv8):
+@pytest.mark.parametrize("planned", [False, True])
+def test_batches_on_both_sides_of_the_planner(planned, kv8):
     """The largest batch that streams in equal ranges and the smallest that is planned, with new rows, over every head
-    size and group size of the two kernels' key layouts."""
-    for Hq, Hkv, d in ((8, 2, 128), (16, 2, 128), (8, 2, 64), (2, 2, 128)):
+    size and group size of the two kernels' key layouts and every number of workgroups per range that the line depends on."""
+    for Hq, Hkv, d, most, most_kv8 in ((8, 2, 128, 384, 256), (16, 2, 128, 320, 213), (8, 2, 64, 256, 256), (2, 2, 128, 384, 256),
+                                       (4, 1, 128, 512, 341), (8, 1, 64, 284, 284), (6, 2, 128, 192, 192), (8, 4, 128, 288, 192),
+                                       (10, 5, 128, 192, 192), (32, 4, 128, 192, 192)):
+        n = (most_kv8 if kv8 else most) + planned
         lens = [1 + (i * 29) % 180 for i in range(n)]
         print(f"[case] n={n} Hq={Hq} d={d} kv8={kv8}", flush=True)
         b = W.random_batch(2720 + n, lens, [1] * n, Hq, Hkv, d, torch.bfloat16, num_probe_heads=2, max_sel_q=1, max_spans=2)
@@ -122,7 +125,7 @@ def test_planned_sequences_of_few_and_many_records(Hq, Hkv, d, kv8):
     """The merge gives a head one wave, which takes four records at a time, or sixteen where a sequence has more than four:
     record counts on both sides of those steps, the last record of one key, of one block and whole."""
     counts = [1, 2, 3, 4, 5, 8, 15, 16, 17, 20, 31, 32, 33, 48, 49]
-    lens = [256 * (c - 1) + (1, 16, 256)[k % 3] for k, c in enumerate(counts)] + [1 + i % 9 for i in range(185)]
+    lens = [256 * (c - 1) + (1, 16, 256)[k % 3] for k, c in enumerate(counts)] + [1 + i % 9 for i in range(505)]
     b = W.random_batch(2740 + Hq, lens, [1] * len(lens), Hq, Hkv, d, torch.bfloat16, num_probe_heads=2, max_sel_q=1, max_spans=2)
     if kv8:
         b = W.fp8_cache_variant(b, 2741)
@@ -132,5 +135,5 @@ def test_planned_sequences_of_few_and_many_records(Hq, Hkv, d, kv8):
     call.mass.fill_(float("nan"))
     call.launch()
     torch.cuda.synchronize()
-    assert plan_header(call) == [0, sum(counts) + 185, 256, 0]
+    assert plan_header(call) == [0, sum(counts) + 505, 256, 0]
     print("      ", compare_with_oracle(b, call.out, call.mass, label="records"), flush=True)

@@ -1,4 +1,4 @@
-"""Batches of at most 192 single rows plan themselves: the workgroups find their equal ranges of the contexts from the
+"""Batches of at most 192 single rows (more where there are few heads) plan themselves: the workgroups find their equal ranges of the contexts from the
 lengths, and no planning launch runs.  These cases pin that path against the CPU oracle through the C ABI (needs an
 MI355X)."""
 import pytest

@@ -13,7 +13,8 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("nseq,hi,Hq,Hkv,d", [(64, 300, 8, 2, 128), (65, 300, 8, 2, 128), (512, 90, 8, 2, 64), (513, 90, 8, 2, 64),
-                                              (192, 90, 8, 2, 64), (193, 90, 8, 2, 64), (192, 90, 8, 2, 128), (193, 90, 8, 2, 128),
+                                              (256, 90, 8, 2, 64), (257, 90, 8, 2, 64), (384, 90, 8, 2, 128), (385, 90, 8, 2, 128),
+                                              (512, 90, 4, 1, 128), (513, 90, 4, 1, 128), (192, 90, 32, 8, 128), (193, 90, 32, 8, 128),
                                               (200, 40, 32, 8, 128), (3, 5000, 16, 2, 128),
                                               (14, 500, 32, 8, 128), (4, 131, 64, 8, 128), (95, 200, 32, 8, 128)])
 def test_ranges_over_many_sequences(nseq, hi, Hq, Hkv, d):
@@ -32,7 +33,7 @@ def test_ranges_over_many_sequences(nseq, hi, Hq, Hkv, d):
     torch.cuda.synchronize()
     assert call.device_status() == 0
     items, keys = plan_header(call)[1:3]
-    assert (items > 0) == (keys > 0) == (nseq > 192)
+    assert (items > 0) == (keys > 0) == (nseq > {(4, 1, 128): 512, (8, 2, 128): 384, (8, 2, 64): 256}.get((Hq, Hkv, d), 192))
     print(compare_with_oracle(b, out, mass, label="stream"), flush=True)
 
 

@@ -155,14 +155,15 @@ def test_short_contexts_of_many_sequences_fit_the_static_scratch(binding):
     assert 14 << 20 < need <= lib.hook_attn_probe_static_capacity()
 
 
-@pytest.mark.parametrize("hq,hkv,d,blocks", [(32, 8, 128, 512), (64, 8, 128, 16), (64, 8, 128, 2048), (8, 8, 64, 4), (128, 1, 64, 100), (32, 2, 128, 1)])
+@pytest.mark.parametrize("hq,hkv,d,blocks", [(32, 8, 128, 512), (64, 8, 128, 16), (64, 8, 128, 2048), (8, 8, 64, 4), (128, 1, 64, 100), (32, 2, 128, 1),
+                                              (8, 1, 128, 512), (4, 1, 128, 300), (8, 2, 128, 256), (16, 4, 128, 40)])
 def test_workspace_of_a_larger_batch_serves_the_smaller_ones(binding, hq, hkv, d, blocks):
     lib = binding.load_library()
     size = lambda n, q, b: lib.hook_attn_probe_workspace_bytes(ctypes.byref(_args(
         binding, num_seqs=n, total_q=q, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, max_blocks_per_seq=b, num_blocks=n * b)))
     seqs = [size(n, n, blocks) for n in range(1, 1400)]
     assert all(x <= y for x, y in zip(seqs, seqs[1:])) and seqs[0] > 0
-    for n in (1, 7, 192, 193, 300, 512, 513, 900):
+    for n in (1, 7, 192, 193, 213, 214, 256, 257, 300, 320, 321, 384, 385, 512, 513, 900):
         rows = [size(n, q, blocks) for q in range(1, 4 * n + 200, 3)]
         assert all(x <= y for x, y in zip(rows, rows[1:]))
         ctx = [size(n, n, b) for b in range(1, 3000, 7)]
