@@ -228,6 +228,17 @@ __device__ __forceinline__ int find_probe_slot_uniform(const int* probe_heads, i
   return (lo < P && cload(probe_heads, lo) == head) ? lo : -1;
 }
 
+// The same search in a list of at most 64 that the lanes hold (lane i: element min(i, P - 1)): one trip to memory instead of
+// log2(P).
+__device__ __forceinline__ int find_probe_slot_lanes(int list, int P, int head) {
+  int lo = 0, hi = P;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (__builtin_amdgcn_readlane(list, mid) < head) lo = mid + 1; else hi = mid;
+  }
+  return (lo < P && __builtin_amdgcn_readlane(list, lo) == head) ? lo : -1;
+}
+
 // Calls without a planner: every entry of `mass` is written by the wave that owns its head, so elements of the head list
 // that no head owns (find_probe_slot does not lead to them: repeated, out of range, out of order) are cleared by one
 // workgroup of NT threads.  Whether there can be any: this thread's share of the list, to be fetched with whatever else

@@ -8,32 +8,43 @@
 //     tile: the block of a kv head is one contiguous run, so one block id, one 64-bit address and
 //     16 D bytes / 1 KB load instructions with constant offsets do it.  16-byte chunks are XOR-swizzled inside
 //     each LDS row so that the MFMA operand reads below are free of bank conflicts although rows are
-//     unpadded;
+//     unpadded; K rows are kept as D / 64 parts of 128 bytes, so that four addresses reach every operand of a tile;
 //   * V stays in its natural [key][dim] layout and is read TRANSPOSED with
 //     ds_read_b64_tr_b16, which hands each lane four consecutive keys of one output
 //     dimension - the A operand of O^T = V^T P^T.
 //
 // Per wave the score tile is computed transposed, S^T = K Q^T (32x32x16 MFMA, keys = M,
-// queries = N): lane l owns query l % 32 and 16 keys per 32-key block, so softmax row
-// statistics are in-lane reductions plus one exchange between lane halves, and the
+// queries = N): lane l owns query l % 32 and 16 keys per 32-key block, so row sums are in-lane, and the
 // exponentials, rounded to bf16, already form the B operand of the second MFMA.
 //
-// The loop is software pipelined inside each wave: while the vector ALUs run the softmax
-// of tile t, the matrix cores compute the scores of tile t+1 (the two instruction streams
-// are interleaved explicitly), then P V of tile t follows.  K tiles are fetched two tiles
-// ahead and V tiles one tile ahead, which makes one workgroup barrier per tile sufficient
-// with two LDS buffers each.
+// The loop goes by half tiles of 32 keys: the exponentials of one run on the vector ALUs while the matrix cores
+// alternate between the scores of the next and P V of the one before, a matrix instruction and its share of the
+// exponentials at a time.  That even mix is what the two waves of a SIMD need to keep its matrix core busy (synthetic
+// loops with all operand reads and fetches in place: 33 cycles per 32-cycle matrix instruction; this loop 31-34 while
+// both waves are inside it, 39 on a 32 k prompt, where the chip is at its power limit and holds 1.5-1.6 GHz).  Phases, with
+// the scores of a tile under its predecessor's exponentials and P V after them, took 44.
+// A row's softmax reference is its maximum over the first tile and stays that: no maxima, no exchange between lanes and no
+// rescaling inside the loop (a fifth of its vector instructions), and nothing waits for a whole tile's scores.  The sums
+// are exact softmax sums under any reference while they are finite; rows where they are not are done over (rows_alone).
+// 32768 tokens at 64 / 8 heads 14.9 -> 14.4 ms, one prompt of 2048 at 32 / 8 51.1 -> 44.6 us, 16 ragged prompts of 512-2048
+// 253.8 -> 242.8 us, the same at head size 64 156.4 -> 148 us, 8 chunks over an 8-bit cache 251 -> 243 us.
+//
+// K tiles are fetched two tiles ahead and V tiles one tile ahead, which makes one workgroup barrier per tile sufficient
+// with two LDS buffers each.  (Fetches issued right behind the barrier instead of in the first slots of the next
+// iteration: 3-6 % slower, with branches or with lanes switched off where nothing is left to fetch.)
 //
 // 8-bit caches (KV8): the bytes go direct to LDS too, one tile earlier, into a staging area of each wave's own
-// (2 x 16 D bytes); in the P V stage of the tile before they are needed the wave reads its block back, widens it
+// (2 x 16 D bytes); in the tile before they are needed the wave reads its block back, widens it
 // to bf16 (exact: every E4M3 number is a bf16 number) and writes it to the same swizzled buffers as
 // above, so the rest of the loop is the 16-bit one and every byte is widened once for the four heads
 // that share it.  The key scale goes into the softmax scale, the value scale into the normalisation of `out`.
 //
-// Probe span sums are taken from the fp32 exponentials under the same running reference
+// Probe span sums are taken from the fp32 exponentials under the same reference
 // as the normaliser and divided by it at the end: the captured mass is the exact softmax
 // mass of the row.  Waves that probe run a second instantiation of the same loop whose
 // arithmetic for `out` is identical.
+#include <type_traits>
+
 #include "fp8_device.h"
 #include "hook_device.h"
 
@@ -45,50 +56,60 @@ typedef short v4i16 __attribute__((ext_vector_type(4)));
 
 template <int D, bool KV8>
 struct Cfg {
-  static constexpr int RB = 2 * D;                          // bytes of one key row in the bf16 LDS buffers
+  static constexpr int RB = 2 * D;                          // bytes of one bf16 row
   static constexpr int TILE = kTileKeys * RB;
-  static constexpr int KSTEPS = D / 16;                     // MFMA k-steps of the scores
+  static constexpr int KBLK = kBlock * RB;                  // a cache block in a K buffer: D / 64 parts of 64 dimensions, rows of 128 bytes
+  static constexpr int KSTEPS = D / 16;                     // MFMA k-steps of the scores of a half tile
   static constexpr int MB = D / 32;                         // 32-dimension blocks of the output
+  static constexpr int SLOTS = KSTEPS + 2 * MB;             // matrix instructions per half tile (scores and P V alternate)
   static constexpr int BLK = kBlock * D * (KV8 ? 1 : 2);    // bytes of one (cache block, kv head) run
   static constexpr int NI = BLK / 1024;                     // load instructions per run
-  static constexpr int RPI = kBlock / NI;                   // rows per load instruction
-  static constexpr int LPR = 64 / RPI;                      // lanes (16-byte pieces) per row
+  static constexpr int RPI = kBlock / NI;                   // rows per load instruction of a run fetched as it lies (V, bytes)
+  static constexpr int LPR = 64 / RPI;                      // lanes (16-byte pieces) per row of such a run
   static constexpr int STAGE = KV8 ? 2 * BLK : 0;           // staging bytes per wave: K run, V run
   static constexpr int LDS = 4 * TILE + 4 * STAGE;          // K[2], V[2], staging
   static constexpr int CH = D / 8;                          // 16-byte chunks per bf16 row
+  static constexpr int RING = 4;                            // operands requested ahead, K and V^T each
 };
 
-// Swizzle of the 16-byte chunks of LDS row r (what a chunk index is XORed with): the 16 rows a K read touches
-// and the four rows a transposed V read touches then lie in different banks (64 banks of 4 bytes; a row is
-// all of them at D = 128 and half of them at D = 64).
-template <int D> __device__ __forceinline__ int k_swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+// Swizzles of the 16-byte chunks (what a chunk index is XORed with).  K buffers have rows of 128 bytes, half of the
+// 64 banks: 16 neighbouring rows read with one chunk index then touch every bank once.  V rows have 2 D bytes: the four
+// rows a transposed read touches lie in different banks.  The output rows on their way through LDS use out_swizzle.
+__device__ __forceinline__ int k_swizzle(int r) { return (r >> 1) & 7; }
 template <int D> __device__ __forceinline__ int v_swizzle(int r) { return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); }
+template <int D> __device__ __forceinline__ int out_swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// 16-byte direct-to-LDS load: lane i's data lands at lds + OFF + 16 * i, from base + OFF + its own offset.
-// Written as assembly so that its completion is tracked only by the explicit vmcnt waits; the compiler would
-// otherwise make every later LDS read wait for the load.
-template <int OFF>
-__device__ __forceinline__ void dma16(unsigned long long base, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
-               :: "s"(lds_addr), "v"(voff), "s"(base), "n"(OFF) : "memory", "m0");
+// 16-byte direct-to-LDS loads, N of them: lane i's data of load j lands at lds + OFF + 1024 j + 16 i, from base + OFF + 1024 j +
+// its own offset voff[j].
+// Written as assembly so that their completion is tracked only by the explicit vmcnt waits; the compiler would
+// otherwise make every later LDS read wait for them.
+template <int N, int OFF>
+__device__ __forceinline__ void dma16(unsigned long long base, const unsigned* voff, unsigned lds_addr) {
+  static_assert(N == 1 || N == 2, "");
+  if constexpr (N == 1)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3"
+                 :: "s"(lds_addr), "v"(voff[0]), "s"(base), "n"(OFF) : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3 offset:%4\n\tglobal_load_lds_dwordx4 %2, %3 offset:%5"
+                 :: "s"(lds_addr), "v"(voff[0]), "v"(voff[1]), "s"(base), "n"(OFF), "n"(OFF + 1024) : "memory", "m0");
 }
+
+__device__ __forceinline__ bf16x8 as_bf16x8(u32x4 x) { return __builtin_bit_cast(bf16x8, x); }
 
 struct WaveCtx {
   // loop-invariant per-lane / per-wave values
-  unsigned k_read_addr;   // LDS byte offset of this lane's K row with its swizzle term folded in
-  unsigned v_read_addr;   // same for the transposed V reads
-  int hf, qi;
+  int hf;
   int pos;                // causal horizon of this lane's query row
+  int pos_min;            // of the wave's first row
   float c;                // scale * log2(e)
-  int S;                  // number of spans
   // direct-to-LDS fetches
   unsigned long long kbase, vbase;   // cache + kv-head offset
   unsigned lds_base;      // LDS address of the buffers
   unsigned blk_bytes;     // bytes per cache block (all kv heads)
   int num_blocks;
-  unsigned k_off, v_off;  // this lane's source offset in a run (first load instruction)
+  unsigned k_off[4], v_off[2];  // this lane's source offsets in a run, less 1024 per load instruction before
   int L, last_blk, w, lane;
 };
 
@@ -99,37 +120,12 @@ __device__ __forceinline__ float half_max(float mx) {
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
-// mask (optional) and row maximum of a raw score tile; both lane halves end up with the same value
-template <bool MASK>
-__device__ __forceinline__ float tile_max(const WaveCtx& cx, int key0, f32x16 (&S)[2]) {
-  if constexpr (MASK) {
+// scores of the keys behind this lane's row; `key0`: first key of the half tile
+__device__ __forceinline__ void mask_half(const WaveCtx& cx, int key0, f32x16& S) {
+  const int last = cx.pos - key0 - 4 * cx.hf;
 #pragma unroll
-    for (int kbk = 0; kbk < 2; ++kbk)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = key0 + 32 * kbk + 8 * (r >> 2) + 4 * cx.hf + (r & 3);
-        if (key > cx.pos) S[kbk][r] = -INFINITY;
-      }
-  }
-  float m0 = fmaxf(S[0][0], S[0][1]), m1 = fmaxf(S[1][0], S[1][1]);
-#pragma unroll
-  for (int r = 2; r < 16; r += 2) {
-    m0 = fmaxf(m0, fmaxf(S[0][r], S[0][r + 1]));
-    m1 = fmaxf(m1, fmaxf(S[1][r], S[1][r + 1]));
-  }
-  return half_max(fmaxf(m0, m1));
-}
-
-// Block ids of 64 consecutive blocks (16 tiles) live in one register per lane; two registers
-// cover the group being consumed and the next one.  They are kept as they come (ids outside the cache are
-// replaced by block 0 when one is used), so that nothing waits for them before that.
-struct BlockIds {
-  int grp;
-  int cur, nxt;
-};
-
-__device__ __forceinline__ int load_ids(const int* bt, int first, int lane, int last_blk) {
-  return bt[min(first + lane, last_blk)];
+  for (int r = 0; r < 16; ++r)
+    S[r] = 8 * (r >> 2) + (r & 3) > last ? -INFINITY : S[r];
 }
 
 // byte offset of a block in the cache
@@ -137,406 +133,472 @@ __device__ __forceinline__ unsigned long long block_bytes(const WaveCtx& cx, int
   return (unsigned long long)((unsigned)blk < (unsigned)cx.num_blocks ? (unsigned)blk : 0u) * cx.blk_bytes;
 }
 
-// the same for this wave's block of a tile (past the last block: the last block again)
-__device__ __forceinline__ unsigned long long block_offset(const WaveCtx& cx, int sel, int tile) {
-  const int bidx = min(4 * tile + cx.w, cx.last_blk);      // same 64-block group as block 4 * tile
-  return block_bytes(cx, __builtin_amdgcn_readlane(sel, bidx & 63));
+// Id of this wave's block of a tile (past the last block: the last block again).  It is loaded an iteration before the
+// fetch that needs it, into a vector register: a scalar load would have every operand read from LDS wait for it.
+__device__ __forceinline__ int load_id(const WaveCtx& cx, const int* bt, int tile) {
+  int i = min(4 * tile + cx.w, cx.last_blk);
+  asm("" : "+v"(i));
+  return bt[i];
 }
 
-// Load instruction J of this wave's K run.  A K row past the last token may hold anything: it only
-// produces scores of keys beyond every row's horizon, which are overwritten with -inf before use, and
-// it still lies inside a block the sequence owns.
+// Load instructions J and, where there are as many, J + 1 of this wave's K run.  16-bit: instruction J takes eight rows of one
+// 64-dimension part, rows 8 (J & 1) .. + 7 of part J >> 1; bytes: 1 KB of the run as it lies.  A K row past the last
+// token may hold anything: it only produces scores of keys beyond every row's horizon, which are overwritten with -inf
+// before use, and it still lies inside a block the sequence owns.
 template <int D, bool KV8, int J>
 __device__ __forceinline__ void fetch_k(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
-  // (the swizzle of rows RPI J .. differs from that of the first rows by bit 2 of the chunk index times J)
-  unsigned off = cx.k_off;
-  if constexpr (!KV8 && J > 0) {
-    asm("" : "+v"(off));      // computed here and not kept in a register of its own across the loop
-    off ^= 64u * J;
-  }
-  dma16<1024 * J>(cx.kbase + boff, off, lds);
+  dma16<(Cfg<D, KV8>::NI > 1 ? 2 : 1), 1024 * J>(cx.kbase + boff, cx.k_off + (KV8 ? 0 : J), lds);
 }
 
-// Load instruction J of this wave's V run.  CLAMP: rows past the last token re-read the last valid row of the
-// last block - P is 0 there, and 0 * NaN would poison the output - so a lane's source row may differ from the
-// row its data is meant for.
-template <int D, bool KV8, int J, bool CLAMP>
-__device__ __forceinline__ void fetch_v(const WaveCtx& cx, unsigned long long boff, int tile, unsigned lds) {
-  using C = Cfg<D, KV8>;
-  if constexpr (CLAMP) {
-    int ln = cx.lane;
-    asm("" : "+v"(ln));       // likewise
-    const int r = C::RPI * J + ln / C::LPR;
-    const int rmax = cx.L - 1 - kBlock * min(4 * tile + cx.w, cx.last_blk);      // >= 0
-    const unsigned row_bytes = C::BLK / kBlock;
-    dma16<0>(cx.vbase + boff, cx.v_off + (unsigned)(min(r, rmax) - ln / C::LPR) * row_bytes, lds + 1024 * J);
-  } else {
-    dma16<1024 * J>(cx.vbase + boff, cx.v_off, lds);
-  }
+// The same of this wave's V run: 1 KB each as it lies.  Rows past the last token are cleared once they have landed
+// (clear_past_end): P is 0 there, and 0 * NaN would poison the output.
+template <int D, bool KV8, int J>
+__device__ __forceinline__ void fetch_v(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
+  dma16<(Cfg<D, KV8>::NI > 1 ? 2 : 1), 1024 * J>(cx.vbase + boff, cx.v_off, lds);
 }
 
+// whole runs
+template <int D, bool KV8>
+__device__ __forceinline__ void fetch_v_tile(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
+  fetch_v<D, KV8, 0>(cx, boff, lds);
+  if constexpr (Cfg<D, KV8>::NI > 2) fetch_v<D, KV8, 2>(cx, boff, lds);
+}
+template <int D, bool KV8>
+__device__ __forceinline__ void fetch_k_tile(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
+  fetch_k<D, KV8, 0>(cx, boff, lds);
+  if constexpr (Cfg<D, KV8>::NI > 2) fetch_k<D, KV8, 2>(cx, boff, lds);
+}
+
+// LDS positions, in bytes from the start of the buffers: this wave's rows of K buffer `b` and V buffer `b`, its staging area
+template <int D, bool KV8> __device__ __forceinline__ unsigned k_rows(const WaveCtx& cx, int b) {
+  return b * Cfg<D, KV8>::TILE + cx.w * Cfg<D, KV8>::KBLK;
+}
+template <int D, bool KV8> __device__ __forceinline__ unsigned v_rows(const WaveCtx& cx, int b) {
+  return (2 + b) * Cfg<D, KV8>::TILE + cx.w * kBlock * Cfg<D, KV8>::RB;
+}
+template <int D, bool KV8> __device__ __forceinline__ unsigned staged(const WaveCtx& cx) {
+  return 4 * Cfg<D, KV8>::TILE + cx.w * Cfg<D, KV8>::STAGE;
+}
+
+// operand of score k-step s, half tile `half`; `addr`: LDS addresses of this lane's row of the K buffer
+template <int D, bool KV8>
+__device__ __forceinline__ bf16x8 read_k(const unsigned (&addr)[4], int s, int half) {
+  return *(const __attribute__((address_space(3))) bf16x8*)(size_t)(addr[s & 3] + (s >> 2) * (kBlock * 128) + half * 2 * Cfg<D, KV8>::KBLK);
+}
+
+// operand of P V: keys 16 m .. 16 m + 15 of the V buffer, dimensions 32 mb .. 32 mb + 31
 template <int D>
-__device__ __forceinline__ bf16x8 read_k(const WaveCtx& cx, const unsigned char* kb, int s, int kbk) {
-  const unsigned a = cx.k_read_addr ^ (32u * s);
-  return *reinterpret_cast<const bf16x8*>(kb + a + kbk * 32 * 2 * D);
-}
-
-template <int D>
-__device__ __forceinline__ bf16x8 read_vt(const WaveCtx& cx, const unsigned char* vb, int m, int mb) {
-  const unsigned a = (cx.v_read_addr ^ (64u * mb)) + (16 * m) * 2 * D;
+__device__ __forceinline__ bf16x8 read_vt(const unsigned (&addr)[4], int m, int mb) {
   union { v4i16 h[2]; bf16x8 v; } av;
-  av.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)(vb + a));
-  av.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)(vb + a + 8 * 2 * D));
+  const unsigned a = addr[mb] + 16 * m * 2 * D;
+  av.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)(size_t)a);
+  av.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) v4i16*)(size_t)(a + 8 * 2 * D));
   return av.v;
 }
 
-// 8-bit caches: half of a 16-byte piece of this wave's staged run - eight bytes of row `r`, chunk `ch` - widened into
-// an LDS buffer row
+// 8-bit caches: eight bytes (row `r` of this wave's block, 16-byte chunk `ch` of the bf16 row) widened into its rows of a
+// K or V buffer
 template <int D>
-__device__ __forceinline__ void widen_to(unsigned char* buf, int r, int ch, int swz, unsigned lo, unsigned hi) {
-  *reinterpret_cast<uint4*>(buf + r * 2 * D + ((ch ^ swz) << 4)) = e4m3x8_to_bf16x8(make_uint2(lo, hi));
+__device__ __forceinline__ void widen_to_k(unsigned char* rows, int r, int ch, unsigned lo, unsigned hi) {
+  *reinterpret_cast<uint4*>(rows + (ch >> 3) * (kBlock * 128) + r * 128 + (((ch & 7) ^ k_swizzle(r)) << 4)) =
+      e4m3x8_to_bf16x8(make_uint2(lo, hi));
+}
+template <int D>
+__device__ __forceinline__ void widen_to_v(unsigned char* rows, int r, int ch, unsigned lo, unsigned hi) {
+  *reinterpret_cast<uint4*>(rows + r * 2 * D + ((ch ^ v_swizzle<D>(r)) << 4)) = e4m3x8_to_bf16x8(make_uint2(lo, hi));
 }
 
-template <int D>
-__device__ __forceinline__ void qk_tile(const WaveCtx& cx, const unsigned char* kb, const bf16x8 (&qf)[D / 16],
-                                        f32x16 (&S)[2]) {
-#pragma unroll
-  for (int kbk = 0; kbk < 2; ++kbk)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) S[kbk][r] = 0.0f;
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s) {
-    S[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D>(cx, kb, s, 0), qf[s], S[0], 0, 0, 0);
-    S[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D>(cx, kb, s, 1), qf[s], S[1], 0, 0, 0);
+// f(0), f(1), ... f(N - 1) with the number as a constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
   }
+}
+
+// What a wave carries from half tile to half tile.
+template <int D>
+struct Pipe {
+  f32x16 S[2];            // raw scores (and exponentials) of a tile's two halves
+  u32x4 P[2][2];          // probabilities of a half tile, rounded: [half][16-key group]
+  bf16x8 ka[4], va[4];    // operand rings
+  unsigned k_addr[4];     // LDS positions of this lane's K row in the buffer being read, one per k-step of a 64-dimension part
+  unsigned v_addr[4];     // the same for the transposed V reads, one per 32-dimension block of the output
+  f32x16 O[D / 32];
+  float l;                // normaliser
+  float am[kMaxSpans];    // span sums
+};
+
+// Exponentials of half a tile, EPS elements to a slot and software pipelined: an element's multiply-add, its exponential,
+// and its sum and rounding lie in three neighbouring slots, so that none waits for the one before it.
+struct HalfExp { float x[4], sum; };
+
+template <int EPS>
+__device__ __forceinline__ void exp_begin(const WaveCtx& cx, const f32x16& S, float m, HalfExp& h) {
+  h.sum = 0.0f;
+#pragma unroll
+  for (int e = 0; e < EPS; ++e) h.x[e] = __builtin_fmaf(S[e], cx.c, -m);
+}
+__device__ __forceinline__ void exp_done(const f32x16& S, HalfExp& h, u32x4 (&P)[2], int e) {   // element e of S is an exponential
+  h.sum += S[e];
+  if (e & 1) P[e >> 3][(e & 7) >> 1] = pack_bf16(S[e - 1], S[e]);
+}
+template <int EPS>
+__device__ __forceinline__ void exp_slot(const WaveCtx& cx, f32x16& S, float m, HalfExp& h, u32x4 (&P)[2], int j) {
+#pragma unroll
+  for (int e = 0; e < EPS; ++e) {
+    const int n = j * EPS + e;
+    float ex = fast_exp2(h.x[e]);
+    asm volatile("" : "+v"(ex));       // (in this slot, not where it is used)
+    if (n + EPS < 16) h.x[e] = __builtin_fmaf(S[n + EPS], cx.c, -m);
+    if (j > 0) exp_done(S, h, P, n - EPS);
+    S[n] = ex;
+  }
+}
+template <int EPS>
+__device__ __forceinline__ float exp_end(const f32x16& S, HalfExp& h, u32x4 (&P)[2]) {
+#pragma unroll
+  for (int e = 16 - EPS; e < 16; ++e) exp_done(S, h, P, e);
+  return h.sum;
+}
+
+// Spans of a sequence; no span that is not behind us begins before key `lo` or ends after key `hi`.
+struct Spans { int a[kMaxSpans], b[kMaxSpans], lo, hi, n; };
+
+template <int S = 0>
+__device__ __forceinline__ void add_span(const WaveCtx& cx, const Spans& sp, int key0, const f32x16& ex, float sum,
+                                         float (&am)[kMaxSpans], int& next) {
+  if constexpr (S < kMaxSpans) {
+    if (S >= sp.n) return;
+    const int a = sp.a[S], b = sp.b[S];
+    if (b > key0 && a < key0 + 32) {
+      if (a <= key0 && b >= key0 + 32) {
+        am[S] += sum;
+      } else {
+        float acc = 0.0f;
+        const unsigned lo = a - key0 - 4 * cx.hf, len = b - a;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc += 8 * (r >> 2) + (r & 3) - lo < len ? ex[r] : 0.0f;
+        am[S] += acc;
+      }
+    }
+    if (b > key0 + 32) next = min(next, a);
+    add_span<S + 1>(cx, sp, key0, ex, sum, am, next);
+  }
+}
+
+// Span sums of the half tile at key0 from its exponentials (masked keys are 0).
+template <int D>
+__device__ __forceinline__ void add_spans(const WaveCtx& cx, Spans& sp, int key0, const f32x16& ex, float sum,
+                                          float (&am)[kMaxSpans]) {
+  if (__builtin_expect(sp.hi > key0 && sp.lo < key0 + 32, 0)) {
+    int next = sp.hi;
+    add_span(cx, sp, key0, ex, sum, am, next);
+    sp.lo = next;
+  }
+}
+
+// the barrier after which the tiles fetched during an iteration may be read and the ones read in it overwritten
+template <bool KV8>
+__device__ __forceinline__ void tile_barrier() {
+  if constexpr (!KV8) wait_vmem();     // (bytes only go to the wave's own staging area)
+  __syncthreads();
 }
 
 // ---- one pipelined iteration --------------------------------------------------------------
-// On entry Scur holds the raw (already masked) scores of tile kt and mx_cur their row maximum.
-//   stage B  raise the running reference if needed (rare);
-//   stage C  exponentials of tile kt on the vector ALUs while the matrix cores compute the
-//            scores of tile kt+1 into Snext (8 slices: D / 64 MFMAs + 4 exponentials each);
-//   stage D  O += P V of tile kt on the matrix cores (one MFMA per slice) while the scalar/vector units
-//            issue the fetches of V(kt+1) and K(kt+2) (8-bit caches: widen those two from the staging area and fetch
-//            V(kt+2) and K(kt+3) into it) and reduce the row maximum of tile kt+1; V^T operands are
-//            requested two MFMAs ahead of their use (the first two during stage C).
-// The slices are fenced so the instruction streams stay interleaved as written.  Fetches are
-// issued unconditionally with the tile index clamped to the last tile: the buffers they land
-// in are free by then and are never read again.
-// boff: cache offset of this wave's block of the tile whose V comes next (its K was the last one fetched).
-// Returns the row maximum of tile kt+1.
-template <int D, bool KV8, bool MASKNEXT, bool NEXT, bool PROBE>
-__device__ __forceinline__ float tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles,
-                                           BlockIds& ids, const int* bt, unsigned long long& boff,
-                                           f32x16 (&Scur)[2], float mx_cur, f32x16 (&Snext)[2],
-                                           const bf16x8 (&qf)[D / 16], f32x16 (&O)[D / 32], float& m_run, float& l_run,
-                                           float (&am)[kMaxSpans], const int (&sp_a)[kMaxSpans],
-                                           const int (&sp_b)[kMaxSpans]) {
+// On entry P[0] holds the probabilities of the first half of tile kt, S[1] the raw scores of its second half, and the
+// rings the first operands of K(kt+1) and V(kt).  Half a tile at a time,
+//   the matrix cores compute the scores of a half tile of kt+1 and P V of a half tile of kt, alternating,
+//   the vector ALUs the exponentials of the half tile between the two,
+// one matrix instruction and 16 / SLOTS exponentials to a slot; the slots are fenced so that the streams stay interleaved.
+// Fetches of V(kt+1) and K(kt+2) (8-bit caches: the bytes of V(kt+2) and K(kt+3), once those of V(kt+1) and K(kt+2) are
+// widened) are issued first; the barrier that closes the iteration stands as many slots before its end as operands are
+// in flight, so nothing waits for the first operands of the next one.  The tile index of a fetch is clamped to the last
+// tile: the buffers are free by then and are never read again.
+// boff: cache offset of this wave's block of the tile whose V comes next (its K was the last one requested); id: its block
+// of the tile after that.
+template <int D, bool KV8, bool PROBE>
+__device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
+                                          const int* bt, unsigned long long& boff, Pipe<D>& t, float m,
+                                          const bf16x8 (&qf)[D / 16], Spans& sp) {
   using C = Cfg<D, KV8>;
-  const int key0 = kt * kTileKeys;
-  unsigned char* const Kbuf = smem;
-  unsigned char* const Vbuf = smem + 2 * C::TILE;
-  const unsigned char* kb = Kbuf + ((kt + 1) & 1) * C::TILE;  // K of tile kt+1
-  const unsigned char* vb = Vbuf + (kt & 1) * C::TILE;        // V of tile kt
-
-  // what was fetched one iteration ago has landed (and, widened, is written); after the barrier every wave
-  // has also finished reading the buffers that this iteration fills
-  wait_vmem();
-  __syncthreads();
-
-  // -- stage B
-  const float mt = mx_cur * cx.c;
-  const bool upd = mt > m_run + kLazyTau;
-  if (__builtin_amdgcn_ballot_w64(upd) != 0) {
-    const float alpha = upd ? fast_exp2(m_run - mt) : 1.0f;
-    m_run = upd ? mt : m_run;
-    l_run *= alpha;
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) O[mb][r] *= alpha;
-    if constexpr (PROBE) {
-#pragma unroll
-      for (int s = 0; s < kMaxSpans; ++s) am[s] *= alpha;
+  constexpr int NS = C::SLOTS, EPS = 16 / NS, R = C::RING, NQ = C::KSTEPS, NP = 2 * C::MB, NI = C::NI;
+  static_assert(NQ == NP && 2 * NQ % R == 0, "scores and P V alternate; the rings turn whole rounds");
+  constexpr int BAR = 2 * NS - 2 * R + 2;              // slot in front of which the barrier stands
+  const unsigned v_dst = v_rows<D, KV8>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8>(cx, kt & 1);
+  const unsigned stage = staged<D, KV8>(cx);
+  uint4 st[2];                     // staged pieces on their way through the registers
+  unsigned long long next_boff = 0;
+  float sum[2];
+  HalfExp h;
+  // operand `n` of the scores / of P V, counted through the iteration; beyond it, the next iteration's
+  auto request_k = [&](auto n) { t.ka[n % R] = read_k<D, KV8>(t.k_addr, n % NQ, n % (2 * NQ) / NQ); };
+  auto request_v = [&](auto n) { t.va[n % R] = read_vt<D>(t.v_addr, n % (2 * NP) / C::MB, n % C::MB); };
+  static_for<2 * NS>([&](auto slot) {
+    constexpr int i = slot, half = i / NS, j = i % NS, u = j / 2;
+    // half 0: exponentials of the second half of kt, half 1: of the first half of kt + 1
+    f32x16& Sx = t.S[half ^ 1];
+    const int key0 = kTileKeys * kt + 32 * (half + 1);
+    if (j == 0) {
+      if (key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
+      __builtin_amdgcn_sched_barrier(0);
+      exp_begin<EPS>(cx, Sx, m, h);
     }
-  }
-  const float m_safe = (m_run == -INFINITY) ? 0.0f : m_run;
-  // block-id registers: the K fetch (two tiles ahead, three with staging) may enter a new group of 64 blocks
-  const int tv = min(kt + (KV8 ? 2 : 1), ntiles - 1), tk = min(kt + (KV8 ? 3 : 2), ntiles - 1);
-  if ((tk >> 4) > ids.grp + 1) {
-    ids.grp += 1;
-    ids.cur = ids.nxt;
-    ids.nxt = load_ids(bt, 64 * (ids.grp + 1), cx.lane, cx.last_blk);
-  }
-  const int sel = ((tk >> 4) == ids.grp) ? ids.cur : ids.nxt;
-  __builtin_amdgcn_sched_barrier(0);
-
-  // -- stage C
-  float tsum = 0.0f;
-  union PB { uint32_t u[4]; bf16x8 v; } pb[4];
-  bf16x8 va[3];   // ring of V^T operands: requested two matrix instructions ahead of their use
-  {
-    constexpr int PER = C::KSTEPS / 4 > 1 ? 2 : 1;      // MFMAs per slice: D = 128 both key halves of one k-step, D = 64 one
-    bf16x8 ka[2][PER];
-    auto request = [&](int s) {
-      if constexpr (PER == 2) {
-        ka[s & 1][0] = read_k<D>(cx, kb, s, 0);
-        ka[s & 1][PER - 1] = read_k<D>(cx, kb, s, 1);
-      } else {
-        ka[s & 1][0] = read_k<D>(cx, kb, s >> 1, s & 1);
-      }
-    };
-    if constexpr (NEXT) request(0);
+    if (i == BAR) {
+      __builtin_amdgcn_sched_barrier(0);
+      tile_barrier<KV8>();
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      if constexpr (NEXT) {
-        if (s < 7) {
-          request(s + 1);
-          __builtin_amdgcn_sched_barrier(0);   // requested a whole slice before their use
-        }
-        const f32x16 z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-        if constexpr (PER == 2) {
-          Snext[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s & 1][0], qf[s % C::KSTEPS], s == 0 ? z : Snext[0], 0, 0, 0);
-          Snext[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s & 1][PER - 1], qf[s % C::KSTEPS], s == 0 ? z : Snext[1], 0, 0, 0);
-        } else {
-          Snext[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[s & 1][0], qf[s >> 1], s < 2 ? z : Snext[s & 1], 0, 0, 0);
-        }
+      for (int b = 0; b < 4; ++b) {       // on to the other buffers
+        t.k_addr[b] += (kt & 1) ? C::TILE : -C::TILE;
+        if (b < C::MB) t.v_addr[b] += (kt & 1) ? -C::TILE : C::TILE;
       }
-      // the first V^T operands of the P V stage are requested here, two slices before their use
-      if (s == 6) va[0] = read_vt<D>(cx, vb, 0, 0);
-      if (s == 7) va[1] = read_vt<D>(cx, vb, 0, 1);
-      // exponentials of elements 4s .. 4s+3 of the current tile
-      const int kbk = s >> 2, r0 = 4 * (s & 3);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float ex = fast_exp2(__builtin_fmaf(Scur[kbk][r0 + e], cx.c, -m_safe));
-        Scur[kbk][r0 + e] = ex;
-        tsum += ex;
-      }
-      const int m = 2 * kbk + ((s & 3) >> 1);
-      pb[m].u[2 * (s & 1)] = pack_bf16(Scur[kbk][r0], Scur[kbk][r0 + 1]);
-      pb[m].u[2 * (s & 1) + 1] = pack_bf16(Scur[kbk][r0 + 2], Scur[kbk][r0 + 3]);
+      // what could not be requested before
+      static_for<BAR / 2 + R - 2 * NQ>([&](auto k) {
+        request_k(std::integral_constant<int, 2 * NQ + k>{});
+        request_v(std::integral_constant<int, 2 * NP + k>{});
+      });
       __builtin_amdgcn_sched_barrier(0);
     }
-  }
-  l_run += tsum;
-
-  if constexpr (PROBE) {
-#pragma unroll
-    for (int s = 0; s < kMaxSpans; ++s) {
-      if (s < cx.S) {
-        const int a = sp_a[s], b = sp_b[s];
-        if (b > key0 && a < key0 + kTileKeys) {
-          if (a <= key0 && b >= key0 + kTileKeys) {
-            am[s] += tsum;  // whole tile inside the span; masked keys contributed 0
-          } else {
-            float acc = 0.0f;
-#pragma unroll
-            for (int kbk = 0; kbk < 2; ++kbk)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int key = key0 + 32 * kbk + 8 * (r >> 2) + 4 * cx.hf + (r & 3);
-                acc += (key >= a && key < b) ? Scur[kbk][r] : 0.0f;
-              }
-            am[s] += acc;
-          }
-        }
+    if (j % 2 == 0) {
+      const f32x16 z = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+      constexpr int n = half * NQ + u;
+      t.S[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.ka[n % R], qf[u], u == 0 ? z : t.S[half], 0, 0, 0);
+      if constexpr (n + R < 2 * NQ || i >= BAR) request_k(std::integral_constant<int, n + R>{});
+    } else {
+      constexpr int n = half * NP + u;
+      t.O[n % C::MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.va[n % R], as_bf16x8(t.P[half][(n / C::MB) % 2]), t.O[n % C::MB], 0, 0, 0);
+      if constexpr (n + R < 2 * NP || i >= BAR) request_v(std::integral_constant<int, n + R>{});
+    }
+    if constexpr (!KV8) {
+      if constexpr (i == 0) {
+        next_boff = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
+        id = load_id(cx, bt, kt + 3);
+      }
+      if constexpr (i == 1) fetch_v<D, false, 0>(cx, boff, cx.lds_base + v_dst);
+      if constexpr (i == 3 && NI > 2) fetch_v<D, false, 2>(cx, boff, cx.lds_base + v_dst);
+      if constexpr (i == 5) boff = next_boff;
+      if constexpr (i == 5) fetch_k<D, false, 0>(cx, boff, cx.lds_base + k_dst);
+      if constexpr (i == 7 && NI > 2) fetch_k<D, false, 2>(cx, boff, cx.lds_base + k_dst);
+    } else {
+      // piece p = 0 .. 2 NI - 1 (K run, then V run): read in slice 2p, its halves widened in slices 2p+2 and 2p+3
+      if (i == 0) wait_vmem();
+      if (i % 2 == 0 && i / 2 < 2 * NI) {
+        const int p = i / 2;
+        st[p & 1] = *reinterpret_cast<const uint4*>(smem + stage + (p / NI) * C::BLK + (p % NI) * 1024 + 16 * cx.lane);
+      }
+      if (i >= 2 && (i - 2) / 2 < 2 * NI) {
+        const int p = (i - 2) / 2, hh = i % 2;
+        const int r = C::RPI * (p % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR) + hh;
+        const uint4& v = st[p & 1];
+        if (p < NI) widen_to_k<D>(smem + k_dst, r, ch, hh ? v.z : v.x, hh ? v.w : v.y);
+        else widen_to_v<D>(smem + v_dst, r, ch, hh ? v.z : v.x, hh ? v.w : v.y);
+      }
+      // the staging area is free once its last piece sits in registers
+      constexpr int F = 4 * NI + 2;
+      static_assert(F + 2 < 2 * NS, "");
+      if constexpr (i == F) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      if constexpr (i == F - 1) next_boff = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
+      if constexpr (i == F - 1) id = load_id(cx, bt, kt + 4);
+      if constexpr (i == F) fetch_v<D, true, 0>(cx, boff, cx.lds_base + stage + C::BLK);
+      if constexpr (i == F + 2) boff = next_boff;
+      if constexpr (i == F + 2) fetch_k<D, true, 0>(cx, boff, cx.lds_base + stage);
+    }
+    exp_slot<EPS>(cx, Sx, m, h, t.P[half ^ 1], j);
+    __builtin_amdgcn_sched_barrier(0);
+    if (j == NS - 1) {
+      sum[half] = exp_end<EPS>(Sx, h, t.P[half ^ 1]);
+      asm volatile("" : "+v"(t.P[half ^ 1][0]), "+v"(t.P[half ^ 1][1]), "+v"(sum[half]));      // (likewise)
+      if constexpr (PROBE) {
+        add_spans<D>(cx, sp, key0, Sx, sum[half], t.am);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-
-  // -- stage D
-  float mx_acc = -INFINITY;   // running maximum of the next tile's scores
-  if constexpr (NEXT && MASKNEXT) {
-#pragma unroll
-    for (int kbk = 0; kbk < 2; ++kbk)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = key0 + kTileKeys + 32 * kbk + 8 * (r >> 2) + 4 * cx.hf + (r & 3);
-        if (key > cx.pos) Snext[kbk][r] = -INFINITY;
-      }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  __builtin_amdgcn_s_setprio(2);   // the matrix-core-bound stage wins issue arbitration over the other wave
-  constexpr int NS = 4 * C::MB;    // slices
-  constexpr int NI = C::NI;
-  unsigned char* const v_dst = Vbuf + ((kt + 1) & 1) * C::TILE + cx.w * kBlock * C::RB;   // this wave's rows of V(kt+1)
-  unsigned char* const k_dst = Kbuf + (kt & 1) * C::TILE + cx.w * kBlock * C::RB;         // and of K(kt+2)
-  const unsigned lds_v = cx.lds_base + (2 + ((kt + 1) & 1)) * C::TILE + cx.w * kBlock * C::RB;
-  const unsigned lds_k = cx.lds_base + (kt & 1) * C::TILE + cx.w * kBlock * C::RB;
-  unsigned char* const stage = smem + 4 * C::TILE + cx.w * C::STAGE;
-  const unsigned lds_stage = cx.lds_base + 4 * C::TILE + cx.w * C::STAGE;
-  uint4 st[2];                     // staged pieces on their way through the registers
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    const int m = i / C::MB, mb = i % C::MB;
-    if (i + 2 < NS) va[(i + 2) % 3] = read_vt<D>(cx, vb, (i + 2) / C::MB, (i + 2) % C::MB);
-    __builtin_amdgcn_sched_barrier(0);
-    O[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[i % 3], pb[m].v, O[mb], 0, 0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (NEXT) {   // the last tile of an item has nothing left to fetch
-      if constexpr (!KV8) {
-        if (i < NI) {
-          // (only a tile that needs the causal mask can reach past the last token)
-          switch (i) {
-            case 0: fetch_v<D, false, 0, MASKNEXT>(cx, boff, tv, lds_v); break;
-            case 1: fetch_v<D, false, (NI > 1 ? 1 : 0), MASKNEXT>(cx, boff, tv, lds_v); break;
-            case 2: fetch_v<D, false, (NI > 2 ? 2 : 0), MASKNEXT>(cx, boff, tv, lds_v); break;
-            case 3: fetch_v<D, false, (NI > 2 ? 3 : 0), MASKNEXT>(cx, boff, tv, lds_v); break;
-          }
-        } else if (i < 2 * NI) {
-          if (i == NI) boff = block_offset(cx, sel, tk);
-          switch (i - NI) {
-            case 0: fetch_k<D, false, 0>(cx, boff, lds_k); break;
-            case 1: fetch_k<D, false, (NI > 1 ? 1 : 0)>(cx, boff, lds_k); break;
-            case 2: fetch_k<D, false, (NI > 2 ? 2 : 0)>(cx, boff, lds_k); break;
-            case 3: fetch_k<D, false, (NI > 2 ? 3 : 0)>(cx, boff, lds_k); break;
-          }
-        }
-      } else {
-        // piece p = 0 .. 2 NI - 1 (K run, then V run): read in slice 2p, its halves widened in slices 2p+2 and 2p+3
-        if (i % 2 == 0 && i / 2 < 2 * NI) {
-          const int p = i / 2;
-          st[p & 1] = *reinterpret_cast<const uint4*>(stage + (p / NI) * C::BLK + (p % NI) * 1024 + 16 * cx.lane);
-        }
-        if (i >= 2 && (i - 2) / 2 < 2 * NI) {
-          const int p = (i - 2) / 2, half = i % 2;
-          const int r = C::RPI * (p % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR) + half;
-          const uint4& v = st[p & 1];
-          widen_to<D>(p < NI ? k_dst : v_dst, r, ch, p < NI ? k_swizzle<D>(r) : v_swizzle<D>(r), half ? v.z : v.x, half ? v.w : v.y);
-        }
-        // the staging area is free once its last piece sits in registers
-        constexpr int F = 4 * NI + 2 < NS - 2 * NI ? 4 * NI + 2 : NS - 2 * NI;
-        if (i >= F && i < F + 2 * NI) {
-          if (i == F) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-          const int q = i - F;
-          if (q == 0) fetch_v<D, true, 0, true>(cx, boff, tv, lds_stage + C::BLK);
-          if (NI > 1 && q == 1) fetch_v<D, true, (NI > 1 ? 1 : 0), true>(cx, boff, tv, lds_stage + C::BLK);
-          if (q == NI) { boff = block_offset(cx, sel, tk); fetch_k<D, true, 0>(cx, boff, lds_stage); }
-          if (NI > 1 && q == NI + 1) fetch_k<D, true, (NI > 1 ? 1 : 0)>(cx, boff, lds_stage);
-        }
-      }
-      // scores of the next tile, four at a time, spread over the last eight slices
-      if (i >= NS - 8) {
-        const int q = i - (NS - 8);
-        const int kbk = q >> 2, r0 = 4 * (q & 3);
-        // three-operand maxima written out (fmaxf() would first canonicalise every score with a v_max
-        // of its own), both in one statement so that nothing is put between them
-        asm volatile("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4"
-                     : "+v"(mx_acc)
-                     : "v"(Snext[kbk][r0]), "v"(Snext[kbk][r0 + 1]), "v"(Snext[kbk][r0 + 2]), "v"(Snext[kbk][r0 + 3]));
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  __builtin_amdgcn_s_setprio(0);
-  float mx_next = 0.0f;
-  if constexpr (NEXT) {
-    mx_next = half_max(mx_acc);
-  }
-  return mx_next;
+  });
+  t.l += sum[0] + sum[1];
 }
 
 // The same iteration for a wave that has no key left: the tiles behind its rows' positions are for the other row blocks
 // of the workgroup (groups of fewer than four heads), and it only fetches its cache blocks of them.  (Going through
 // them with every score masked would let 0 * Inf from their values into its rows.)
 template <int D, bool KV8>
-__device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, BlockIds& ids,
+__device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
                                            const int* bt, unsigned long long& boff) {
   using C = Cfg<D, KV8>;
   constexpr int NI = C::NI;
-  wait_vmem();
-  __syncthreads();
-  if (kt == ntiles - 1) return;
-  const int tv = min(kt + (KV8 ? 2 : 1), ntiles - 1), tk = min(kt + (KV8 ? 3 : 2), ntiles - 1);
-  if ((tk >> 4) > ids.grp + 1) {
-    ids.grp += 1;
-    ids.cur = ids.nxt;
-    ids.nxt = load_ids(bt, 64 * (ids.grp + 1), cx.lane, cx.last_blk);
-  }
-  const int sel = ((tk >> 4) == ids.grp) ? ids.cur : ids.nxt;
-  const unsigned rows = cx.w * kBlock * C::RB, vb = (2 + ((kt + 1) & 1)) * C::TILE + rows, kb = (kt & 1) * C::TILE + rows;
-  unsigned lds_v = cx.lds_base + vb, lds_k = cx.lds_base + kb;
   if constexpr (KV8) {
-    const unsigned staged = 4 * C::TILE + cx.w * C::STAGE;
+    const unsigned v_dst = v_rows<D, KV8>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8>(cx, kt & 1), stage = staged<D, KV8>(cx);
+    wait_vmem();
 #pragma unroll
     for (int q = 0; q < 2 * NI; ++q) {
-      const uint4 st = *reinterpret_cast<const uint4*>(smem + staged + (q / NI) * C::BLK + (q % NI) * 1024 + 16 * cx.lane);
+      const uint4 st = *reinterpret_cast<const uint4*>(smem + stage + (q / NI) * C::BLK + (q % NI) * 1024 + 16 * cx.lane);
       const int r = C::RPI * (q % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR);
-      unsigned char* const dst = smem + (q < NI ? kb : vb);
-      const int swz = q < NI ? k_swizzle<D>(r) : v_swizzle<D>(r);
-      widen_to<D>(dst, r, ch, swz, st.x, st.y);
-      widen_to<D>(dst, r, ch + 1, swz, st.z, st.w);
+      if (q < NI) {
+        widen_to_k<D>(smem + k_dst, r, ch, st.x, st.y);
+        widen_to_k<D>(smem + k_dst, r, ch + 1, st.z, st.w);
+      } else {
+        widen_to_v<D>(smem + v_dst, r, ch, st.x, st.y);
+        widen_to_v<D>(smem + v_dst, r, ch + 1, st.z, st.w);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
+    const unsigned long long next = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
+    id = load_id(cx, bt, kt + 4);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the staging area is free
-    lds_k = cx.lds_base + staged;
-    lds_v = lds_k + C::BLK;
+    fetch_v_tile<D, true>(cx, boff, cx.lds_base + stage + C::BLK);
+    boff = next;
+    fetch_k_tile<D, true>(cx, boff, cx.lds_base + stage);
+    tile_barrier<true>();
+  } else {
+    const unsigned long long next = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
+    id = load_id(cx, bt, kt + 3);
+    fetch_v_tile<D, false>(cx, boff, cx.lds_base + v_rows<D, KV8>(cx, (kt + 1) & 1));
+    boff = next;
+    fetch_k_tile<D, false>(cx, boff, cx.lds_base + k_rows<D, KV8>(cx, kt & 1));
+    tile_barrier<false>();
   }
-  fetch_v<D, KV8, 0, true>(cx, boff, tv, lds_v);
-  if constexpr (NI > 1) fetch_v<D, KV8, 1, true>(cx, boff, tv, lds_v);
-  if constexpr (NI > 2) { fetch_v<D, KV8, 2, true>(cx, boff, tv, lds_v); fetch_v<D, KV8, 3, true>(cx, boff, tv, lds_v); }
-  boff = block_offset(cx, sel, tk);
-  fetch_k<D, KV8, 0>(cx, boff, lds_k);
-  if constexpr (NI > 1) fetch_k<D, KV8, 1>(cx, boff, lds_k);
-  if constexpr (NI > 2) { fetch_k<D, KV8, 2>(cx, boff, lds_k); fetch_k<D, KV8, 3>(cx, boff, lds_k); }
 }
 
-// mine: tiles up to the position of the wave's last row.  SHARED: that can be fewer than the workgroup's.
-template <int D, bool KV8, bool SHARED, bool PROBE>
-__device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, int mine, int n_nomask, BlockIds& ids,
-                                          unsigned long long& boff, const bf16x8 (&qf)[D / 16], f32x16 (&O)[D / 32],
-                                          float& m_run, float& l_run, float (&am)[kMaxSpans],
-                                          const int (&sp_a)[kMaxSpans], const int (&sp_b)[kMaxSpans], const int* bt) {
-  // The lane values are made opaque here: what is derived from them would otherwise be computed once for both
-  // instantiations (probing or not) and spilled (57 registers, some of them in the loop) instead of recomputed.
-  WaveCtx cy = cx;
-  asm volatile("" : "+v"(cy.k_read_addr), "+v"(cy.v_read_addr), "+v"(cy.pos), "+v"(cy.k_off), "+v"(cy.v_off), "+v"(cy.hf), "+v"(cy.lane));
-  f32x16 S0[2], S1[2];
-  qk_tile<D>(cy, smem, qf, S0);
+// This wave's rows past the last token of the V buffer that holds the last tile.
+template <int D, bool KV8>
+__device__ __forceinline__ void clear_past_end(const WaveCtx& cx, unsigned char* smem, int kt) {
+  constexpr int RB = Cfg<D, KV8>::RB, CH = Cfg<D, KV8>::CH;
+  const int first = cx.L - (kTileKeys * kt + kBlock * cx.w);      // first row of this wave's 16 past the end
+  unsigned char* const rows = smem + v_rows<D, KV8>(cx, kt & 1);
 #pragma unroll
-  for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-    for (int rr = 0; rr < 16; ++rr) O[mb][rr] = 0.0f;
-  m_run = -INFINITY;
-  l_run = 0.0f;
-#pragma unroll
-  for (int s = 0; s < kMaxSpans; ++s) am[s] = 0.0f;
-  float mx = (n_nomask > 0) ? tile_max<false>(cy, 0, S0) : tile_max<true>(cy, 0, S0);
+  for (int j = 0; j < kBlock * CH / 64; ++j) {
+    const int r = (64 / CH) * j + cx.lane / CH;
+    if (r >= first) *reinterpret_cast<uint4*>(rows + r * RB + 16 * (cx.lane % CH)) = make_uint4(0, 0, 0, 0);
+  }
+}
 
-  // tile kt+1 needs no mask while kt+1 < n_nomask
+// What is left once all K and V tiles lie in LDS: the last tile's second half and P V of both.
+template <int D, bool KV8, bool PROBE>
+__device__ __forceinline__ void last_tile(const WaveCtx& cx, int kt, Pipe<D>& t, float m, int pos_max, Spans& sp) {
+  using C = Cfg<D, KV8>;
+  constexpr int R = C::RING, NP = 2 * C::MB, EPS = 16 / NP;
+  const int key0 = kTileKeys * kt + 32;
+  const bool second = key0 <= pos_max;            // some row sees keys of the second half
+  HalfExp h;
+  if (second) {
+    mask_half(cx, key0, t.S[1]);
+    exp_begin<EPS>(cx, t.S[1], m, h);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<NP>([&](auto slot) {
+    constexpr int n = slot;
+    t.O[n % C::MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.va[n % R], as_bf16x8(t.P[0][n / C::MB]), t.O[n % C::MB], 0, 0, 0);
+    t.va[n % R] = read_vt<D>(t.v_addr, (n + R) / C::MB, (n + R) % C::MB);
+    if (second) exp_slot<EPS>(cx, t.S[1], m, h, t.P[1], n);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  if (!second) return;
+  const float sum = exp_end<EPS>(t.S[1], h, t.P[1]);
+  t.l += sum;
+  if constexpr (PROBE) add_spans<D>(cx, sp, key0, t.S[1], sum, t.am);
+  __builtin_amdgcn_sched_barrier(0);
+  static_for<NP>([&](auto slot) {
+    constexpr int n = NP + slot;
+    t.O[n % C::MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(t.va[n % R], as_bf16x8(t.P[1][(n - NP) / C::MB]), t.O[n % C::MB], 0, 0, 0);
+    if (n + R < 2 * NP) t.va[n % R] = read_vt<D>(t.v_addr, (n + R) / C::MB, (n + R) % C::MB);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+// The first tile's scores, on which the softmax reference of each row rests (`m`: the row's maximum in them, and it stays
+// that; row_alone deals with rows whose later scores are far above it), and the probabilities of its first half.
+// On entry K(0) lies in LDS; V(0) and K(1) are on their way, and there on return.
+template <int D, bool KV8>
+__device__ __forceinline__ void first_half(const WaveCtx& cx, const bf16x8 (&qf)[D / 16], Pipe<D>& t, float& m) {
+  using C = Cfg<D, KV8>;
+  constexpr int EPS = 16 / C::SLOTS;
+  // K reads: lane (row qi [+32], half hf) reads chunk 2s + hf of a 64-dimension part
+  const int qi = cx.lane & 31;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) t.k_addr[s] = cx.lds_base + (unsigned)(qi >> 4) * C::KBLK + (unsigned)(qi & 15) * 128 + ((unsigned)((2 * s + cx.hf) ^ k_swizzle(qi)) << 4);
+  {
+    // transposed V reads: within a 16-lane group lane s supplies row (s >> 2) and 8-byte piece (s & 3)
+    const int g = cx.lane >> 4, s16 = cx.lane & 15;
+    const int hfv = g >> 1, ddhalf = g & 1;
+    const unsigned rowc = (unsigned)(4 * hfv + (s16 >> 2)) * C::RB;
+    const unsigned lowc = (unsigned)(2 * ddhalf + ((s16 & 3) >> 1)) * 16 + (unsigned)(s16 & 1) * 8;
+    const unsigned xorc = (unsigned)v_swizzle<D>(s16 >> 2) * 16;
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb) t.v_addr[mb] = cx.lds_base + 2 * C::TILE + ((rowc | (lowc ^ xorc)) ^ (64u * mb));
+  }
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t.S[half][r] = 0.0f;
+  }
+#pragma unroll
+  for (int s = 0; s < C::KSTEPS; ++s)
+#pragma unroll
+    for (int half = 0; half < 2; ++half)
+      t.S[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D, KV8>(t.k_addr, s, half), qf[s], t.S[half], 0, 0, 0);
+  if (31 > cx.pos_min) mask_half(cx, 0, t.S[0]);
+  if (63 > cx.pos_min) mask_half(cx, 32, t.S[1]);
+  float mx = fmaxf(t.S[0][0], t.S[1][0]);
+#pragma unroll
+  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(t.S[0][r], t.S[1][r]));
+  mx = half_max(mx) * cx.c;
+  m = mx == -INFINITY ? 0.0f : mx;
+  HalfExp h;
+  exp_begin<EPS>(cx, t.S[0], m, h);
+#pragma unroll
+  for (int j = 0; j < C::SLOTS; ++j) exp_slot<EPS>(cx, t.S[0], m, h, t.P[0], j);
+  t.l = exp_end<EPS>(t.S[0], h, t.P[0]);
+  // V(0) and K(1) (8-bit caches: they were there before, but every wave has to be done with K(0))
+  if constexpr (!KV8) wait_vmem();
+  __syncthreads();
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    t.k_addr[s] += C::TILE;
+    asm volatile("" : "+v"(t.k_addr[s]));       // (in registers of their own)
+    if (s < C::MB) asm volatile("" : "+v"(t.v_addr[s]));
+  }
+#pragma unroll
+  for (int n = 0; n < C::RING; ++n) {
+    t.ka[n] = read_k<D, KV8>(t.k_addr, n, 0);
+    t.va[n] = read_vt<D>(t.v_addr, n / C::MB, n % C::MB);
+  }
+}
+
+// All that follows.  mine: tiles up to the position of the wave's last row, pos_max.  SHARED: that can be fewer than the
+// workgroup's.
+template <int D, bool KV8, bool SHARED, bool PROBE>
+__device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, int mine, int pos_max, int id,
+                                          unsigned long long& boff, const bf16x8 (&qf)[D / 16], Pipe<D>& t, float& m,
+                                          Spans& sp, const int* bt) {
+  using C = Cfg<D, KV8>;
+  // The lane values are made opaque here: what is derived from them would otherwise be computed once for both
+  // instantiations (probing or not) and spilled instead of recomputed.
+  WaveCtx cy = cx;
+  asm volatile("" : "+v"(cy.pos), "+v"(cy.k_off[0]), "+v"(cy.v_off[0]), "+v"(cy.hf), "+v"(cy.lane));
+  cy.v_off[1] = cy.v_off[0];
+  if constexpr (KV8) cy.k_off[1] = cy.k_off[0];
+  else asm volatile("" : "+v"(cy.k_off[1]), "+v"(cy.k_off[2]), "+v"(cy.k_off[3]));
+#pragma unroll
+  for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t.O[mb][r] = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kMaxSpans; ++s) t.am[s] = 0.0f;
+  first_half<D, KV8>(cy, qf, t, m);
+  if constexpr (PROBE) add_spans<D>(cy, sp, 0, t.S[0], t.l, t.am);
+  __builtin_amdgcn_sched_barrier(0);
+  const int full = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
   int kt = 0;
-  const int end_nomask = min(n_nomask - 1, ntiles - 1);
-  // two tiles per trip so the score registers ping-pong without copies
-  while (kt + 2 <= end_nomask) {
-    mx = tile_iter<D, KV8, false, true, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
-                                               l_run, am, sp_a, sp_b);
-    mx = tile_iter<D, KV8, false, true, PROBE>(cy, smem, kt + 1, ntiles, ids, bt, boff, S1, mx, S0, qf, O,
-                                               m_run, l_run, am, sp_a, sp_b);
-    kt += 2;
+  for (; kt < full; ++kt) tile_iter<D, KV8, PROBE>(cy, smem, kt, ntiles, id, bt, boff, t, m, qf, sp);
+  if (SHARED)
+    for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8>(cy, smem, kt, ntiles, id, bt, boff);
+  if (kTileKeys * ntiles > cy.L) {        // (the same for all waves)
+    clear_past_end<D, KV8>(cy, smem, ntiles - 1);
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < C::RING; ++n) t.va[n] = read_vt<D>(t.v_addr, n / C::MB, n % C::MB);
   }
-  if (kt < end_nomask) {
-    mx = tile_iter<D, KV8, false, true, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
-                                               l_run, am, sp_a, sp_b);
-    S0[0] = S1[0]; S0[1] = S1[1];
-    kt += 1;
-  }
-  // tiles whose successor needs the causal mask
-  const int fetching = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
-  while (kt < fetching) {
-    mx = tile_iter<D, KV8, true, true, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
-                                              l_run, am, sp_a, sp_b);
-    S0[0] = S1[0]; S0[1] = S1[1];
-    kt += 1;
-  }
-  if (SHARED && mine < ntiles) {
-    for (; kt < ntiles; ++kt) fetch_iter<D, KV8>(cy, smem, kt, ntiles, ids, bt, boff);
-    return;
-  }
-  // last tile
-  (void)tile_iter<D, KV8, true, false, PROBE>(cy, smem, kt, ntiles, ids, bt, boff, S0, mx, S1, qf, O, m_run,
-                                              l_run, am, sp_a, sp_b);
+  if (!SHARED || mine == ntiles) last_tile<D, KV8, PROBE>(cy, kt, t, m, pos_max, sp);
 }
 
 // The first tiles of an item into the LDS buffers.  16-bit: K(0) is requested here, V(0) and K(1) by the second
@@ -547,84 +609,262 @@ __device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned char* sm
                                             unsigned long long boff1, unsigned long long boff2) {
   using C = Cfg<D, KV8>;
   constexpr int NI = C::NI;
-  const unsigned lds_k = cx.lds_base + cx.w * kBlock * C::RB;                    // this wave's rows of K buffer 0
   if constexpr (!KV8) {
-    fetch_k<D, false, 0>(cx, boff0, lds_k);
-    if constexpr (NI > 1) fetch_k<D, false, 1>(cx, boff0, lds_k);
-    if constexpr (NI > 2) { fetch_k<D, false, 2>(cx, boff0, lds_k); fetch_k<D, false, 3>(cx, boff0, lds_k); }
+    fetch_k_tile<D, false>(cx, boff0, cx.lds_base + k_rows<D, KV8>(cx, 0));
   } else {
     // through registers: nothing to overlap with yet
-    const int t1 = min(1, ntiles - 1);
-    const int rmax = cx.L - 1 - kBlock * min(cx.w, cx.last_blk);
     uint4 k0[NI], v0[NI], k1[NI];
 #pragma unroll
     for (int jj = 0; jj < NI; ++jj) {
       const int r = C::RPI * jj + cx.lane / C::LPR;
       const unsigned piece = 16 * (cx.lane % C::LPR);
       k0[jj] = load_global16((global_bytes)(cx.kbase + boff0 + r * D + piece));
-      v0[jj] = load_global16((global_bytes)(cx.vbase + boff0 + min(r, rmax) * D + piece));
+      v0[jj] = load_global16((global_bytes)(cx.vbase + boff0 + r * D + piece));
       k1[jj] = load_global16((global_bytes)(cx.kbase + boff1 + r * D + piece));
     }
     // V(1), then K(2): the order in which the loop fetches
-    const unsigned lds_stage = cx.lds_base + 4 * C::TILE + cx.w * C::STAGE;
-    fetch_v<D, true, 0, true>(cx, boff1, t1, lds_stage + C::BLK);
-    if constexpr (NI > 1) fetch_v<D, true, 1, true>(cx, boff1, t1, lds_stage + C::BLK);
-    fetch_k<D, true, 0>(cx, boff2, lds_stage);
-    if constexpr (NI > 1) fetch_k<D, true, 1>(cx, boff2, lds_stage);
-    unsigned char* const kd = smem + cx.w * kBlock * C::RB;
+    const unsigned lds_stage = cx.lds_base + staged<D, KV8>(cx);
+    fetch_v_tile<D, true>(cx, boff1, lds_stage + C::BLK);
+    fetch_k_tile<D, true>(cx, boff2, lds_stage);
+    unsigned char* const kd = smem + k_rows<D, KV8>(cx, 0);
+    unsigned char* const vd = smem + v_rows<D, KV8>(cx, 0);
 #pragma unroll
     for (int jj = 0; jj < NI; ++jj) {
       const int r = C::RPI * jj + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR);
-      widen_to<D>(kd, r, ch, k_swizzle<D>(r), k0[jj].x, k0[jj].y);
-      widen_to<D>(kd, r, ch + 1, k_swizzle<D>(r), k0[jj].z, k0[jj].w);
-      widen_to<D>(kd + 2 * C::TILE, r, ch, v_swizzle<D>(r), v0[jj].x, v0[jj].y);
-      widen_to<D>(kd + 2 * C::TILE, r, ch + 1, v_swizzle<D>(r), v0[jj].z, v0[jj].w);
-      widen_to<D>(kd + C::TILE, r, ch, k_swizzle<D>(r), k1[jj].x, k1[jj].y);
-      widen_to<D>(kd + C::TILE, r, ch + 1, k_swizzle<D>(r), k1[jj].z, k1[jj].w);
+      widen_to_k<D>(kd, r, ch, k0[jj].x, k0[jj].y);
+      widen_to_k<D>(kd, r, ch + 1, k0[jj].z, k0[jj].w);
+      widen_to_v<D>(vd, r, ch, v0[jj].x, v0[jj].y);
+      widen_to_v<D>(vd, r, ch + 1, v0[jj].z, v0[jj].w);
+      widen_to_k<D>(kd + C::TILE, r, ch, k1[jj].x, k1[jj].y);
+      widen_to_k<D>(kd + C::TILE, r, ch + 1, k1[jj].z, k1[jj].w);
     }
   }
 }
 
 template <int D, bool KV8>
 __device__ __forceinline__ void rest_of_first_tiles(const WaveCtx& cx, unsigned long long boff0, unsigned long long boff1) {
-  using C = Cfg<D, KV8>;
   if constexpr (!KV8) {
-    constexpr int NI = C::NI;
-    const unsigned lds_k = cx.lds_base + cx.w * kBlock * C::RB;
-    const unsigned lds_v = lds_k + 2 * C::TILE;
-    fetch_v<D, false, 0, true>(cx, boff0, 0, lds_v);
-    if constexpr (NI > 1) fetch_v<D, false, 1, true>(cx, boff0, 0, lds_v);
-    if constexpr (NI > 2) { fetch_v<D, false, 2, true>(cx, boff0, 0, lds_v); fetch_v<D, false, 3, true>(cx, boff0, 0, lds_v); }
-    fetch_k<D, false, 0>(cx, boff1, lds_k + C::TILE);
-    if constexpr (NI > 1) fetch_k<D, false, 1>(cx, boff1, lds_k + C::TILE);
-    if constexpr (NI > 2) { fetch_k<D, false, 2>(cx, boff1, lds_k + C::TILE); fetch_k<D, false, 3>(cx, boff1, lds_k + C::TILE); }
+    fetch_v_tile<D, false>(cx, boff0, cx.lds_base + v_rows<D, KV8>(cx, 0));
+    fetch_k_tile<D, false>(cx, boff1, cx.lds_base + k_rows<D, KV8>(cx, 1));
   }
 }
 
+// Raw, masked scores of the half tile at key0, straight from the cache.
+template <int D, bool KV8>
+__device__ __forceinline__ f32x16 scores_from_cache(const WaveCtx& cx, const int* bt, int key0, const bf16x8 (&qf)[D / 16]) {
+  constexpr int E = KV8 ? 1 : 2;
+  const int key = key0 + (cx.lane & 31);
+  const int blk = bt[min(key >> 4, cx.last_blk)];
+  const global_bytes row = (global_bytes)(cx.kbase + (KV8 ? 0 : 2048) + block_bytes(cx, blk) + (key & 15) * (D * E) + 8 * E * cx.hf);
+  f32x16 S;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) S[r] = 0.0f;
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    uint4 a;
+    if constexpr (KV8) {
+      const u32x2 b = *(const __attribute__((address_space(1))) u32x2*)(row + 16 * s);
+      a = e4m3x8_to_bf16x8(make_uint2(b.x, b.y));
+    } else {
+      a = load_global16(row + 32 * s);
+    }
+    bf16x8 av;
+    __builtin_memcpy(&av, &a, 16);
+    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qf[s], S, 0, 0, 0);
+  }
+  mask_half(cx, key0, S);
+  return S;
+}
+
 // One work item: rows [row0, row0 + rows_per_wg) of sequence `seq` (context L, n rows, first q row
-// qbase) for the heads of (kvh, hg).  ZERO_REST (self-planned calls): the wave that owns a probed
+// qbase) for the heads of (kvh, hg).
+struct Item { int kvh, hg, seq, row0, L, n, qbase; };
+
+// What a wave knows about its part of an item beyond WaveCtx.
+struct WaveItem {
+  int ntiles, mine, pos_max, head, wrow0;
+  bool active;
+  int pslot, qsel_b, qsel_e;      // probed head's place in the list (-1: not probed), selected rows
+};
+
+// Normalise, transpose through LDS (16-byte chunks swizzled by row; each wave in rows of its own of the K buffers, which
+// are free), coalesced stores; the span sums.  rows: bit per row of the wave that is to be written.
+template <int D, bool KV8, bool PROBE>
+__device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi, const WaveCtx& cx,
+                                       const Spans& sp, const Pipe<D>& t, float l_tot, unsigned rows) {
+  using C = Cfg<D, KV8>;
+  const float inv_l = 1.0f / l_tot;
+  const float inv = KV8 ? inv_l * p.v_scale[it.kvh] : inv_l;     // `out` carries the value scale, `mass` does not
+  unsigned char* const ot = smem + cx.w * (kWaveRows * C::RB);
+  const int qi = cx.lane & 31;
+#pragma unroll
+  for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+    for (int g4 = 0; g4 < 4; ++g4) {
+      uint2 v;
+      v.x = pack_bf16(t.O[mb][4 * g4] * inv, t.O[mb][4 * g4 + 1] * inv);
+      v.y = pack_bf16(t.O[mb][4 * g4 + 2] * inv, t.O[mb][4 * g4 + 3] * inv);
+      const int ch = 4 * mb + g4;
+      *reinterpret_cast<uint2*>(ot + qi * C::RB + ((ch ^ out_swizzle<D>(qi)) << 4) + 8 * cx.hf) = v;
+    }
+  __bf16* const og = static_cast<__bf16*>(p.out);
+#pragma unroll
+  for (int j = 0; j < C::CH / 2; ++j) {
+    const int rr = cx.lane / C::CH + (64 / C::CH) * j;
+    const int ch = cx.lane % C::CH;
+    const int tr = wi.wrow0 + rr;
+    if (rows >> rr & 1) {
+      const uint4 v = *reinterpret_cast<const uint4*>(ot + rr * C::RB + ((ch ^ out_swizzle<D>(rr)) << 4));
+      *reinterpret_cast<uint4*>(og + ((size_t)(it.qbase + tr) * p.Hq + wi.head) * D + 8 * ch) = v;
+    }
+  }
+  if constexpr (PROBE) {
+#pragma unroll
+    for (int s = 0; s < kMaxSpans; ++s) {
+      if (s < sp.n) {
+        const float a_tot = t.am[s] + __shfl_xor(t.am[s], 32);
+        const int tr = wi.wrow0 + qi;
+        if (cx.hf == 0 && (rows >> qi & 1) && tr >= wi.qsel_b && tr < wi.qsel_e)
+          p.mass[(((size_t)it.seq * p.P + wi.pslot) * p.NQ + (tr - wi.qsel_b)) * p.S + s] = a_tot * inv_l;
+      }
+    }
+  }
+}
+
+// A row's sums are exact under any reference that keeps them finite.  It is done over, from its true maximum, if later
+// scores lie 2^64 above its first tile's, or if its output is not finite although large values alone are no reason for
+// that (with sums below 2^8 they are).
+template <int D>
+__device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
+  bool again = !(l_tot < 0x1p64f);
+  if (__builtin_amdgcn_ballot_w64(l_tot >= 0x1p8f) != 0) {
+    float zs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) zs[r & 3] = __builtin_fmaf(t.O[mb][r], 0.0f, zs[r & 3]);
+    float z = (zs[0] + zs[1]) + (zs[2] + zs[3]);
+    z += __shfl_xor(z, 32);
+    again = again || (l_tot >= 0x1p8f && !(z == 0.0f));
+  }
+  return again;
+}
+
+// The wave's rows from their true maxima, without the other waves: keys straight from the cache, values through the rows of
+// LDS that its output passed through.  Rows that need it are rare, so this is short rather than fast.
+template <int D, bool KV8>
+__device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
+                                           const WaveCtx& cx, Spans& sp, const int* bt, unsigned rows) {
+  using C = Cfg<D, KV8>;
+  constexpr int E = KV8 ? 1 : 2, LPR = D / 8, RPL = 64 / LPR;      // lanes per row, rows per load (eight values to a lane)
+  bf16x8 qf[C::KSTEPS];
+  {
+    const int t = wi.wrow0 + min(cx.lane & 31, it.n - 1 - wi.wrow0);
+    const __bf16* const qg = static_cast<const __bf16*>(p.q) + ((size_t)(it.qbase + t) * p.Hq + wi.head) * D + 8 * cx.hf;
+#pragma unroll
+    for (int s = 0; s < C::KSTEPS; ++s) {
+      const uint4 v = load_global16((global_bytes)(unsigned long long)(size_t)(qg + 16 * s));
+      __builtin_memcpy(&qf[s], &v, 16);
+    }
+  }
+  float m = -INFINITY;
+  for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
+    const f32x16 S = scores_from_cache<D, KV8>(cx, bt, key0, qf);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m = fmaxf(m, S[r] * cx.c);
+  }
+  m = half_max(m);
+  if (m == -INFINITY) m = 0.0f;
+  sp.lo = 0;
+  Pipe<D> t;
+  t.l = 0.0f;
+#pragma unroll
+  for (int s = 0; s < kMaxSpans; ++s) t.am[s] = 0.0f;
+#pragma unroll
+  for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) t.O[mb][r] = 0.0f;
+  unsigned char* const vrows = smem + cx.w * (kWaveRows * C::RB);
+  unsigned v_addr[4];
+  {
+    const int g = cx.lane >> 4, s16 = cx.lane & 15;
+    const unsigned a = (4 * (g >> 1) + (s16 >> 2)) * C::RB + (((2 * (g & 1) + ((s16 & 3) >> 1)) ^ v_swizzle<D>(s16 >> 2)) << 4) + 8 * (s16 & 1);
+#pragma unroll
+    for (int mb = 0; mb < C::MB; ++mb) v_addr[mb] = cx.lds_base + cx.w * (kWaveRows * C::RB) + (a ^ (64u * mb));
+  }
+  for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
+#pragma unroll
+    for (int j = 0; j < 32 / RPL; ++j) {
+      const int r = RPL * j + cx.lane / LPR, ch = cx.lane % LPR, key = key0 + r;
+      const int blk = bt[min(key >> 4, cx.last_blk)];
+      const global_bytes src = (global_bytes)(cx.vbase + block_bytes(cx, blk) + (key & 15) * (D * E) + 8 * E * ch);
+      uint4 v;
+      if constexpr (KV8) {
+        const u32x2 b = *(const __attribute__((address_space(1))) u32x2*)src;
+        v = e4m3x8_to_bf16x8(make_uint2(b.x, b.y));
+      } else {
+        v = load_global16(src);
+      }
+      if (key >= cx.L) v = make_uint4(0, 0, 0, 0);
+      *reinterpret_cast<uint4*>(vrows + r * C::RB + ((ch ^ v_swizzle<D>(r)) << 4)) = v;
+    }
+    f32x16 S = scores_from_cache<D, KV8>(cx, bt, key0, qf);
+    u32x4 P[2];
+    HalfExp h;
+    exp_begin<1>(cx, S, m, h);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) exp_slot<1>(cx, S, m, h, P, j);
+    const float sum = exp_end<1>(S, h, P);
+    t.l += sum;
+    add_spans<D>(cx, sp, key0, S, sum, t.am);
+#pragma unroll
+    for (int n = 0; n < 2 * C::MB; ++n)
+      t.O[n % C::MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_vt<D>(v_addr, n / C::MB, n % C::MB), as_bf16x8(P[n / C::MB]),
+                                                              t.O[n % C::MB], 0, 0, 0);
+  }
+  finish<D, KV8, true>(p, smem, it, wi, cx, sp, t, t.l + __shfl_xor(t.l, 32), rows);
+}
+
+template <int D, bool KV8, bool SHARED, bool PROBE>
+__device__ __forceinline__ unsigned tiles_and_output(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
+                                                     const WaveCtx& cx, int id, unsigned long long boff,
+                                                     const bf16x8 (&qf)[D / 16], Spans& sp, const int* bt) {
+  Pipe<D> t;
+  float m;
+  run_tiles<D, KV8, SHARED, PROBE>(cx, smem, wi.ntiles, wi.mine, wi.pos_max, id, boff, qf, t, m, sp, bt);
+  if constexpr (KV8) wait_vmem();   // (bytes that nobody waits for any more: no fetch may outlive its buffers)
+  const float l_tot = t.l + __shfl_xor(t.l, 32);
+  const unsigned rows = wi.active ? (unsigned)((1ull << min(kWaveRows, it.n - wi.wrow0)) - 1) : 0u;
+  if (wi.active) finish<D, KV8, PROBE>(p, smem, it, wi, cx, sp, t, l_tot, rows);
+  return rows & (unsigned)__builtin_amdgcn_ballot_w64(out_of_range<D>(t, l_tot));
+}
+
+// ZERO_REST (self-planned calls): the wave that owns a probed
 // head in the item of row 0 also writes zeros to that head's `mass` slots that hold no row, so that
 // every entry of `mass` is written exactly once without a planner's zero-fill.
 template <int D, bool KV8, bool SHARED, bool ZERO_REST>
-__device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem, int kvh, int hg, int seq,
-                                             int row0, int L, int n, int qbase) {
+__device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem, const Item& it) {
   using C = Cfg<D, KV8>;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int L = it.L, n = it.n;
   const int hh = w % p.hpw, rb = w / p.hpw;
-  const int head = kvh * p.G + hg * p.hpw + hh;
-  const int wrow0 = row0 + rb * kWaveRows;
-  const bool wave_active = wrow0 < n;
+  const int head = it.kvh * p.G + it.hg * p.hpw + hh;
+  const int wrow0 = it.row0 + rb * kWaveRows;
   const int qi = lane & 31, hf = lane >> 5;
   const int t = max(min(wrow0 + qi, n - 1), 0);
-  const int wave_pos_min = L - n + min(wrow0, n - 1);
-  const int wg_pos_max = L - n + min(row0 + p.rows_per_wg, n) - 1;
+  const int wg_pos_max = L - n + min(it.row0 + p.rows_per_wg, n) - 1;
   const int ntiles = wg_pos_max / kTileKeys + 1;
-  const int n_nomask = (wave_pos_min + 1) / kTileKeys;   // tiles whose last key is within every row's horizon
-  const int mine = (L - n + min(wrow0 + kWaveRows, n) - 1) / kTileKeys + 1;     // tiles with a key within some row's
+  WaveItem wi;
+  wi.ntiles = ntiles;
+  wi.pos_max = L - n + min(wrow0 + kWaveRows, n) - 1;
+  wi.mine = wi.pos_max / kTileKeys + 1;     // tiles with a key within some row's horizon
+  wi.head = head;
+  wi.wrow0 = wrow0;
+  wi.active = wrow0 < n;
 
-  const int* const bt = p.block_table + (size_t)seq * p.max_blocks;
+  const int* const bt = p.block_table + (size_t)it.seq * p.max_blocks;
   WaveCtx cx;
   cx.L = L;
   cx.last_blk = (L - 1) >> 4;
@@ -634,72 +874,72 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   // this wave's blocks of the first tiles by scalar loads: the wait for them leaves vector loads alone
   cx.num_blocks = p.num_blocks;
   auto first_id = [&](int tile) { return cload(bt, min(4 * min(tile, ntiles - 1) + w, cx.last_blk)); };
-  const int id0 = first_id(0), id1 = first_id(1), id2 = KV8 ? first_id(2) : 0;
+  const int id0 = first_id(0), id1 = first_id(1), id2 = first_id(2);
 
   // Query rows.  The compiler does not count the tile fetches (assembly), so its wait for these rows is a wait for
   // the fetches issued before it as well: only K(0) is (first_tiles / rest_of_first_tiles).
+  const int probe_list = p.P > 0 ? p.probe_heads[min(lane, p.P - 1)] : 0;
   uint4 qraw[C::KSTEPS];
   {
-    const __bf16* const qg = static_cast<const __bf16*>(p.q) + ((size_t)(qbase + t) * p.Hq + head) * D + 8 * hf;
+    const __bf16* const qg = static_cast<const __bf16*>(p.q) + ((size_t)(it.qbase + t) * p.Hq + head) * D + 8 * hf;
 #pragma unroll
     for (int s = 0; s < C::KSTEPS; ++s) qraw[s] = load_global16((global_bytes)(unsigned long long)(size_t)(qg + 16 * s));
   }
 
   cx.hf = hf;
-  cx.qi = qi;
   cx.pos = L - n + t;
-  cx.c = KV8 ? p.scale_log2 * p.k_scale[kvh] : p.scale_log2;
-  cx.S = p.S;
-  // K reads: lane (row qi [+32], half hf) reads logical chunk 2s + hf
-  cx.k_read_addr = (unsigned)qi * C::RB | ((unsigned)(hf ^ k_swizzle<D>(qi)) << 4);
-  {
-    // transposed V reads: within a 16-lane group lane s supplies row (s >> 2) and 8-byte piece (s & 3)
-    const int g = lane >> 4, s16 = lane & 15;
-    const int hfv = g >> 1, ddhalf = g & 1;
-    const unsigned rowc = (unsigned)(4 * hfv + (s16 >> 2)) * C::RB;
-    const unsigned lowc = (unsigned)(2 * ddhalf + ((s16 & 3) >> 1)) * 16 + (unsigned)(s16 & 1) * 8;
-    const unsigned xorc = (unsigned)v_swizzle<D>(s16 >> 2) * 16;
-    cx.v_read_addr = rowc | (lowc ^ xorc);
-  }
-  cx.kbase = (unsigned long long)(size_t)p.k_cache + (size_t)kvh * C::BLK;
-  cx.vbase = (unsigned long long)(size_t)p.v_cache + (size_t)kvh * C::BLK;
+  cx.pos_min = L - n + min(wrow0, n - 1);
+  cx.c = KV8 ? p.scale_log2 * p.k_scale[it.kvh] : p.scale_log2;
+  cx.kbase = (unsigned long long)(size_t)p.k_cache + (size_t)it.kvh * C::BLK;
+  cx.vbase = (unsigned long long)(size_t)p.v_cache + (size_t)it.kvh * C::BLK;
   // per-lane source offsets of the direct-to-LDS loads: LDS slot (row r, physical chunk pc)
   // receives logical chunk pc ^ swizzle(r); bytes are staged as they lie in the cache
   {
     const int r = lane / C::LPR, pc = lane % C::LPR;
     const unsigned row = (unsigned)r * (C::BLK / kBlock);
-    cx.k_off = row + (unsigned)(KV8 ? pc : pc ^ k_swizzle<D>(r)) * 16;
-    cx.v_off = row + (unsigned)(KV8 ? pc : pc ^ v_swizzle<D>(r)) * 16;
+    cx.v_off[0] = cx.v_off[1] = row + (unsigned)(KV8 ? pc : pc ^ v_swizzle<D>(r)) * 16;
+    if (KV8) {
+      cx.k_off[0] = cx.k_off[1] = row + (unsigned)pc * 16;
+    } else {
+      // (2048 more, which kbase is short of, so that none is negative)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int rk = 8 * (j & 1) + lane / 8;
+        cx.k_off[j] = (unsigned)rk * C::RB + (j >> 1) * 128 + (unsigned)((lane % 8) ^ k_swizzle(rk)) * 16 + 2048 - 1024 * j;
+      }
+      cx.kbase -= 2048;
+    }
   }
   cx.lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)smem;
 
-  BlockIds ids;
-  ids.grp = 0;
-  ids.cur = load_ids(bt, 0, lane, cx.last_blk);
-  ids.nxt = load_ids(bt, 64, lane, cx.last_blk);
-
+  int id = KV8 ? first_id(3) : id2;
+  asm("" : "+v"(id));
   const unsigned long long boff0 = block_bytes(cx, id0), boff1 = block_bytes(cx, id1), boff2 = block_bytes(cx, id2);
   first_tiles<D, KV8>(cx, smem, ntiles, boff0, boff1, boff2);
-  unsigned long long boff = KV8 ? boff2 : boff1;      // of the last K run fetched
 
-  int pslot = -1, qsel_b = 0, qsel_e = 0;
-  int sp_a[kMaxSpans], sp_b[kMaxSpans];
-#pragma unroll
-  for (int s = 0; s < kMaxSpans; ++s) { sp_a[s] = 0; sp_b[s] = 0; }
+  Spans sp;
+  sp.n = 0;
+  wi.pslot = -1;
+  wi.qsel_b = wi.qsel_e = 0;
   if (p.P > 0) {
-    pslot = find_probe_slot_uniform(p.probe_heads, p.P, head);
-    qsel_b = cload(p.query_sel, 2 * seq);
-    qsel_e = min(cload(p.query_sel, 2 * seq + 1), qsel_b + p.NQ);
-    load_spans_uniform(p.key_spans, seq, p.S, sp_a, sp_b);
+    wi.pslot = p.P <= 64 ? find_probe_slot_lanes(probe_list, p.P, head) : find_probe_slot_uniform(p.probe_heads, p.P, head);
+    wi.qsel_b = cload(p.query_sel, 2 * it.seq);
+    wi.qsel_e = min(cload(p.query_sel, 2 * it.seq + 1), wi.qsel_b + p.NQ);
+    sp.n = p.S;
+    load_spans_uniform(p.key_spans, it.seq, p.S, sp.a, sp.b);
   }
-  const bool wave_probe = wave_active && pslot >= 0 && qsel_b < min(wrow0 + kWaveRows, n) && qsel_e > wrow0;
-
-  f32x16 O[C::MB];
-  float m_run, l_run;
-  float am[kMaxSpans];
+  const bool wave_probe = wi.active && wi.pslot >= 0 && wi.qsel_b < min(wrow0 + kWaveRows, n) && wi.qsel_e > wrow0;
+  if (!wave_probe) sp.n = 0;
+  sp.lo = 0;
+  sp.hi = 0;
+#pragma unroll
+  for (int s = 0; s < kMaxSpans; ++s)
+    if (s < sp.n) {
+      sp.b[s] = max(sp.b[s], sp.a[s]);      // (an empty one stays empty)
+      sp.hi = max(sp.hi, sp.b[s]);
+    }
 
   // the first scores need Q and K(0); V(0) and K(1) (2 NI loads; with staging K(2) and V(1)) may stay in flight
-  // until the top of the first iteration
   bf16x8 qf[C::KSTEPS];
 #pragma unroll
   for (int s = 0; s < C::KSTEPS; ++s) __builtin_memcpy(&qf[s], &qraw[s], 16);
@@ -708,62 +948,16 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   rest_of_first_tiles<D, KV8>(cx, boff0, boff1);
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NI) : "memory");
   __syncthreads();
-
-  if (wave_probe)
-    run_tiles<D, KV8, SHARED, true>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
-  else
-    run_tiles<D, KV8, SHARED, false>(cx, smem, ntiles, mine, n_nomask, ids, boff, qf, O, m_run, l_run, am, sp_a, sp_b, bt);
-
-  // epilogue: normalise, transpose through LDS (16-byte chunks swizzled by row), coalesced stores
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const float inv_l = 1.0f / l_tot;
-  const float inv = KV8 ? inv_l * p.v_scale[kvh] : inv_l;     // `out` carries the value scale, `mass` does not
-  wait_vmem();   // the clamped fetches of the last iterations must have landed before LDS is reused
-  __syncthreads();
-  unsigned char* const ot = smem + w * (kWaveRows * C::RB);
-  if (wave_active) {
-#pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        uint2 v;
-        v.x = pack_bf16(O[mb][4 * g4] * inv, O[mb][4 * g4 + 1] * inv);
-        v.y = pack_bf16(O[mb][4 * g4 + 2] * inv, O[mb][4 * g4 + 3] * inv);
-        const int ch = 4 * mb + g4;
-        *reinterpret_cast<uint2*>(ot + qi * C::RB + ((ch ^ k_swizzle<D>(qi)) << 4) + 8 * hf) = v;
-      }
-  }
-  __syncthreads();
-  if (wave_active) {
-    __bf16* const og = static_cast<__bf16*>(p.out);
-#pragma unroll
-    for (int j = 0; j < C::CH / 2; ++j) {
-      const int rr = lane / C::CH + (64 / C::CH) * j;
-      const int ch = lane % C::CH;
-      const int tr = wrow0 + rr;
-      if (tr < n) {
-        const uint4 v = *reinterpret_cast<const uint4*>(ot + rr * C::RB + ((ch ^ k_swizzle<D>(rr)) << 4));
-        *reinterpret_cast<uint4*>(og + ((size_t)(qbase + tr) * p.Hq + head) * D + 8 * ch) = v;
-      }
-    }
-    if (wave_probe) {
-#pragma unroll
-      for (int s = 0; s < kMaxSpans; ++s) {
-        if (s < p.S) {
-          const float a_tot = am[s] + __shfl_xor(am[s], 32);
-          const int tr = wrow0 + qi;
-          if (hf == 0 && tr < n && tr >= qsel_b && tr < qsel_e)
-            p.mass[(((size_t)seq * p.P + pslot) * p.NQ + (tr - qsel_b)) * p.S + s] = a_tot * inv_l;
-        }
-      }
-    }
-  }
+  const unsigned long long boff = KV8 ? boff2 : boff1;      // of the last K run fetched
+  const unsigned again = wave_probe ? tiles_and_output<D, KV8, SHARED, true>(p, smem, it, wi, cx, id, boff, qf, sp, bt)
+                                    : tiles_and_output<D, KV8, SHARED, false>(p, smem, it, wi, cx, id, boff, qf, sp, bt);
+  if (__builtin_expect(again != 0, 0)) rows_alone<D, KV8>(p, smem, it, wi, cx, sp, bt, again);
   if constexpr (ZERO_REST) {
-    if (row0 == 0 && rb == 0 && pslot >= 0 && p.plan_fresh) {
-      const int lo = max(qsel_b, 0), hi = min(qsel_e, n);     // slots lo - qsel_b .. hi - qsel_b - 1 hold rows
+    if (it.row0 == 0 && rb == 0 && wi.pslot >= 0 && p.plan_fresh) {
+      const int lo = max(wi.qsel_b, 0), hi = min(wi.qsel_e, n);     // slots lo - qsel_b .. hi - qsel_b - 1 hold rows
       for (int e = lane; e < p.NQ * p.S; e += 64) {
-        const int tr = qsel_b + e / p.S;
-        if (tr < lo || tr >= hi) p.mass[((size_t)seq * p.P + pslot) * p.NQ * p.S + e] = 0.0f;
+        const int tr = wi.qsel_b + e / p.S;
+        if (tr < lo || tr >= hi) p.mass[((size_t)it.seq * p.P + wi.pslot) * p.NQ * p.S + e] = 0.0f;
       }
     }
   }
@@ -922,7 +1116,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     asm volatile("" :: "s"(it.x), "s"(it.y), "s"(it.z), "s"(it.w), "s"(qbase), "s"(nitems), "s"(p.block_table), "s"(p.q),
                  "s"(p.k_cache), "s"(p.v_cache));
     if (item >= nitems) return;
-    prefill_item<D, KV8, SHARED, false>(p, smem, kvh, hg, it.x, it.y, it.z, it.w, qbase);
+    prefill_item<D, KV8, SHARED, false>(p, smem, {kvh, hg, it.x, it.y, it.z, it.w, qbase});
   } else {
     if (bid == (int)gridDim.x - 1) {
       settle_chunks(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
@@ -932,7 +1126,7 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     const bool some = find_item(p, item, threadIdx.x & 63, it);
     asm volatile("" :: "s"(p.block_table), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache));
     if (!some) return;
-    prefill_item<D, KV8, SHARED, true>(p, smem, kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase);
+    prefill_item<D, KV8, SHARED, true>(p, smem, {kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase});
   }
 }
 
