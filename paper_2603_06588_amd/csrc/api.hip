@@ -16,12 +16,21 @@ constexpr size_t kAlign = 256;
 // than that and sorts better: 2 prompts of 200 tokens 16.2 us planned, 11.6 by themselves; 8 of 200-600 (800
 // workgroups) 31.6 and 29.3; 3 of 1500-2048 (1350 workgroups) 81.1 and 82.7.
 constexpr long long kSelfPlanMaxWgs = 1024;
+// Row blocks go to workgroups of eight waves (twice the rows, or all eight heads of a group, to each fetched tile) from this
+// many of those and so many rows to a sequence: two rounds of the compute units, and contexts deep enough to
+// pay for a start-up that no second workgroup covers.  Four waves and eight, 32 / 8 heads, us: 1 x 2048 43.1 and 48.5, 3000 75.9
+// and 78.8, 4096 131.8 and 124.6, 8192 474 and 459, 2 x 2048 75.8 and 75.9, 4 x 2048 143.0 and 139.6, 16 x 512-2048 243.7 and 241.2,
+// 4 x 1000-1500 behind 3000 tokens 304 and 286, but 16 x 200-600 47.5 and 52.3, 8 x 300-1000 46.8 and 47.0; 64 / 8 heads: 1 x 2048
+// 71.0 and 66.8, 8192 940 and 905, 8 x 300-1000 86.5 and 96.3.  (32 chunks of 64-200 rows behind 2000 tokens would
+// gain, 188.8 and 179.3, but the host sees rows and not depths.)
+constexpr long long kEightWaveMinWgs = 512;
+constexpr long long kEightWaveMinRows = 768;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
   size_t off_hdr, off_pf, off_dec, off_seq, off_part;
   size_t needed, reported;      // smallest workspace that is accepted; size to ask for
-  int pf_cap, dec_cap, ranges, hpw, rows_per_wg, hgroups, dec_hp, dec_hgroups;
+  int pf_cap, dec_cap, ranges, pf_waves, hpw, rows_per_wg, hgroups, dec_hp, dec_hgroups;
 };
 
 bool shapes_supported(const hook_attn_probe_args* a) {
@@ -106,13 +115,20 @@ size_t place(const hook_attn_probe_args* a, Layout& l) {
 Layout make_layout(const hook_attn_probe_args* a, size_t bytes) {
   Layout l{};
   const int G = a->num_q_heads / a->num_kv_heads;
+  l.pf_waves = 4;
   l.hpw = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
-  l.rows_per_wg = kWaveRows * (4 / l.hpw);
+  const int rows = kWaveRows * (4 / l.hpw);      // of a workgroup of four waves
+  if (a->head_dim == 128 && G % 4 == 0 && (long long)(a->total_q / (2 * rows)) * a->num_kv_heads * (G / 4) >= kEightWaveMinWgs &&
+      a->total_q >= kEightWaveMinRows * a->num_seqs) {
+    l.pf_waves = 8;
+    if (G % 8 == 0) l.hpw = 8;
+  }
+  l.rows_per_wg = kWaveRows * (l.pf_waves / l.hpw);
   l.hgroups = G / l.hpw;
   l.dec_hp = (G % 8 == 0) ? 8 : (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
   l.dec_hgroups = G / l.dec_hp;
   if (a->dtype == HOOK_BF16) {
-    l.pf_cap = a->total_q / l.rows_per_wg + a->num_seqs;
+    l.pf_cap = a->total_q / rows + a->num_seqs;
     l.dec_cap = decode_item_bound(a->num_seqs < a->total_q ? a->num_seqs : a->total_q,
                                   (long long)a->max_blocks_per_seq * kBlock, a->num_kv_heads * l.dec_hgroups);
     l.needed = l.reported = place(a, l);
@@ -235,7 +251,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.dec_cap = l.dec_cap;
   p.seq_dec = reinterpret_cast<int2*>(ws + l.off_seq);
   p.partials = reinterpret_cast<float*>(ws + l.off_part);
-  p.hpw = l.hpw; p.rows_per_wg = l.rows_per_wg; p.hgroups = l.hgroups;
+  p.pf_waves = l.pf_waves; p.hpw = l.hpw; p.rows_per_wg = l.rows_per_wg; p.hgroups = l.hgroups;
   p.dec_hp = l.dec_hp; p.dec_hgroups = l.dec_hgroups;
   p.batch_kind = a->batch_kind;
   // single rows of few sequences find their work themselves (make_layout), and so do row blocks while there are
@@ -244,7 +260,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.dec_ranges = streams ? l.ranges : 0;
   p.pf_self = a->dtype == HOOK_BF16 && a->num_seqs <= kScanMaxSeqs && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
               (streams || a->batch_kind == HOOK_BATCH_PREFILL_ONLY) &&
-              (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups <= kSelfPlanMaxWgs);
+              (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups * (l.pf_waves / 4) <= kSelfPlanMaxWgs);
   // The streaming kernel can do without a write ahead of it while a wave can hold every new row's place, one per lane.
   // (A launch ahead costs a call 4 us: 1 x 1237 tokens 16.6 us against 11.7, 8 x 4096 30.2 against 26.3, 64 x 2048 77.2
   // against 72.8.  Where to look would take more registers for more sequences, and the loop has none to spare.)

@@ -116,8 +116,9 @@ struct AttnParams {
   int pf_self;                      // the chunk kernel finds its row blocks itself, no planner
   // geometry chosen on the host from G
   int batch_kind;                   // 0 mixed, 1 no single-row sequences, 2 only single-row sequences
-  int hpw;                          // q heads per prefill workgroup (4, 2 or 1)
-  int rows_per_wg;                  // 32 * (4 / hpw)
+  int pf_waves;                     // waves of a prefill workgroup (4 or 8)
+  int hpw;                          // q heads per prefill workgroup (8, 4, 2 or 1)
+  int rows_per_wg;                  // 32 * (pf_waves / hpw)
   int hgroups;                      // G / hpw
   int dec_hp;                       // q heads per decode workgroup (8, 4, 2 or 1)
   int dec_hgroups;                  // G / dec_hp

@@ -1,11 +1,11 @@
 // Tiled causal attention for query chunks (n_i >= 2), bf16 MFMA, head_dim 64 and 128, 16-bit and 8-bit caches.
 //
-// Workgroup = 4 waves = (hpw q heads of one kv head) x (4 / hpw blocks of 32 query rows),
+// Workgroup = 4 or 8 waves = (hpw q heads of one kv head) x (waves / hpw blocks of 32 query rows),
 // all sharing the K/V tiles (64 keys = 4 cache blocks) of their kv head.  Data movement is built around two
 // gfx950 features:
 //   * K and V go from the paged cache straight into LDS with 16-byte direct-to-LDS loads, so staging
-//     costs no vector registers and almost no vector ALU work.  Wave w fetches cache block w of every
-//     tile: the block of a kv head is one contiguous run, so one block id, one 64-bit address and
+//     costs no vector registers and almost no vector ALU work.  Wave w of four fetches cache block w of every
+//     tile (two of eight waves half a block each): the block of a kv head is one contiguous run, so one block id, one 64-bit address and
 //     16 D bytes / 1 KB load instructions with constant offsets do it.  16-byte chunks are XOR-swizzled inside
 //     each LDS row so that the MFMA operand reads below are free of bank conflicts although rows are
 //     unpadded; K rows are kept as D / 64 parts of 128 bytes, so that four addresses reach every operand of a tile;
@@ -33,6 +33,17 @@
 // with two LDS buffers each.  (Fetches issued right behind the barrier instead of in the first slots of the next
 // iteration: 3-6 % slower, with branches or with lanes switched off where nothing is left to fetch.)
 //
+// Query rows come through LDS as well, requested in one go with the first tiles (a compiler that does not count the tile
+// fetches waits for all of them when it waits for rows loaded to registers).
+//
+// Eight waves share a tile's fetch where row blocks are deep and many (kEightWaveMinWgs in api.hip): half the fetches per
+// matrix instruction, which matters because the chip is at its power limit there (all fetches left out of a copy
+// of the kernel: 12 % less time on the 32 k prompt, 19 % on ragged prompts); a compute unit then holds one workgroup, whose
+// start-up nothing covers, so short contexts keep four.
+// (One workgroup per compute unit that goes from row block to row block, the next one's rows and tiles requested
+// during the last tile of the one before: 244 us against 242 on the ragged prompts; the cycles it saves come back as
+// a lower clock.  Three waves to a SIMD at head size 64: 149.5 -> 157.8 us.)
+//
 // 8-bit caches (KV8): the bytes go direct to LDS too, one tile earlier, into a staging area of each wave's own
 // (2 x 16 D bytes); in the tile before they are needed the wave reads its block back, widens it
 // to bf16 (exact: every E4M3 number is a bf16 number) and writes it to the same swizzled buffers as
@@ -54,7 +65,7 @@ namespace {
 
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 struct Cfg {
   static constexpr int RB = 2 * D;                          // bytes of one bf16 row
   static constexpr int TILE = kTileKeys * RB;
@@ -63,11 +74,18 @@ struct Cfg {
   static constexpr int MB = D / 32;                         // 32-dimension blocks of the output
   static constexpr int SLOTS = KSTEPS + 2 * MB;             // matrix instructions per half tile (scores and P V alternate)
   static constexpr int BLK = kBlock * D * (KV8 ? 1 : 2);    // bytes of one (cache block, kv head) run
-  static constexpr int NI = BLK / 1024;                     // load instructions per run
-  static constexpr int RPI = kBlock / NI;                   // rows per load instruction of a run fetched as it lies (V, bytes)
-  static constexpr int LPR = 64 / RPI;                      // lanes (16-byte pieces) per row of such a run
-  static constexpr int STAGE = KV8 ? 2 * BLK : 0;           // staging bytes per wave: K run, V run
-  static constexpr int LDS = 4 * TILE + 4 * STAGE;          // K[2], V[2], staging
+  static constexpr int WPB = NW / 4;                        // waves that share the fetch of a run
+  static constexpr int SHARE = BLK / WPB;                   // bytes of it for each
+  static constexpr int ROWS = kBlock / WPB;                 // rows of V (and of bytes) for each
+  static constexpr int NI = SHARE / 1024;                   // load instructions for each
+  static_assert(NI >= 1, "");
+  static constexpr int LPR = BLK / kBlock / 16;             // lanes (16-byte pieces) per row of a run fetched as it lies (V, bytes)
+  static constexpr int RPI = 64 / LPR;                      // rows per load instruction of 1 KB
+  static constexpr int STAGE = KV8 ? 2 * SHARE : 0;         // staging bytes per wave: of the K run, of the V run
+  static constexpr int QHALF = kBlock * RB;                 // half of a wave's query rows on their way through LDS (16-bit caches)
+  static constexpr int OUT = NW == 4 ? 0 : 4 * TILE + NW * STAGE;           // output rows: over the K buffers, or behind everything
+  // K[2], V[2], staging, query rows on their way in (eight waves: output rows on their way out)
+  static constexpr int LDS = 4 * TILE + NW * STAGE + (NW == 8 ? NW * 2 * QHALF : KV8 ? 0 : NW * QHALF);
   static constexpr int CH = D / 8;                          // 16-byte chunks per bf16 row
   static constexpr int RING = 4;                            // operands requested ahead, K and V^T each
 };
@@ -78,6 +96,10 @@ struct Cfg {
 __device__ __forceinline__ int k_swizzle(int r) { return (r >> 1) & 7; }
 template <int D> __device__ __forceinline__ int v_swizzle(int r) { return D == 128 ? ((r & 3) << 2) : (((r >> 1) & 1) << 2); }
 template <int D> __device__ __forceinline__ int out_swizzle(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+
+// A wave's own LDS accesses complete in order, so data that only passes through it from lane to lane needs no wait; but the
+// compiler has to leave them in order too (what is written as one type is read as another).
+__device__ __forceinline__ void in_order() { asm volatile("" ::: "memory"); }
 
 __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
@@ -111,6 +133,7 @@ struct WaveCtx {
   int num_blocks;
   unsigned k_off[4], v_off[2];  // this lane's source offsets in a run, less 1024 per load instruction before
   int L, last_blk, w, lane;
+  int wb, ws;             // the block of every tile that this wave fetches, which share of it
 };
 
 // lane l and lane l ^ 32 hold the two key halves of one query: maximum over both (one swap between
@@ -136,7 +159,7 @@ __device__ __forceinline__ unsigned long long block_bytes(const WaveCtx& cx, int
 // Id of this wave's block of a tile (past the last block: the last block again).  It is loaded an iteration before the
 // fetch that needs it, into a vector register: a scalar load would have every operand read from LDS wait for it.
 __device__ __forceinline__ int load_id(const WaveCtx& cx, const int* bt, int tile) {
-  int i = min(4 * tile + cx.w, cx.last_blk);
+  int i = min(4 * tile + cx.wb, cx.last_blk);
   asm("" : "+v"(i));
   return bt[i];
 }
@@ -145,45 +168,53 @@ __device__ __forceinline__ int load_id(const WaveCtx& cx, const int* bt, int til
 // 64-dimension part, rows 8 (J & 1) .. + 7 of part J >> 1; bytes: 1 KB of the run as it lies.  A K row past the last
 // token may hold anything: it only produces scores of keys beyond every row's horizon, which are overwritten with -inf
 // before use, and it still lies inside a block the sequence owns.
-template <int D, bool KV8, int J>
+template <int D, bool KV8, int NW, int J>
 __device__ __forceinline__ void fetch_k(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
-  dma16<(Cfg<D, KV8>::NI > 1 ? 2 : 1), 1024 * J>(cx.kbase + boff, cx.k_off + (KV8 ? 0 : J), lds);
+  using C = Cfg<D, KV8, NW>;
+  dma16<(C::NI > 1 ? 2 : 1), 1024 * J>(cx.kbase + boff, cx.k_off + (KV8 ? 0 : J), lds);
 }
 
 // The same of this wave's V run: 1 KB each as it lies.  Rows past the last token are cleared once they have landed
 // (clear_past_end): P is 0 there, and 0 * NaN would poison the output.
-template <int D, bool KV8, int J>
+template <int D, bool KV8, int NW, int J>
 __device__ __forceinline__ void fetch_v(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
-  dma16<(Cfg<D, KV8>::NI > 1 ? 2 : 1), 1024 * J>(cx.vbase + boff, cx.v_off, lds);
+  using C = Cfg<D, KV8, NW>;
+  dma16<(C::NI > 1 ? 2 : 1), 1024 * J>(cx.vbase + boff, cx.v_off, lds);
 }
 
 // whole runs
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void fetch_v_tile(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
-  fetch_v<D, KV8, 0>(cx, boff, lds);
-  if constexpr (Cfg<D, KV8>::NI > 2) fetch_v<D, KV8, 2>(cx, boff, lds);
+  fetch_v<D, KV8, NW, 0>(cx, boff, lds);
+  if constexpr (Cfg<D, KV8, NW>::NI > 2) fetch_v<D, KV8, NW, 2>(cx, boff, lds);
 }
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void fetch_k_tile(const WaveCtx& cx, unsigned long long boff, unsigned lds) {
-  fetch_k<D, KV8, 0>(cx, boff, lds);
-  if constexpr (Cfg<D, KV8>::NI > 2) fetch_k<D, KV8, 2>(cx, boff, lds);
+  fetch_k<D, KV8, NW, 0>(cx, boff, lds);
+  if constexpr (Cfg<D, KV8, NW>::NI > 2) fetch_k<D, KV8, NW, 2>(cx, boff, lds);
 }
 
-// LDS positions, in bytes from the start of the buffers: this wave's rows of K buffer `b` and V buffer `b`, its staging area
-template <int D, bool KV8> __device__ __forceinline__ unsigned k_rows(const WaveCtx& cx, int b) {
-  return b * Cfg<D, KV8>::TILE + cx.w * Cfg<D, KV8>::KBLK;
+// LDS positions, in bytes from the start of the buffers: this wave's share of K buffer `b` (8-bit caches: its block) and of V
+// buffer `b`, its staging area, its 32 rows of output
+template <int D, bool KV8, int NW> __device__ __forceinline__ unsigned k_rows(const WaveCtx& cx, int b) {
+  using C = Cfg<D, KV8, NW>;
+  return b * C::TILE + cx.wb * C::KBLK + (KV8 ? 0 : cx.ws * C::SHARE);
 }
-template <int D, bool KV8> __device__ __forceinline__ unsigned v_rows(const WaveCtx& cx, int b) {
-  return (2 + b) * Cfg<D, KV8>::TILE + cx.w * kBlock * Cfg<D, KV8>::RB;
+template <int D, bool KV8, int NW> __device__ __forceinline__ unsigned v_rows(const WaveCtx& cx, int b) {
+  using C = Cfg<D, KV8, NW>;
+  return (2 + b) * C::TILE + cx.wb * kBlock * C::RB + (KV8 ? 0 : cx.ws * C::SHARE);
 }
-template <int D, bool KV8> __device__ __forceinline__ unsigned staged(const WaveCtx& cx) {
-  return 4 * Cfg<D, KV8>::TILE + cx.w * Cfg<D, KV8>::STAGE;
+template <int D, bool KV8, int NW> __device__ __forceinline__ unsigned staged(const WaveCtx& cx) {
+  return 4 * Cfg<D, KV8, NW>::TILE + cx.w * Cfg<D, KV8, NW>::STAGE;
+}
+template <int D, bool KV8, int NW> __device__ __forceinline__ unsigned out_rows(const WaveCtx& cx) {
+  return Cfg<D, KV8, NW>::OUT + cx.w * kWaveRows * Cfg<D, KV8, NW>::RB;
 }
 
 // operand of score k-step s, half tile `half`; `addr`: LDS addresses of this lane's row of the K buffer
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ bf16x8 read_k(const unsigned (&addr)[4], int s, int half) {
-  return *(const __attribute__((address_space(3))) bf16x8*)(size_t)(addr[s & 3] + (s >> 2) * (kBlock * 128) + half * 2 * Cfg<D, KV8>::KBLK);
+  return *(const __attribute__((address_space(3))) bf16x8*)(size_t)(addr[s & 3] + (s >> 2) * (kBlock * 128) + half * 2 * Cfg<D, KV8, NW>::KBLK);
 }
 
 // operand of P V: keys 16 m .. 16 m + 15 of the V buffer, dimensions 32 mb .. 32 mb + 31
@@ -196,7 +227,12 @@ __device__ __forceinline__ bf16x8 read_vt(const unsigned (&addr)[4], int m, int 
   return av.v;
 }
 
-// 8-bit caches: eight bytes (row `r` of this wave's block, 16-byte chunk `ch` of the bf16 row) widened into its rows of a
+// 8-bit caches: row of the block that a lane's piece of load j belongs to
+template <int D, int NW> __device__ __forceinline__ int piece_row(const WaveCtx& cx, int j) {
+  using C = Cfg<D, true, NW>;
+  return cx.ws * C::ROWS + C::RPI * j + cx.lane / C::LPR;
+}
+// eight bytes (row `r` of this wave's block, 16-byte chunk `ch` of the bf16 row) widened into the block's rows of a
 // K or V buffer
 template <int D>
 __device__ __forceinline__ void widen_to_k(unsigned char* rows, int r, int ch, unsigned lo, unsigned hi) {
@@ -318,22 +354,22 @@ __device__ __forceinline__ void tile_barrier() {
 // tile: the buffers are free by then and are never read again.
 // boff: cache offset of this wave's block of the tile whose V comes next (its K was the last one requested); id: its block
 // of the tile after that.
-template <int D, bool KV8, bool PROBE>
+template <int D, bool KV8, int NW, bool PROBE>
 __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
                                           const int* bt, unsigned long long& boff, Pipe<D>& t, float m,
                                           const bf16x8 (&qf)[D / 16], Spans& sp) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   constexpr int NS = C::SLOTS, EPS = 16 / NS, R = C::RING, NQ = C::KSTEPS, NP = 2 * C::MB, NI = C::NI;
   static_assert(NQ == NP && 2 * NQ % R == 0, "scores and P V alternate; the rings turn whole rounds");
   constexpr int BAR = 2 * NS - 2 * R + 2;              // slot in front of which the barrier stands
-  const unsigned v_dst = v_rows<D, KV8>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8>(cx, kt & 1);
-  const unsigned stage = staged<D, KV8>(cx);
+  const unsigned v_dst = v_rows<D, KV8, NW>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8, NW>(cx, kt & 1);
+  const unsigned stage = staged<D, KV8, NW>(cx);
   uint4 st[2];                     // staged pieces on their way through the registers
   unsigned long long next_boff = 0;
   float sum[2];
   HalfExp h;
   // operand `n` of the scores / of P V, counted through the iteration; beyond it, the next iteration's
-  auto request_k = [&](auto n) { t.ka[n % R] = read_k<D, KV8>(t.k_addr, n % NQ, n % (2 * NQ) / NQ); };
+  auto request_k = [&](auto n) { t.ka[n % R] = read_k<D, KV8, NW>(t.k_addr, n % NQ, n % (2 * NQ) / NQ); };
   auto request_v = [&](auto n) { t.va[n % R] = read_vt<D>(t.v_addr, n % (2 * NP) / C::MB, n % C::MB); };
   static_for<2 * NS>([&](auto slot) {
     constexpr int i = slot, half = i / NS, j = i % NS, u = j / 2;
@@ -375,21 +411,21 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
         next_boff = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
         id = load_id(cx, bt, kt + 3);
       }
-      if constexpr (i == 1) fetch_v<D, false, 0>(cx, boff, cx.lds_base + v_dst);
-      if constexpr (i == 3 && NI > 2) fetch_v<D, false, 2>(cx, boff, cx.lds_base + v_dst);
+      if constexpr (i == 1) fetch_v<D, false, NW, 0>(cx, boff, cx.lds_base + v_dst);
+      if constexpr (i == 3 && NI > 2) fetch_v<D, false, NW, 2>(cx, boff, cx.lds_base + v_dst);
       if constexpr (i == 5) boff = next_boff;
-      if constexpr (i == 5) fetch_k<D, false, 0>(cx, boff, cx.lds_base + k_dst);
-      if constexpr (i == 7 && NI > 2) fetch_k<D, false, 2>(cx, boff, cx.lds_base + k_dst);
+      if constexpr (i == 5) fetch_k<D, false, NW, 0>(cx, boff, cx.lds_base + k_dst);
+      if constexpr (i == 7 && NI > 2) fetch_k<D, false, NW, 2>(cx, boff, cx.lds_base + k_dst);
     } else {
       // piece p = 0 .. 2 NI - 1 (K run, then V run): read in slice 2p, its halves widened in slices 2p+2 and 2p+3
       if (i == 0) wait_vmem();
       if (i % 2 == 0 && i / 2 < 2 * NI) {
         const int p = i / 2;
-        st[p & 1] = *reinterpret_cast<const uint4*>(smem + stage + (p / NI) * C::BLK + (p % NI) * 1024 + 16 * cx.lane);
+        st[p & 1] = *reinterpret_cast<const uint4*>(smem + stage + (p / NI) * C::SHARE + (p % NI) * 1024 + 16 * cx.lane);
       }
       if (i >= 2 && (i - 2) / 2 < 2 * NI) {
         const int p = (i - 2) / 2, hh = i % 2;
-        const int r = C::RPI * (p % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR) + hh;
+        const int r = piece_row<D, NW>(cx, p % NI), ch = 2 * (cx.lane % C::LPR) + hh;
         const uint4& v = st[p & 1];
         if (p < NI) widen_to_k<D>(smem + k_dst, r, ch, hh ? v.z : v.x, hh ? v.w : v.y);
         else widen_to_v<D>(smem + v_dst, r, ch, hh ? v.z : v.x, hh ? v.w : v.y);
@@ -400,9 +436,9 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
       if constexpr (i == F) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       if constexpr (i == F - 1) next_boff = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
       if constexpr (i == F - 1) id = load_id(cx, bt, kt + 4);
-      if constexpr (i == F) fetch_v<D, true, 0>(cx, boff, cx.lds_base + stage + C::BLK);
+      if constexpr (i == F) fetch_v<D, true, NW, 0>(cx, boff, cx.lds_base + stage + C::SHARE);
       if constexpr (i == F + 2) boff = next_boff;
-      if constexpr (i == F + 2) fetch_k<D, true, 0>(cx, boff, cx.lds_base + stage);
+      if constexpr (i == F + 2) fetch_k<D, true, NW, 0>(cx, boff, cx.lds_base + stage);
     }
     exp_slot<EPS>(cx, Sx, m, h, t.P[half ^ 1], j);
     __builtin_amdgcn_sched_barrier(0);
@@ -421,18 +457,18 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
 // The same iteration for a wave that has no key left: the tiles behind its rows' positions are for the other row blocks
 // of the workgroup (groups of fewer than four heads), and it only fetches its cache blocks of them.  (Going through
 // them with every score masked would let 0 * Inf from their values into its rows.)
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
                                            const int* bt, unsigned long long& boff) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   constexpr int NI = C::NI;
   if constexpr (KV8) {
-    const unsigned v_dst = v_rows<D, KV8>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8>(cx, kt & 1), stage = staged<D, KV8>(cx);
+    const unsigned v_dst = v_rows<D, KV8, NW>(cx, (kt + 1) & 1), k_dst = k_rows<D, KV8, NW>(cx, kt & 1), stage = staged<D, KV8, NW>(cx);
     wait_vmem();
 #pragma unroll
     for (int q = 0; q < 2 * NI; ++q) {
-      const uint4 st = *reinterpret_cast<const uint4*>(smem + stage + (q / NI) * C::BLK + (q % NI) * 1024 + 16 * cx.lane);
-      const int r = C::RPI * (q % NI) + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR);
+      const uint4 st = *reinterpret_cast<const uint4*>(smem + stage + (q / NI) * C::SHARE + (q % NI) * 1024 + 16 * cx.lane);
+      const int r = piece_row<D, NW>(cx, q % NI), ch = 2 * (cx.lane % C::LPR);
       if (q < NI) {
         widen_to_k<D>(smem + k_dst, r, ch, st.x, st.y);
         widen_to_k<D>(smem + k_dst, r, ch + 1, st.z, st.w);
@@ -445,37 +481,37 @@ __device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* sme
     const unsigned long long next = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
     id = load_id(cx, bt, kt + 4);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the staging area is free
-    fetch_v_tile<D, true>(cx, boff, cx.lds_base + stage + C::BLK);
+    fetch_v_tile<D, true, NW>(cx, boff, cx.lds_base + stage + C::SHARE);
     boff = next;
-    fetch_k_tile<D, true>(cx, boff, cx.lds_base + stage);
+    fetch_k_tile<D, true, NW>(cx, boff, cx.lds_base + stage);
     tile_barrier<true>();
   } else {
     const unsigned long long next = block_bytes(cx, __builtin_amdgcn_readfirstlane(id));
     id = load_id(cx, bt, kt + 3);
-    fetch_v_tile<D, false>(cx, boff, cx.lds_base + v_rows<D, KV8>(cx, (kt + 1) & 1));
+    fetch_v_tile<D, false, NW>(cx, boff, cx.lds_base + v_rows<D, KV8, NW>(cx, (kt + 1) & 1));
     boff = next;
-    fetch_k_tile<D, false>(cx, boff, cx.lds_base + k_rows<D, KV8>(cx, kt & 1));
+    fetch_k_tile<D, false, NW>(cx, boff, cx.lds_base + k_rows<D, KV8, NW>(cx, kt & 1));
     tile_barrier<false>();
   }
 }
 
 // This wave's rows past the last token of the V buffer that holds the last tile.
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void clear_past_end(const WaveCtx& cx, unsigned char* smem, int kt) {
-  constexpr int RB = Cfg<D, KV8>::RB, CH = Cfg<D, KV8>::CH;
-  const int first = cx.L - (kTileKeys * kt + kBlock * cx.w);      // first row of this wave's 16 past the end
-  unsigned char* const rows = smem + v_rows<D, KV8>(cx, kt & 1);
+  using C = Cfg<D, KV8, NW>;
+  const int first = cx.L - (kTileKeys * kt + kBlock * cx.wb + C::ROWS * cx.ws);      // first row of this wave's share past the end
+  unsigned char* const rows = smem + v_rows<D, KV8, NW>(cx, kt & 1) + (KV8 ? cx.ws * C::ROWS * C::RB : 0);
 #pragma unroll
-  for (int j = 0; j < kBlock * CH / 64; ++j) {
-    const int r = (64 / CH) * j + cx.lane / CH;
-    if (r >= first) *reinterpret_cast<uint4*>(rows + r * RB + 16 * (cx.lane % CH)) = make_uint4(0, 0, 0, 0);
+  for (int j = 0; j < C::ROWS * C::CH / 64; ++j) {
+    const int r = (64 / C::CH) * j + cx.lane / C::CH;
+    if (r >= first) *reinterpret_cast<uint4*>(rows + r * C::RB + 16 * (cx.lane % C::CH)) = make_uint4(0, 0, 0, 0);
   }
 }
 
 // What is left once all K and V tiles lie in LDS: the last tile's second half and P V of both.
-template <int D, bool KV8, bool PROBE>
+template <int D, bool KV8, int NW, bool PROBE>
 __device__ __forceinline__ void last_tile(const WaveCtx& cx, int kt, Pipe<D>& t, float m, int pos_max, Spans& sp) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   constexpr int R = C::RING, NP = 2 * C::MB, EPS = 16 / NP;
   const int key0 = kTileKeys * kt + 32;
   const bool second = key0 <= pos_max;            // some row sees keys of the second half
@@ -508,9 +544,9 @@ __device__ __forceinline__ void last_tile(const WaveCtx& cx, int kt, Pipe<D>& t,
 // The first tile's scores, on which the softmax reference of each row rests (`m`: the row's maximum in them, and it stays
 // that; row_alone deals with rows whose later scores are far above it), and the probabilities of its first half.
 // On entry K(0) lies in LDS; V(0) and K(1) are on their way, and there on return.
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void first_half(const WaveCtx& cx, const bf16x8 (&qf)[D / 16], Pipe<D>& t, float& m) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   constexpr int EPS = 16 / C::SLOTS;
   // K reads: lane (row qi [+32], half hf) reads chunk 2s + hf of a 64-dimension part
   const int qi = cx.lane & 31;
@@ -535,7 +571,7 @@ __device__ __forceinline__ void first_half(const WaveCtx& cx, const bf16x8 (&qf)
   for (int s = 0; s < C::KSTEPS; ++s)
 #pragma unroll
     for (int half = 0; half < 2; ++half)
-      t.S[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D, KV8>(t.k_addr, s, half), qf[s], t.S[half], 0, 0, 0);
+      t.S[half] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_k<D, KV8, NW>(t.k_addr, s, half), qf[s], t.S[half], 0, 0, 0);
   if (31 > cx.pos_min) mask_half(cx, 0, t.S[0]);
   if (63 > cx.pos_min) mask_half(cx, 32, t.S[1]);
   float mx = fmaxf(t.S[0][0], t.S[1][0]);
@@ -559,98 +595,127 @@ __device__ __forceinline__ void first_half(const WaveCtx& cx, const bf16x8 (&qf)
   }
 #pragma unroll
   for (int n = 0; n < C::RING; ++n) {
-    t.ka[n] = read_k<D, KV8>(t.k_addr, n, 0);
+    t.ka[n] = read_k<D, KV8, NW>(t.k_addr, n, 0);
     t.va[n] = read_vt<D>(t.v_addr, n / C::MB, n % C::MB);
   }
 }
 
 // All that follows.  mine: tiles up to the position of the wave's last row, pos_max.  SHARED: that can be fewer than the
 // workgroup's.
-template <int D, bool KV8, bool SHARED, bool PROBE>
+template <int D, bool KV8, int NW, bool SHARED, bool PROBE>
 __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, int mine, int pos_max, int id,
                                           unsigned long long& boff, const bf16x8 (&qf)[D / 16], Pipe<D>& t, float& m,
                                           Spans& sp, const int* bt) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   // The lane values are made opaque here: what is derived from them would otherwise be computed once for both
   // instantiations (probing or not) and spilled instead of recomputed.
   WaveCtx cy = cx;
   asm volatile("" : "+v"(cy.pos), "+v"(cy.k_off[0]), "+v"(cy.v_off[0]), "+v"(cy.hf), "+v"(cy.lane));
   cy.v_off[1] = cy.v_off[0];
   if constexpr (KV8) cy.k_off[1] = cy.k_off[0];
-  else asm volatile("" : "+v"(cy.k_off[1]), "+v"(cy.k_off[2]), "+v"(cy.k_off[3]));
+  else if constexpr (C::NI > 1) asm volatile("" : "+v"(cy.k_off[1]));
+  if constexpr (C::NI > 2) asm volatile("" : "+v"(cy.k_off[2]), "+v"(cy.k_off[3]));
 #pragma unroll
   for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) t.O[mb][r] = 0.0f;
 #pragma unroll
   for (int s = 0; s < kMaxSpans; ++s) t.am[s] = 0.0f;
-  first_half<D, KV8>(cy, qf, t, m);
+  first_half<D, KV8, NW>(cy, qf, t, m);
   if constexpr (PROBE) add_spans<D>(cy, sp, 0, t.S[0], t.l, t.am);
   __builtin_amdgcn_sched_barrier(0);
   const int full = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
   int kt = 0;
-  for (; kt < full; ++kt) tile_iter<D, KV8, PROBE>(cy, smem, kt, ntiles, id, bt, boff, t, m, qf, sp);
+  for (; kt < full; ++kt) tile_iter<D, KV8, NW, PROBE>(cy, smem, kt, ntiles, id, bt, boff, t, m, qf, sp);
   if (SHARED)
-    for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8>(cy, smem, kt, ntiles, id, bt, boff);
+    for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8, NW>(cy, smem, kt, ntiles, id, bt, boff);
   if (kTileKeys * ntiles > cy.L) {        // (the same for all waves)
-    clear_past_end<D, KV8>(cy, smem, ntiles - 1);
+    clear_past_end<D, KV8, NW>(cy, smem, ntiles - 1);
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < C::RING; ++n) t.va[n] = read_vt<D>(t.v_addr, n / C::MB, n % C::MB);
   }
-  if (!SHARED || mine == ntiles) last_tile<D, KV8, PROBE>(cy, kt, t, m, pos_max, sp);
+  if (!SHARED || mine == ntiles) last_tile<D, KV8, NW, PROBE>(cy, kt, t, m, pos_max, sp);
 }
 
-// The first tiles of an item into the LDS buffers.  16-bit: K(0) is requested here, V(0) and K(1) by the second
-// function once the query rows have arrived.  8-bit caches: K(0), V(0) and K(1) here, and the bytes of V(1)
-// and K(2) into the staging area.
-template <int D, bool KV8>
-__device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned char* smem, int ntiles, unsigned long long boff0,
-                                            unsigned long long boff1, unsigned long long boff2) {
-  using C = Cfg<D, KV8>;
-  constexpr int NI = C::NI;
-  if constexpr (!KV8) {
-    fetch_k_tile<D, false>(cx, boff0, cx.lds_base + k_rows<D, KV8>(cx, 0));
-  } else {
-    // through registers: nothing to overlap with yet
-    uint4 k0[NI], v0[NI], k1[NI];
+// 16-bit caches: where the two halves of this wave's query rows pass through LDS on their way to registers.  Four waves: the first
+// lies in its rows of V buffer 1, which it fetches itself after that.  D = 128: a half is one 64-dimension part of all rows, D = 64: 16 rows.
+template <int D, int NW>
+__device__ __forceinline__ unsigned q_half(const WaveCtx& cx, int i) {
+  using C = Cfg<D, false, NW>;
+  if (NW == 8) return out_rows<D, false, NW>(cx) + i * C::QHALF;
+  return i == 0 ? v_rows<D, false, NW>(cx, 1) : 4 * C::TILE + cx.w * C::QHALF;
+}
+
+// Requests the query rows, K(0), V(0) and K(1) of an item, in this order.  rows: the wave's first query row, of `n_rows`, which
+// are `stride` bytes apart (rows past the last repeat it).
+template <int D, int NW>
+__device__ __forceinline__ void first_tiles(const WaveCtx& cx, unsigned long long rows, int n_rows, unsigned stride,
+                                            unsigned long long boff0, unsigned long long boff1) {
+  using C = Cfg<D, false, NW>;
 #pragma unroll
-    for (int jj = 0; jj < NI; ++jj) {
-      const int r = C::RPI * jj + cx.lane / C::LPR;
-      const unsigned piece = 16 * (cx.lane % C::LPR);
-      k0[jj] = load_global16((global_bytes)(cx.kbase + boff0 + r * D + piece));
-      v0[jj] = load_global16((global_bytes)(cx.vbase + boff0 + r * D + piece));
-      k1[jj] = load_global16((global_bytes)(cx.kbase + boff1 + r * D + piece));
-    }
-    // V(1), then K(2): the order in which the loop fetches
-    const unsigned lds_stage = cx.lds_base + staged<D, KV8>(cx);
-    fetch_v_tile<D, true>(cx, boff1, lds_stage + C::BLK);
-    fetch_k_tile<D, true>(cx, boff2, lds_stage);
-    unsigned char* const kd = smem + k_rows<D, KV8>(cx, 0);
-    unsigned char* const vd = smem + v_rows<D, KV8>(cx, 0);
+  for (int j = 0; j < 4; j += 2) {      // 16 rows of 64 dimensions: two instructions of eight
+    unsigned voff[2];
 #pragma unroll
-    for (int jj = 0; jj < NI; ++jj) {
-      const int r = C::RPI * jj + cx.lane / C::LPR, ch = 2 * (cx.lane % C::LPR);
-      widen_to_k<D>(kd, r, ch, k0[jj].x, k0[jj].y);
-      widen_to_k<D>(kd, r, ch + 1, k0[jj].z, k0[jj].w);
-      widen_to_v<D>(vd, r, ch, v0[jj].x, v0[jj].y);
-      widen_to_v<D>(vd, r, ch + 1, v0[jj].z, v0[jj].w);
-      widen_to_k<D>(kd + C::TILE, r, ch, k1[jj].x, k1[jj].y);
-      widen_to_k<D>(kd + C::TILE, r, ch + 1, k1[jj].z, k1[jj].w);
+    for (int i = 0; i < 2; ++i) {
+      const int r = 8 * (j + i) + cx.lane / 8;
+      voff[i] = (unsigned)min(r, n_rows - 1) * stride + (unsigned)((cx.lane % 8) ^ k_swizzle(r)) * 16 + 1024 * (1 - i);
     }
+#pragma unroll
+    for (int part = 0; part < D / 64; ++part)
+      dma16<2, 0>(rows - 1024 + 128 * part, voff, cx.lds_base + (D == 128 ? q_half<D, NW>(cx, part) + 1024 * j : q_half<D, NW>(cx, j / 2)));
+  }
+  fetch_k_tile<D, false, NW>(cx, boff0, cx.lds_base + k_rows<D, false, NW>(cx, 0));
+  fetch_v_tile<D, false, NW>(cx, boff0, cx.lds_base + v_rows<D, false, NW>(cx, 0));
+  fetch_k_tile<D, false, NW>(cx, boff1, cx.lds_base + k_rows<D, false, NW>(cx, 1));
+}
+
+template <int D, int NW>
+__device__ __forceinline__ void read_queries(const WaveCtx& cx, const unsigned char* smem, bf16x8 (&qf)[D / 16]) {
+  const int qi = cx.lane & 31;
+#pragma unroll
+  for (int s = 0; s < D / 16; ++s) {
+    const unsigned a = D == 128 ? q_half<D, NW>(cx, s >> 2) + qi * 128 : q_half<D, NW>(cx, qi >> 4) + (qi & 15) * 128;
+    qf[s] = *reinterpret_cast<const bf16x8*>(smem + a + (((2 * (s & 3) + cx.hf) ^ k_swizzle(qi)) << 4));
   }
 }
 
-template <int D, bool KV8>
-__device__ __forceinline__ void rest_of_first_tiles(const WaveCtx& cx, unsigned long long boff0, unsigned long long boff1) {
-  if constexpr (!KV8) {
-    fetch_v_tile<D, false>(cx, boff0, cx.lds_base + v_rows<D, KV8>(cx, 0));
-    fetch_k_tile<D, false>(cx, boff1, cx.lds_base + k_rows<D, KV8>(cx, 1));
+// 8-bit caches: K(0), V(0) and K(1) through registers (there is nothing to overlap with yet), the bytes of V(1) and K(2)
+// into the staging area.
+template <int D, int NW>
+__device__ __forceinline__ void first_tiles_kv8(const WaveCtx& cx, unsigned char* smem, unsigned long long boff0,
+                                                unsigned long long boff1, unsigned long long boff2) {
+  using C = Cfg<D, true, NW>;
+  constexpr int NI = C::NI;
+  uint4 k0[NI], v0[NI], k1[NI];
+#pragma unroll
+  for (int jj = 0; jj < NI; ++jj) {
+    const int r = piece_row<D, NW>(cx, jj);
+    const unsigned piece = 16 * (cx.lane % C::LPR);
+    k0[jj] = load_global16((global_bytes)(cx.kbase + boff0 + r * D + piece));
+    v0[jj] = load_global16((global_bytes)(cx.vbase + boff0 + r * D + piece));
+    k1[jj] = load_global16((global_bytes)(cx.kbase + boff1 + r * D + piece));
+  }
+  // V(1), then K(2): the order in which the loop fetches
+  const unsigned lds_stage = cx.lds_base + staged<D, true, NW>(cx);
+  fetch_v_tile<D, true, NW>(cx, boff1, lds_stage + C::SHARE);
+  fetch_k_tile<D, true, NW>(cx, boff2, lds_stage);
+  unsigned char* const kd = smem + k_rows<D, true, NW>(cx, 0);
+  unsigned char* const vd = smem + v_rows<D, true, NW>(cx, 0);
+#pragma unroll
+  for (int jj = 0; jj < NI; ++jj) {
+    const int r = piece_row<D, NW>(cx, jj), ch = 2 * (cx.lane % C::LPR);
+    widen_to_k<D>(kd, r, ch, k0[jj].x, k0[jj].y);
+    widen_to_k<D>(kd, r, ch + 1, k0[jj].z, k0[jj].w);
+    widen_to_v<D>(vd, r, ch, v0[jj].x, v0[jj].y);
+    widen_to_v<D>(vd, r, ch + 1, v0[jj].z, v0[jj].w);
+    widen_to_k<D>(kd + C::TILE, r, ch, k1[jj].x, k1[jj].y);
+    widen_to_k<D>(kd + C::TILE, r, ch + 1, k1[jj].z, k1[jj].w);
   }
 }
 
 // Raw, masked scores of the half tile at key0, straight from the cache.
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ f32x16 scores_from_cache(const WaveCtx& cx, const int* bt, int key0, const bf16x8 (&qf)[D / 16]) {
   constexpr int E = KV8 ? 1 : 2;
   const int key = key0 + (cx.lane & 31);
@@ -689,13 +754,13 @@ struct WaveItem {
 
 // Normalise, transpose through LDS (16-byte chunks swizzled by row; each wave in rows of its own of the K buffers, which
 // are free), coalesced stores; the span sums.  rows: bit per row of the wave that is to be written.
-template <int D, bool KV8, bool PROBE>
+template <int D, bool KV8, int NW, bool PROBE>
 __device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi, const WaveCtx& cx,
                                        const Spans& sp, const Pipe<D>& t, float l_tot, unsigned rows) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   const float inv_l = 1.0f / l_tot;
   const float inv = KV8 ? inv_l * p.v_scale[it.kvh] : inv_l;     // `out` carries the value scale, `mass` does not
-  unsigned char* const ot = smem + cx.w * (kWaveRows * C::RB);
+  unsigned char* const ot = smem + out_rows<D, KV8, NW>(cx);
   const int qi = cx.lane & 31;
 #pragma unroll
   for (int mb = 0; mb < C::MB; ++mb)
@@ -707,6 +772,7 @@ __device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem,
       const int ch = 4 * mb + g4;
       *reinterpret_cast<uint2*>(ot + qi * C::RB + ((ch ^ out_swizzle<D>(qi)) << 4) + 8 * cx.hf) = v;
     }
+  in_order();
   __bf16* const og = static_cast<__bf16*>(p.out);
 #pragma unroll
   for (int j = 0; j < C::CH / 2; ++j) {
@@ -752,10 +818,10 @@ __device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
 
 // The wave's rows from their true maxima, without the other waves: keys straight from the cache, values through the rows of
 // LDS that its output passed through.  Rows that need it are rare, so this is short rather than fast.
-template <int D, bool KV8>
+template <int D, bool KV8, int NW>
 __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
                                            const WaveCtx& cx, Spans& sp, const int* bt, unsigned rows) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   constexpr int E = KV8 ? 1 : 2, LPR = D / 8, RPL = 64 / LPR;      // lanes per row, rows per load (eight values to a lane)
   bf16x8 qf[C::KSTEPS];
   {
@@ -769,7 +835,7 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
   }
   float m = -INFINITY;
   for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
-    const f32x16 S = scores_from_cache<D, KV8>(cx, bt, key0, qf);
+    const f32x16 S = scores_from_cache<D, KV8, NW>(cx, bt, key0, qf);
 #pragma unroll
     for (int r = 0; r < 16; ++r) m = fmaxf(m, S[r] * cx.c);
   }
@@ -784,13 +850,13 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
   for (int mb = 0; mb < C::MB; ++mb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) t.O[mb][r] = 0.0f;
-  unsigned char* const vrows = smem + cx.w * (kWaveRows * C::RB);
+  unsigned char* const vrows = smem + out_rows<D, KV8, NW>(cx);
   unsigned v_addr[4];
   {
     const int g = cx.lane >> 4, s16 = cx.lane & 15;
     const unsigned a = (4 * (g >> 1) + (s16 >> 2)) * C::RB + (((2 * (g & 1) + ((s16 & 3) >> 1)) ^ v_swizzle<D>(s16 >> 2)) << 4) + 8 * (s16 & 1);
 #pragma unroll
-    for (int mb = 0; mb < C::MB; ++mb) v_addr[mb] = cx.lds_base + cx.w * (kWaveRows * C::RB) + (a ^ (64u * mb));
+    for (int mb = 0; mb < C::MB; ++mb) v_addr[mb] = cx.lds_base + out_rows<D, KV8, NW>(cx) + (a ^ (64u * mb));
   }
   for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
 #pragma unroll
@@ -808,7 +874,8 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
       if (key >= cx.L) v = make_uint4(0, 0, 0, 0);
       *reinterpret_cast<uint4*>(vrows + r * C::RB + ((ch ^ v_swizzle<D>(r)) << 4)) = v;
     }
-    f32x16 S = scores_from_cache<D, KV8>(cx, bt, key0, qf);
+    in_order();
+    f32x16 S = scores_from_cache<D, KV8, NW>(cx, bt, key0, qf);
     u32x4 P[2];
     HalfExp h;
     exp_begin<1>(cx, S, m, h);
@@ -821,30 +888,31 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
     for (int n = 0; n < 2 * C::MB; ++n)
       t.O[n % C::MB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_vt<D>(v_addr, n / C::MB, n % C::MB), as_bf16x8(P[n / C::MB]),
                                                               t.O[n % C::MB], 0, 0, 0);
+    in_order();
   }
-  finish<D, KV8, true>(p, smem, it, wi, cx, sp, t, t.l + __shfl_xor(t.l, 32), rows);
+  finish<D, KV8, NW, true>(p, smem, it, wi, cx, sp, t, t.l + __shfl_xor(t.l, 32), rows);
 }
 
-template <int D, bool KV8, bool SHARED, bool PROBE>
+template <int D, bool KV8, int NW, bool SHARED, bool PROBE>
 __device__ __forceinline__ unsigned tiles_and_output(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
                                                      const WaveCtx& cx, int id, unsigned long long boff,
                                                      const bf16x8 (&qf)[D / 16], Spans& sp, const int* bt) {
   Pipe<D> t;
   float m;
-  run_tiles<D, KV8, SHARED, PROBE>(cx, smem, wi.ntiles, wi.mine, wi.pos_max, id, boff, qf, t, m, sp, bt);
+  run_tiles<D, KV8, NW, SHARED, PROBE>(cx, smem, wi.ntiles, wi.mine, wi.pos_max, id, boff, qf, t, m, sp, bt);
   if constexpr (KV8) wait_vmem();   // (bytes that nobody waits for any more: no fetch may outlive its buffers)
   const float l_tot = t.l + __shfl_xor(t.l, 32);
   const unsigned rows = wi.active ? (unsigned)((1ull << min(kWaveRows, it.n - wi.wrow0)) - 1) : 0u;
-  if (wi.active) finish<D, KV8, PROBE>(p, smem, it, wi, cx, sp, t, l_tot, rows);
+  if (wi.active) finish<D, KV8, NW, PROBE>(p, smem, it, wi, cx, sp, t, l_tot, rows);
   return rows & (unsigned)__builtin_amdgcn_ballot_w64(out_of_range<D>(t, l_tot));
 }
 
 // ZERO_REST (self-planned calls): the wave that owns a probed
 // head in the item of row 0 also writes zeros to that head's `mass` slots that hold no row, so that
 // every entry of `mass` is written exactly once without a planner's zero-fill.
-template <int D, bool KV8, bool SHARED, bool ZERO_REST>
+template <int D, bool KV8, int NW, bool SHARED, bool ZERO_REST>
 __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char* smem, const Item& it) {
-  using C = Cfg<D, KV8>;
+  using C = Cfg<D, KV8, NW>;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -869,18 +937,19 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   cx.L = L;
   cx.last_blk = (L - 1) >> 4;
   cx.w = w;
+  cx.wb = w / C::WPB;
+  cx.ws = w % C::WPB;
   cx.lane = lane;
   cx.blk_bytes = (unsigned)p.Hkv * C::BLK;
   // this wave's blocks of the first tiles by scalar loads: the wait for them leaves vector loads alone
   cx.num_blocks = p.num_blocks;
-  auto first_id = [&](int tile) { return cload(bt, min(4 * min(tile, ntiles - 1) + w, cx.last_blk)); };
+  auto first_id = [&](int tile) { return cload(bt, min(4 * min(tile, ntiles - 1) + cx.wb, cx.last_blk)); };
   const int id0 = first_id(0), id1 = first_id(1), id2 = first_id(2);
 
-  // Query rows.  The compiler does not count the tile fetches (assembly), so its wait for these rows is a wait for
-  // the fetches issued before it as well: only K(0) is (first_tiles / rest_of_first_tiles).
-  const int probe_list = p.P > 0 ? p.probe_heads[min(lane, p.P - 1)] : 0;
-  uint4 qraw[C::KSTEPS];
-  {
+  int probe_list = p.P > 0 ? p.probe_heads[min(lane, p.P - 1)] : 0;
+  bf16x8 qf[C::KSTEPS];
+  uint4 qraw[KV8 ? C::KSTEPS : 1];
+  if constexpr (KV8) {
     const __bf16* const qg = static_cast<const __bf16*>(p.q) + ((size_t)(it.qbase + t) * p.Hq + head) * D + 8 * hf;
 #pragma unroll
     for (int s = 0; s < C::KSTEPS; ++s) qraw[s] = load_global16((global_bytes)(unsigned long long)(size_t)(qg + 16 * s));
@@ -896,16 +965,15 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   // receives logical chunk pc ^ swizzle(r); bytes are staged as they lie in the cache
   {
     const int r = lane / C::LPR, pc = lane % C::LPR;
-    const unsigned row = (unsigned)r * (C::BLK / kBlock);
-    cx.v_off[0] = cx.v_off[1] = row + (unsigned)(KV8 ? pc : pc ^ v_swizzle<D>(r)) * 16;
     if (KV8) {
-      cx.k_off[0] = cx.k_off[1] = row + (unsigned)pc * 16;
+      cx.v_off[0] = cx.v_off[1] = cx.k_off[0] = cx.k_off[1] = cx.ws * C::SHARE + 16 * lane;
     } else {
+      cx.v_off[0] = cx.v_off[1] = cx.ws * C::SHARE + (unsigned)r * C::RB + (unsigned)(pc ^ v_swizzle<D>(r)) * 16;
       // (2048 more, which kbase is short of, so that none is negative)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int rk = 8 * (j & 1) + lane / 8;
-        cx.k_off[j] = (unsigned)rk * C::RB + (j >> 1) * 128 + (unsigned)((lane % 8) ^ k_swizzle(rk)) * 16 + 2048 - 1024 * j;
+      for (int i = 0; i < C::NI; ++i) {
+        const int j = cx.ws * C::NI + i, rk = 8 * (j & 1) + lane / 8;
+        cx.k_off[i] = (unsigned)rk * C::RB + (j >> 1) * 128 + (unsigned)((lane % 8) ^ k_swizzle(rk)) * 16 + 2048 - 1024 * i;
       }
       cx.kbase -= 2048;
     }
@@ -915,7 +983,16 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   int id = KV8 ? first_id(3) : id2;
   asm("" : "+v"(id));
   const unsigned long long boff0 = block_bytes(cx, id0), boff1 = block_bytes(cx, id1), boff2 = block_bytes(cx, id2);
-  first_tiles<D, KV8>(cx, smem, ntiles, boff0, boff1, boff2);
+  if constexpr (KV8) {
+    first_tiles_kv8<D, NW>(cx, smem, boff0, boff1, boff2);
+  } else {
+    // (The compiler does not count these loads: what it counts has to have arrived before them, or waiting for that
+    // would be waiting for all of them.)
+    asm volatile("" : "+v"(probe_list));
+    const int row = min(wrow0, n - 1);
+    first_tiles<D, NW>(cx, (unsigned long long)(size_t)p.q + ((size_t)(it.qbase + row) * p.Hq + head) * C::RB, n - row, p.Hq * C::RB,
+                   boff0, boff1);
+  }
 
   Spans sp;
   sp.n = 0;
@@ -939,19 +1016,20 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
       sp.hi = max(sp.hi, sp.b[s]);
     }
 
-  // the first scores need Q and K(0); V(0) and K(1) (2 NI loads; with staging K(2) and V(1)) may stay in flight
-  bf16x8 qf[C::KSTEPS];
+  // the first scores need the query rows and K(0); V(0) and K(1) (2 NI loads; with staging K(2) and V(1)) may stay in flight
+  if constexpr (KV8) {
 #pragma unroll
-  for (int s = 0; s < C::KSTEPS; ++s) __builtin_memcpy(&qf[s], &qraw[s], 16);
+    for (int s = 0; s < C::KSTEPS; ++s) __builtin_memcpy(&qf[s], &qraw[s], 16);
 #pragma unroll
-  for (int s = 0; s < C::KSTEPS; ++s) asm volatile("" : "+v"(qf[s]) :: "memory");     // Q has arrived here
-  rest_of_first_tiles<D, KV8>(cx, boff0, boff1);
+    for (int s = 0; s < C::KSTEPS; ++s) asm volatile("" : "+v"(qf[s]) :: "memory");     // (they have arrived here)
+  }
   asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * C::NI) : "memory");
+  if constexpr (!KV8) read_queries<D, NW>(cx, smem, qf);
   __syncthreads();
   const unsigned long long boff = KV8 ? boff2 : boff1;      // of the last K run fetched
-  const unsigned again = wave_probe ? tiles_and_output<D, KV8, SHARED, true>(p, smem, it, wi, cx, id, boff, qf, sp, bt)
-                                    : tiles_and_output<D, KV8, SHARED, false>(p, smem, it, wi, cx, id, boff, qf, sp, bt);
-  if (__builtin_expect(again != 0, 0)) rows_alone<D, KV8>(p, smem, it, wi, cx, sp, bt, again);
+  const unsigned again = wave_probe ? tiles_and_output<D, KV8, NW, SHARED, true>(p, smem, it, wi, cx, id, boff, qf, sp, bt)
+                                    : tiles_and_output<D, KV8, NW, SHARED, false>(p, smem, it, wi, cx, id, boff, qf, sp, bt);
+  if (__builtin_expect(again != 0, 0)) rows_alone<D, KV8, NW>(p, smem, it, wi, cx, sp, bt, again);
   if constexpr (ZERO_REST) {
     if (it.row0 == 0 && rb == 0 && wi.pslot >= 0 && p.plan_fresh) {
       const int lo = max(wi.qsel_b, 0), hi = min(wi.qsel_e, n);     // slots lo - qsel_b .. hi - qsel_b - 1 hold rows
@@ -1071,13 +1149,14 @@ __device__ __forceinline__ bool find_item(const AttnParams& p, int item, int lan
 // What the planner does besides, by a workgroup of its own: the header with the status word, and zeros in the `mass`
 // entries of sequences without row blocks (in a mixed batch the merge kernel of the single rows has those) and of elements
 // of the head list that no head owns.
+template <int NT>
 __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   int* const skip = sh + 2;     // [kScanMaxSeqs]
   const int tid = threadIdx.x;
   if (tid < 2) sh[tid] = 0;
   __syncthreads();
-  int bits = p.plan_fresh && bad_head_list<256>(p) ? kBadHeadList : 0, blocks = 0;
-  for (int i = tid; i < p.num_seqs; i += 256) {
+  int bits = p.plan_fresh && bad_head_list<NT>(p) ? kBadHeadList : 0, blocks = 0;
+  for (int i = tid; i < p.num_seqs; i += NT) {
     const ChunkSeq s = chunk_seq(p, p.seq_lens[i], p.cu_q_lens[i], p.cu_q_lens[i + 1]);
     bits |= s.bits;
     if (s.valid) blocks += (s.n + p.rows_per_wg - 1) / p.rows_per_wg;
@@ -1090,16 +1169,16 @@ __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
   if (p.batch_kind == 1 && p.plan_fresh && p.P > 0)
     for (int i = 0; i < p.num_seqs; ++i)
       if (skip[i])
-        for (int e = tid; e < p.P * p.NQ * p.S; e += 256) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
-  if (sh[0] & kBadHeadList) zero_unowned_mass<256>(p);
+        for (int e = tid; e < p.P * p.NQ * p.S; e += NT) p.mass[(size_t)i * p.P * p.NQ * p.S + e] = 0.0f;
+  if (sh[0] & kBadHeadList) zero_unowned_mass<NT>(p);
 }
 
 // PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
 // of the grid settles the rest, and `mass` is written entry by entry by the waves that own the entries.
 // SHARED: several row blocks to a workgroup (groups of fewer than four heads).  An instantiation of its own, because the
 // spills that the fetch-only iterations bring cost a prompt of 2048 tokens at 32 / 8 heads 1.5 of its 49.5 us.
-template <int D, bool KV8, bool SHARED, bool PLANNED>
-__global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
+template <int D, bool KV8, int NW, bool SHARED, bool PLANNED>
+__global__ __launch_bounds__(64 * NW, 2) void k_prefill(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
   const int bid = blockIdx.x;
@@ -1116,41 +1195,48 @@ __global__ __launch_bounds__(256, 2) void k_prefill(const AttnParams p) {
     asm volatile("" :: "s"(it.x), "s"(it.y), "s"(it.z), "s"(it.w), "s"(qbase), "s"(nitems), "s"(p.block_table), "s"(p.q),
                  "s"(p.k_cache), "s"(p.v_cache));
     if (item >= nitems) return;
-    prefill_item<D, KV8, SHARED, false>(p, smem, {kvh, hg, it.x, it.y, it.z, it.w, qbase});
+    prefill_item<D, KV8, NW, SHARED, false>(p, smem, {kvh, hg, it.x, it.y, it.z, it.w, qbase});
   } else {
     if (bid == (int)gridDim.x - 1) {
-      settle_chunks(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
+      settle_chunks<64 * NW>(reread_arguments(), reinterpret_cast<int*>(smem));   // (or its arguments take registers from the rest)
       return;
     }
     ChunkItem it;
     const bool some = find_item(p, item, threadIdx.x & 63, it);
     asm volatile("" :: "s"(p.block_table), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache));
     if (!some) return;
-    prefill_item<D, KV8, SHARED, true>(p, smem, {kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase});
+    prefill_item<D, KV8, NW, SHARED, true>(p, smem, {kvh, hg, it.seq, it.block * p.rows_per_wg, it.L, it.n, it.qbase});
   }
 }
 
-template <int D, bool KV8, bool SHARED, bool PLANNED>
+template <int D, bool KV8, int NW, bool SHARED, bool PLANNED>
 hipError_t launch_kernel(const AttnParams& p, long long grid, hipStream_t st) {
   static std::atomic<unsigned long long> configured{0};
-  constexpr int lds = Cfg<D, KV8>::LDS;
-  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, SHARED, PLANNED>), lds, configured);
+  constexpr int lds = Cfg<D, KV8, NW>::LDS;
+  const hipError_t e = raise_lds_limit_once(reinterpret_cast<const void*>(&k_prefill<D, KV8, NW, SHARED, PLANNED>), lds, configured);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_prefill<D, KV8, SHARED, PLANNED>), dim3((unsigned)grid), dim3(256), lds, st, p);
+  hipLaunchKernelGGL((k_prefill<D, KV8, NW, SHARED, PLANNED>), dim3((unsigned)grid), dim3(64 * NW), lds, st, p);
   return hipGetLastError();
+}
+
+template <int D, bool KV8, int NW>
+hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
+  if (p.rows_per_wg == kWaveRows)
+    return p.pf_self ? launch_kernel<D, KV8, NW, false, false>(p, grid, st) : launch_kernel<D, KV8, NW, false, true>(p, grid, st);
+  return p.pf_self ? launch_kernel<D, KV8, NW, true, false>(p, grid, st) : launch_kernel<D, KV8, NW, true, true>(p, grid, st);
 }
 
 template <int D, bool KV8>
 hipError_t launch(const AttnParams& p, long long grid, hipStream_t st) {
-  if (p.rows_per_wg == kWaveRows)
-    return p.pf_self ? launch_kernel<D, KV8, false, false>(p, grid, st) : launch_kernel<D, KV8, false, true>(p, grid, st);
-  return p.pf_self ? launch_kernel<D, KV8, true, false>(p, grid, st) : launch_kernel<D, KV8, true, true>(p, grid, st);
+  if constexpr (D == 128)
+    if (p.pf_waves == 8) return launch<D, KV8, 8>(p, grid, st);
+  return launch<D, KV8, 4>(p, grid, st);
 }
 
 }  // namespace
 
 hipError_t launch_prefill(const AttnParams& p, int D, hipStream_t st) {
-  const long long grid = (long long)p.pf_cap * p.Hkv * p.hgroups + (p.pf_self ? 1 : 0);
+  const long long grid = (long long)(p.total_q / p.rows_per_wg + p.num_seqs) * p.Hkv * p.hgroups + (p.pf_self ? 1 : 0);
   if (grid <= 0) return hipSuccess;
   if (!grid_fits(grid)) return hipErrorInvalidValue;
   if (D == 128) return !p.kv8 ? launch<128, false>(p, grid, st) : launch<128, true>(p, grid, st);
