@@ -13,7 +13,7 @@ CSRC = os.path.join(_HERE, "csrc")
 OBJ = os.path.join(_HERE, "_build")
 LIB = os.path.join(_HERE, "libhook.so")
 BENCH_LIB = os.path.join(_HERE, "libhook_bench.so")
-SOURCES = ["api.hip", "plan.hip", "prefill.hip", "decode.hip", "attn_f32.hip", "steer.hip",
+SOURCES = ["api.hip", "plan.hip", "prefill.hip", "mixed.hip", "decode.hip", "attn_f32.hip", "steer.hip",
            "capture.hip", "reduce.hip", "residual_steer.hip", "span_mass.hip", "config_json.hip", "kv_write.hip",
            "validate.hip"]
 BENCH_SOURCES = ["bench.hip"]

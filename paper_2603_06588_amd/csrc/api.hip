@@ -4,6 +4,7 @@
 #include "../../include/hook_api.h"
 #include "hook_device.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace {
@@ -62,17 +63,35 @@ int decode_item_bound(long long num_decode_seqs, long long max_context, int wg_p
   return (int)cap;
 }
 
+// Ranges per kv head and head group that give every one of the 256 compute units `each` workgroups.
+int ranges_of_one_round(const Layout& l, const hook_attn_probe_args* a, int each) {
+  const long long wgs = (long long)a->num_kv_heads * l.dec_hgroups;
+  return (int)((256 * each + wgs - 1) / wgs);
+}
+
 // Ranges of a self-planned batch of single rows (decode.hip): one resident
 // round of workgroups - a second, partial round costs more than its finer balance gains - but no range shorter than
 // kStreamMinBlocks.  A round is taken as 3 workgroups for each of 256 compute units, 2 for groups of 8 heads: what the
 // kernel's launch bounds promise and head size 128 over a 16-bit cache holds.  (Instantiations with fewer registers,
 // at head size 64 or over an 8-bit cache, hold 4 in some cases; a finer cut for them has not been measured.)
 int stream_ranges(const hook_attn_probe_args* a, const Layout& l, int num_seqs) {
-  const long long one_round = 256 * (l.dec_hp == 8 ? 2 : 3), wgs = (long long)a->num_kv_heads * l.dec_hgroups;
   // (and one range per sequence more, for ranges that end with their sequence)
   const long long finest = ((long long)num_seqs * a->max_blocks_per_seq + kStreamMinBlocks - 1) / kStreamMinBlocks + num_seqs;
-  const long long ranges = (one_round + wgs - 1) / wgs;
+  const long long ranges = ranges_of_one_round(l, a, l.dec_hp == 8 ? 2 : 3);
   return (int)(ranges < finest ? ranges : finest);
+}
+
+// Row blocks and single rows of a mixed batch share a launch (mixed.hip) where the single rows plan themselves and are few: no
+// more sequences than ranges at one workgroup per compute unit, so that hardly a range pays for more than two start-ups, which
+// nothing covers there.  Apart and together, 32 / 8 heads, us: 8 x 1000 tokens and a chunk of 512 rows 32.8 and 23.9, with new rows 38.2
+// and 29.7, 4 x 6000 and 130 35.7 and 29.8, 16 x 3000-6000 and 2 x 1000 100 and 88, 28 x 4096 and 4 x 2048 233 and 213, 30 x 500-5000 and 200
+// over an 8-bit cache 57 and 55; 20 x 4096 and 200 at 64 / 8 heads over an 8-bit cache 68.6 and 63.8; 30 x 1000-4000 and 4 x 300 at 8 / 1
+// 34.1 and 25.3.  With more sequences either way: 60 x 4096 and 4 x 2048 312 and 291, with new rows 326 and 332, 60 x 500-5000 and 200 over
+// an 8-bit cache 88 and 99, 180 x 500-2000 and 2 x 300 184 and 193.  Groups of four heads and more; four waves to a row block (eight
+// leave no room on their compute unit).
+bool shares_launch(const hook_attn_probe_args* a, const Layout& l) {
+  return a->dtype == HOOK_BF16 && a->batch_kind == HOOK_BATCH_MIXED && l.ranges > 0 && l.pf_waves == 4 && l.hpw == 4 &&
+         a->num_seqs <= kStreamSeqs && a->num_seqs <= ranges_of_one_round(l, a, 1);
 }
 
 // Sequences up to which single rows plan themselves; up to kStreamSeqs of them do in any case (why there: hook_device.h).
@@ -193,6 +212,11 @@ __attribute__((visibility("hidden"))) hook_status check_attn_probe_args(const ho
   return HOOK_OK;
 }
 
+// (for a caller that times the launches)
+__attribute__((visibility("hidden"))) bool attn_probe_shares_launch(const hook_attn_probe_args* a) {
+  return shares_launch(a, make_layout(a, a->workspace_bytes));
+}
+
 __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn_probe_args* a, hipEvent_t* ev,
                                                                  void* workspace, size_t workspace_bytes) {
   bool nothing_to_do = false;
@@ -261,6 +285,8 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   p.pf_self = a->dtype == HOOK_BF16 && a->num_seqs <= kScanMaxSeqs && a->batch_kind != HOOK_BATCH_DECODE_ONLY &&
               (streams || a->batch_kind == HOOK_BATCH_PREFILL_ONLY) &&
               (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups * (l.pf_waves / 4) <= kSelfPlanMaxWgs);
+  p.one_launch = shares_launch(a, l) ? 1 : 0;
+  if (p.one_launch) p.dec_ranges = std::min(l.ranges, ranges_of_one_round(l, a, 1));
   // The streaming kernel can do without a write ahead of it while a wave can hold every new row's place, one per lane.
   // (A launch ahead costs a call 4 us: 1 x 1237 tokens 16.6 us against 11.7, 8 x 4096 30.2 against 26.3, 64 x 2048 77.2
   // against 72.8.  Where to look would take more registers for more sequences, and the loop has none to spare.)
@@ -285,8 +311,9 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
   // (a reusing call finds the work lists of the same batch in the workspace)
   if ((plans && launch_plan(p, st) != hipSuccess) || !mark(1)) return HOOK_ERR_LAUNCH;
   const bool chunks = a->batch_kind != HOOK_BATCH_DECODE_ONLY, singles = a->batch_kind != HOOK_BATCH_PREFILL_ONLY;
-  if ((chunks && launch_prefill(p, a->head_dim, st) != hipSuccess) || !mark(2)) return HOOK_ERR_LAUNCH;
-  if ((singles && launch_decode(p, a->head_dim, st) != hipSuccess) || !mark(3)) return HOOK_ERR_LAUNCH;
+  if ((p.one_launch ? launch_mixed(p, a->head_dim, st) : chunks ? launch_prefill(p, a->head_dim, st) : hipSuccess) != hipSuccess || !mark(2))
+    return HOOK_ERR_LAUNCH;
+  if ((singles && !p.one_launch && launch_decode(p, a->head_dim, st) != hipSuccess) || !mark(3)) return HOOK_ERR_LAUNCH;
   if ((singles && launch_combine(p, a->head_dim, st) != hipSuccess) || !mark(4)) return HOOK_ERR_LAUNCH;
   return HOOK_OK;
 }

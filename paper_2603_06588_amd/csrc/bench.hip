@@ -11,6 +11,7 @@
 
 namespace hook {
 hook_status run_attn_probe(const hook_attn_probe_args* a, hipEvent_t* ev, void* workspace, size_t workspace_bytes);
+bool attn_probe_shares_launch(const hook_attn_probe_args* a);
 
 namespace {
 
@@ -83,6 +84,7 @@ void zero_skipped(const hook_attn_probe_args* a, float* kernel_ms) {
     kernel_ms[0] = 0.0f;
   if (a->batch_kind == HOOK_BATCH_DECODE_ONLY) kernel_ms[1] = 0.0f;
   if (a->batch_kind == HOOK_BATCH_PREFILL_ONLY) kernel_ms[2] = kernel_ms[3] = 0.0f;
+  if (attn_probe_shares_launch(a)) kernel_ms[2] = 0.0f;      // (the chunk kernel's time is that of both)
 }
 
 }  // namespace

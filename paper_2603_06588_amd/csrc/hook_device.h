@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include <atomic>
+#include <type_traits>
 
 namespace hook {
 
@@ -38,7 +39,7 @@ constexpr int kDecodeFillWgs = 2048;
 // cache 546 and 480.  Over 16-bit caches the line could lie higher for some batches, which lose the planning launch: 200 x
 // 1000-4000 334 and 338, one of 32768 tokens among 199 of 300 82 and 86; but 256 x 20-200 takes 49 and 42.
 constexpr int kStreamSeqs = 192;
-constexpr int kScanMaxSeqs = 512;   // the most whose lengths a workgroup scans to plan itself, here and in prefill.hip
+constexpr int kScanMaxSeqs = 512;   // the most whose lengths a workgroup scans to plan itself, here and in prefill_device.h
 constexpr int kStreamMinBlocks = 4;
 // A running maximum is only raised when a tile's maximum exceeds it by more than this many
 // powers of two; exponentials then stay below 2^kLazyTau, far inside fp32 range, and the
@@ -113,6 +114,7 @@ struct AttnParams {
   int dec_ranges;                   // > 0: no planner; the blocks of all single rows are cut into this many ranges
   int dec_write;                    // the streaming kernel stores the new rows (k_new / v_new) itself
   int plan_fresh;                   // the call promises a fully written `mass` (not a reused plan)
+  int one_launch;                   // row blocks and single rows share a launch (mixed.hip)
   int pf_self;                      // the chunk kernel finds its row blocks itself, no planner
   // geometry chosen on the host from G
   int batch_kind;                   // 0 mixed, 1 no single-row sequences, 2 only single-row sequences
@@ -294,6 +296,15 @@ __device__ __forceinline__ void load_spans_uniform(const int* key_spans, int seq
   }
 }
 
+// f(0), f(1), ... f(N - 1) with the number as a constant
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 // launchers (defined next to their kernels); all return hipGetLastError() after the launch
 // The dynamic-LDS limit of a kernel is an attribute per device: it is raised on the first launch
 // on each device (bit per device id in `done`), from whichever host thread gets there first.
@@ -315,6 +326,7 @@ inline bool grid_fits(long long workgroups) { return workgroups >= 0 && workgrou
 hipError_t launch_plan(const AttnParams& p, hipStream_t st);
 hipError_t launch_kv_write(const KvWriteParams& p, hipStream_t st);
 hipError_t launch_prefill(const AttnParams& p, int D, hipStream_t st);
+hipError_t launch_mixed(const AttnParams& p, int D, hipStream_t st);
 hipError_t launch_decode(const AttnParams& p, int D, hipStream_t st);
 hipError_t launch_combine(const AttnParams& p, int D, hipStream_t st);
 hipError_t launch_attn_f32(const AttnParams& p, int D, hipStream_t st);
