@@ -530,7 +530,7 @@ __device__ __forceinline__ void stream_range(const AttnParams& p, float (&red)[4
     // (the same bytes) before it reads.
     if (__builtin_amdgcn_ballot_w64((sc.bits & kStatHint) != 0) != 0) {
       for (int t = 0; t * kKvRowTile < p.total_q; ++t)
-        kv_write_tile<256, 1>(p.kvw, t, tid, reinterpret_cast<long long*>(&red[0][0][0]));
+        kv_write_tile<256, 1>(p.kvw, t, tid, reinterpret_cast<long long*>(&red[0][0][0]), p.kvw.cu_q_lens);
       __threadfence();
       __syncthreads();
     }

@@ -9,7 +9,13 @@ namespace {
 
 __global__ __launch_bounds__(256) void k_kv_write(const KvWriteParams p) {
   __shared__ long long dst_row[kKvRowTile];   // blk * Hkv * kBlock + slot, or -1: do not write
-  kv_write_tile<256>(p, blockIdx.x, threadIdx.x, dst_row);
+  __shared__ int sh_cu[256];
+  if (p.num_seqs < 256) {
+    if ((int)threadIdx.x <= p.num_seqs) sh_cu[threadIdx.x] = p.cu_q_lens[threadIdx.x];      // (the tile code waits for all of them)
+    kv_write_tile<256>(p, blockIdx.x, threadIdx.x, dst_row, sh_cu);
+  } else {
+    kv_write_tile<256>(p, blockIdx.x, threadIdx.x, dst_row, p.cu_q_lens);
+  }
 }
 
 }  // namespace

@@ -56,10 +56,14 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(const AttnParams p) {
     if (p.kvw.k_new != nullptr) {
       constexpr int kGroups = kPlanThreads / 256;
       __shared__ long long dst_row[kGroups][kKvRowTile];
+      __shared__ int sh_cu[kPlanThreads];
+      const bool copied = p.kvw.num_seqs < kPlanThreads;
+      if (tid <= p.kvw.num_seqs && copied) sh_cu[tid] = p.kvw.cu_q_lens[tid];      // (the tile code waits for all of them)
       const int ntiles = (p.kvw.total_q + kKvRowTile - 1) / kKvRowTile;
       const int group = tid >> 8;
       for (int t0 = (blockIdx.x - 1) * kGroups; t0 < ntiles; t0 += (gridDim.x - 1) * kGroups)
-        kv_write_tile<256>(p.kvw, t0 + group, tid & 255, dst_row[group]);
+        if (copied) kv_write_tile<256>(p.kvw, t0 + group, tid & 255, dst_row[group], sh_cu);
+        else kv_write_tile<256>(p.kvw, t0 + group, tid & 255, dst_row[group], p.kvw.cu_q_lens);
     }
     return;
   }
