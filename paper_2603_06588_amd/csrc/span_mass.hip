@@ -43,6 +43,7 @@ struct SpanParams {
   float2* stats;    // split path: (max, sum) of every (sequence, probed head, row slot, key split)
   int nsplit;       // key splits of pass 1
   int sgroups;      // span groups of pass 2
+  int span_turn;    // spans of a workgroup of pass 2 at a time (8, 4, 2 or 1)
   int nq_pad;       // NQ rounded up to whole 16-row blocks
 };
 
@@ -74,7 +75,7 @@ __device__ __forceinline__ void load_keys(const SpanParams& p, int blk, int g, i
 template <int D>
 __device__ __forceinline__ f32x4 scores(const Frag<D>& f, const bf16x8 (&qf)[D / 32]);
 
-// A stream of key groups (kSmGroup tiles of 16 keys; group n starts at key first + n * step) run
+// (k_span_mass.)  A stream of key groups (kSmGroup tiles of 16 keys; group n starts at key first + n * step) run
 // as a three-stage pipeline per wave: block ids two groups ahead, K rows one group ahead,
 // arithmetic on the current group - so neither load latency sits on the critical path.
 // `use(tile_first_key, scores[NB])` is called for every tile whose first key is below `end`; NB blocks
@@ -135,6 +136,73 @@ __device__ __forceinline__ f32x4 scores(const Frag<D>& f, const bf16x8 (&qf)[D /
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, qf[s], acc, 0, 0, 0);
   }
   return acc;
+}
+
+// The tiles [0, ntiles) behind tile `first` of a sequence whose last block is last_blk, kTileRing of them requested ahead and the
+// scores of the next one computed beside `use` of the one before.  Block ids come 64 at a time, one per lane, so a tile costs
+// one scalar address instead of one per lane.  Past the end all lanes fetch the same 16 bytes, so that the compiler knows how many
+// loads are in flight.  4 prompts of 40-100 documents on 8 heads 38.1 us with stream_keys, 36.4 so (4 tiles ahead 37.1), on 32 heads 119.8 and
+// 108.5; 16 prompts 117.5 and 110.
+constexpr int kTileRing = 2;
+template <int D, int NB, bool KV8, typename F>
+__device__ __forceinline__ void stream_tiles(const SpanParams& p, const int* bt, int g, int lane, const bf16x8 (&qf)[NB][D / 32],
+                                             int first, int ntiles, int last_blk, F&& use) {
+  constexpr int KS = D / 32, ESZ = KV8 ? 1 : 2;
+  struct Raw { uint4 k[KV8 ? (KS + 1) / 2 : KS]; };      // 8-bit: two k-steps to a register quad, widened before use
+  if (ntiles <= 0) return;
+  const char* const base = static_cast<const char*>(p.k_cache) + (size_t)g * kBlock * D * ESZ;
+  const unsigned blk_bytes = (unsigned)p.Hkv * kBlock * D * ESZ, lane_off = (unsigned)(lane & 15) * D * ESZ + 8 * ESZ * (lane >> 4);
+  auto load_ids = [&](int t) {
+    const int blk = bt[min(first + t + lane, last_blk)];
+    return (unsigned)blk < (unsigned)p.num_blocks ? blk : 0;
+  };
+  int ids = load_ids(0), ids_next = 0;
+  if (ntiles > 64) ids_next = load_ids(64);
+  auto request = [&](int t, Raw& f) {
+    const global_bytes src = (global_bytes)(base + (unsigned long long)(unsigned)__builtin_amdgcn_readlane(ids, t & 63) * blk_bytes);
+    unsigned off = t < ntiles ? lane_off : 0;
+    asm("" : "+v"(off));
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if constexpr (KV8) {
+        const u32x2 v = *(const __attribute__((address_space(1))) u32x2*)(src + off + 32 * s);
+        if (s & 1) { f.k[s / 2].z = v.x; f.k[s / 2].w = v.y; } else { f.k[s / 2].x = v.x; f.k[s / 2].y = v.y; }
+      } else {
+        f.k[s] = load_global16(src + off + 64 * s);
+      }
+    }
+  };
+  auto tile_scores = [&](const Raw& d, f32x4 (&sc)[NB]) {
+    Frag<D> f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      if constexpr (KV8) f.k[s] = e4m3x8_to_bf16x8((s & 1) ? make_uint2(d.k[s / 2].z, d.k[s / 2].w) : make_uint2(d.k[s / 2].x, d.k[s / 2].y));
+      else f.k[s] = d.k[s];
+    }
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) sc[nb] = scores<D>(f, qf[nb]);
+  };
+  Raw ring[kTileRing];
+#pragma unroll
+  for (int u = 0; u < kTileRing; ++u) request(u, ring[u]);
+  f32x4 sc[NB], next[NB];
+  tile_scores(ring[0], sc);
+  for (int t = 0; t < ntiles; t += kTileRing) {
+#pragma unroll
+    for (int u = 0; u < kTileRing; ++u) {
+      if (u == 0 && ((t + kTileRing) & 63) == 0) {
+        ids = ids_next;
+        ids_next = load_ids(t + kTileRing + 64);
+      }
+      request(t + u + kTileRing, ring[u]);
+      __builtin_amdgcn_sched_barrier(0);
+      tile_scores(ring[(u + 1) % kTileRing], next);      // (beside the exponentials of the tile before it)
+      if (u == 0 || t + u < ntiles) use(16 * (first + t + u), sc);      // uniform
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) sc[nb] = next[nb];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
 }
 
 template <int D, bool KV8>
@@ -265,17 +333,26 @@ struct RowBlock {
   bool row_ok;
 };
 
-__device__ __forceinline__ bool row_block(const SpanParams& p, int i, int ps, int rb, int j, RowBlock& r) {
-  const int Lraw = p.seq_lens[i];
-  r.row0 = p.cu_q_lens[i];
-  const int n = p.cu_q_lens[i + 1] - r.row0;
-  const int L = min(Lraw, p.max_blocks * kBlock);
-  if (Lraw < 0 || n <= 0 || n > L || r.row0 < 0 || r.row0 + n > p.total_q) return false;
-  r.h = p.probe_heads[ps];
+// What it rests on, requested in one go.
+struct RowSource { int L, first, end, head, sel_b, sel_e; };
+
+__device__ __forceinline__ RowSource row_source(const SpanParams& p, int i, int ps) {
+  const RowSource q = {cload(p.seq_lens, i), cload(p.cu_q_lens, i), cload(p.cu_q_lens, i + 1), cload(p.probe_heads, ps),
+                       cload(p.query_sel, 2 * i), cload(p.query_sel, 2 * i + 1)};
+  asm volatile("" :: "s"(q.L), "s"(q.first), "s"(q.end), "s"(q.head), "s"(q.sel_b), "s"(q.sel_e));      // (not one behind the other's check)
+  return q;
+}
+
+__device__ __forceinline__ bool row_block(const SpanParams& p, const RowSource& q, int rb, int j, RowBlock& r) {
+  r.row0 = q.first;
+  const int n = q.end - r.row0;
+  const int L = min(q.L, p.max_blocks * kBlock);
+  if (q.L < 0 || n <= 0 || n > L || r.row0 < 0 || r.row0 + n > p.total_q) return false;
+  r.h = q.head;
   if ((unsigned)r.h >= (unsigned)p.Hq) return false;
   r.g = r.h / p.G;
-  const int qb = p.query_sel[2 * i];
-  const int qe = min(min(p.query_sel[2 * i + 1], n), qb + p.NQ);
+  const int qb = q.sel_b;
+  const int qe = min(min(q.sel_e, n), qb + p.NQ);
   r.slot0 = kSmRows * rb;
   const int t_lo = max(qb + r.slot0, 0), t_hi = min(qb + r.slot0 + kSmRows, qe);
   if (t_hi <= t_lo) return false;
@@ -298,10 +375,10 @@ __device__ __forceinline__ void load_q(const SpanParams& p, const RowBlock& r, i
 // Both kernels are bound by latency, not by the bytes (4 prompts of 6-14 k tokens, 8 heads: 84 MB of keys): a wave spends
 // most of its time in the chain lengths -> rows -> block ids -> keys.  So the work is cut fine and the workgroups are small,
 // which lets the chip start them all at once and even out sequences of unequal length: pass 1 takes 1024 keys with 4
-// waves (2048 keys: 4 waves 38 us, 16 waves 40; 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27), and the second kernel
-// gives every span a wave of its own, two to a workgroup.
+// waves (2048 keys: 4 waves 38 us, 16 waves 40; 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27).
 constexpr int kStatWaves = 4;     // waves per workgroup of pass 1
-constexpr int kSumWaves = 2;      // waves (spans at a time) per workgroup of the second kernel
+constexpr int kSumWaves = 8;      // waves per workgroup of the second kernel, and spans at a time
+constexpr int kSumWgs = 128;      // workgroups that it has at least, or else fewer spans to each: walks should be spread over the chip
 constexpr int kSplitBlocks = 2;   // blocks of 16 rows per workgroup: they share every K fetch
 constexpr int kSplitRows = kSplitBlocks * kSmRows;
 constexpr int kSplitKeys = 1024;  // keys of one workgroup of pass 1 (until kMaxSplits is reached)
@@ -309,8 +386,8 @@ constexpr int kMaxSplits = 16;    // key splits of pass 1
 // A span is summed by the workgroup whose split it begins in, which reads on behind its split to the end of its last span.
 // The spans of a split have to be disjoint and in order for that, and at most kListSpans; where they are not, the split's
 // sum of exponentials carries a minus sign, and every span that begins in it gets its own walk over its keys in the
-// second kernel.  So does a span that ends behind its split in a sequence with a span of more than kOverhang keys (a mark, -1, in
-// `mass` says so): one such walk takes as long as many, and reading on would come on top.
+// second kernel.  So does a span that ends behind its split in a sequence with a span of more than kOverhang keys: one such walk takes as
+// long as many, and reading on would come on top.
 // The list holds as many spans as leave four workgroups to a compute unit their LDS: 4 keys each in 1024 keys, 16 each in the
 // 4096 keys that a split of a 64 k context has.  (64 spans: 654 documents of 5-20 keys in each of 4 prompts of 8200 tokens 106.8
 // us, 48.0 so; 1024 of 30-50 in 65536 76.7 and 57.3; all walked, without the list in the first kernel, 105.4 and 72.7.)
@@ -322,8 +399,9 @@ constexpr int kOverhang = 512;
 __device__ __forceinline__ bool row_blocks(const SpanParams& p, int i, int ps, int bx, int j,
                                            RowBlock (&r)[kSplitBlocks], bool (&has)[kSplitBlocks], int& pos_max) {
   static_assert(kSplitBlocks == 2, "each block has one other block to shadow");
+  const RowSource q = row_source(p, i, ps);
 #pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) has[nb] = row_block(p, i, ps, kSplitBlocks * bx + nb, j, r[nb]);
+  for (int nb = 0; nb < kSplitBlocks; ++nb) has[nb] = row_block(p, q, kSplitBlocks * bx + nb, j, r[nb]);
   if (!has[0] && !has[1]) return false;
 #pragma unroll
   for (int nb = 0; nb < kSplitBlocks; ++nb) {
@@ -345,8 +423,8 @@ __device__ __forceinline__ int split_tiles(int pos_max, int nsplit) { return (po
 // the same reference.  The waves take runs of tiles one behind the other, so a wave meets the spans in order and
 // keeps the sum of the one it is in, in registers; a finished span's sum goes to LDS, where the waves are merged.  Two waves
 // have at most one span in common, so slot k + w is written by no other wave than w.
-// 4 prompts of 7-16 k tokens, 8 heads, 32 rows, documents of 64-256 keys: 27 us and 8 for the second kernel (24 and 30 when the
-// second one read all documents again); 7 documents of 20-40 keys 9.1 + 3.6 (7.6 + 5.0).
+// 4 prompts of 7-16 k tokens, 8 heads, 32 rows, documents of 64-256 keys: 25 us and 4.8 for the second kernel (24 and 30 when the
+// second one read all documents again); 7 documents of 20-40 keys 10 + 3.8.
 template <int D, bool KV8>
 __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams p) {
   __shared__ float sh_m[kStatWaves][kSplitRows];
@@ -442,8 +520,8 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
       acc[nb] = 0.0f;
     }
   };
-  stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, w_lo, 16 * kSmGroup, w_hi, pos_max,
-                                    [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+  stream_tiles<D, kSplitBlocks, KV8>(p, bt, r[0].g, lane, qf, w_lo / 16, (w_hi - w_lo + 15) / 16, pos_max / 16,
+                                     [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
     float ex[kSplitBlocks][4], sum[kSplitBlocks];
 #pragma unroll
     for (int nb = 0; nb < kSplitBlocks; ++nb) {
@@ -522,118 +600,143 @@ __global__ __launch_bounds__(kStatWaves * 64) void k_span_stats(const SpanParams
       v += a < lo + 16 * run * (w + 1) && e > lo + 16 * run * w ? sh_part[kk + w][row] * wgt[w] : 0.0f;
     mass[sh_s[kk]] = v;
   }
-  if (listed && summed < count && threadIdx.x < kSplitRows) mass[sh_s[summed]] = -1.0f;
+}
+
+// Maximum and sum over the 16 lanes of a DPP row, in all of them.
+template <int N>
+__device__ __forceinline__ float rotate16(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x120 + N, 0xf, 0xf, false));
+}
+__device__ __forceinline__ float max16(float v) {
+  v = fmaxf(v, rotate16<8>(v));
+  v = fmaxf(v, rotate16<4>(v));
+  v = fmaxf(v, rotate16<2>(v));
+  return fmaxf(v, rotate16<1>(v));
+}
+__device__ __forceinline__ float sum16(float v) {
+  v += rotate16<8>(v);
+  v += rotate16<4>(v);
+  v += rotate16<2>(v);
+  return v + rotate16<1>(v);
 }
 
 // The second kernel: from the splits' references to the row's, divided by its normaliser; zeros where there is no row or
-// no key; and the walk over the keys of spans that the first kernel left out.
+// no key; and the walk over the keys of spans that the first kernel left out.  A workgroup takes p.span_turn spans of 32 rows: a
+// thread per row and split finds what the split's sums are multiplied by, a thread per row and span multiplies, so that
+// eight neighbouring lanes read and write 32 bytes of a row of `mass` (a wave to a span, four bytes of every row at a time, took 8.0 us for
+// 4 x 40-100 documents on 8 heads and 32 rows; this takes 4.8).  The waves share out the walks: 16 spans of 600-1500 keys 47.7 us with
+// the first kernel and a wave to a walk, 33.4 so.
 template <int D, bool KV8>
-__global__ __launch_bounds__(kSumWaves * 64) void k_span_sums(const SpanParams p) {
+__global__ __launch_bounds__(kSumWaves * 64, 4) void k_span_sums(const SpanParams p) {
+  static_assert(kSumWaves * 64 == kSplitRows * kMaxSplits && kSmRows == 16, "");
+  __shared__ float sh_f[kSplitRows][kMaxSplits + 1];     // factor of a row's sums over the spans that begin in a split
+  __shared__ float sh_M[kSplitRows], sh_inv[kSplitRows];
+  __shared__ float sh_part[kSumWaves][kSplitRows];
+  __shared__ unsigned sh_bits;                           // splits without a list; kLong: some span is long
+  constexpr unsigned kLong = 1u << kMaxSplits;
   const int i = blockIdx.z / p.sgroups, sg = blockIdx.z % p.sgroups, ps = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, quarter = lane >> 4;
   float* const mass = p.mass + ((size_t)i * p.P + ps) * p.NQ * p.S;
-  const int slot0 = kSplitRows * blockIdx.x;
+  const int2* const spans = reinterpret_cast<const int2*>(p.key_spans) + (size_t)i * p.S;
+  const int slot0 = kSplitRows * blockIdx.x, turn = p.span_turn, turn_log2 = 31 - __builtin_clz(turn);
+  const int row = tid >> turn_log2, slot = slot0 + row, k = tid & (turn - 1);      // this thread's row, and its span of a turn
+  const bool mine = row < kSplitRows && slot < p.NQ;
+  if (tid == 0) sh_bits = 0;
   RowBlock r[kSplitBlocks];
   bool has[kSplitBlocks];
   int pos_max;
   if (!row_blocks(p, i, ps, blockIdx.x, j, r, has, pos_max)) {   // uniform
-    for (int s = sg * kSumWaves + wave; s < p.S; s += p.sgroups * kSumWaves)
-      if (lane < kSplitRows && slot0 + lane < p.NQ) mass[(size_t)(slot0 + lane) * p.S + s] = 0.0f;
+    for (int s = sg * turn + k; s < p.S; s += p.sgroups * turn)
+      if (mine) mass[(size_t)slot * p.S + s] = 0.0f;
     return;
   }
   const int per = split_tiles(pos_max, p.nsplit);
-  // each row's reference and normaliser from the key splits of the first kernel
-  float M[kSplitBlocks], inv[kSplitBlocks];
-  float2 v[kSplitBlocks][kMaxSplits / 4];
-#pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) {
-    // the four lanes of a row take a quarter of the splits each (a block without rows reads the other one's)
-    const int block = has[nb] ? nb : 1 - nb;
-    const float2* st = p.stats + (((size_t)i * p.P + ps) * p.nq_pad + slot0 + kSmRows * block + j) * p.nsplit;
-#pragma unroll
-    for (int u = 0; u < kMaxSplits / 4; ++u) {
-      const int sp = kMaxSplits / 4 * quarter + u;
-      v[nb][u] = sp < p.nsplit ? st[sp] : make_float2(-INFINITY, 0.0f);
+  int s0 = sg * turn;
+  if (s0 >= p.S) return;
+  const unsigned rows_ok = ((unsigned)__builtin_amdgcn_ballot_w64(r[0].row_ok) & 0xffffu) |
+                           ((unsigned)__builtin_amdgcn_ballot_w64(r[1].row_ok) << 16);
+  const bool ok = mine && ((rows_ok >> (row & (kSplitRows - 1))) & 1);
+  int2 span = spans[min(s0 + k, p.S - 1)];
+  float out = ok && s0 + k < p.S ? mass[(size_t)slot * p.S + s0 + k] : 0.0f;
+  {
+    const int sp = tid % kMaxSplits, rr = tid / kMaxSplits;
+    // (a block without rows reads the other one's)
+    const int from = slot0 + (has[0] && has[1] ? rr : has[0] ? rr % kSmRows : kSmRows + rr % kSmRows);
+    const float2 v = sp < p.nsplit ? p.stats[(((size_t)i * p.P + ps) * p.nq_pad + from) * p.nsplit + sp] : make_float2(-INFINITY, 0.0f);
+    bool any_long = false;
+    for (int s = tid; s < p.S; s += kSumWaves * 64) {
+      const int2 x = spans[s];
+      any_long = any_long || min(x.y, pos_max + 1) - max(x.x, 0) > kOverhang;
     }
+    const float M = max16(v.x);
+    const float inv = 1.0f / sum16(fabsf(v.y) * fast_exp2(v.x - M));      // an empty split adds 0
+    sh_f[rr][sp] = v.x == -INFINITY ? 0.0f : fast_exp2(v.x - M) * inv;    // -inf: the row sees no key of this split
+    if (sp == 0) { sh_M[rr] = M; sh_inv[rr] = inv; }
+    unsigned long long hit = __builtin_amdgcn_ballot_w64(__float_as_int(v.y) < 0);
+    hit |= hit >> 32;
+    hit |= hit >> 16;
+    const unsigned bits = ((unsigned)hit & (kLong - 1)) | (__builtin_amdgcn_ballot_w64(any_long) != 0 ? kLong : 0u);
+    __syncthreads();
+    if (lane == 0 && bits) atomicOr(&sh_bits, bits);
+    __syncthreads();
   }
-  const int2* const spans = reinterpret_cast<const int2*>(p.key_spans) + (size_t)i * p.S;
-  int s = sg * kSumWaves + wave;
-  if (s >= p.S) return;
-  int2 span = spans[s];
-  float out[kSplitBlocks];
-#pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) out[nb] = r[nb].row_ok ? mass[(size_t)(r[nb].slot0 + j) * p.S + s] : 0.0f;
-#pragma unroll
-  for (int nb = 0; nb < kSplitBlocks; ++nb) {
-    float mx = -INFINITY, Lsum = 0.0f;
-#pragma unroll
-    for (int u = 0; u < kMaxSplits / 4; ++u) mx = fmaxf(mx, v[nb][u].x);
-    mx = row_max(mx);
-#pragma unroll
-    for (int u = 0; u < kMaxSplits / 4; ++u) Lsum += fabsf(v[nb][u].y) * fast_exp2(v[nb][u].x - mx);   // an empty split adds 0
-    M[nb] = mx;
-    inv[nb] = 1.0f / row_sum(Lsum);
-  }
+  const unsigned bits = sh_bits;
   for (;;) {
-    const int a = max(span.x, 0), e = min(span.y, pos_max + 1);
-    bool walk = false;
-    if (e > a) {                                   // uniform
-      const int sp = a / 16 / per, from = sp / (kMaxSplits / 4) * 16 + j;
+    const int s = s0 + k, a = max(span.x, 0), e = min(span.y, pos_max + 1);
+    const bool some = s < p.S && e > a;
+    const int sp = some ? a / 16 / per : 0;
+    // (what the first kernel did not sum: any span of a split without a list, and behind a split with long spans in the sequence)
+    const bool left_out = some && (((bits >> sp) & 1) || ((bits & kLong) && e > 16 * per * (sp + 1)));
+    const unsigned walk = (unsigned)__builtin_amdgcn_ballot_w64(left_out) & ((1u << turn) - 1);      // (lane k of each wave: span k)
+    if (mine && s < p.S && !((walk >> k) & 1)) mass[(size_t)slot * p.S + s] = ok && some ? out * sh_f[row][sp] : 0.0f;
+    if (walk) {                                      // (the same in all waves)
+      const int parts = kSumWaves >> turn_log2, wk = wave / parts, part = wave % parts;
+      if ((walk >> wk) & 1) {
+        const int wa = __builtin_amdgcn_readlane(a, wk), we = __builtin_amdgcn_readlane(e, wk);
+        const int* bt = p.block_table + (size_t)i * p.max_blocks;
+        bf16x8 qf[kSplitBlocks][D / 32];
 #pragma unroll
-      for (int nb = 0; nb < kSplitBlocks; ++nb) {
-        float ref = v[nb][0].x, sum = v[nb][0].y;
+        for (int nb = 0; nb < kSplitBlocks; ++nb) load_q<D>(p, r[nb], quarter, qf[nb]);
+        const float c = KV8 ? p.scale_log2 * p.k_scale[r[0].g] : p.scale_log2;
+        float acc[kSplitBlocks], M[kSplitBlocks];
 #pragma unroll
-        for (int u = 1; u < kMaxSplits / 4; ++u) {
-          ref = sp % (kMaxSplits / 4) == u ? v[nb][u].x : ref;
-          sum = sp % (kMaxSplits / 4) == u ? v[nb][u].y : sum;
+        for (int nb = 0; nb < kSplitBlocks; ++nb) { acc[nb] = 0.0f; M[nb] = sh_M[kSmRows * nb + j]; }
+        const int tiles = (we + 15) / 16 - wa / 16, run = (tiles + parts - 1) / parts;
+        stream_tiles<D, kSplitBlocks, KV8>(p, bt, r[0].g, lane, qf, wa / 16 + run * part, min(run, tiles - run * part), pos_max / 16,
+                                           [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
+#pragma unroll
+          for (int nb = 0; nb < kSplitBlocks; ++nb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int key = key0 + 4 * quarter + q;
+              acc[nb] += (key >= wa && key < we && key <= r[nb].pos) ? fast_exp2(sc[nb][q] * c - M[nb]) : 0.0f;
+            }
+        });
+#pragma unroll
+        for (int nb = 0; nb < kSplitBlocks; ++nb) {
+          const float v = row_sum(acc[nb]);
+          if (quarter == 0) sh_part[wave][kSmRows * nb + j] = v;
         }
-        ref = __shfl(ref, from);                   // -inf: the row sees no key of this split
-        walk = walk || out[nb] < 0.0f || __float_as_int(__shfl(sum, from)) < 0;
-        out[nb] *= ref == -INFINITY ? 0.0f : fast_exp2(ref - M[nb]) * inv[nb];
       }
-      walk = __builtin_amdgcn_ballot_w64(walk) != 0;
-    }
-    if (walk) {
-      const int* bt = p.block_table + (size_t)i * p.max_blocks;
-      bf16x8 qf[kSplitBlocks][D / 32];
-#pragma unroll
-      for (int nb = 0; nb < kSplitBlocks; ++nb) load_q<D>(p, r[nb], quarter, qf[nb]);
-      const float c = KV8 ? p.scale_log2 * p.k_scale[r[0].g] : p.scale_log2;
-      float acc[kSplitBlocks];
-#pragma unroll
-      for (int nb = 0; nb < kSplitBlocks; ++nb) acc[nb] = 0.0f;
-      stream_keys<D, kSplitBlocks, KV8>(p, bt, r[0].g, j, quarter, qf, a, 16 * kSmGroup, e, pos_max,
-                                        [&](int key0, const f32x4 (&sc)[kSplitBlocks]) {
-#pragma unroll
-        for (int nb = 0; nb < kSplitBlocks; ++nb)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int key = key0 + 4 * quarter + q;
-            acc[nb] += (key < e && key <= r[nb].pos) ? fast_exp2(sc[nb][q] * c - M[nb]) : 0.0f;
-          }
-      });
-#pragma unroll
-      for (int nb = 0; nb < kSplitBlocks; ++nb) {
-        out[nb] = row_sum(acc[nb]) * inv[nb];
+      __syncthreads();
+      if (mine && ((walk >> k) & 1)) {
+        float v = 0.0f;
+        for (int w = 0; w < parts; ++w) v += sh_part[k * parts + w][row];
+        mass[(size_t)slot * p.S + s] = ok ? v * sh_inv[row] : 0.0f;
       }
+      __syncthreads();
     }
-#pragma unroll
-    for (int nb = 0; nb < kSplitBlocks; ++nb) {
-      const int slot = slot0 + kSmRows * nb + j;
-      if (quarter == 0 && slot < p.NQ) mass[(size_t)slot * p.S + s] = r[nb].row_ok && e > a ? out[nb] : 0.0f;
-    }
-    s += p.sgroups * kSumWaves;
-    if (s >= p.S) break;
-    span = spans[s];
-#pragma unroll
-    for (int nb = 0; nb < kSplitBlocks; ++nb) out[nb] = r[nb].row_ok ? mass[(size_t)(r[nb].slot0 + j) * p.S + s] : 0.0f;
+    s0 += p.sgroups * turn;
+    if (s0 >= p.S) break;
+    span = spans[min(s0 + k, p.S - 1)];
+    out = ok && s0 + k < p.S ? mass[(size_t)slot * p.S + s0 + k] : 0.0f;
   }
 }
 
 // geometry of the split path from host scalars only
-struct SplitGeom { int nsplit, least, sgroups, nq_pad; size_t bytes; bool usable; };
+struct SplitGeom { int nsplit, least, sgroups, span_turn, nq_pad; size_t bytes; bool usable; };
 
 // Scratch memory for fewer key splits than one per this many keys is not used (nor touched): pass 1 would run on a small
 // part of the chip.
@@ -650,8 +753,13 @@ inline SplitGeom split_geometry(const hook_attn_probe_args* a) {
   // as many as the launch grid's third dimension (65535) holds
   if ((long long)a->num_seqs * g.nsplit > 65535) g.nsplit = 65535 / a->num_seqs;
   if (g.least > g.nsplit) g.least = g.nsplit;
-  // one span per wave, as long as that dimension holds the groups
-  g.sgroups = (a->max_spans + kSumWaves - 1) / kSumWaves;
+  // Spans eight at a time, fewer where that leaves compute units without work, as long as that dimension holds the groups.  (Long
+  // spans, which are walked, ask for more workgroups, many small ones for fewer.  At least 64 and 128, us: 16 of 600-1500 keys on 8 heads
+  // 58.5 and 33.4; at least 128 and 256: 4 x 50 of 20-60 keys on one head 19.7 and 22.0, 3 x 60 on 8 heads 21.9 and 24.3.)
+  const long long blocks = (long long)a->num_seqs * a->num_probe_heads * ((a->max_sel_q + kSplitRows - 1) / kSplitRows);
+  g.span_turn = kSumWaves;
+  while (g.span_turn > 1 && blocks * ((a->max_spans + g.span_turn - 1) / g.span_turn) < kSumWgs) g.span_turn /= 2;
+  g.sgroups = (a->max_spans + g.span_turn - 1) / g.span_turn;
   if (g.sgroups < 1) g.sgroups = 1;
   if (a->num_seqs > 0 && g.sgroups > 65535 / a->num_seqs) g.sgroups = 65535 / a->num_seqs;
   g.nq_pad = (a->max_sel_q + kSmRows - 1) / kSmRows * kSmRows;
@@ -706,7 +814,7 @@ extern "C" hook_status hook_span_mass(const hook_attn_probe_args* a) {
   if (a->workspace_bytes < geo.bytes) geo.nsplit = (int)(a->workspace_bytes / per_split);
   if (geo.usable && a->workspace && geo.nsplit >= geo.least && (reinterpret_cast<uintptr_t>(a->workspace) % 8) == 0) {
     p.stats = static_cast<float2*>(a->workspace);
-    p.nsplit = geo.nsplit; p.sgroups = geo.sgroups; p.nq_pad = geo.nq_pad;
+    p.nsplit = geo.nsplit; p.sgroups = geo.sgroups; p.span_turn = geo.span_turn; p.nq_pad = geo.nq_pad;
     const unsigned gx = (unsigned)((geo.nq_pad / kSmRows + kSplitBlocks - 1) / kSplitBlocks);
     const dim3 ga(gx, (unsigned)P, (unsigned)(p.num_seqs * geo.nsplit)), gb(gx, (unsigned)P, (unsigned)(p.num_seqs * geo.sgroups));
     const dim3 ta(kStatWaves * 64), tb(kSumWaves * 64);
