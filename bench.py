@@ -27,10 +27,10 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 # until the counters are taken again.
 TRAFFIC = {
     # key: (bytes per launch, source files, hash of those files when the counters were taken)
-    "k_prefill/c2": (832380411, ("prefill.hip", "prefill_device.h", "hook_device.h"), "4df5ccb5af9dd9df"),
-    "k_prefill/c4": (5258875412, ("prefill.hip", "prefill_device.h", "hook_device.h"), "4df5ccb5af9dd9df"),
-    "k_decode/c3": (4891087101, ("decode.hip", "decode_device.h", "hook_device.h"), "9c0c08c359d4f7a9"),
-    "k_decode/c3_fp8": (2436617855, ("decode.hip", "decode_device.h", "hook_device.h"), "9c0c08c359d4f7a9"),
+    "k_prefill/c2": (656501520, ("prefill.hip", "prefill_device.h", "hook_device.h"), "b81210cd43fa0172"),
+    "k_prefill/c4": (3354381645, ("prefill.hip", "prefill_device.h", "hook_device.h"), "b81210cd43fa0172"),
+    "k_decode/c3": (4891000941, ("decode.hip", "decode_device.h", "hook_device.h"), "6686ab14b299088e"),
+    "k_decode/c3_fp8": (2436606485, ("decode.hip", "decode_device.h", "hook_device.h"), "6686ab14b299088e"),
 }
 
 
