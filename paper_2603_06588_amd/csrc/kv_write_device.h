@@ -7,7 +7,7 @@
 
 namespace hook {
 
-constexpr int kKvRowTile = 8;    // rows of k_new / v_new per tile (16 rows: 20 us for 8256 rows, 8: 15, 4: 16.4)
+constexpr int kKvRowTile = 8;    // rows of k_new / v_new per tile (16 rows: 20 us for 8256 rows, 8: 15, 4: 16.4, before the search moved to shared memory)
 
 // fl32(x / scale) clamped to the range of the 8-bit format (NaN stays NaN)
 __device__ __forceinline__ float fp8_prescale(float x, float scale) {
@@ -28,7 +28,7 @@ __device__ __forceinline__ uint2 quantize_chunk_e4m3(const uint4 v, float scale)
 // One tile of kKvRowTile consecutive rows, worked on by the NT threads of a workgroup (thread index
 // tid).  dst_row is kKvRowTile entries of shared memory, `cu` the sequences' first rows (p.cu_q_lens or a copy in shared
 // memory, which makes the search one trip to memory instead of log2(num_seqs): 8 single rows and a chunk of 512 29.6 -> 28.7 us, 2 x 200 rows into an
-// 8-bit cache 19.5 -> 19.2, thousands of rows alike).  The tile's rows are requested first, then
+// 8-bit cache 19.5 -> 19.2, 8256 rows in a launch of their own 15.2 -> 12.3, in the planning launch alike).  The tile's rows are requested first, then
 // one thread per row finds the row's sequence (binary search in cu) and its cache slot; then every thread moves 16-byte chunks.
 // Rows of invalid sequences, positions beyond the block table and block ids outside the cache are
 // dropped: nothing outside the cache is ever written.
