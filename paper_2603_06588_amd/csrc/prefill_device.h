@@ -789,12 +789,13 @@ __device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem,
   }
 }
 
-// A row's sums are exact under any reference that keeps them finite.  It is done over, from its true maximum, if later
-// scores lie 2^64 above its first tile's, or if its output is not finite although large values alone are no reason for
-// that (with sums below 2^8 they are).
+// A row's sums are exact under any reference that keeps them within range.  It is done over, from its true maximum, if later
+// scores lie 2^64 above its first tile's, if all scores of its first tile are -inf (there is no maximum to refer to then; every
+// other row's sum holds the 1 of its first tile's maximum), or if its output is not finite although large values alone are no
+// reason for that (with sums below 2^8 they are).
 template <int D>
 __device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
-  bool again = !(l_tot < 0x1p64f);
+  bool again = !(l_tot >= 0.5f && l_tot < 0x1p64f);
   if (__builtin_amdgcn_ballot_w64(l_tot >= 0x1p8f) != 0) {
     float zs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll

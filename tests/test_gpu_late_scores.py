@@ -80,3 +80,24 @@ def test_large_values_under_a_low_reference(d):
     blk, row = _rows_of(b, 0, 0)
     b.v_cache[blk, 1, row] = (b.v_cache[blk, 1, row].float() * 2.0 ** 110).to(torch.bfloat16)
     _check(b, _run(b))
+
+
+@pytest.mark.parametrize("G,d", [(4, 128), (1, 128), (8, 64), (2, 64)])
+@pytest.mark.parametrize("later", [-1.2e-17, -4e-18, -6e-19])
+def test_first_tile_of_minus_infinity(G, d, later):
+    """Rows whose scores over the first tile all leave the range of fp32 downwards, so that no maximum is there to refer to:
+    the keys behind it, at some -150, -50 and -8 powers of two, get the mass."""
+    b = _batch(4400 + d + G, [300, 161], [300, 70], G, d, False)
+    b.query_sel[:, 0] = 64
+    clean = _run(b)
+    b.q[:300, G:], b.k_cache = 0, b.k_cache.clone()
+    b.q[:300, G:, 0] = 1e20
+    blk, row = _rows_of(b, 0, 0)
+    key = torch.arange(300)
+    b.k_cache[blk, 1, row, 0] = torch.where(key < 64, -1e20, later * d ** 0.5 / 128 ** 0.5 * (1.0 + (key % 7) / 50.0)).to(torch.bfloat16)
+    got = _run(b)
+    ref, ref_mass = oracle.attn_probe_batch(b)
+    out = got.out.cpu().double()[64:]
+    assert (out - ref[64:]).abs().max() <= OUT_RTOL_MAX * ref[64:].abs().max()
+    assert (got.mass.cpu().double() - ref_mass).abs().max() <= MASS_ATOL
+    assert torch.equal(bits(got.out[:, :G]), bits(clean.out[:, :G])) and torch.equal(bits(got.out[300:]), bits(clean.out[300:]))
