@@ -24,9 +24,10 @@
 // loops with all operand reads and fetches in place: 33 cycles per 32-cycle matrix instruction; this loop 31-34 while
 // both waves are inside it, 39 on a 32 k prompt, where the chip is at its power limit and holds 1.5-1.6 GHz).  Phases, with
 // the scores of a tile under its predecessor's exponentials and P V after them, took 44.
-// A row's softmax reference is its maximum over the first tile and stays that: no maxima, no exchange between lanes and no
-// rescaling inside the loop (a fifth of its vector instructions), and nothing waits for a whole tile's scores.  The sums
-// are exact softmax sums under any reference while they are finite; rows where they are not are done over (rows_alone).
+// A row's softmax reference is its maximum over the first tile: no maxima and no exchange between lanes inside the loop (a fifth
+// of its vector instructions), and nothing waits for a whole tile's scores.  The sums are exact softmax sums under any
+// reference while they are finite.  Where they grow large because scores have risen far above the reference, it is raised
+// (raise_reference); rows whose sums left the range of fp32 before that are done over (rows_alone).
 // 32768 tokens at 64 / 8 heads 14.9 -> 14.4 ms, one prompt of 2048 at 32 / 8 51.1 -> 44.6 us, 16 ragged prompts of 512-2048
 // 253.8 -> 242.8 us, the same at head size 64 156.4 -> 148 us, 8 chunks over an 8-bit cache 251 -> 243 us.
 //
@@ -255,6 +256,8 @@ struct Pipe {
   unsigned v_addr[4];     // the same for the transposed V reads, one per 32-dimension block of the output
   f32x16 O[D / 32];
   float l;                // normaliser
+  unsigned long long high;      // lanes whose normaliser calls for a higher reference
+  int unusual;            // key from which on a half tile has keys behind some row; -1 where there are such lanes
   float am[kMaxSpans];    // span sums
 };
 
@@ -334,6 +337,45 @@ __device__ __forceinline__ void tile_barrier() {
   __syncthreads();
 }
 
+// In front of an iteration, where some lane's normaliser has reached kRaiseSum (as seen half an iteration before): the reference
+// of such a row is raised by the whole powers of two in it, and everything that counts from it comes down by them: output,
+// sums, the probabilities that wait in P[0].  A row whose output has overflowed already is marked by its normaliser.
+// Scores of unit spread never get here (normalisers of 2^15 at 128 k tokens), and what a wave pays for it is a comparison a
+// tile, 0.5-1 % (32 k prompt 13.30 -> 13.40 ms, 16 ragged prompts 239.3 -> 242, at head size 64 133 -> 134.6 us; with the comparison right in front
+// of the branch another 1 % at head size 64; called in the middle of an iteration 10 % there; at its end 80 vector registers are spilled, as
+// the compiler then keeps the output twice).  Before, rows that had risen by 2^64 were done over.  Keys from 96 on with
+// scores of 12 natural units' spread, 32 / 8 heads, done over, now, and under a running maximum raised by 2^8 at a time: 2048 tokens
+// 250, 47.9 and 52.2 us, 8192 2505, 496 and 493, 16 ragged prompts 954, 269 and 270, at head size 64 532, 155 and 161; of 4 units' spread (where
+// nothing is raised) 43.5, 43.7 and 50.6, 456, 462 and 496, 245, 248 and 264.  Raised from 2^16 on, 8192 tokens of 4 units' spread took 532.
+constexpr float kRaiseSum = 0x1p24f, kSumLimit = 0x1p120f;
+template <int D, bool PROBE>
+__device__ __forceinline__ void raise_reference(const WaveCtx& cx, Pipe<D>& t, float& m) {
+  const float l = half_max(t.l);
+  const bool high = ((unsigned)t.high | (unsigned)(t.high >> 32)) >> (cx.lane & 31) & 1;      // (whatever the other rows do)
+  const int k = high && l < kSumLimit ? __builtin_amdgcn_frexp_expf(l) - 1 : 0;
+  // what the reference really rises by: rounded where it has a fraction, and to less or nothing at all where it is far beyond 2^24
+  const float raised = m + (float)k, by = raised - m;
+  const float f = fast_exp2(-by), f16 = __builtin_ldexpf(1.0f, -(int)__builtin_rintf(by));      // (16-bit values keep their bits)
+  m = raised;
+  float z[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      z[r & 3] = __builtin_fmaf(t.O[mb][r], 0.0f, z[r & 3]);
+      t.O[mb][r] *= f;
+    }
+  t.l = t.l * f + (k > 0 ? (z[0] + z[1]) + (z[2] + z[3]) : 0.0f);
+  if constexpr (PROBE) {
+#pragma unroll
+    for (int i = 0; i < kMaxSpans; ++i) t.am[i] *= f;
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t.P[0][g][i] = pack_bf16(bf16_lo(t.P[0][g][i]) * f16, bf16_hi(t.P[0][g][i]) * f16);
+}
+
 // ---- one pipelined iteration --------------------------------------------------------------
 // On entry P[0] holds the probabilities of the first half of tile kt, S[1] the raw scores of its second half, and the
 // rings the first operands of K(kt+1) and V(kt).  Half a tile at a time,
@@ -348,7 +390,7 @@ __device__ __forceinline__ void tile_barrier() {
 // of the tile after that.
 template <int D, bool KV8, int NW, bool PROBE>
 __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
-                                          const int* bt, unsigned long long& boff, Pipe<D>& t, float m,
+                                          const int* bt, unsigned long long& boff, Pipe<D>& t, float& m,
                                           const bf16x8 (&qf)[D / 16], Spans& sp) {
   using C = Cfg<D, KV8, NW>;
   constexpr int NS = C::SLOTS, EPS = 16 / NS, R = C::RING, NQ = C::KSTEPS, NP = 2 * C::MB, NI = C::NI;
@@ -368,8 +410,20 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
     // half 0: exponentials of the second half of kt, half 1: of the first half of kt + 1
     f32x16& Sx = t.S[half ^ 1];
     const int key0 = kTileKeys * kt + 32 * (half + 1);
-    if (j == 0) {
+    if (i == NS + 2) {       // (not at the end, where the branch would wait)
+      t.l += sum[0];
+      t.high = __builtin_amdgcn_ballot_w64(t.l >= kRaiseSum);
+    }
+    if (i == NS + 4) {
+      t.unusual = t.high != 0 ? -1 : cx.pos_min - 31;
+      asm volatile("" : "+s"(t.unusual));
+    }
+    if (i == 0 && key0 > t.unusual) {       // (one branch for both)
+      if (t.high != 0) raise_reference<D, PROBE>(cx, t, m);
       if (key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
+    }
+    if (j == 0) {
+      if (i > 0 && key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
       __builtin_amdgcn_sched_barrier(0);
       exp_begin<EPS>(cx, Sx, m, h);
     }
@@ -443,7 +497,7 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
       }
     }
   });
-  t.l += sum[0] + sum[1];
+  t.l += sum[1];
 }
 
 // The same iteration for a wave that has no key left: the tiles behind its rows' positions are for the other row blocks
@@ -533,8 +587,8 @@ __device__ __forceinline__ void last_tile(const WaveCtx& cx, int kt, Pipe<D>& t,
   });
 }
 
-// The first tile's scores, on which the softmax reference of each row rests (`m`: the row's maximum in them, and it stays
-// that; row_alone deals with rows whose later scores are far above it), and the probabilities of its first half.
+// The first tile's scores, on which the softmax reference of each row rests (`m`: the row's maximum in them), and the
+// probabilities of its first half.
 // On entry K(0) lies in LDS; V(0) and K(1) are on their way, and there on return.
 template <int D, bool KV8, int NW>
 __device__ __forceinline__ void first_half(const WaveCtx& cx, const bf16x8 (&qf)[D / 16], Pipe<D>& t, float& m) {
@@ -614,6 +668,8 @@ __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem
 #pragma unroll
   for (int s = 0; s < kMaxSpans; ++s) t.am[s] = 0.0f;
   first_half<D, KV8, NW>(cy, qf, t, m);
+  t.high = 0;
+  t.unusual = cy.pos_min - 31;
   if constexpr (PROBE) add_spans<D>(cy, sp, 0, t.S[0], t.l, t.am);
   __builtin_amdgcn_sched_barrier(0);
   const int full = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
@@ -706,33 +762,6 @@ __device__ __forceinline__ void first_tiles_kv8(const WaveCtx& cx, unsigned char
   }
 }
 
-// Raw, masked scores of the half tile at key0, straight from the cache.
-template <int D, bool KV8, int NW>
-__device__ __forceinline__ f32x16 scores_from_cache(const WaveCtx& cx, const int* bt, int key0, const bf16x8 (&qf)[D / 16]) {
-  constexpr int E = KV8 ? 1 : 2;
-  const int key = key0 + (cx.lane & 31);
-  const int blk = bt[min(key >> 4, cx.last_blk)];
-  const global_bytes row = (global_bytes)(cx.kbase + (KV8 ? 0 : 2048) + block_bytes(cx, blk) + (key & 15) * (D * E) + 8 * E * cx.hf);
-  f32x16 S;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) S[r] = 0.0f;
-#pragma unroll
-  for (int s = 0; s < D / 16; ++s) {
-    uint4 a;
-    if constexpr (KV8) {
-      const u32x2 b = *(const __attribute__((address_space(1))) u32x2*)(row + 16 * s);
-      a = e4m3x8_to_bf16x8(make_uint2(b.x, b.y));
-    } else {
-      a = load_global16(row + 32 * s);
-    }
-    bf16x8 av;
-    __builtin_memcpy(&av, &a, 16);
-    S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qf[s], S, 0, 0, 0);
-  }
-  mask_half(cx, key0, S);
-  return S;
-}
-
 // One work item: rows [row0, row0 + rows_per_wg) of sequence `seq` (context L, n rows, first q row
 // qbase) for the heads of (kvh, hg).
 struct Item { int kvh, hg, seq, row0, L, n, qbase; };
@@ -789,13 +818,13 @@ __device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem,
   }
 }
 
-// A row's sums are exact under any reference that keeps them within range.  It is done over, from its true maximum, if later
-// scores lie 2^64 above its first tile's, if all scores of its first tile are -inf (there is no maximum to refer to then; every
-// other row's sum holds the 1 of its first tile's maximum), or if its output is not finite although large values alone are no
-// reason for that (with sums below 2^8 they are).
+// A row's sums are exact under any reference that keeps them within range.  It is done over, under a running maximum, if scores
+// rose beyond that within one tile (a sum of kSumLimit), if all scores of its first tile are -inf (there is no maximum to
+// refer to then; every other row's sum holds the 1 of its first tile's maximum or what raised the reference from there), or if
+// its output is not finite although large values alone are no reason for that (with sums below 2^8 they are).
 template <int D>
 __device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
-  bool again = !(l_tot >= 0.5f && l_tot < 0x1p64f);
+  bool again = !(l_tot >= 0.5f && l_tot < kSumLimit);
   if (__builtin_amdgcn_ballot_w64(l_tot >= 0x1p8f) != 0) {
     float zs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -809,13 +838,16 @@ __device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
   return again;
 }
 
-// The wave's rows from their true maxima, without the other waves: keys straight from the cache, values through the rows of
-// LDS that its output passed through.  Rows that need it are rare, so this is short rather than fast.
+// The wave's rows under a running maximum, without the other waves: keys straight from the cache, values through the rows of LDS
+// that its output passed through, both requested half a tile ahead.  Rows that need it are rare, so this is short rather than fast.
+// All rows done over (keys from 96 on with 40 natural units' spread), 32 / 8 heads, in two passes without requests ahead, now, and by the
+// former loop, which knew no such rows: 2048 tokens 250, 156 and 51 us, 8192 2489, 1704 and 464, 16 ragged prompts 1074, 756 and 246, at head
+// size 64 581, 383 and 153.
 template <int D, bool KV8, int NW>
 __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
                                            const WaveCtx& cx, Spans& sp, const int* bt, unsigned rows) {
   using C = Cfg<D, KV8, NW>;
-  constexpr int E = KV8 ? 1 : 2, LPR = D / 8, RPL = 64 / LPR;      // lanes per row, rows per load (eight values to a lane)
+  constexpr int E = KV8 ? 1 : 2, LPR = D / 8, RPL = 64 / LPR, NV = 32 / RPL;      // lanes per row, rows per load (eight values to a lane), loads
   bf16x8 qf[C::KSTEPS];
   {
     const int t = wi.wrow0 + min(cx.lane & 31, it.n - 1 - wi.wrow0);
@@ -826,14 +858,32 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
       __builtin_memcpy(&qf[s], &v, 16);
     }
   }
-  float m = -INFINITY;
-  for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
-    const f32x16 S = scores_from_cache<D, KV8, NW>(cx, bt, key0, qf);
+  // eight values each: of this lane's key, one piece per k-step; of rows RPL j + lane / LPR
+  std::conditional_t<KV8, u32x2, uint4> kp[C::KSTEPS], vp[NV];
+  auto request = [&](int first) {      // the half tile that begins with block `first`
+    const unsigned long long b0 = block_bytes(cx, cload(bt, min(first, cx.last_blk)));
+    const unsigned long long b1 = block_bytes(cx, cload(bt, min(first + 1, cx.last_blk)));
+    const unsigned long long ka = cx.kbase + (KV8 ? 0 : 2048) + (cx.lane & 16 ? b1 : b0) + (cx.lane & 15) * (D * E) + 8 * E * cx.hf;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) m = fmaxf(m, S[r] * cx.c);
-  }
-  m = half_max(m);
-  if (m == -INFINITY) m = 0.0f;
+    for (int s = 0; s < C::KSTEPS; ++s) {
+      if constexpr (KV8) kp[s] = *(const __attribute__((address_space(1))) u32x2*)(global_bytes)(ka + 16 * s);
+      else kp[s] = load_global16((global_bytes)(ka + 32 * s));
+    }
+    unsigned vo = (cx.lane / LPR) * (D * E) + 8 * E * (cx.lane % LPR);
+    asm("" : "+v"(vo));       // (so that the loads take a scalar base and a 32-bit lane offset)
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      const global_bytes va = (global_bytes)(cx.vbase + (j < NV / 2 ? b0 : b1)) + vo + RPL * (j % (NV / 2)) * (D * E);
+      if constexpr (KV8) vp[j] = *(const __attribute__((address_space(1))) u32x2*)va;
+      else vp[j] = load_global16(va);
+    }
+  };
+  auto widened = [](const auto& x) {
+    if constexpr (KV8) return e4m3x8_to_bf16x8(make_uint2(x.x, x.y));
+    else return x;
+  };
+  request(0);
+  float m = -INFINITY;
   sp.lo = 0;
   Pipe<D> t;
   t.l = 0.0f;
@@ -853,27 +903,48 @@ __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* s
   }
   for (int key0 = 0; key0 <= wi.pos_max; key0 += 32) {
 #pragma unroll
-    for (int j = 0; j < 32 / RPL; ++j) {
-      const int r = RPL * j + cx.lane / LPR, ch = cx.lane % LPR, key = key0 + r;
-      const int blk = bt[min(key >> 4, cx.last_blk)];
-      const global_bytes src = (global_bytes)(cx.vbase + block_bytes(cx, blk) + (key & 15) * (D * E) + 8 * E * ch);
-      uint4 v;
-      if constexpr (KV8) {
-        const u32x2 b = *(const __attribute__((address_space(1))) u32x2*)src;
-        v = e4m3x8_to_bf16x8(make_uint2(b.x, b.y));
-      } else {
-        v = load_global16(src);
-      }
-      if (key >= cx.L) v = make_uint4(0, 0, 0, 0);
+    for (int j = 0; j < NV; ++j) {
+      const int r = RPL * j + cx.lane / LPR, ch = cx.lane % LPR;
+      uint4 v = widened(vp[j]);
+      if (key0 + r >= cx.L) v = make_uint4(0, 0, 0, 0);      // 0 * NaN would poison the output
       *reinterpret_cast<uint4*>(vrows + r * C::RB + ((ch ^ v_swizzle<D>(r)) << 4)) = v;
     }
     in_order();
-    f32x16 S = scores_from_cache<D, KV8, NW>(cx, bt, key0, qf);
+    f32x16 S;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) S[r] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < C::KSTEPS; ++s) {
+      const uint4 a = widened(kp[s]);
+      bf16x8 av;
+      __builtin_memcpy(&av, &a, 16);
+      S = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, qf[s], S, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    request(key0 / kBlock + 2);
+    __builtin_amdgcn_sched_barrier(0);
+    mask_half(cx, key0, S);
+    float mx = S[0] * cx.c;
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, S[r] * cx.c);
+    mx = half_max(mx);
+    const bool up = mx > m + kLazyTau;
+    if (__builtin_amdgcn_ballot_w64(up) != 0) {
+      const float f = up ? fast_exp2(m - mx) : 1.0f;
+      m = up ? mx : m;
+      t.l *= f;
+#pragma unroll
+      for (int i = 0; i < kMaxSpans; ++i) t.am[i] *= f;
+#pragma unroll
+      for (int mb = 0; mb < C::MB; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t.O[mb][r] *= f;
+    }
     u32x4 P[2];
     HalfExp h;
-    exp_begin<1>(cx, S, m, h);
+    exp_begin<1>(cx, S, m == -INFINITY ? 0.0f : m, h);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) exp_slot<1>(cx, S, m, h, P, j);
+    for (int j = 0; j < 16; ++j) exp_slot<1>(cx, S, m == -INFINITY ? 0.0f : m, h, P, j);
     const float sum = exp_end<1>(S, h, P);
     t.l += sum;
     add_spans<D>(cx, sp, key0, S, sum, t.am);
@@ -950,7 +1021,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
 
   cx.hf = hf;
   cx.pos = L - n + t;
-  cx.pos_min = L - n + min(wrow0, n - 1);
+  cx.pos_min = __builtin_amdgcn_readfirstlane(L - n + min(wrow0, n - 1));
   cx.c = KV8 ? p.scale_log2 * p.k_scale[it.kvh] : p.scale_log2;
   cx.kbase = (unsigned long long)(size_t)p.k_cache + (size_t)it.kvh * C::BLK;
   cx.vbase = (unsigned long long)(size_t)p.v_cache + (size_t)it.kvh * C::BLK;

@@ -5,7 +5,7 @@ import torch
 
 import oracle
 from paper_2603_06588_amd import binding, workloads as W
-from helpers import F32_OUT_ATOL, bits
+from helpers import F32_OUT_ATOL, bits, plan_header
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -72,3 +72,26 @@ def test_row_blocks_before_a_tile_whose_value_is_not_finite(G, d, kv8, at):
     assert torch.equal(bits(got.out[:, :G]), bits(clean.out[:, :G])) and torch.equal(bits(got.mass), bits(clean.mass))
     hit = ~torch.isfinite(got.out[at:300, G:, 5].float())
     assert bool(hit.all()) and torch.isfinite(got.out[:300, :, :5].float()).all()
+
+
+@pytest.mark.parametrize("Hq,Hkv,kv8", [(64, 16, False), (64, 16, True), (64, 8, False)])
+def test_row_blocks_of_eight_waves_before_a_value_that_is_not_finite(Hq, Hkv, kv8):
+    """The same where eight waves share a tile's fetch: two row blocks of a group of four heads, one of a group of eight."""
+    L, at, G = 2100, 1100, Hq // Hkv
+    b = W.random_batch(3300 + Hkv, [L], [L], Hq, Hkv, 128, torch.bfloat16, num_probe_heads=2, max_sel_q=2, max_spans=2)
+    b.query_sel[:, 0], b.query_sel[:, 1] = 1000, 1002
+    if kv8:
+        b = W.fp8_cache_variant(b, 3301)
+    clean = _run(b, batch_kind=binding.BATCH_PREFILL_ONLY)
+    assert plan_header(clean)[0] == (L + 32 * 8 // G - 1) // (32 * 8 // G)       # (the number of row blocks says how many waves)
+    bad = b.to("cpu")
+    bad.v_cache = b.v_cache.clone()
+    blk, r = _row(b, 0, at)
+    bad.v_cache[blk, 1, r, 5] = 0x7F if kv8 else float("inf")
+    got = _run(bad, batch_kind=binding.BATCH_PREFILL_ONLY)
+    first = at // 64 * 64
+    assert torch.equal(bits(got.out[:first]), bits(clean.out[:first])) and torch.equal(bits(got.mass), bits(clean.mass))
+    others = [h for h in range(Hq) if h // G != 1]
+    assert torch.equal(bits(got.out[:, others]), bits(clean.out[:, others]))
+    mine = got.out[:, G:2 * G].float()
+    assert bool((~torch.isfinite(mine[at:, :, 5])).all()) and torch.isfinite(mine[:, :, :5]).all()
