@@ -94,6 +94,31 @@ bool shares_launch(const hook_attn_probe_args* a, const Layout& l) {
          a->num_seqs <= kStreamSeqs && a->num_seqs <= ranges_of_one_round(l, a, 1);
 }
 
+// Ranges of the single rows in such a launch.  One workgroup to a compute unit leaves a place for a row block, and streams as fast as
+// memory where its waves' requests are large (16-bit rows of 256 bytes for four heads, three blocks ahead).  Elsewhere it takes two:
+// with one, an 8-bit cache lost to two launches where contexts are deep and row blocks few (28 x 16384 tokens and a chunk of 130 rows at 64 / 8 heads
+// 211 us in two launches, 266 with one workgroup, 202 with two; at 32 / 8 172, 192 and 161; 8 x 32768 and 64 at 64 / 8 124, 154 and 119), and so did groups of
+// eight heads over 16-bit caches (8 x 32768 and 64 183, 189 and 177).  But row blocks that weigh more than the single rows
+// want that place (kRowsWeigh; decided by the kernel, which knows the contexts, or here where no context can be long enough), and cutting
+// each sequence into more than 16 ranges costs the merge more than it gains (8 x 16384 and 130 at 8 / 1 heads 25.0 with one, 28.8 with two).
+// Without a row to spare there is no row block to leave a place for (a batch of single rows without a hint: 8 x 1000 tokens at 32 / 8
+// heads 18.3 in two launches, 20.2 with one workgroup, 16.5 with two; 28 x 16384 of 8 bits at 64 / 8 204, 267 and 203); one sequence alone
+// has enough ranges with one (1 x 32768 at 32 / 8 heads 32.6, 32.1 and 33.8).
+void share_compute_units(const hook_attn_probe_args* a, const Layout& l, hook::AttnParams& p) {
+  const int one = std::min(l.ranges, ranges_of_one_round(l, a, 1)), two = std::min(l.ranges, ranges_of_one_round(l, a, 2));
+  const bool large = a->kv_dtype != HOOK_KV_FP8_E4M3 && a->head_dim == 128 && l.dec_hp == 4;
+  const long long rows = (long long)a->total_q - a->num_seqs, most_blocks = (long long)a->num_seqs * a->max_blocks_per_seq;
+  p.dec_few = 0;
+  if (rows <= 0) {
+    p.dec_ranges = large && a->num_seqs == 1 ? one : two;
+  } else if (large || two > 16 * a->num_seqs || hook::kRowsWeigh * rows >= most_blocks) {
+    p.dec_ranges = one;
+  } else {
+    p.dec_ranges = two;
+    p.dec_few = one;
+  }
+}
+
 // Sequences up to which single rows plan themselves; up to kStreamSeqs of them do in any case (why there: hook_device.h).
 // Where an item is few workgroups the planner cuts contexts down to 256 keys to fill the chip, so more sequences are
 // better off in equal ranges.  Streamed and planned, contexts of 100-1000, 500-4000 and 2000-8000 tokens: 4 / 1 heads, 200
@@ -286,7 +311,7 @@ __attribute__((visibility("hidden"))) hook_status run_attn_probe(const hook_attn
               (streams || a->batch_kind == HOOK_BATCH_PREFILL_ONLY) &&
               (a->num_seqs == 1 || (long long)(a->total_q / l.rows_per_wg) * a->num_kv_heads * l.hgroups * (l.pf_waves / 4) <= kSelfPlanMaxWgs);
   p.one_launch = shares_launch(a, l) ? 1 : 0;
-  if (p.one_launch) p.dec_ranges = std::min(l.ranges, ranges_of_one_round(l, a, 1));
+  if (p.one_launch) share_compute_units(a, l, p);
   // The streaming kernel can do without a write ahead of it while a wave can hold every new row's place, one per lane.
   // (A launch ahead costs a call 4 us: 1 x 1237 tokens 16.6 us against 11.7, 8 x 4096 30.2 against 26.3, 64 x 2048 77.2
   // against 72.8.  Where to look would take more registers for more sequences, and the loop has none to spare.)

@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256, (HP == 8 ? 2 : 3) + (KV8 || D == 64 ? 1 : 0)) 
 template <int D, int HP, bool KV8, bool WHOLE_LINES, int PER_LANE>
 __global__ __launch_bounds__(256, HP == 8 ? 2 : 3) void k_decode_stream(const AttnParams p) {
   __shared__ float red[4][HP][DecodeCfg<D>::PSTR];
-  stream_range<D, HP, KV8, WHOLE_LINES, PER_LANE, 1>(p, red, blockIdx.x);
+  stream_range<D, HP, KV8, WHOLE_LINES, PER_LANE, 1, false>(p, red, blockIdx.x);
 }
 
 // What a planner would have done besides, by one workgroup of the merge kernel: the header with the status word, zeros

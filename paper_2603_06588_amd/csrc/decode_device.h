@@ -459,6 +459,8 @@ __device__ __forceinline__ DecodeSeq decode_seq(const AttnParams& p, int Lraw, i
 // out to the ranges with hardly more blocks each, no range covers two: a sequence then takes its blocks divided by
 // `bpr` ranges, rounded up, which fits while bpr is at least total / (ranges - sequences).  kPieceBlocks is about
 // what a second piece costs in blocks.
+// SHARED_LAUNCH: row blocks in the same launch may call for fewer ranges than there are workgroups (dec_few; the last of them find
+// nothing to do).
 // PER_LANE: sequences that a lane has room for (with room for kScanMaxSeqs in every batch 1 x 1237 tokens take 11.13 instead
 // of 10.98 us).
 constexpr int kPieceBlocks = 4;
@@ -475,7 +477,7 @@ struct BlockScan {
   int bits;                     // status bits of this lane's sequences
 };
 
-template <int PER_LANE>
+template <int PER_LANE, bool SHARED_LAUNCH>
 __device__ __forceinline__ BlockScan<PER_LANE> scan_blocks(const AttnParams& p, int lane) {
   BlockScan<PER_LANE> sc;
   sc.K = (p.num_seqs + 63) >> 6;
@@ -497,8 +499,10 @@ __device__ __forceinline__ BlockScan<PER_LANE> scan_blocks(const AttnParams& p, 
   const int incl = wave_scan(sum);
   sc.excl = incl - sum;
   sc.total = __builtin_amdgcn_readlane(incl, 63);
-  sc.bpr = max((sc.total + p.dec_ranges - 1) / p.dec_ranges, kStreamMinBlocks);
-  const int spare = p.dec_ranges - p.num_seqs;
+  int ranges = p.dec_ranges;
+  if (SHARED_LAUNCH && p.dec_few > 0 && (long long)kRowsWeigh * (p.total_q - p.num_seqs) >= sc.total) ranges = p.dec_few;
+  sc.bpr = max((sc.total + ranges - 1) / ranges, kStreamMinBlocks);
+  const int spare = ranges - p.num_seqs;
   const int bpr_whole = spare > 0 ? max((sc.total + spare - 1) / spare, kStreamMinBlocks) : 0;
   sc.whole = spare > 0 && bpr_whole <= sc.bpr + kPieceBlocks;
   if (sc.whole) sc.bpr = bpr_whole;
@@ -506,7 +510,7 @@ __device__ __forceinline__ BlockScan<PER_LANE> scan_blocks(const AttnParams& p, 
 }
 
 // The work of workgroup `bid`.  AHEAD: blocks requested ahead of the one being computed.
-template <int D, int HP, bool KV8, bool WHOLE_LINES, int PER_LANE, int AHEAD>
+template <int D, int HP, bool KV8, bool WHOLE_LINES, int PER_LANE, int AHEAD, bool SHARED_LAUNCH>
 __device__ __forceinline__ void stream_range(const AttnParams& p, float (&red)[4][HP][DecodeCfg<D>::PSTR], int bid) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -515,7 +519,7 @@ __device__ __forceinline__ void stream_range(const AttnParams& p, float (&red)[4
   const int hg = rest % p.dec_hgroups;
   const int g = rest / p.dec_hgroups;
 
-  const BlockScan<PER_LANE> sc = scan_blocks<PER_LANE>(p, lane);
+  const BlockScan<PER_LANE> sc = scan_blocks<PER_LANE, SHARED_LAUNCH>(p, lane);
 
   // where the new rows go (at most one sequence per lane: dec_write).  A length beyond the block table is clamped, so
   // its new row has no place in the cache.

@@ -41,6 +41,11 @@ constexpr int kDecodeFillWgs = 2048;
 constexpr int kStreamSeqs = 192;
 constexpr int kScanMaxSeqs = 512;   // the most whose lengths a workgroup scans to plan itself, here and in prefill_device.h
 constexpr int kStreamMinBlocks = 4;
+// Cache blocks of single rows that a row of the row blocks in the same launch weighs: with fewer to each of them the single rows'
+// workgroups leave a place on every compute unit free (dec_few).  Two of them to a compute unit and one, over an 8-bit cache,
+// us: 28 x 16384 tokens and a chunk of 1000 rows (29 blocks to a row) 164 and 195, 20 x 4096 and 200 (26) 42.4 and 46.6, 16 x 3000-6000 and 2 x
+// 1000 (2.3) 61.0 and 54.7, 28 x 4096 and 4 x 1024 (1.8) 90.9 and 88.8.
+constexpr int kRowsWeigh = 5;
 // A running maximum is only raised when a tile's maximum exceeds it by more than this many
 // powers of two; exponentials then stay below 2^kLazyTau, far inside fp32 range, and the
 // normaliser carries the same reference, so the result is the exact softmax.
@@ -112,6 +117,7 @@ struct AttnParams {
   int2* seq_dec;                    // per sequence {first partial record, number of records}
   float* partials;                  // [dec_cap, Hq, D + kPartialPad]
   int dec_ranges;                   // > 0: no planner; the blocks of all single rows are cut into this many ranges
+  int dec_few;                      // > 0: into this many where row blocks of the same launch weigh more (kRowsWeigh)
   int dec_write;                    // the streaming kernel stores the new rows (k_new / v_new) itself
   int plan_fresh;                   // the call promises a fully written `mass` (not a reused plan)
   int one_launch;                   // row blocks and single rows share a launch (mixed.hip)

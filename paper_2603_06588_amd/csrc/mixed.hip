@@ -13,17 +13,25 @@ namespace hook {
 
 namespace {
 
-// The first workgroups take ranges of the single rows' contexts, one workgroup to a compute unit (dec_ranges), the rest row blocks.
-// Three blocks are requested ahead: the registers are there, and a wave has its SIMD's single rows to itself.
+// The first workgroups take ranges of the single rows' contexts, one or two workgroups to a compute unit (dec_ranges), the rest row blocks.
+// Three blocks are requested ahead: the registers are there, and a wave has its SIMD's single rows to itself or shares them with one other.
+// (Groups of eight heads over a 16-bit cache at head size 128 would spill eight registers, and have two workgroups to a
+// compute unit instead: one workgroup and three blocks, two and three, two and one, 28 x 16384 tokens and a chunk of 130 rows 320, 335 and
+// 305 us, 28 x 4096 and 100 92, 101 and 87.)
+// K rows by half lines at head size 128 for groups of four, as in the launch of their own beyond kLineSeqs: whole lines, 32 / 8 heads, 16 x 3000-6000
+// tokens and 2 x 1000 rows 69.9 -> 65.9, 28 x 4096 and 4 x 2048 199 -> 191, but 8 x 32768 and 64 168 -> 172, 28 x 8192 and 130 150 -> 152,
+// and no line between the two has been looked for.
 template <int D, bool KV8, int HP, bool PLANNED>
 __global__ __launch_bounds__(256, 2) void k_mixed(const AttnParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   typedef float Red[4][HP][DecodeCfg<D>::PSTR];
   static_assert(sizeof(Red) <= Cfg<D, KV8, 4>::LDS, "");
+  constexpr int AHEAD = HP == 8 && D == 128 && !KV8 ? 1 : 3;
   const int rows = p.dec_ranges * p.Hkv * p.dec_hgroups, first = (rows + 7) & ~7;      // (row blocks keep their chiplets)
   const int bid = blockIdx.x;
   if (bid < first) {
-    if (bid < rows) stream_range<D, HP, KV8, lines_always<D, HP, KV8>(), kStreamSeqs / 64, 3>(p, *reinterpret_cast<Red*>(smem), bid);
+    if (bid < rows)
+      stream_range<D, HP, KV8, lines_always<D, HP, KV8>(), kStreamSeqs / 64, AHEAD, true>(p, *reinterpret_cast<Red*>(smem), bid);
     return;
   }
   row_block<D, KV8, 4, false, PLANNED>(p, smem, bid - first, gridDim.x - first - 1);

@@ -1,11 +1,14 @@
 """Mixed batches of few sequences: row blocks and single rows share a launch.  Row blocks give the bits they have by
 themselves, single rows (other ranges, other partial sums) the oracle's results, on both sides of the line on the number of
-sequences and of the one on self-planning (needs an MI355X)."""
+sequences, of the one on self-planning and of the ones on the workgroups per compute unit.  That the launch is one is read from a
+captured graph (needs an MI355X)."""
+import ctypes
+
 import pytest
 import torch
 
-from paper_2603_06588_amd import benchlib, binding, workloads as W
-from helpers import bits, compare_with_oracle, planned_reference
+from paper_2603_06588_amd import binding, workloads as W
+from helpers import bits, compare_with_oracle, plan_header, planned_reference
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -22,7 +25,32 @@ CASES = [
     (6008, [700, 30, 1, 513], [(2100, 2080), (2100, 2063)], 32, 8, 128, False, True),             # row blocks behind the planner
     (6009, [2500, 77, 640], [(1700, 1650), (900, 900), (1650, 1640)], 32, 8, 128, True, True),     # the same over an 8-bit cache
     (6010, [100, 50], [(300, 300)], 8, 4, 128, False, False),                             # groups of 2
+    # two workgroups of single rows to a compute unit ...
+    (6011, [1500, 2900, 800, 1700], [(200, 33)], 64, 8, 128, True, True),
+    (6012, [1500, 2900, 800, 1700], [(200, 33)], 64, 8, 128, False, True),
+    (6013, [1500, 2900, 800, 1700], [(200, 33)], 32, 8, 64, False, True),
+    (6014, [2900, 1100, 60, 40], [(60, 60)], 32, 8, 128, True, True),
+    # ... unless the row blocks weigh more than contexts of these lengths, which only the kernel sees
+    (6015, [2900, 100, 60, 40], [(60, 60)], 32, 8, 128, True, True),
+    (6016, [2900, 100, 60, 40], [(60, 60)], 64, 8, 128, False, True),
+    # no row blocks at all: two workgroups; one sequence: one
+    (6017, [500, 1200, 64], [], 32, 8, 128, False, True),
+    (6018, [500, 1200, 64], [], 64, 8, 128, True, True),
+    (6019, [1290], [], 32, 8, 128, False, True),
 ]
+
+
+def _kernels(call):
+    """Launches of the call: the nodes of a graph that captures it."""
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        call.launch(torch.cuda.current_stream())
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    nodes = ctypes.c_size_t(0)
+    get = ctypes.CDLL(path).hipGraphGetNodes
+    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get(g.raw_cuda_graph(), None, ctypes.byref(nodes)) == 0
+    return nodes.value
 
 
 @pytest.mark.parametrize("seed,ctx,chunks,Hq,Hkv,D,kv8,shared", CASES)
@@ -49,4 +77,5 @@ def test_row_blocks_and_single_rows_together(seed, ctx, chunks, Hq, Hkv, D, kv8,
         rows += range(first, first + min(x, 6))       # (what is selected)
         first += x
     print("      ", compare_with_oracle(b, call.out, call.mass, rows=rows), flush=True)
-    assert (benchlib.launch_timed(call)[2] == 0.0) == shared
+    planned = plan_header(call)[2] != 0
+    assert _kernels(call) == (2 if shared else 3) + planned       # (planner), row blocks and single rows, merge
