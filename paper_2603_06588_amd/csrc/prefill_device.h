@@ -158,7 +158,7 @@ __device__ __forceinline__ unsigned long long block_bytes(const WaveCtx& cx, int
   return (unsigned long long)((unsigned)blk < (unsigned)cx.num_blocks ? (unsigned)blk : 0u) * cx.blk_bytes;
 }
 
-// Id of this wave's block of a tile (past the last block: the last block again).  It is loaded an iteration before the
+// Id of this wave's block of a tile (past the workgroup's last block: that block again).  It is loaded an iteration before the
 // fetch that needs it, into a vector register: a scalar load would have every operand read from LDS wait for it.
 __device__ __forceinline__ int load_id(const WaveCtx& cx, const int* bt, int tile) {
   int i = min(4 * tile + cx.wb, cx.last_blk);
@@ -384,12 +384,12 @@ __device__ __forceinline__ void raise_reference(const WaveCtx& cx, Pipe<D>& t, f
 // one matrix instruction and 16 / SLOTS exponentials to a slot; the slots are fenced so that the streams stay interleaved.
 // Fetches of V(kt+1) and K(kt+2) (8-bit caches: the bytes of V(kt+2) and K(kt+3), once those of V(kt+1) and K(kt+2) are
 // widened) are issued first; the barrier that closes the iteration stands as many slots before its end as operands are
-// in flight, so nothing waits for the first operands of the next one.  The tile index of a fetch is clamped to the last
-// tile: the buffers are free by then and are never read again.
+// in flight, so nothing waits for the first operands of the next one.  A fetch behind the last tile takes the last tile's last block again:
+// the buffers are free by then and are never read again.
 // boff: cache offset of this wave's block of the tile whose V comes next (its K was the last one requested); id: its block
 // of the tile after that.
 template <int D, bool KV8, int NW, bool PROBE>
-__device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
+__device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int& id,
                                           const int* bt, unsigned long long& boff, Pipe<D>& t, float& m,
                                           const bf16x8 (&qf)[D / 16], Spans& sp) {
   using C = Cfg<D, KV8, NW>;
@@ -504,7 +504,7 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
 // of the workgroup (groups of fewer than four heads), and it only fetches its cache blocks of them.  (Going through
 // them with every score masked would let 0 * Inf from their values into its rows.)
 template <int D, bool KV8, int NW>
-__device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int ntiles, int& id,
+__device__ __forceinline__ void fetch_iter(const WaveCtx& cx, unsigned char* smem, int kt, int& id,
                                            const int* bt, unsigned long long& boff) {
   using C = Cfg<D, KV8, NW>;
   constexpr int NI = C::NI;
@@ -674,9 +674,9 @@ __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem
   __builtin_amdgcn_sched_barrier(0);
   const int full = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
   int kt = 0;
-  for (; kt < full; ++kt) tile_iter<D, KV8, NW, PROBE>(cy, smem, kt, ntiles, id, bt, boff, t, m, qf, sp);
+  for (; kt < full; ++kt) tile_iter<D, KV8, NW, PROBE>(cy, smem, kt, id, bt, boff, t, m, qf, sp);
   if (SHARED)
-    for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8, NW>(cy, smem, kt, ntiles, id, bt, boff);
+    for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8, NW>(cy, smem, kt, id, bt, boff);
   if (kTileKeys * ntiles > cy.L) {        // (the same for all waves)
     clear_past_end<D, KV8, NW>(cy, smem, ntiles - 1);
     __syncthreads();
@@ -999,7 +999,7 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   const int* const bt = p.block_table + (size_t)it.seq * p.max_blocks;
   WaveCtx cx;
   cx.L = L;
-  cx.last_blk = (L - 1) >> 4;
+  cx.last_blk = min((L - 1) >> 4, 4 * ntiles - 1);
   cx.w = w;
   cx.wb = w / C::WPB;
   cx.ws = w % C::WPB;
