@@ -117,7 +117,6 @@ struct AttnParams {
   int2* seq_dec;                    // per sequence {first partial record, number of records}
   float* partials;                  // [dec_cap, Hq, D + kPartialPad]
   int dec_ranges;                   // > 0: no planner; the blocks of all single rows are cut into this many ranges
-  int dec_few;                      // > 0: into this many where row blocks of the same launch weigh more (kRowsWeigh)
   int dec_write;                    // the streaming kernel stores the new rows (k_new / v_new) itself
   int plan_fresh;                   // the call promises a fully written `mass` (not a reused plan)
   int one_launch;                   // row blocks and single rows share a launch (mixed.hip)
@@ -130,6 +129,7 @@ struct AttnParams {
   int hgroups;                      // G / hpw
   int dec_hp;                       // q heads per decode workgroup (8, 4, 2 or 1)
   int dec_hgroups;                  // G / dec_hp
+  int dec_few;                      // > 0: ranges instead of dec_ranges where row blocks of the same launch weigh more (kRowsWeigh)
 };
 
 // The kernel's argument block, through a pointer whose origin the compiler cannot see.

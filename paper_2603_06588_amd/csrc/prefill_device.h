@@ -256,8 +256,6 @@ struct Pipe {
   unsigned v_addr[4];     // the same for the transposed V reads, one per 32-dimension block of the output
   f32x16 O[D / 32];
   float l;                // normaliser
-  unsigned long long high;      // lanes whose normaliser calls for a higher reference
-  int unusual;            // key from which on a half tile has keys behind some row; -1 where there are such lanes
   float am[kMaxSpans];    // span sums
 };
 
@@ -337,22 +335,23 @@ __device__ __forceinline__ void tile_barrier() {
   __syncthreads();
 }
 
-// In front of an iteration, where some lane's normaliser has reached kRaiseSum (as seen half an iteration before): the reference
-// of such a row is raised by the whole powers of two in it, and everything that counts from it comes down by them: output,
-// sums, the probabilities that wait in P[0].  A row whose output has overflowed already is marked by its normaliser.
-// Scores of unit spread never get here (normalisers of 2^15 at 128 k tokens), and what a wave pays for it is a comparison a
-// tile, 0.5-1 % (32 k prompt 13.30 -> 13.40 ms, 16 ragged prompts 239.3 -> 242, at head size 64 133 -> 134.6 us; with the comparison right in front
-// of the branch another 1 % at head size 64; called in the middle of an iteration 10 % there; at its end 80 vector registers are spilled, as
-// the compiler then keeps the output twice).  Before, rows that had risen by 2^64 were done over.  Keys from 96 on with
-// scores of 12 natural units' spread, 32 / 8 heads, done over, now, and under a running maximum raised by 2^8 at a time: 2048 tokens
-// 250, 47.9 and 52.2 us, 8192 2505, 496 and 493, 16 ragged prompts 954, 269 and 270, at head size 64 532, 155 and 161; of 4 units' spread (where
-// nothing is raised) 43.5, 43.7 and 50.6, 456, 462 and 496, 245, 248 and 264.  Raised from 2^16 on, 8192 tokens of 4 units' spread took 532.
+// Every kRaiseTiles tiles, where some lane's normaliser has reached kRaiseSum: the reference of such a row is raised by the whole
+// powers of two in it, and everything that counts from it comes down by them: output, sums, the probabilities that wait in
+// P[0].  A row whose output has overflowed already is marked by its normaliser.  Scores of unit spread never get here
+// (normalisers of 2^15 at 128 k tokens).
+// What a wave pays for it is a comparison that its branch waits for, up to 0.6 % (32 k prompt 13.47 -> 13.53 ms, 16 ragged prompts 242 -> 243 us, at head
+// size 64 143.5 -> 144.5; every tile 1 % more; at the end of a tile's code 80 vector registers are spilled, as the compiler
+// then keeps the output twice, and in its middle head size 64 takes 10 % more).  Eight tiles instead of four: 0.2 % less, but rounding of up to 8 %
+// more in span masses under scores of 16 units' spread.
+// Before, rows that had risen by 2^64 were done over.  Keys from 96 on with scores of 12 natural units' spread, 32 / 8 heads, done
+// over, now, and under a running maximum raised by 2^8 at a time: 2048 tokens 250, 44.7 and 51.7 us, 8192 2513, 472 and 501, 16 ragged prompts
+// 954, 252 and 272, at head size 64 531, 146 and 163.
 constexpr float kRaiseSum = 0x1p24f, kSumLimit = 0x1p120f;
+constexpr int kRaiseTiles = 4;
 template <int D, bool PROBE>
-__device__ __forceinline__ void raise_reference(const WaveCtx& cx, Pipe<D>& t, float& m) {
+__device__ __forceinline__ void raise_reference(Pipe<D>& t, float& m) {
   const float l = half_max(t.l);
-  const bool high = ((unsigned)t.high | (unsigned)(t.high >> 32)) >> (cx.lane & 31) & 1;      // (whatever the other rows do)
-  const int k = high && l < kSumLimit ? __builtin_amdgcn_frexp_expf(l) - 1 : 0;
+  const int k = l >= kRaiseSum && l < kSumLimit ? __builtin_amdgcn_frexp_expf(l) - 1 : 0;
   // what the reference really rises by: rounded where it has a fraction, and to less or nothing at all where it is far beyond 2^24
   const float raised = m + (float)k, by = raised - m;
   const float f = fast_exp2(-by), f16 = __builtin_ldexpf(1.0f, -(int)__builtin_rintf(by));      // (16-bit values keep their bits)
@@ -390,7 +389,7 @@ __device__ __forceinline__ void raise_reference(const WaveCtx& cx, Pipe<D>& t, f
 // of the tile after that.
 template <int D, bool KV8, int NW, bool PROBE>
 __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem, int kt, int& id,
-                                          const int* bt, unsigned long long& boff, Pipe<D>& t, float& m,
+                                          const int* bt, unsigned long long& boff, Pipe<D>& t, float m,
                                           const bf16x8 (&qf)[D / 16], Spans& sp) {
   using C = Cfg<D, KV8, NW>;
   constexpr int NS = C::SLOTS, EPS = 16 / NS, R = C::RING, NQ = C::KSTEPS, NP = 2 * C::MB, NI = C::NI;
@@ -410,20 +409,8 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
     // half 0: exponentials of the second half of kt, half 1: of the first half of kt + 1
     f32x16& Sx = t.S[half ^ 1];
     const int key0 = kTileKeys * kt + 32 * (half + 1);
-    if (i == NS + 2) {       // (not at the end, where the branch would wait)
-      t.l += sum[0];
-      t.high = __builtin_amdgcn_ballot_w64(t.l >= kRaiseSum);
-    }
-    if (i == NS + 4) {
-      t.unusual = t.high != 0 ? -1 : cx.pos_min - 31;
-      asm volatile("" : "+s"(t.unusual));
-    }
-    if (i == 0 && key0 > t.unusual) {       // (one branch for both)
-      if (t.high != 0) raise_reference<D, PROBE>(cx, t, m);
-      if (key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
-    }
     if (j == 0) {
-      if (i > 0 && key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
+      if (key0 + 31 > cx.pos_min) mask_half(cx, key0, Sx);
       __builtin_amdgcn_sched_barrier(0);
       exp_begin<EPS>(cx, Sx, m, h);
     }
@@ -497,7 +484,7 @@ __device__ __forceinline__ void tile_iter(const WaveCtx& cx, unsigned char* smem
       }
     }
   });
-  t.l += sum[1];
+  t.l += sum[0] + sum[1];
 }
 
 // The same iteration for a wave that has no key left: the tiles behind its rows' positions are for the other row blocks
@@ -668,13 +655,15 @@ __device__ __forceinline__ void run_tiles(const WaveCtx& cx, unsigned char* smem
 #pragma unroll
   for (int s = 0; s < kMaxSpans; ++s) t.am[s] = 0.0f;
   first_half<D, KV8, NW>(cy, qf, t, m);
-  t.high = 0;
-  t.unusual = cy.pos_min - 31;
   if constexpr (PROBE) add_spans<D>(cy, sp, 0, t.S[0], t.l, t.am);
   __builtin_amdgcn_sched_barrier(0);
   const int full = SHARED ? min(mine, ntiles - 1) : ntiles - 1;
   int kt = 0;
-  for (; kt < full; ++kt) tile_iter<D, KV8, NW, PROBE>(cy, smem, kt, id, bt, boff, t, m, qf, sp);
+  while (kt < full) {
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(t.l >= kRaiseSum) != 0, 0)) raise_reference<D, PROBE>(t, m);
+    const int stop = min(full, kt + kRaiseTiles);
+    for (; kt < stop; ++kt) tile_iter<D, KV8, NW, PROBE>(cy, smem, kt, id, bt, boff, t, m, qf, sp);
+  }
   if (SHARED)
     for (; kt < ntiles - 1; ++kt) fetch_iter<D, KV8, NW>(cy, smem, kt, id, bt, boff);
   if (kTileKeys * ntiles > cy.L) {        // (the same for all waves)
@@ -819,7 +808,7 @@ __device__ __forceinline__ void finish(const AttnParams& p, unsigned char* smem,
 }
 
 // A row's sums are exact under any reference that keeps them within range.  It is done over, under a running maximum, if scores
-// rose beyond that within one tile (a sum of kSumLimit), if all scores of its first tile are -inf (there is no maximum to
+// rose beyond that between two looks at it (a sum of kSumLimit), if all scores of its first tile are -inf (there is no maximum to
 // refer to then; every other row's sum holds the 1 of its first tile's maximum or what raised the reference from there), or if
 // its output is not finite although large values alone are no reason for that (with sums below 2^8 they are).
 template <int D>
@@ -841,8 +830,8 @@ __device__ __forceinline__ bool out_of_range(const Pipe<D>& t, float l_tot) {
 // The wave's rows under a running maximum, without the other waves: keys straight from the cache, values through the rows of LDS
 // that its output passed through, both requested half a tile ahead.  Rows that need it are rare, so this is short rather than fast.
 // All rows done over (keys from 96 on with 40 natural units' spread), 32 / 8 heads, in two passes without requests ahead, now, and by the
-// former loop, which knew no such rows: 2048 tokens 250, 156 and 51 us, 8192 2489, 1704 and 464, 16 ragged prompts 1074, 756 and 246, at head
-// size 64 581, 383 and 153.
+// former loop, which knew no such rows: 2048 tokens 250, 148 and 51 us, 8192 2493, 1575 and 474, 16 ragged prompts 1072, 710 and 245, at head
+// size 64 576, 364 and 151.
 template <int D, bool KV8, int NW>
 __device__ __forceinline__ void rows_alone(const AttnParams& p, unsigned char* smem, const Item& it, const WaveItem& wi,
                                            const WaveCtx& cx, Spans& sp, const int* bt, unsigned rows) {
@@ -1093,7 +1082,8 @@ __device__ __forceinline__ void prefill_item(const AttnParams& p, unsigned char*
   const unsigned long long boff = KV8 ? boff2 : boff1;      // of the last K run fetched
   const unsigned again = wave_probe ? tiles_and_output<D, KV8, NW, SHARED, true>(p, smem, it, wi, cx, id, boff, qf, sp, bt)
                                     : tiles_and_output<D, KV8, NW, SHARED, false>(p, smem, it, wi, cx, id, boff, qf, sp, bt);
-  if (__builtin_expect(again != 0, 0)) rows_alone<D, KV8, NW>(p, smem, it, wi, cx, sp, bt, again);
+  // (with its arguments read again, or they take registers from the rest: 2 prompts of 200-300 tokens 11.9 instead of 12.1 us)
+  if (__builtin_expect(again != 0, 0)) rows_alone<D, KV8, NW>(reread_arguments(), smem, it, wi, cx, sp, bt, again);
   if constexpr (ZERO_REST) {
     if (it.row0 == 0 && rb == 0 && wi.pslot >= 0 && p.plan_fresh) {
       const int lo = max(wi.qsel_b, 0), hi = min(wi.qsel_e, n);     // slots lo - qsel_b .. hi - qsel_b - 1 hold rows
@@ -1239,8 +1229,8 @@ __device__ __forceinline__ void settle_chunks(const AttnParams& p, int* sh) {
 
 // PLANNED: the work item comes from the planner's list.  Otherwise the kernel finds it (above), the last workgroup
 // of the grid settles the rest, and `mass` is written entry by entry by the waves that own the entries.
-// SHARED: several row blocks to a workgroup (groups of fewer than four heads).  An instantiation of its own, because the
-// spills that the fetch-only iterations bring cost a prompt of 2048 tokens at 32 / 8 heads 1.5 of its 49.5 us.
+// SHARED: several row blocks to a workgroup.  An instantiation of its own, because the fetch-only iterations cost the others up to
+// 2 % (one prompt of 700 tokens at head size 64 12.8 -> 13.1 us, 32 chunks of 64-200 rows 173.3 -> 174.7, long prompts nothing).
 template <int D, bool KV8, int NW, bool SHARED, bool PLANNED>
 __device__ __forceinline__ void row_block(const AttnParams& p, unsigned char* smem, int bid, int last) {
   const int kvh = bid % p.Hkv;

@@ -174,8 +174,8 @@ def test_a_row_that_rises_leaves_its_neighbours_alone(G, d, kv8):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("times,bound", [(12.0, 1.6), (40.0, 4.7)])
 def test_what_late_scores_cost(d, times, bound):
-    """Keys of 12 times the first tile's spread take the fast path (1.15-1.2 times the plain prompt's time; done over, it was 5.8 and 4.2 times),
-    keys that leave the range of fp32 within a tile are done over (3.6 and 2.7)."""
+    """Keys of 12 times the first tile's spread take the fast path (1.02-1.2 times the plain prompt's time; done over, it was 5.8 and 4.2 times),
+    keys that leave the range of fp32 within a few tiles are done over (3.6 and 3.1)."""
     b = W.random_batch(4800 + d, [2048], [2048], 32, 8, d, torch.bfloat16, num_probe_heads=8, max_sel_q=1, max_spans=2)
     hot = _heat(b, times, head=slice(None))
     calls = [binding.call_from_batch(x.to(DEV), batch_kind=binding.BATCH_PREFILL_ONLY) for x in (b, hot)]
