@@ -21,6 +21,7 @@ TOL = 2e-4
     (2, 4, 17, 33, 64),      # two, one in the last; two blocks of 32 rows
     (1, 1, 9, 32, 128),      # one
     (1, 2, 1, 40, 64),
+    (4, 8, 5, 100, 64),      # four where eight would do, since the table is wide enough for long ones; four blocks of 32 rows
 ])
 def test_spans_taken_in_turns(seqs, heads, spans, rows, d, layout):
     print(f"[case] span turns: {seqs} sequences, {heads} heads, {spans} spans, {rows} rows, d {d}, {layout}", flush=True)
