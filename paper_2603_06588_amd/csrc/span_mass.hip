@@ -378,7 +378,7 @@ __device__ __forceinline__ void load_q(const SpanParams& p, const RowBlock& r, i
 // waves (2048 keys: 4 waves 38 us, 16 waves 40; 1024 keys: 16 waves 40 us, 8 waves 29, 4 waves 27).
 constexpr int kStatWaves = 4;     // waves per workgroup of pass 1
 constexpr int kSumWaves = 8;      // waves per workgroup of the second kernel, and spans at a time
-constexpr int kSumWgs = 128;      // workgroups that it has at least, or else fewer spans to each; twice as many where spans can be long
+constexpr int kSumWgs = 144, kSumWgsLong = 256;      // workgroups that it has at least, or else fewer spans to each; where spans can be long
 constexpr int kSplitBlocks = 2;   // blocks of 16 rows per workgroup: they share every K fetch
 constexpr int kSplitRows = kSplitBlocks * kSmRows;
 constexpr int kSplitKeys = 1024;  // keys of one workgroup of pass 1 (until kMaxSplits is reached)
@@ -753,13 +753,15 @@ inline SplitGeom split_geometry(const hook_attn_probe_args* a) {
   // as many as the launch grid's third dimension (65535) holds
   if ((long long)a->num_seqs * g.nsplit > 65535) g.nsplit = 65535 / a->num_seqs;
   if (g.least > g.nsplit) g.least = g.nsplit;
-  // Spans eight at a time, fewer where that leaves compute units without work, as long as that dimension holds the groups.  Long
-  // spans are walked, and walks should be spread over the chip; many small ones ask for fewer workgroups.  At least 64, 128 and 256, us: 16 of
-  // 600-1500 keys on 8 heads 58.5, 33.4 and 33.3, the same in 4 prompts -, 73.9 and 58.0 (a wave to a span 63.5), in 8 -, 127 and 107 (109);
-  // 3 x 60 of 20-60 keys -, 20.2 and 21.4.  So it is 256 where the table is wide enough for spans that are walked on average.
+  // Spans eight at a time, fewer where that leaves compute units without work, as long as that dimension holds the groups.  Spans
+  // that are walked (long ones, overlapping ones) should be spread over the chip, the others ask for fewer workgroups.  Wave-to-a-span form, 128
+  // and 256 workgroups, us: 4 prompts on 8 heads, 16 spans of 600-1500 keys 63.5, 73.9 and 58.0, 16 overlapping ones of 170-270 24.2, 27.3 and 24.4,
+  // 30 of 820-860 43.7, 65.1 and 43.8; 16 apart of 20-60 18.7, 18.7 and 18.8.  But 3 x 60 of 20-60 on 8 heads 20.2 with 192 and 21.4 with 360, 1 x 100 of
+  // 64-256 on 12 22.7 with 156 and 23.6 with 300, so spans that can only be short on average (by the width of the table) need 144.
+  // (100 overlapping spans of 2000 keys in each of 4 prompts: 416 workgroups, two on some compute units, 243 against 190 in the former form.)
   const long long blocks = (long long)a->num_seqs * a->num_probe_heads * ((a->max_sel_q + kSplitRows - 1) / kSplitRows);
   const bool can_be_long = (long long)a->max_blocks_per_seq * kBlock > (long long)kOverhang * a->max_spans;
-  const int least_wgs = can_be_long ? 2 * kSumWgs : kSumWgs;
+  const int least_wgs = can_be_long ? kSumWgsLong : kSumWgs;
   g.span_turn = kSumWaves;
   while (g.span_turn > 1 && blocks * ((a->max_spans + g.span_turn - 1) / g.span_turn) < least_wgs) g.span_turn /= 2;
   g.sgroups = (a->max_spans + g.span_turn - 1) / g.span_turn;

@@ -17,7 +17,8 @@ TOL = 2e-4
 @pytest.mark.parametrize("layout", ["in order", "long", "overlapping"])
 @pytest.mark.parametrize("seqs,heads,spans,rows,d", [
     (4, 8, 33, 17, 64),      # eight at a time, one in the last turn
-    (2, 8, 30, 1, 128),      # four, two in the last
+    (4, 8, 18, 1, 128),      # four, two in the last
+    (2, 8, 30, 1, 128),      # two
     (2, 4, 17, 33, 64),      # two, one in the last; two blocks of 32 rows
     (1, 1, 9, 32, 128),      # one
     (1, 2, 1, 40, 64),
