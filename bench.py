@@ -27,10 +27,10 @@ PEAK_HBM_GBS = 8000.0            # MI355X HBM3E
 # until the counters are taken again.
 TRAFFIC = {
     # key: (bytes per launch, source files, hash of those files when the counters were taken)
-    "k_prefill/c2": (656501520, ("prefill.hip", "prefill_device.h", "hook_device.h"), "b81210cd43fa0172"),
-    "k_prefill/c4": (3354381645, ("prefill.hip", "prefill_device.h", "hook_device.h"), "b81210cd43fa0172"),
-    "k_decode/c3": (4891000941, ("decode.hip", "decode_device.h", "hook_device.h"), "6686ab14b299088e"),
-    "k_decode/c3_fp8": (2436606485, ("decode.hip", "decode_device.h", "hook_device.h"), "6686ab14b299088e"),
+    "k_prefill/c2": (643728772, ("prefill.hip", "prefill_device.h", "hook_device.h"), "9ff41c3f803bbb1c"),
+    "k_prefill/c4": (3345165015, ("prefill.hip", "prefill_device.h", "hook_device.h"), "9ff41c3f803bbb1c"),
+    "k_decode/c3": (4891082913, ("decode.hip", "decode_device.h", "hook_device.h"), "2c1de434d85e96dc"),
+    "k_decode/c3_fp8": (2436599976, ("decode.hip", "decode_device.h", "hook_device.h"), "2c1de434d85e96dc"),
 }
 
 

@@ -83,12 +83,12 @@ int stream_ranges(const hook_attn_probe_args* a, const Layout& l, int num_seqs) 
 
 // Row blocks and single rows of a mixed batch share a launch (mixed.hip) where the single rows plan themselves and are few: no
 // more sequences than ranges at one workgroup per compute unit, so that hardly a range pays for more than two start-ups, which
-// nothing covers there.  Apart and together, 32 / 8 heads, us: 8 x 1000 tokens and a chunk of 512 rows 32.8 and 23.9, with new rows 38.2
-// and 29.7, 4 x 6000 and 130 35.7 and 29.8, 16 x 3000-6000 and 2 x 1000 100 and 88, 28 x 4096 and 4 x 2048 233 and 213, 30 x 500-5000 and 200
-// over an 8-bit cache 57 and 55; 20 x 4096 and 200 at 64 / 8 heads over an 8-bit cache 68.6 and 63.8; 30 x 1000-4000 and 4 x 300 at 8 / 1
-// 34.1 and 25.3.  With more sequences either way: 60 x 4096 and 4 x 2048 312 and 291, with new rows 326 and 332, 60 x 500-5000 and 200 over
-// an 8-bit cache 88 and 99, 180 x 500-2000 and 2 x 300 184 and 193.  Groups of four heads and more; four waves to a row block (eight
-// leave no room on their compute unit).
+// nothing covers there.  Apart and together, 32 / 8 heads, us: 8 x 1000 tokens and a chunk of 512 rows 32.1 and 23.5, with new rows 37.8
+// and 28.3, 4 x 6000 and 130 34.6 and 28.6, 16 x 3000-6000 and 2 x 1000 90.0 and 70.5, 28 x 4096 and 4 x 2048 230 and 205, 28 x 16384 and 130 over an
+// 8-bit cache 172 and 161; 20 x 4096 and 200 at 64 / 8 heads over an 8-bit cache 66.5 and 55.0; 28 x 4096 and 4 x 2048 at 8 / 1 78.2 and 57.6.  (How
+// many workgroups the single rows take there: share_compute_units.)  With more sequences, at one workgroup, either way: 60 x 4096 and 4 x 2048 312
+// and 291, with new rows 326 and 332, 60 x 500-5000 and 200 over an 8-bit cache 88 and 99, 180 x 500-2000 and 2 x 300 184 and 193.  Groups of
+// four heads and more; four waves to a row block (eight leave no room on their compute unit).
 bool shares_launch(const hook_attn_probe_args* a, const Layout& l) {
   return a->dtype == HOOK_BF16 && a->batch_kind == HOOK_BATCH_MIXED && l.ranges > 0 && l.pf_waves == 4 && l.hpw == 4 &&
          a->num_seqs <= kStreamSeqs && a->num_seqs <= ranges_of_one_round(l, a, 1);
